@@ -53,11 +53,12 @@ TTGG_TRAFFIC_BYTES_PER_KEPT_EVENT = 1071.0
 TTG_TRAFFIC_BYTES = 52.7e6
 
 
-def flops_per_event(m: int) -> int:
+def flops_per_event(m: int, fp64: bool = False) -> int:
+    """Operations per kept event; the FP64 amplitudes sum over one antitop helicity."""
     sys.path.insert(0, os.path.join(ROOT, "paper_2105_10529_amd", "gen"))
     import gen_me
 
-    return gen_me.flop_count(m)["total"]
+    return gen_me.flop_count(m)["total_one_antitop" if fp64 else "total"]
 
 
 def ttgg_config(prec: str, seed: int = SEEDS[0], **kw):
@@ -514,7 +515,7 @@ def ttg_fp64(events: int = EVENTS, iters: int = 10, warmup: int = 2) -> dict:
     r = p.integrate(iters, events, adapt=True, iter_offset=warmup)
     torch.cuda.synchronize()
     dt = time.perf_counter() - t0
-    fpe = flops_per_event(3)
+    fpe = flops_per_event(3, fp64=True)
     kavg = r.kernel_seconds / iters
     passing = r.n_nonzero / iters
     ach = fpe * passing / kavg

@@ -44,6 +44,17 @@ template <class T> __device__ __forceinline__ Dual<T> dsqrt(Dual<T> x) {
 __device__ __forceinline__ double dlog(double x) { return log(x); }
 template <class T> __device__ __forceinline__ Dual<T> dlog(Dual<T> x) { return Dual<T>(dlog(x.v), x.d / x.v); }
 
+// Amplitude types whose values are FP64.
+template <class R> struct fp64_amp {
+  static constexpr bool value = false;
+};
+template <> struct fp64_amp<double> {
+  static constexpr bool value = true;
+};
+template <> struct fp64_amp<Dual<double>> {
+  static constexpr bool value = true;
+};
+
 // Conversion from the kinematic type (FP64 or its dual) to the amplitude type.
 template <class R> __device__ __forceinline__ R cvt(double x) { return R(x); }
 template <> __device__ __forceinline__ float cvt<float>(double x) { return (float)x; }

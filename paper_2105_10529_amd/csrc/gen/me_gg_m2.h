@@ -29,7 +29,7 @@ __device__ __forceinline__ R me_gg_m2(const V4<RK>* K, const V4<R> (*E)[2], cons
   const R IQ2 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, PK2) + mdot(PK2, PK2)));
   R total = R(0.0);
 #pragma unroll 1
-  for (int ht = 0; ht < 2; ++ht) {
+  for (int ht = 0; ht < (fp64_amp<R>::value ? 1 : 2); ++ht) {
     const Sp<R> S_ = VS[ht];
 #pragma unroll 1
     for (int hg = 0; hg < 4; ++hg) {
@@ -65,6 +65,6 @@ __device__ __forceinline__ R me_gg_m2(const V4<RK>* K, const V4<R> (*E)[2], cons
       }
     }
   }
-  return total * R(1.0 / 3.0);
+  return total * R((fp64_amp<R>::value ? 2.0 : 1.0) / 3.0);
 }
 }  // namespace mf

@@ -44,17 +44,11 @@ __device__ __forceinline__ R me_gg_m3(const V4<RK>* K, const V4<R> (*E)[2], cons
       const V4<R> E1 = ((hg >> 1) & 1) ? E[1][1] : E[1][0];
       const V4<R> E2 = ((hg >> 0) & 1) ? E[2][1] : E[2][0];
       C2<R> A0h0_0, A1h0_0;
-      C2<R> A0h1_0, A1h1_0;
       C2<R> A0h0_1, A1h0_1;
-      C2<R> A0h1_1, A1h1_1;
       C2<R> A0h0_2, A1h0_2;
-      C2<R> A0h1_2, A1h1_2;
       C2<R> A0h0_3, A1h0_3;
-      C2<R> A0h1_3, A1h1_3;
       C2<R> A0h0_4, A1h0_4;
-      C2<R> A0h1_4, A1h1_4;
       C2<R> A0h0_5, A1h0_5;
-      C2<R> A0h1_5, A1h1_5;
       {  // orderings (0, 1, 2), (0, 2, 1), (1, 0, 2), (1, 2, 0), (2, 0, 1), (2, 1, 0)
         V4<R> J0 = E0; opaque4(J0);
         V4<R> k0 = K0; opaque4(k0);
@@ -103,34 +97,6 @@ __device__ __forceinline__ R me_gg_m3(const V4<RK>* K, const V4<R> (*E)[2], cons
         const Sp<R> Fh0_5 = slash_acc(J012, Sh0_, slash_acc(J21, Sh0_0, slash(J2, Sh0_10)));
         A0h0_5 = ubar_dot(UB[0], Fh0_5);
         A1h0_5 = ubar_dot(UB[1], Fh0_5);
-        Sp<R> Sh1_ = VS[1]; opaque_sp(Sh1_);
-        const Sp<R> Sh1_2 = prop_neg(pb + k2, MT, IQ4, slash(J2, Sh1_));
-        const Sp<R> Sh1_12 = prop_neg(pb + p6, MT, IQ6, slash_acc(J12, Sh1_, slash(J1, Sh1_2)));
-        const Sp<R> Fh1_0 = slash_acc(J012, Sh1_, slash_acc(J01, Sh1_2, slash(J0, Sh1_12)));
-        A0h1_0 = ubar_dot(UB[0], Fh1_0);
-        A1h1_0 = ubar_dot(UB[1], Fh1_0);
-        const Sp<R> Sh1_1 = prop_neg(pb + k1, MT, IQ2, slash(J1, Sh1_));
-        const Sp<R> Sh1_21 = prop_neg(pb + p6, MT, IQ6, slash_acc(J21, Sh1_, slash(J2, Sh1_1)));
-        const Sp<R> Fh1_1 = slash_acc(J021, Sh1_, slash_acc(J02, Sh1_1, slash(J0, Sh1_21)));
-        A0h1_1 = ubar_dot(UB[0], Fh1_1);
-        A1h1_1 = ubar_dot(UB[1], Fh1_1);
-        const Sp<R> Sh1_02 = prop_neg(pb + p5, MT, IQ5, slash_acc(J02, Sh1_, slash(J0, Sh1_2)));
-        const Sp<R> Fh1_2 = slash_acc(J102, Sh1_, slash_acc(J10, Sh1_2, slash(J1, Sh1_02)));
-        A0h1_2 = ubar_dot(UB[0], Fh1_2);
-        A1h1_2 = ubar_dot(UB[1], Fh1_2);
-        const Sp<R> Sh1_0 = prop_neg(pb + k0, MT, IQ1, slash(J0, Sh1_));
-        const Sp<R> Sh1_20 = prop_neg(pb + p5, MT, IQ5, slash_acc(J20, Sh1_, slash(J2, Sh1_0)));
-        const Sp<R> Fh1_3 = slash_acc(J021, Sh1_, slash_acc(J12, Sh1_0, slash(J1, Sh1_20)));
-        A0h1_3 = ubar_dot(UB[0], Fh1_3);
-        A1h1_3 = ubar_dot(UB[1], Fh1_3);
-        const Sp<R> Sh1_01 = prop_neg(pb + p3, MT, IQ3, slash_acc(J01, Sh1_, slash(J0, Sh1_1)));
-        const Sp<R> Fh1_4 = slash_acc(J102, Sh1_, slash_acc(J20, Sh1_1, slash(J2, Sh1_01)));
-        A0h1_4 = ubar_dot(UB[0], Fh1_4);
-        A1h1_4 = ubar_dot(UB[1], Fh1_4);
-        const Sp<R> Sh1_10 = prop_neg(pb + p3, MT, IQ3, slash_acc(J10, Sh1_, slash(J1, Sh1_0)));
-        const Sp<R> Fh1_5 = slash_acc(J012, Sh1_, slash_acc(J21, Sh1_0, slash(J2, Sh1_10)));
-        A0h1_5 = ubar_dot(UB[0], Fh1_5);
-        A1h1_5 = ubar_dot(UB[1], Fh1_5);
       }
       {
         R s = cre_dot(A0h0_0, A0h0_1);
@@ -178,54 +144,8 @@ __device__ __forceinline__ R me_gg_m3(const V4<RK>* K, const V4<R> (*E)[2], cons
         s = cabs2_acc(A1h0_4, s); s = cabs2_acc(A1h0_5, s);
         total = total + R(64.0) * s;
       }
-      {
-        R s = cre_dot(A0h1_0, A0h1_1);
-        s = cre_dot_acc(A0h1_0, A0h1_2, s); s = cre_dot_acc(A0h1_1, A0h1_4, s); s = cre_dot_acc(A0h1_2, A0h1_3, s);
-        s = cre_dot_acc(A0h1_3, A0h1_5, s); s = cre_dot_acc(A0h1_4, A0h1_5, s);
-        total = total + R(-16.0) * s;
-      }
-      {
-        R s = cre_dot(A0h1_0, A0h1_3);
-        s = cre_dot_acc(A0h1_0, A0h1_4, s); s = cre_dot_acc(A0h1_1, A0h1_2, s); s = cre_dot_acc(A0h1_1, A0h1_5, s);
-        s = cre_dot_acc(A0h1_2, A0h1_5, s); s = cre_dot_acc(A0h1_3, A0h1_4, s);
-        total = total + R(2.0) * s;
-      }
-      {
-        R s = cre_dot(A0h1_0, A0h1_5);
-        s = cre_dot_acc(A0h1_1, A0h1_3, s); s = cre_dot_acc(A0h1_2, A0h1_4, s);
-        total = total + R(20.0) * s;
-      }
-      {
-        R s = cabs2(A0h1_0);
-        s = cabs2_acc(A0h1_1, s); s = cabs2_acc(A0h1_2, s); s = cabs2_acc(A0h1_3, s);
-        s = cabs2_acc(A0h1_4, s); s = cabs2_acc(A0h1_5, s);
-        total = total + R(64.0) * s;
-      }
-      {
-        R s = cre_dot(A1h1_0, A1h1_1);
-        s = cre_dot_acc(A1h1_0, A1h1_2, s); s = cre_dot_acc(A1h1_1, A1h1_4, s); s = cre_dot_acc(A1h1_2, A1h1_3, s);
-        s = cre_dot_acc(A1h1_3, A1h1_5, s); s = cre_dot_acc(A1h1_4, A1h1_5, s);
-        total = total + R(-16.0) * s;
-      }
-      {
-        R s = cre_dot(A1h1_0, A1h1_3);
-        s = cre_dot_acc(A1h1_0, A1h1_4, s); s = cre_dot_acc(A1h1_1, A1h1_2, s); s = cre_dot_acc(A1h1_1, A1h1_5, s);
-        s = cre_dot_acc(A1h1_2, A1h1_5, s); s = cre_dot_acc(A1h1_3, A1h1_4, s);
-        total = total + R(2.0) * s;
-      }
-      {
-        R s = cre_dot(A1h1_0, A1h1_5);
-        s = cre_dot_acc(A1h1_1, A1h1_3, s); s = cre_dot_acc(A1h1_2, A1h1_4, s);
-        total = total + R(20.0) * s;
-      }
-      {
-        R s = cabs2(A1h1_0);
-        s = cabs2_acc(A1h1_1, s); s = cabs2_acc(A1h1_2, s); s = cabs2_acc(A1h1_3, s);
-        s = cabs2_acc(A1h1_4, s); s = cabs2_acc(A1h1_5, s);
-        total = total + R(64.0) * s;
-      }
     }
   }
-  return total * R(1.0 / 9.0);
+  return total * R(2.0 / 9.0);
 }
 }  // namespace mf

@@ -76,9 +76,7 @@ __device__ __forceinline__ R me_gg_m4(const V4<RK>* K, const V4<R> (*E)[2], cons
       const V4<R> E2 = ((hg >> 1) & 1) ? E[2][1] : E[2][0];
       const V4<R> E3 = ((hg >> 0) & 1) ? E[3][1] : E[3][0];
       C2<R> A0h0_0, A1h0_0;
-      C2<R> A0h1_0, A1h1_0;
       C2<R> A0h0_6, A1h0_6;
-      C2<R> A0h1_6, A1h1_6;
       {  // orderings (0, 1, 2, 3), (1, 0, 2, 3)
         V4<R> J0 = E0; opaque4(J0);
         V4<R> k0 = K0; opaque4(k0);
@@ -118,22 +116,9 @@ __device__ __forceinline__ R me_gg_m4(const V4<RK>* K, const V4<R> (*E)[2], cons
         const Sp<R> Fh0_6 = slash_acc(J1023, Sh0_, slash_acc(J102, Sh0_3, slash_acc(J10, Sh0_23, slash(J1, Sh0_023))));
         A0h0_6 = ubar_dot(UB[0], Fh0_6);
         A1h0_6 = ubar_dot(UB[1], Fh0_6);
-        Sp<R> Sh1_ = VS[1]; opaque_sp(Sh1_);
-        const Sp<R> Sh1_3 = prop_neg(pb + k3, MT, IQ8, slash(J3, Sh1_));
-        const Sp<R> Sh1_23 = prop_neg(pb + p12, MT, IQ12, slash_acc(J23, Sh1_, slash(J2, Sh1_3)));
-        const Sp<R> Sh1_123 = prop_neg(pb + p14, MT, IQ14, slash_acc(J123, Sh1_, slash_acc(J12, Sh1_3, slash(J1, Sh1_23))));
-        const Sp<R> Fh1_0 = slash_acc(J0123, Sh1_, slash_acc(J012, Sh1_3, slash_acc(J01, Sh1_23, slash(J0, Sh1_123))));
-        A0h1_0 = ubar_dot(UB[0], Fh1_0);
-        A1h1_0 = ubar_dot(UB[1], Fh1_0);
-        const Sp<R> Sh1_023 = prop_neg(pb + p13, MT, IQ13, slash_acc(J023, Sh1_, slash_acc(J02, Sh1_3, slash(J0, Sh1_23))));
-        const Sp<R> Fh1_6 = slash_acc(J1023, Sh1_, slash_acc(J102, Sh1_3, slash_acc(J10, Sh1_23, slash(J1, Sh1_023))));
-        A0h1_6 = ubar_dot(UB[0], Fh1_6);
-        A1h1_6 = ubar_dot(UB[1], Fh1_6);
       }
       C2<R> A0h0_1, A1h0_1;
-      C2<R> A0h1_1, A1h1_1;
       C2<R> A0h0_7, A1h0_7;
-      C2<R> A0h1_7, A1h1_7;
       {  // orderings (0, 1, 3, 2), (1, 0, 3, 2)
         V4<R> J0 = E0; opaque4(J0);
         V4<R> k0 = K0; opaque4(k0);
@@ -173,22 +158,9 @@ __device__ __forceinline__ R me_gg_m4(const V4<RK>* K, const V4<R> (*E)[2], cons
         const Sp<R> Fh0_7 = slash_acc(J1032, Sh0_, slash_acc(J103, Sh0_2, slash_acc(J10, Sh0_32, slash(J1, Sh0_032))));
         A0h0_7 = ubar_dot(UB[0], Fh0_7);
         A1h0_7 = ubar_dot(UB[1], Fh0_7);
-        Sp<R> Sh1_ = VS[1]; opaque_sp(Sh1_);
-        const Sp<R> Sh1_2 = prop_neg(pb + k2, MT, IQ4, slash(J2, Sh1_));
-        const Sp<R> Sh1_32 = prop_neg(pb + p12, MT, IQ12, slash_acc(J32, Sh1_, slash(J3, Sh1_2)));
-        const Sp<R> Sh1_132 = prop_neg(pb + p14, MT, IQ14, slash_acc(J132, Sh1_, slash_acc(J13, Sh1_2, slash(J1, Sh1_32))));
-        const Sp<R> Fh1_1 = slash_acc(J0132, Sh1_, slash_acc(J013, Sh1_2, slash_acc(J01, Sh1_32, slash(J0, Sh1_132))));
-        A0h1_1 = ubar_dot(UB[0], Fh1_1);
-        A1h1_1 = ubar_dot(UB[1], Fh1_1);
-        const Sp<R> Sh1_032 = prop_neg(pb + p13, MT, IQ13, slash_acc(J032, Sh1_, slash_acc(J03, Sh1_2, slash(J0, Sh1_32))));
-        const Sp<R> Fh1_7 = slash_acc(J1032, Sh1_, slash_acc(J103, Sh1_2, slash_acc(J10, Sh1_32, slash(J1, Sh1_032))));
-        A0h1_7 = ubar_dot(UB[0], Fh1_7);
-        A1h1_7 = ubar_dot(UB[1], Fh1_7);
       }
       C2<R> A0h0_2, A1h0_2;
-      C2<R> A0h1_2, A1h1_2;
       C2<R> A0h0_12, A1h0_12;
-      C2<R> A0h1_12, A1h1_12;
       {  // orderings (0, 2, 1, 3), (2, 0, 1, 3)
         V4<R> J0 = E0; opaque4(J0);
         V4<R> k0 = K0; opaque4(k0);
@@ -228,22 +200,9 @@ __device__ __forceinline__ R me_gg_m4(const V4<RK>* K, const V4<R> (*E)[2], cons
         const Sp<R> Fh0_12 = slash_acc(J2013, Sh0_, slash_acc(J201, Sh0_3, slash_acc(J20, Sh0_13, slash(J2, Sh0_013))));
         A0h0_12 = ubar_dot(UB[0], Fh0_12);
         A1h0_12 = ubar_dot(UB[1], Fh0_12);
-        Sp<R> Sh1_ = VS[1]; opaque_sp(Sh1_);
-        const Sp<R> Sh1_3 = prop_neg(pb + k3, MT, IQ8, slash(J3, Sh1_));
-        const Sp<R> Sh1_13 = prop_neg(pb + p10, MT, IQ10, slash_acc(J13, Sh1_, slash(J1, Sh1_3)));
-        const Sp<R> Sh1_213 = prop_neg(pb + p14, MT, IQ14, slash_acc(J213, Sh1_, slash_acc(J21, Sh1_3, slash(J2, Sh1_13))));
-        const Sp<R> Fh1_2 = slash_acc(J0213, Sh1_, slash_acc(J021, Sh1_3, slash_acc(J02, Sh1_13, slash(J0, Sh1_213))));
-        A0h1_2 = ubar_dot(UB[0], Fh1_2);
-        A1h1_2 = ubar_dot(UB[1], Fh1_2);
-        const Sp<R> Sh1_013 = prop_neg(pb + p11, MT, IQ11, slash_acc(J013, Sh1_, slash_acc(J01, Sh1_3, slash(J0, Sh1_13))));
-        const Sp<R> Fh1_12 = slash_acc(J2013, Sh1_, slash_acc(J201, Sh1_3, slash_acc(J20, Sh1_13, slash(J2, Sh1_013))));
-        A0h1_12 = ubar_dot(UB[0], Fh1_12);
-        A1h1_12 = ubar_dot(UB[1], Fh1_12);
       }
       C2<R> A0h0_3, A1h0_3;
-      C2<R> A0h1_3, A1h1_3;
       C2<R> A0h0_13, A1h0_13;
-      C2<R> A0h1_13, A1h1_13;
       {  // orderings (0, 2, 3, 1), (2, 0, 3, 1)
         V4<R> J0 = E0; opaque4(J0);
         V4<R> k0 = K0; opaque4(k0);
@@ -283,22 +242,9 @@ __device__ __forceinline__ R me_gg_m4(const V4<RK>* K, const V4<R> (*E)[2], cons
         const Sp<R> Fh0_13 = slash_acc(J2031, Sh0_, slash_acc(J203, Sh0_1, slash_acc(J20, Sh0_31, slash(J2, Sh0_031))));
         A0h0_13 = ubar_dot(UB[0], Fh0_13);
         A1h0_13 = ubar_dot(UB[1], Fh0_13);
-        Sp<R> Sh1_ = VS[1]; opaque_sp(Sh1_);
-        const Sp<R> Sh1_1 = prop_neg(pb + k1, MT, IQ2, slash(J1, Sh1_));
-        const Sp<R> Sh1_31 = prop_neg(pb + p10, MT, IQ10, slash_acc(J31, Sh1_, slash(J3, Sh1_1)));
-        const Sp<R> Sh1_231 = prop_neg(pb + p14, MT, IQ14, slash_acc(J231, Sh1_, slash_acc(J23, Sh1_1, slash(J2, Sh1_31))));
-        const Sp<R> Fh1_3 = slash_acc(J0231, Sh1_, slash_acc(J023, Sh1_1, slash_acc(J02, Sh1_31, slash(J0, Sh1_231))));
-        A0h1_3 = ubar_dot(UB[0], Fh1_3);
-        A1h1_3 = ubar_dot(UB[1], Fh1_3);
-        const Sp<R> Sh1_031 = prop_neg(pb + p11, MT, IQ11, slash_acc(J031, Sh1_, slash_acc(J03, Sh1_1, slash(J0, Sh1_31))));
-        const Sp<R> Fh1_13 = slash_acc(J2031, Sh1_, slash_acc(J203, Sh1_1, slash_acc(J20, Sh1_31, slash(J2, Sh1_031))));
-        A0h1_13 = ubar_dot(UB[0], Fh1_13);
-        A1h1_13 = ubar_dot(UB[1], Fh1_13);
       }
       C2<R> A0h0_4, A1h0_4;
-      C2<R> A0h1_4, A1h1_4;
       C2<R> A0h0_18, A1h0_18;
-      C2<R> A0h1_18, A1h1_18;
       {  // orderings (0, 3, 1, 2), (3, 0, 1, 2)
         V4<R> J0 = E0; opaque4(J0);
         V4<R> k0 = K0; opaque4(k0);
@@ -338,22 +284,9 @@ __device__ __forceinline__ R me_gg_m4(const V4<RK>* K, const V4<R> (*E)[2], cons
         const Sp<R> Fh0_18 = slash_acc(J3012, Sh0_, slash_acc(J301, Sh0_2, slash_acc(J30, Sh0_12, slash(J3, Sh0_012))));
         A0h0_18 = ubar_dot(UB[0], Fh0_18);
         A1h0_18 = ubar_dot(UB[1], Fh0_18);
-        Sp<R> Sh1_ = VS[1]; opaque_sp(Sh1_);
-        const Sp<R> Sh1_2 = prop_neg(pb + k2, MT, IQ4, slash(J2, Sh1_));
-        const Sp<R> Sh1_12 = prop_neg(pb + p6, MT, IQ6, slash_acc(J12, Sh1_, slash(J1, Sh1_2)));
-        const Sp<R> Sh1_312 = prop_neg(pb + p14, MT, IQ14, slash_acc(J312, Sh1_, slash_acc(J31, Sh1_2, slash(J3, Sh1_12))));
-        const Sp<R> Fh1_4 = slash_acc(J0312, Sh1_, slash_acc(J031, Sh1_2, slash_acc(J03, Sh1_12, slash(J0, Sh1_312))));
-        A0h1_4 = ubar_dot(UB[0], Fh1_4);
-        A1h1_4 = ubar_dot(UB[1], Fh1_4);
-        const Sp<R> Sh1_012 = prop_neg(pb + p7, MT, IQ7, slash_acc(J012, Sh1_, slash_acc(J01, Sh1_2, slash(J0, Sh1_12))));
-        const Sp<R> Fh1_18 = slash_acc(J3012, Sh1_, slash_acc(J301, Sh1_2, slash_acc(J30, Sh1_12, slash(J3, Sh1_012))));
-        A0h1_18 = ubar_dot(UB[0], Fh1_18);
-        A1h1_18 = ubar_dot(UB[1], Fh1_18);
       }
       C2<R> A0h0_5, A1h0_5;
-      C2<R> A0h1_5, A1h1_5;
       C2<R> A0h0_19, A1h0_19;
-      C2<R> A0h1_19, A1h1_19;
       {  // orderings (0, 3, 2, 1), (3, 0, 2, 1)
         V4<R> J0 = E0; opaque4(J0);
         V4<R> k0 = K0; opaque4(k0);
@@ -393,22 +326,9 @@ __device__ __forceinline__ R me_gg_m4(const V4<RK>* K, const V4<R> (*E)[2], cons
         const Sp<R> Fh0_19 = slash_acc(J3021, Sh0_, slash_acc(J302, Sh0_1, slash_acc(J30, Sh0_21, slash(J3, Sh0_021))));
         A0h0_19 = ubar_dot(UB[0], Fh0_19);
         A1h0_19 = ubar_dot(UB[1], Fh0_19);
-        Sp<R> Sh1_ = VS[1]; opaque_sp(Sh1_);
-        const Sp<R> Sh1_1 = prop_neg(pb + k1, MT, IQ2, slash(J1, Sh1_));
-        const Sp<R> Sh1_21 = prop_neg(pb + p6, MT, IQ6, slash_acc(J21, Sh1_, slash(J2, Sh1_1)));
-        const Sp<R> Sh1_321 = prop_neg(pb + p14, MT, IQ14, slash_acc(J321, Sh1_, slash_acc(J32, Sh1_1, slash(J3, Sh1_21))));
-        const Sp<R> Fh1_5 = slash_acc(J0321, Sh1_, slash_acc(J032, Sh1_1, slash_acc(J03, Sh1_21, slash(J0, Sh1_321))));
-        A0h1_5 = ubar_dot(UB[0], Fh1_5);
-        A1h1_5 = ubar_dot(UB[1], Fh1_5);
-        const Sp<R> Sh1_021 = prop_neg(pb + p7, MT, IQ7, slash_acc(J021, Sh1_, slash_acc(J02, Sh1_1, slash(J0, Sh1_21))));
-        const Sp<R> Fh1_19 = slash_acc(J3021, Sh1_, slash_acc(J302, Sh1_1, slash_acc(J30, Sh1_21, slash(J3, Sh1_021))));
-        A0h1_19 = ubar_dot(UB[0], Fh1_19);
-        A1h1_19 = ubar_dot(UB[1], Fh1_19);
       }
       C2<R> A0h0_8, A1h0_8;
-      C2<R> A0h1_8, A1h1_8;
       C2<R> A0h0_14, A1h0_14;
-      C2<R> A0h1_14, A1h1_14;
       {  // orderings (1, 2, 0, 3), (2, 1, 0, 3)
         V4<R> J0 = E0; opaque4(J0);
         V4<R> k0 = K0; opaque4(k0);
@@ -448,22 +368,9 @@ __device__ __forceinline__ R me_gg_m4(const V4<RK>* K, const V4<R> (*E)[2], cons
         const Sp<R> Fh0_14 = slash_acc(J2103, Sh0_, slash_acc(J210, Sh0_3, slash_acc(J21, Sh0_03, slash(J2, Sh0_103))));
         A0h0_14 = ubar_dot(UB[0], Fh0_14);
         A1h0_14 = ubar_dot(UB[1], Fh0_14);
-        Sp<R> Sh1_ = VS[1]; opaque_sp(Sh1_);
-        const Sp<R> Sh1_3 = prop_neg(pb + k3, MT, IQ8, slash(J3, Sh1_));
-        const Sp<R> Sh1_03 = prop_neg(pb + p9, MT, IQ9, slash_acc(J03, Sh1_, slash(J0, Sh1_3)));
-        const Sp<R> Sh1_203 = prop_neg(pb + p13, MT, IQ13, slash_acc(J203, Sh1_, slash_acc(J20, Sh1_3, slash(J2, Sh1_03))));
-        const Sp<R> Fh1_8 = slash_acc(J1203, Sh1_, slash_acc(J120, Sh1_3, slash_acc(J12, Sh1_03, slash(J1, Sh1_203))));
-        A0h1_8 = ubar_dot(UB[0], Fh1_8);
-        A1h1_8 = ubar_dot(UB[1], Fh1_8);
-        const Sp<R> Sh1_103 = prop_neg(pb + p11, MT, IQ11, slash_acc(J103, Sh1_, slash_acc(J10, Sh1_3, slash(J1, Sh1_03))));
-        const Sp<R> Fh1_14 = slash_acc(J2103, Sh1_, slash_acc(J210, Sh1_3, slash_acc(J21, Sh1_03, slash(J2, Sh1_103))));
-        A0h1_14 = ubar_dot(UB[0], Fh1_14);
-        A1h1_14 = ubar_dot(UB[1], Fh1_14);
       }
       C2<R> A0h0_9, A1h0_9;
-      C2<R> A0h1_9, A1h1_9;
       C2<R> A0h0_15, A1h0_15;
-      C2<R> A0h1_15, A1h1_15;
       {  // orderings (1, 2, 3, 0), (2, 1, 3, 0)
         V4<R> J0 = E0; opaque4(J0);
         V4<R> k0 = K0; opaque4(k0);
@@ -503,22 +410,9 @@ __device__ __forceinline__ R me_gg_m4(const V4<RK>* K, const V4<R> (*E)[2], cons
         const Sp<R> Fh0_15 = slash_acc(J2130, Sh0_, slash_acc(J213, Sh0_0, slash_acc(J21, Sh0_30, slash(J2, Sh0_130))));
         A0h0_15 = ubar_dot(UB[0], Fh0_15);
         A1h0_15 = ubar_dot(UB[1], Fh0_15);
-        Sp<R> Sh1_ = VS[1]; opaque_sp(Sh1_);
-        const Sp<R> Sh1_0 = prop_neg(pb + k0, MT, IQ1, slash(J0, Sh1_));
-        const Sp<R> Sh1_30 = prop_neg(pb + p9, MT, IQ9, slash_acc(J30, Sh1_, slash(J3, Sh1_0)));
-        const Sp<R> Sh1_230 = prop_neg(pb + p13, MT, IQ13, slash_acc(J230, Sh1_, slash_acc(J23, Sh1_0, slash(J2, Sh1_30))));
-        const Sp<R> Fh1_9 = slash_acc(J1230, Sh1_, slash_acc(J123, Sh1_0, slash_acc(J12, Sh1_30, slash(J1, Sh1_230))));
-        A0h1_9 = ubar_dot(UB[0], Fh1_9);
-        A1h1_9 = ubar_dot(UB[1], Fh1_9);
-        const Sp<R> Sh1_130 = prop_neg(pb + p11, MT, IQ11, slash_acc(J130, Sh1_, slash_acc(J13, Sh1_0, slash(J1, Sh1_30))));
-        const Sp<R> Fh1_15 = slash_acc(J2130, Sh1_, slash_acc(J213, Sh1_0, slash_acc(J21, Sh1_30, slash(J2, Sh1_130))));
-        A0h1_15 = ubar_dot(UB[0], Fh1_15);
-        A1h1_15 = ubar_dot(UB[1], Fh1_15);
       }
       C2<R> A0h0_10, A1h0_10;
-      C2<R> A0h1_10, A1h1_10;
       C2<R> A0h0_20, A1h0_20;
-      C2<R> A0h1_20, A1h1_20;
       {  // orderings (1, 3, 0, 2), (3, 1, 0, 2)
         V4<R> J0 = E0; opaque4(J0);
         V4<R> k0 = K0; opaque4(k0);
@@ -558,22 +452,9 @@ __device__ __forceinline__ R me_gg_m4(const V4<RK>* K, const V4<R> (*E)[2], cons
         const Sp<R> Fh0_20 = slash_acc(J3102, Sh0_, slash_acc(J310, Sh0_2, slash_acc(J31, Sh0_02, slash(J3, Sh0_102))));
         A0h0_20 = ubar_dot(UB[0], Fh0_20);
         A1h0_20 = ubar_dot(UB[1], Fh0_20);
-        Sp<R> Sh1_ = VS[1]; opaque_sp(Sh1_);
-        const Sp<R> Sh1_2 = prop_neg(pb + k2, MT, IQ4, slash(J2, Sh1_));
-        const Sp<R> Sh1_02 = prop_neg(pb + p5, MT, IQ5, slash_acc(J02, Sh1_, slash(J0, Sh1_2)));
-        const Sp<R> Sh1_302 = prop_neg(pb + p13, MT, IQ13, slash_acc(J302, Sh1_, slash_acc(J30, Sh1_2, slash(J3, Sh1_02))));
-        const Sp<R> Fh1_10 = slash_acc(J1302, Sh1_, slash_acc(J130, Sh1_2, slash_acc(J13, Sh1_02, slash(J1, Sh1_302))));
-        A0h1_10 = ubar_dot(UB[0], Fh1_10);
-        A1h1_10 = ubar_dot(UB[1], Fh1_10);
-        const Sp<R> Sh1_102 = prop_neg(pb + p7, MT, IQ7, slash_acc(J102, Sh1_, slash_acc(J10, Sh1_2, slash(J1, Sh1_02))));
-        const Sp<R> Fh1_20 = slash_acc(J3102, Sh1_, slash_acc(J310, Sh1_2, slash_acc(J31, Sh1_02, slash(J3, Sh1_102))));
-        A0h1_20 = ubar_dot(UB[0], Fh1_20);
-        A1h1_20 = ubar_dot(UB[1], Fh1_20);
       }
       C2<R> A0h0_11, A1h0_11;
-      C2<R> A0h1_11, A1h1_11;
       C2<R> A0h0_21, A1h0_21;
-      C2<R> A0h1_21, A1h1_21;
       {  // orderings (1, 3, 2, 0), (3, 1, 2, 0)
         V4<R> J0 = E0; opaque4(J0);
         V4<R> k0 = K0; opaque4(k0);
@@ -613,22 +494,9 @@ __device__ __forceinline__ R me_gg_m4(const V4<RK>* K, const V4<R> (*E)[2], cons
         const Sp<R> Fh0_21 = slash_acc(J3120, Sh0_, slash_acc(J312, Sh0_0, slash_acc(J31, Sh0_20, slash(J3, Sh0_120))));
         A0h0_21 = ubar_dot(UB[0], Fh0_21);
         A1h0_21 = ubar_dot(UB[1], Fh0_21);
-        Sp<R> Sh1_ = VS[1]; opaque_sp(Sh1_);
-        const Sp<R> Sh1_0 = prop_neg(pb + k0, MT, IQ1, slash(J0, Sh1_));
-        const Sp<R> Sh1_20 = prop_neg(pb + p5, MT, IQ5, slash_acc(J20, Sh1_, slash(J2, Sh1_0)));
-        const Sp<R> Sh1_320 = prop_neg(pb + p13, MT, IQ13, slash_acc(J320, Sh1_, slash_acc(J32, Sh1_0, slash(J3, Sh1_20))));
-        const Sp<R> Fh1_11 = slash_acc(J1320, Sh1_, slash_acc(J132, Sh1_0, slash_acc(J13, Sh1_20, slash(J1, Sh1_320))));
-        A0h1_11 = ubar_dot(UB[0], Fh1_11);
-        A1h1_11 = ubar_dot(UB[1], Fh1_11);
-        const Sp<R> Sh1_120 = prop_neg(pb + p7, MT, IQ7, slash_acc(J120, Sh1_, slash_acc(J12, Sh1_0, slash(J1, Sh1_20))));
-        const Sp<R> Fh1_21 = slash_acc(J3120, Sh1_, slash_acc(J312, Sh1_0, slash_acc(J31, Sh1_20, slash(J3, Sh1_120))));
-        A0h1_21 = ubar_dot(UB[0], Fh1_21);
-        A1h1_21 = ubar_dot(UB[1], Fh1_21);
       }
       C2<R> A0h0_16, A1h0_16;
-      C2<R> A0h1_16, A1h1_16;
       C2<R> A0h0_22, A1h0_22;
-      C2<R> A0h1_22, A1h1_22;
       {  // orderings (2, 3, 0, 1), (3, 2, 0, 1)
         V4<R> J0 = E0; opaque4(J0);
         V4<R> k0 = K0; opaque4(k0);
@@ -668,22 +536,9 @@ __device__ __forceinline__ R me_gg_m4(const V4<RK>* K, const V4<R> (*E)[2], cons
         const Sp<R> Fh0_22 = slash_acc(J3201, Sh0_, slash_acc(J320, Sh0_1, slash_acc(J32, Sh0_01, slash(J3, Sh0_201))));
         A0h0_22 = ubar_dot(UB[0], Fh0_22);
         A1h0_22 = ubar_dot(UB[1], Fh0_22);
-        Sp<R> Sh1_ = VS[1]; opaque_sp(Sh1_);
-        const Sp<R> Sh1_1 = prop_neg(pb + k1, MT, IQ2, slash(J1, Sh1_));
-        const Sp<R> Sh1_01 = prop_neg(pb + p3, MT, IQ3, slash_acc(J01, Sh1_, slash(J0, Sh1_1)));
-        const Sp<R> Sh1_301 = prop_neg(pb + p11, MT, IQ11, slash_acc(J301, Sh1_, slash_acc(J30, Sh1_1, slash(J3, Sh1_01))));
-        const Sp<R> Fh1_16 = slash_acc(J2301, Sh1_, slash_acc(J230, Sh1_1, slash_acc(J23, Sh1_01, slash(J2, Sh1_301))));
-        A0h1_16 = ubar_dot(UB[0], Fh1_16);
-        A1h1_16 = ubar_dot(UB[1], Fh1_16);
-        const Sp<R> Sh1_201 = prop_neg(pb + p7, MT, IQ7, slash_acc(J201, Sh1_, slash_acc(J20, Sh1_1, slash(J2, Sh1_01))));
-        const Sp<R> Fh1_22 = slash_acc(J3201, Sh1_, slash_acc(J320, Sh1_1, slash_acc(J32, Sh1_01, slash(J3, Sh1_201))));
-        A0h1_22 = ubar_dot(UB[0], Fh1_22);
-        A1h1_22 = ubar_dot(UB[1], Fh1_22);
       }
       C2<R> A0h0_17, A1h0_17;
-      C2<R> A0h1_17, A1h1_17;
       C2<R> A0h0_23, A1h0_23;
-      C2<R> A0h1_23, A1h1_23;
       {  // orderings (2, 3, 1, 0), (3, 2, 1, 0)
         V4<R> J0 = E0; opaque4(J0);
         V4<R> k0 = K0; opaque4(k0);
@@ -723,17 +578,6 @@ __device__ __forceinline__ R me_gg_m4(const V4<RK>* K, const V4<R> (*E)[2], cons
         const Sp<R> Fh0_23 = slash_acc(J3210, Sh0_, slash_acc(J321, Sh0_0, slash_acc(J32, Sh0_10, slash(J3, Sh0_210))));
         A0h0_23 = ubar_dot(UB[0], Fh0_23);
         A1h0_23 = ubar_dot(UB[1], Fh0_23);
-        Sp<R> Sh1_ = VS[1]; opaque_sp(Sh1_);
-        const Sp<R> Sh1_0 = prop_neg(pb + k0, MT, IQ1, slash(J0, Sh1_));
-        const Sp<R> Sh1_10 = prop_neg(pb + p3, MT, IQ3, slash_acc(J10, Sh1_, slash(J1, Sh1_0)));
-        const Sp<R> Sh1_310 = prop_neg(pb + p11, MT, IQ11, slash_acc(J310, Sh1_, slash_acc(J31, Sh1_0, slash(J3, Sh1_10))));
-        const Sp<R> Fh1_17 = slash_acc(J2310, Sh1_, slash_acc(J231, Sh1_0, slash_acc(J23, Sh1_10, slash(J2, Sh1_310))));
-        A0h1_17 = ubar_dot(UB[0], Fh1_17);
-        A1h1_17 = ubar_dot(UB[1], Fh1_17);
-        const Sp<R> Sh1_210 = prop_neg(pb + p7, MT, IQ7, slash_acc(J210, Sh1_, slash_acc(J21, Sh1_0, slash(J2, Sh1_10))));
-        const Sp<R> Fh1_23 = slash_acc(J3210, Sh1_, slash_acc(J321, Sh1_0, slash_acc(J32, Sh1_10, slash(J3, Sh1_210))));
-        A0h1_23 = ubar_dot(UB[0], Fh1_23);
-        A1h1_23 = ubar_dot(UB[1], Fh1_23);
       }
       {
         R s = cre_dot(A0h0_0, A0h0_1);
@@ -1007,280 +851,8 @@ __device__ __forceinline__ R me_gg_m4(const V4<RK>* K, const V4<R> (*E)[2], cons
         s = cabs2_acc(A1h0_22, s); s = cabs2_acc(A1h0_23, s);
         total = total + R(512.0) * s;
       }
-      {
-        R s = cre_dot(A0h1_0, A0h1_1);
-        s = cre_dot_acc(A0h1_0, A0h1_2, s); s = cre_dot_acc(A0h1_0, A0h1_6, s); s = cre_dot_acc(A0h1_1, A0h1_4, s);
-        s = cre_dot_acc(A0h1_1, A0h1_7, s); s = cre_dot_acc(A0h1_2, A0h1_3, s); s = cre_dot_acc(A0h1_2, A0h1_12, s);
-        s = cre_dot_acc(A0h1_3, A0h1_5, s); s = cre_dot_acc(A0h1_3, A0h1_13, s); s = cre_dot_acc(A0h1_4, A0h1_5, s);
-        s = cre_dot_acc(A0h1_4, A0h1_18, s); s = cre_dot_acc(A0h1_5, A0h1_19, s); s = cre_dot_acc(A0h1_6, A0h1_7, s);
-        s = cre_dot_acc(A0h1_6, A0h1_8, s); s = cre_dot_acc(A0h1_7, A0h1_10, s); s = cre_dot_acc(A0h1_8, A0h1_9, s);
-        s = cre_dot_acc(A0h1_8, A0h1_14, s); s = cre_dot_acc(A0h1_9, A0h1_11, s); s = cre_dot_acc(A0h1_9, A0h1_15, s);
-        s = cre_dot_acc(A0h1_10, A0h1_11, s); s = cre_dot_acc(A0h1_10, A0h1_20, s); s = cre_dot_acc(A0h1_11, A0h1_21, s);
-        s = cre_dot_acc(A0h1_12, A0h1_13, s); s = cre_dot_acc(A0h1_12, A0h1_14, s); s = cre_dot_acc(A0h1_13, A0h1_16, s);
-        s = cre_dot_acc(A0h1_14, A0h1_15, s); s = cre_dot_acc(A0h1_15, A0h1_17, s); s = cre_dot_acc(A0h1_16, A0h1_17, s);
-        s = cre_dot_acc(A0h1_16, A0h1_22, s); s = cre_dot_acc(A0h1_17, A0h1_23, s); s = cre_dot_acc(A0h1_18, A0h1_19, s);
-        s = cre_dot_acc(A0h1_18, A0h1_20, s); s = cre_dot_acc(A0h1_19, A0h1_22, s); s = cre_dot_acc(A0h1_20, A0h1_21, s);
-        s = cre_dot_acc(A0h1_21, A0h1_23, s); s = cre_dot_acc(A0h1_22, A0h1_23, s);
-        total = total + R(-128.0) * s;
-      }
-      {
-        R s = cre_dot(A0h1_0, A0h1_23);
-        s = cre_dot_acc(A0h1_1, A0h1_17, s); s = cre_dot_acc(A0h1_2, A0h1_21, s); s = cre_dot_acc(A0h1_3, A0h1_11, s);
-        s = cre_dot_acc(A0h1_4, A0h1_15, s); s = cre_dot_acc(A0h1_5, A0h1_9, s); s = cre_dot_acc(A0h1_6, A0h1_22, s);
-        s = cre_dot_acc(A0h1_7, A0h1_16, s); s = cre_dot_acc(A0h1_8, A0h1_19, s); s = cre_dot_acc(A0h1_10, A0h1_13, s);
-        s = cre_dot_acc(A0h1_12, A0h1_20, s); s = cre_dot_acc(A0h1_14, A0h1_18, s);
-        total = total + R(-56.0) * s;
-      }
-      {
-        R s = cre_dot(A0h1_0, A0h1_11);
-        s = cre_dot_acc(A0h1_0, A0h1_15, s); s = cre_dot_acc(A0h1_0, A0h1_19, s); s = cre_dot_acc(A0h1_0, A0h1_20, s);
-        s = cre_dot_acc(A0h1_1, A0h1_9, s); s = cre_dot_acc(A0h1_1, A0h1_13, s); s = cre_dot_acc(A0h1_1, A0h1_14, s);
-        s = cre_dot_acc(A0h1_1, A0h1_21, s); s = cre_dot_acc(A0h1_2, A0h1_9, s); s = cre_dot_acc(A0h1_2, A0h1_17, s);
-        s = cre_dot_acc(A0h1_2, A0h1_18, s); s = cre_dot_acc(A0h1_2, A0h1_22, s); s = cre_dot_acc(A0h1_3, A0h1_7, s);
-        s = cre_dot_acc(A0h1_3, A0h1_8, s); s = cre_dot_acc(A0h1_3, A0h1_15, s); s = cre_dot_acc(A0h1_3, A0h1_23, s);
-        s = cre_dot_acc(A0h1_4, A0h1_11, s); s = cre_dot_acc(A0h1_4, A0h1_12, s); s = cre_dot_acc(A0h1_4, A0h1_16, s);
-        s = cre_dot_acc(A0h1_4, A0h1_23, s); s = cre_dot_acc(A0h1_5, A0h1_6, s); s = cre_dot_acc(A0h1_5, A0h1_10, s);
-        s = cre_dot_acc(A0h1_5, A0h1_17, s); s = cre_dot_acc(A0h1_5, A0h1_21, s); s = cre_dot_acc(A0h1_6, A0h1_13, s);
-        s = cre_dot_acc(A0h1_6, A0h1_18, s); s = cre_dot_acc(A0h1_6, A0h1_21, s); s = cre_dot_acc(A0h1_7, A0h1_12, s);
-        s = cre_dot_acc(A0h1_7, A0h1_15, s); s = cre_dot_acc(A0h1_7, A0h1_19, s); s = cre_dot_acc(A0h1_8, A0h1_16, s);
-        s = cre_dot_acc(A0h1_8, A0h1_20, s); s = cre_dot_acc(A0h1_8, A0h1_23, s); s = cre_dot_acc(A0h1_9, A0h1_13, s);
-        s = cre_dot_acc(A0h1_9, A0h1_22, s); s = cre_dot_acc(A0h1_10, A0h1_14, s); s = cre_dot_acc(A0h1_10, A0h1_17, s);
-        s = cre_dot_acc(A0h1_10, A0h1_22, s); s = cre_dot_acc(A0h1_11, A0h1_16, s); s = cre_dot_acc(A0h1_11, A0h1_19, s);
-        s = cre_dot_acc(A0h1_12, A0h1_19, s); s = cre_dot_acc(A0h1_12, A0h1_23, s); s = cre_dot_acc(A0h1_13, A0h1_18, s);
-        s = cre_dot_acc(A0h1_14, A0h1_21, s); s = cre_dot_acc(A0h1_14, A0h1_22, s); s = cre_dot_acc(A0h1_15, A0h1_20, s);
-        s = cre_dot_acc(A0h1_16, A0h1_20, s); s = cre_dot_acc(A0h1_17, A0h1_18, s);
-        total = total + R(-20.0) * s;
-      }
-      {
-        R s = cre_dot(A0h1_0, A0h1_9);
-        s = cre_dot_acc(A0h1_0, A0h1_10, s); s = cre_dot_acc(A0h1_0, A0h1_13, s); s = cre_dot_acc(A0h1_0, A0h1_18, s);
-        s = cre_dot_acc(A0h1_1, A0h1_8, s); s = cre_dot_acc(A0h1_1, A0h1_11, s); s = cre_dot_acc(A0h1_1, A0h1_12, s);
-        s = cre_dot_acc(A0h1_1, A0h1_19, s); s = cre_dot_acc(A0h1_2, A0h1_7, s); s = cre_dot_acc(A0h1_2, A0h1_15, s);
-        s = cre_dot_acc(A0h1_2, A0h1_16, s); s = cre_dot_acc(A0h1_2, A0h1_19, s); s = cre_dot_acc(A0h1_3, A0h1_6, s);
-        s = cre_dot_acc(A0h1_3, A0h1_14, s); s = cre_dot_acc(A0h1_3, A0h1_17, s); s = cre_dot_acc(A0h1_3, A0h1_18, s);
-        s = cre_dot_acc(A0h1_4, A0h1_6, s); s = cre_dot_acc(A0h1_4, A0h1_13, s); s = cre_dot_acc(A0h1_4, A0h1_21, s);
-        s = cre_dot_acc(A0h1_4, A0h1_22, s); s = cre_dot_acc(A0h1_5, A0h1_7, s); s = cre_dot_acc(A0h1_5, A0h1_12, s);
-        s = cre_dot_acc(A0h1_5, A0h1_20, s); s = cre_dot_acc(A0h1_5, A0h1_23, s); s = cre_dot_acc(A0h1_6, A0h1_15, s);
-        s = cre_dot_acc(A0h1_6, A0h1_20, s); s = cre_dot_acc(A0h1_7, A0h1_14, s); s = cre_dot_acc(A0h1_7, A0h1_21, s);
-        s = cre_dot_acc(A0h1_8, A0h1_13, s); s = cre_dot_acc(A0h1_8, A0h1_17, s); s = cre_dot_acc(A0h1_8, A0h1_21, s);
-        s = cre_dot_acc(A0h1_9, A0h1_12, s); s = cre_dot_acc(A0h1_9, A0h1_16, s); s = cre_dot_acc(A0h1_9, A0h1_20, s);
-        s = cre_dot_acc(A0h1_10, A0h1_15, s); s = cre_dot_acc(A0h1_10, A0h1_19, s); s = cre_dot_acc(A0h1_10, A0h1_23, s);
-        s = cre_dot_acc(A0h1_11, A0h1_14, s); s = cre_dot_acc(A0h1_11, A0h1_18, s); s = cre_dot_acc(A0h1_11, A0h1_22, s);
-        s = cre_dot_acc(A0h1_12, A0h1_22, s); s = cre_dot_acc(A0h1_13, A0h1_23, s); s = cre_dot_acc(A0h1_14, A0h1_23, s);
-        s = cre_dot_acc(A0h1_15, A0h1_22, s); s = cre_dot_acc(A0h1_16, A0h1_18, s); s = cre_dot_acc(A0h1_16, A0h1_21, s);
-        s = cre_dot_acc(A0h1_17, A0h1_19, s); s = cre_dot_acc(A0h1_17, A0h1_20, s);
-        total = total + R(-2.0) * s;
-      }
-      {
-        R s = cre_dot(A0h1_0, A0h1_3);
-        s = cre_dot_acc(A0h1_0, A0h1_4, s); s = cre_dot_acc(A0h1_0, A0h1_7, s); s = cre_dot_acc(A0h1_0, A0h1_8, s);
-        s = cre_dot_acc(A0h1_0, A0h1_12, s); s = cre_dot_acc(A0h1_1, A0h1_2, s); s = cre_dot_acc(A0h1_1, A0h1_5, s);
-        s = cre_dot_acc(A0h1_1, A0h1_6, s); s = cre_dot_acc(A0h1_1, A0h1_10, s); s = cre_dot_acc(A0h1_1, A0h1_18, s);
-        s = cre_dot_acc(A0h1_2, A0h1_5, s); s = cre_dot_acc(A0h1_2, A0h1_6, s); s = cre_dot_acc(A0h1_2, A0h1_13, s);
-        s = cre_dot_acc(A0h1_2, A0h1_14, s); s = cre_dot_acc(A0h1_3, A0h1_4, s); s = cre_dot_acc(A0h1_3, A0h1_12, s);
-        s = cre_dot_acc(A0h1_3, A0h1_16, s); s = cre_dot_acc(A0h1_3, A0h1_19, s); s = cre_dot_acc(A0h1_4, A0h1_7, s);
-        s = cre_dot_acc(A0h1_4, A0h1_19, s); s = cre_dot_acc(A0h1_4, A0h1_20, s); s = cre_dot_acc(A0h1_5, A0h1_13, s);
-        s = cre_dot_acc(A0h1_5, A0h1_18, s); s = cre_dot_acc(A0h1_5, A0h1_22, s); s = cre_dot_acc(A0h1_6, A0h1_9, s);
-        s = cre_dot_acc(A0h1_6, A0h1_10, s); s = cre_dot_acc(A0h1_6, A0h1_14, s); s = cre_dot_acc(A0h1_7, A0h1_8, s);
-        s = cre_dot_acc(A0h1_7, A0h1_11, s); s = cre_dot_acc(A0h1_7, A0h1_20, s); s = cre_dot_acc(A0h1_8, A0h1_11, s);
-        s = cre_dot_acc(A0h1_8, A0h1_12, s); s = cre_dot_acc(A0h1_8, A0h1_15, s); s = cre_dot_acc(A0h1_9, A0h1_10, s);
-        s = cre_dot_acc(A0h1_9, A0h1_14, s); s = cre_dot_acc(A0h1_9, A0h1_17, s); s = cre_dot_acc(A0h1_9, A0h1_21, s);
-        s = cre_dot_acc(A0h1_10, A0h1_18, s); s = cre_dot_acc(A0h1_10, A0h1_21, s); s = cre_dot_acc(A0h1_11, A0h1_15, s);
-        s = cre_dot_acc(A0h1_11, A0h1_20, s); s = cre_dot_acc(A0h1_11, A0h1_23, s); s = cre_dot_acc(A0h1_12, A0h1_15, s);
-        s = cre_dot_acc(A0h1_12, A0h1_16, s); s = cre_dot_acc(A0h1_13, A0h1_14, s); s = cre_dot_acc(A0h1_13, A0h1_17, s);
-        s = cre_dot_acc(A0h1_13, A0h1_22, s); s = cre_dot_acc(A0h1_14, A0h1_17, s); s = cre_dot_acc(A0h1_15, A0h1_16, s);
-        s = cre_dot_acc(A0h1_15, A0h1_23, s); s = cre_dot_acc(A0h1_16, A0h1_19, s); s = cre_dot_acc(A0h1_16, A0h1_23, s);
-        s = cre_dot_acc(A0h1_17, A0h1_21, s); s = cre_dot_acc(A0h1_17, A0h1_22, s); s = cre_dot_acc(A0h1_18, A0h1_21, s);
-        s = cre_dot_acc(A0h1_18, A0h1_22, s); s = cre_dot_acc(A0h1_19, A0h1_20, s); s = cre_dot_acc(A0h1_19, A0h1_23, s);
-        s = cre_dot_acc(A0h1_20, A0h1_23, s); s = cre_dot_acc(A0h1_21, A0h1_22, s);
-        total = total + R(16.0) * s;
-      }
-      {
-        R s = cre_dot(A0h1_0, A0h1_17);
-        s = cre_dot_acc(A0h1_0, A0h1_21, s); s = cre_dot_acc(A0h1_0, A0h1_22, s); s = cre_dot_acc(A0h1_1, A0h1_15, s);
-        s = cre_dot_acc(A0h1_1, A0h1_16, s); s = cre_dot_acc(A0h1_1, A0h1_23, s); s = cre_dot_acc(A0h1_2, A0h1_11, s);
-        s = cre_dot_acc(A0h1_2, A0h1_20, s); s = cre_dot_acc(A0h1_2, A0h1_23, s); s = cre_dot_acc(A0h1_3, A0h1_9, s);
-        s = cre_dot_acc(A0h1_3, A0h1_10, s); s = cre_dot_acc(A0h1_3, A0h1_21, s); s = cre_dot_acc(A0h1_4, A0h1_9, s);
-        s = cre_dot_acc(A0h1_4, A0h1_14, s); s = cre_dot_acc(A0h1_4, A0h1_17, s); s = cre_dot_acc(A0h1_5, A0h1_8, s);
-        s = cre_dot_acc(A0h1_5, A0h1_11, s); s = cre_dot_acc(A0h1_5, A0h1_15, s); s = cre_dot_acc(A0h1_6, A0h1_16, s);
-        s = cre_dot_acc(A0h1_6, A0h1_19, s); s = cre_dot_acc(A0h1_6, A0h1_23, s); s = cre_dot_acc(A0h1_7, A0h1_13, s);
-        s = cre_dot_acc(A0h1_7, A0h1_17, s); s = cre_dot_acc(A0h1_7, A0h1_22, s); s = cre_dot_acc(A0h1_8, A0h1_18, s);
-        s = cre_dot_acc(A0h1_8, A0h1_22, s); s = cre_dot_acc(A0h1_9, A0h1_19, s); s = cre_dot_acc(A0h1_10, A0h1_12, s);
-        s = cre_dot_acc(A0h1_10, A0h1_16, s); s = cre_dot_acc(A0h1_11, A0h1_13, s); s = cre_dot_acc(A0h1_12, A0h1_18, s);
-        s = cre_dot_acc(A0h1_12, A0h1_21, s); s = cre_dot_acc(A0h1_13, A0h1_20, s); s = cre_dot_acc(A0h1_14, A0h1_19, s);
-        s = cre_dot_acc(A0h1_14, A0h1_20, s); s = cre_dot_acc(A0h1_15, A0h1_18, s);
-        total = total + R(124.0) * s;
-      }
-      {
-        R s = cre_dot(A0h1_0, A0h1_16);
-        s = cre_dot_acc(A0h1_1, A0h1_22, s); s = cre_dot_acc(A0h1_2, A0h1_10, s); s = cre_dot_acc(A0h1_3, A0h1_20, s);
-        s = cre_dot_acc(A0h1_4, A0h1_8, s); s = cre_dot_acc(A0h1_5, A0h1_14, s); s = cre_dot_acc(A0h1_6, A0h1_17, s);
-        s = cre_dot_acc(A0h1_7, A0h1_23, s); s = cre_dot_acc(A0h1_9, A0h1_18, s); s = cre_dot_acc(A0h1_11, A0h1_12, s);
-        s = cre_dot_acc(A0h1_13, A0h1_21, s); s = cre_dot_acc(A0h1_15, A0h1_19, s);
-        total = total + R(142.0) * s;
-      }
-      {
-        R s = cre_dot(A0h1_0, A0h1_5);
-        s = cre_dot_acc(A0h1_0, A0h1_14, s); s = cre_dot_acc(A0h1_1, A0h1_3, s); s = cre_dot_acc(A0h1_1, A0h1_20, s);
-        s = cre_dot_acc(A0h1_2, A0h1_4, s); s = cre_dot_acc(A0h1_2, A0h1_8, s); s = cre_dot_acc(A0h1_3, A0h1_22, s);
-        s = cre_dot_acc(A0h1_4, A0h1_10, s); s = cre_dot_acc(A0h1_5, A0h1_16, s); s = cre_dot_acc(A0h1_6, A0h1_11, s);
-        s = cre_dot_acc(A0h1_6, A0h1_12, s); s = cre_dot_acc(A0h1_7, A0h1_9, s); s = cre_dot_acc(A0h1_7, A0h1_18, s);
-        s = cre_dot_acc(A0h1_8, A0h1_10, s); s = cre_dot_acc(A0h1_9, A0h1_23, s); s = cre_dot_acc(A0h1_11, A0h1_17, s);
-        s = cre_dot_acc(A0h1_12, A0h1_17, s); s = cre_dot_acc(A0h1_13, A0h1_15, s); s = cre_dot_acc(A0h1_13, A0h1_19, s);
-        s = cre_dot_acc(A0h1_14, A0h1_16, s); s = cre_dot_acc(A0h1_15, A0h1_21, s); s = cre_dot_acc(A0h1_18, A0h1_23, s);
-        s = cre_dot_acc(A0h1_19, A0h1_21, s); s = cre_dot_acc(A0h1_20, A0h1_22, s);
-        total = total + R(160.0) * s;
-      }
-      {
-        R s = cabs2(A0h1_0);
-        s = cabs2_acc(A0h1_1, s); s = cabs2_acc(A0h1_2, s); s = cabs2_acc(A0h1_3, s);
-        s = cabs2_acc(A0h1_4, s); s = cabs2_acc(A0h1_5, s); s = cabs2_acc(A0h1_6, s);
-        s = cabs2_acc(A0h1_7, s); s = cabs2_acc(A0h1_8, s); s = cabs2_acc(A0h1_9, s);
-        s = cabs2_acc(A0h1_10, s); s = cabs2_acc(A0h1_11, s); s = cabs2_acc(A0h1_12, s);
-        s = cabs2_acc(A0h1_13, s); s = cabs2_acc(A0h1_14, s); s = cabs2_acc(A0h1_15, s);
-        s = cabs2_acc(A0h1_16, s); s = cabs2_acc(A0h1_17, s); s = cabs2_acc(A0h1_18, s);
-        s = cabs2_acc(A0h1_19, s); s = cabs2_acc(A0h1_20, s); s = cabs2_acc(A0h1_21, s);
-        s = cabs2_acc(A0h1_22, s); s = cabs2_acc(A0h1_23, s);
-        total = total + R(512.0) * s;
-      }
-      {
-        R s = cre_dot(A1h1_0, A1h1_1);
-        s = cre_dot_acc(A1h1_0, A1h1_2, s); s = cre_dot_acc(A1h1_0, A1h1_6, s); s = cre_dot_acc(A1h1_1, A1h1_4, s);
-        s = cre_dot_acc(A1h1_1, A1h1_7, s); s = cre_dot_acc(A1h1_2, A1h1_3, s); s = cre_dot_acc(A1h1_2, A1h1_12, s);
-        s = cre_dot_acc(A1h1_3, A1h1_5, s); s = cre_dot_acc(A1h1_3, A1h1_13, s); s = cre_dot_acc(A1h1_4, A1h1_5, s);
-        s = cre_dot_acc(A1h1_4, A1h1_18, s); s = cre_dot_acc(A1h1_5, A1h1_19, s); s = cre_dot_acc(A1h1_6, A1h1_7, s);
-        s = cre_dot_acc(A1h1_6, A1h1_8, s); s = cre_dot_acc(A1h1_7, A1h1_10, s); s = cre_dot_acc(A1h1_8, A1h1_9, s);
-        s = cre_dot_acc(A1h1_8, A1h1_14, s); s = cre_dot_acc(A1h1_9, A1h1_11, s); s = cre_dot_acc(A1h1_9, A1h1_15, s);
-        s = cre_dot_acc(A1h1_10, A1h1_11, s); s = cre_dot_acc(A1h1_10, A1h1_20, s); s = cre_dot_acc(A1h1_11, A1h1_21, s);
-        s = cre_dot_acc(A1h1_12, A1h1_13, s); s = cre_dot_acc(A1h1_12, A1h1_14, s); s = cre_dot_acc(A1h1_13, A1h1_16, s);
-        s = cre_dot_acc(A1h1_14, A1h1_15, s); s = cre_dot_acc(A1h1_15, A1h1_17, s); s = cre_dot_acc(A1h1_16, A1h1_17, s);
-        s = cre_dot_acc(A1h1_16, A1h1_22, s); s = cre_dot_acc(A1h1_17, A1h1_23, s); s = cre_dot_acc(A1h1_18, A1h1_19, s);
-        s = cre_dot_acc(A1h1_18, A1h1_20, s); s = cre_dot_acc(A1h1_19, A1h1_22, s); s = cre_dot_acc(A1h1_20, A1h1_21, s);
-        s = cre_dot_acc(A1h1_21, A1h1_23, s); s = cre_dot_acc(A1h1_22, A1h1_23, s);
-        total = total + R(-128.0) * s;
-      }
-      {
-        R s = cre_dot(A1h1_0, A1h1_23);
-        s = cre_dot_acc(A1h1_1, A1h1_17, s); s = cre_dot_acc(A1h1_2, A1h1_21, s); s = cre_dot_acc(A1h1_3, A1h1_11, s);
-        s = cre_dot_acc(A1h1_4, A1h1_15, s); s = cre_dot_acc(A1h1_5, A1h1_9, s); s = cre_dot_acc(A1h1_6, A1h1_22, s);
-        s = cre_dot_acc(A1h1_7, A1h1_16, s); s = cre_dot_acc(A1h1_8, A1h1_19, s); s = cre_dot_acc(A1h1_10, A1h1_13, s);
-        s = cre_dot_acc(A1h1_12, A1h1_20, s); s = cre_dot_acc(A1h1_14, A1h1_18, s);
-        total = total + R(-56.0) * s;
-      }
-      {
-        R s = cre_dot(A1h1_0, A1h1_11);
-        s = cre_dot_acc(A1h1_0, A1h1_15, s); s = cre_dot_acc(A1h1_0, A1h1_19, s); s = cre_dot_acc(A1h1_0, A1h1_20, s);
-        s = cre_dot_acc(A1h1_1, A1h1_9, s); s = cre_dot_acc(A1h1_1, A1h1_13, s); s = cre_dot_acc(A1h1_1, A1h1_14, s);
-        s = cre_dot_acc(A1h1_1, A1h1_21, s); s = cre_dot_acc(A1h1_2, A1h1_9, s); s = cre_dot_acc(A1h1_2, A1h1_17, s);
-        s = cre_dot_acc(A1h1_2, A1h1_18, s); s = cre_dot_acc(A1h1_2, A1h1_22, s); s = cre_dot_acc(A1h1_3, A1h1_7, s);
-        s = cre_dot_acc(A1h1_3, A1h1_8, s); s = cre_dot_acc(A1h1_3, A1h1_15, s); s = cre_dot_acc(A1h1_3, A1h1_23, s);
-        s = cre_dot_acc(A1h1_4, A1h1_11, s); s = cre_dot_acc(A1h1_4, A1h1_12, s); s = cre_dot_acc(A1h1_4, A1h1_16, s);
-        s = cre_dot_acc(A1h1_4, A1h1_23, s); s = cre_dot_acc(A1h1_5, A1h1_6, s); s = cre_dot_acc(A1h1_5, A1h1_10, s);
-        s = cre_dot_acc(A1h1_5, A1h1_17, s); s = cre_dot_acc(A1h1_5, A1h1_21, s); s = cre_dot_acc(A1h1_6, A1h1_13, s);
-        s = cre_dot_acc(A1h1_6, A1h1_18, s); s = cre_dot_acc(A1h1_6, A1h1_21, s); s = cre_dot_acc(A1h1_7, A1h1_12, s);
-        s = cre_dot_acc(A1h1_7, A1h1_15, s); s = cre_dot_acc(A1h1_7, A1h1_19, s); s = cre_dot_acc(A1h1_8, A1h1_16, s);
-        s = cre_dot_acc(A1h1_8, A1h1_20, s); s = cre_dot_acc(A1h1_8, A1h1_23, s); s = cre_dot_acc(A1h1_9, A1h1_13, s);
-        s = cre_dot_acc(A1h1_9, A1h1_22, s); s = cre_dot_acc(A1h1_10, A1h1_14, s); s = cre_dot_acc(A1h1_10, A1h1_17, s);
-        s = cre_dot_acc(A1h1_10, A1h1_22, s); s = cre_dot_acc(A1h1_11, A1h1_16, s); s = cre_dot_acc(A1h1_11, A1h1_19, s);
-        s = cre_dot_acc(A1h1_12, A1h1_19, s); s = cre_dot_acc(A1h1_12, A1h1_23, s); s = cre_dot_acc(A1h1_13, A1h1_18, s);
-        s = cre_dot_acc(A1h1_14, A1h1_21, s); s = cre_dot_acc(A1h1_14, A1h1_22, s); s = cre_dot_acc(A1h1_15, A1h1_20, s);
-        s = cre_dot_acc(A1h1_16, A1h1_20, s); s = cre_dot_acc(A1h1_17, A1h1_18, s);
-        total = total + R(-20.0) * s;
-      }
-      {
-        R s = cre_dot(A1h1_0, A1h1_9);
-        s = cre_dot_acc(A1h1_0, A1h1_10, s); s = cre_dot_acc(A1h1_0, A1h1_13, s); s = cre_dot_acc(A1h1_0, A1h1_18, s);
-        s = cre_dot_acc(A1h1_1, A1h1_8, s); s = cre_dot_acc(A1h1_1, A1h1_11, s); s = cre_dot_acc(A1h1_1, A1h1_12, s);
-        s = cre_dot_acc(A1h1_1, A1h1_19, s); s = cre_dot_acc(A1h1_2, A1h1_7, s); s = cre_dot_acc(A1h1_2, A1h1_15, s);
-        s = cre_dot_acc(A1h1_2, A1h1_16, s); s = cre_dot_acc(A1h1_2, A1h1_19, s); s = cre_dot_acc(A1h1_3, A1h1_6, s);
-        s = cre_dot_acc(A1h1_3, A1h1_14, s); s = cre_dot_acc(A1h1_3, A1h1_17, s); s = cre_dot_acc(A1h1_3, A1h1_18, s);
-        s = cre_dot_acc(A1h1_4, A1h1_6, s); s = cre_dot_acc(A1h1_4, A1h1_13, s); s = cre_dot_acc(A1h1_4, A1h1_21, s);
-        s = cre_dot_acc(A1h1_4, A1h1_22, s); s = cre_dot_acc(A1h1_5, A1h1_7, s); s = cre_dot_acc(A1h1_5, A1h1_12, s);
-        s = cre_dot_acc(A1h1_5, A1h1_20, s); s = cre_dot_acc(A1h1_5, A1h1_23, s); s = cre_dot_acc(A1h1_6, A1h1_15, s);
-        s = cre_dot_acc(A1h1_6, A1h1_20, s); s = cre_dot_acc(A1h1_7, A1h1_14, s); s = cre_dot_acc(A1h1_7, A1h1_21, s);
-        s = cre_dot_acc(A1h1_8, A1h1_13, s); s = cre_dot_acc(A1h1_8, A1h1_17, s); s = cre_dot_acc(A1h1_8, A1h1_21, s);
-        s = cre_dot_acc(A1h1_9, A1h1_12, s); s = cre_dot_acc(A1h1_9, A1h1_16, s); s = cre_dot_acc(A1h1_9, A1h1_20, s);
-        s = cre_dot_acc(A1h1_10, A1h1_15, s); s = cre_dot_acc(A1h1_10, A1h1_19, s); s = cre_dot_acc(A1h1_10, A1h1_23, s);
-        s = cre_dot_acc(A1h1_11, A1h1_14, s); s = cre_dot_acc(A1h1_11, A1h1_18, s); s = cre_dot_acc(A1h1_11, A1h1_22, s);
-        s = cre_dot_acc(A1h1_12, A1h1_22, s); s = cre_dot_acc(A1h1_13, A1h1_23, s); s = cre_dot_acc(A1h1_14, A1h1_23, s);
-        s = cre_dot_acc(A1h1_15, A1h1_22, s); s = cre_dot_acc(A1h1_16, A1h1_18, s); s = cre_dot_acc(A1h1_16, A1h1_21, s);
-        s = cre_dot_acc(A1h1_17, A1h1_19, s); s = cre_dot_acc(A1h1_17, A1h1_20, s);
-        total = total + R(-2.0) * s;
-      }
-      {
-        R s = cre_dot(A1h1_0, A1h1_3);
-        s = cre_dot_acc(A1h1_0, A1h1_4, s); s = cre_dot_acc(A1h1_0, A1h1_7, s); s = cre_dot_acc(A1h1_0, A1h1_8, s);
-        s = cre_dot_acc(A1h1_0, A1h1_12, s); s = cre_dot_acc(A1h1_1, A1h1_2, s); s = cre_dot_acc(A1h1_1, A1h1_5, s);
-        s = cre_dot_acc(A1h1_1, A1h1_6, s); s = cre_dot_acc(A1h1_1, A1h1_10, s); s = cre_dot_acc(A1h1_1, A1h1_18, s);
-        s = cre_dot_acc(A1h1_2, A1h1_5, s); s = cre_dot_acc(A1h1_2, A1h1_6, s); s = cre_dot_acc(A1h1_2, A1h1_13, s);
-        s = cre_dot_acc(A1h1_2, A1h1_14, s); s = cre_dot_acc(A1h1_3, A1h1_4, s); s = cre_dot_acc(A1h1_3, A1h1_12, s);
-        s = cre_dot_acc(A1h1_3, A1h1_16, s); s = cre_dot_acc(A1h1_3, A1h1_19, s); s = cre_dot_acc(A1h1_4, A1h1_7, s);
-        s = cre_dot_acc(A1h1_4, A1h1_19, s); s = cre_dot_acc(A1h1_4, A1h1_20, s); s = cre_dot_acc(A1h1_5, A1h1_13, s);
-        s = cre_dot_acc(A1h1_5, A1h1_18, s); s = cre_dot_acc(A1h1_5, A1h1_22, s); s = cre_dot_acc(A1h1_6, A1h1_9, s);
-        s = cre_dot_acc(A1h1_6, A1h1_10, s); s = cre_dot_acc(A1h1_6, A1h1_14, s); s = cre_dot_acc(A1h1_7, A1h1_8, s);
-        s = cre_dot_acc(A1h1_7, A1h1_11, s); s = cre_dot_acc(A1h1_7, A1h1_20, s); s = cre_dot_acc(A1h1_8, A1h1_11, s);
-        s = cre_dot_acc(A1h1_8, A1h1_12, s); s = cre_dot_acc(A1h1_8, A1h1_15, s); s = cre_dot_acc(A1h1_9, A1h1_10, s);
-        s = cre_dot_acc(A1h1_9, A1h1_14, s); s = cre_dot_acc(A1h1_9, A1h1_17, s); s = cre_dot_acc(A1h1_9, A1h1_21, s);
-        s = cre_dot_acc(A1h1_10, A1h1_18, s); s = cre_dot_acc(A1h1_10, A1h1_21, s); s = cre_dot_acc(A1h1_11, A1h1_15, s);
-        s = cre_dot_acc(A1h1_11, A1h1_20, s); s = cre_dot_acc(A1h1_11, A1h1_23, s); s = cre_dot_acc(A1h1_12, A1h1_15, s);
-        s = cre_dot_acc(A1h1_12, A1h1_16, s); s = cre_dot_acc(A1h1_13, A1h1_14, s); s = cre_dot_acc(A1h1_13, A1h1_17, s);
-        s = cre_dot_acc(A1h1_13, A1h1_22, s); s = cre_dot_acc(A1h1_14, A1h1_17, s); s = cre_dot_acc(A1h1_15, A1h1_16, s);
-        s = cre_dot_acc(A1h1_15, A1h1_23, s); s = cre_dot_acc(A1h1_16, A1h1_19, s); s = cre_dot_acc(A1h1_16, A1h1_23, s);
-        s = cre_dot_acc(A1h1_17, A1h1_21, s); s = cre_dot_acc(A1h1_17, A1h1_22, s); s = cre_dot_acc(A1h1_18, A1h1_21, s);
-        s = cre_dot_acc(A1h1_18, A1h1_22, s); s = cre_dot_acc(A1h1_19, A1h1_20, s); s = cre_dot_acc(A1h1_19, A1h1_23, s);
-        s = cre_dot_acc(A1h1_20, A1h1_23, s); s = cre_dot_acc(A1h1_21, A1h1_22, s);
-        total = total + R(16.0) * s;
-      }
-      {
-        R s = cre_dot(A1h1_0, A1h1_17);
-        s = cre_dot_acc(A1h1_0, A1h1_21, s); s = cre_dot_acc(A1h1_0, A1h1_22, s); s = cre_dot_acc(A1h1_1, A1h1_15, s);
-        s = cre_dot_acc(A1h1_1, A1h1_16, s); s = cre_dot_acc(A1h1_1, A1h1_23, s); s = cre_dot_acc(A1h1_2, A1h1_11, s);
-        s = cre_dot_acc(A1h1_2, A1h1_20, s); s = cre_dot_acc(A1h1_2, A1h1_23, s); s = cre_dot_acc(A1h1_3, A1h1_9, s);
-        s = cre_dot_acc(A1h1_3, A1h1_10, s); s = cre_dot_acc(A1h1_3, A1h1_21, s); s = cre_dot_acc(A1h1_4, A1h1_9, s);
-        s = cre_dot_acc(A1h1_4, A1h1_14, s); s = cre_dot_acc(A1h1_4, A1h1_17, s); s = cre_dot_acc(A1h1_5, A1h1_8, s);
-        s = cre_dot_acc(A1h1_5, A1h1_11, s); s = cre_dot_acc(A1h1_5, A1h1_15, s); s = cre_dot_acc(A1h1_6, A1h1_16, s);
-        s = cre_dot_acc(A1h1_6, A1h1_19, s); s = cre_dot_acc(A1h1_6, A1h1_23, s); s = cre_dot_acc(A1h1_7, A1h1_13, s);
-        s = cre_dot_acc(A1h1_7, A1h1_17, s); s = cre_dot_acc(A1h1_7, A1h1_22, s); s = cre_dot_acc(A1h1_8, A1h1_18, s);
-        s = cre_dot_acc(A1h1_8, A1h1_22, s); s = cre_dot_acc(A1h1_9, A1h1_19, s); s = cre_dot_acc(A1h1_10, A1h1_12, s);
-        s = cre_dot_acc(A1h1_10, A1h1_16, s); s = cre_dot_acc(A1h1_11, A1h1_13, s); s = cre_dot_acc(A1h1_12, A1h1_18, s);
-        s = cre_dot_acc(A1h1_12, A1h1_21, s); s = cre_dot_acc(A1h1_13, A1h1_20, s); s = cre_dot_acc(A1h1_14, A1h1_19, s);
-        s = cre_dot_acc(A1h1_14, A1h1_20, s); s = cre_dot_acc(A1h1_15, A1h1_18, s);
-        total = total + R(124.0) * s;
-      }
-      {
-        R s = cre_dot(A1h1_0, A1h1_16);
-        s = cre_dot_acc(A1h1_1, A1h1_22, s); s = cre_dot_acc(A1h1_2, A1h1_10, s); s = cre_dot_acc(A1h1_3, A1h1_20, s);
-        s = cre_dot_acc(A1h1_4, A1h1_8, s); s = cre_dot_acc(A1h1_5, A1h1_14, s); s = cre_dot_acc(A1h1_6, A1h1_17, s);
-        s = cre_dot_acc(A1h1_7, A1h1_23, s); s = cre_dot_acc(A1h1_9, A1h1_18, s); s = cre_dot_acc(A1h1_11, A1h1_12, s);
-        s = cre_dot_acc(A1h1_13, A1h1_21, s); s = cre_dot_acc(A1h1_15, A1h1_19, s);
-        total = total + R(142.0) * s;
-      }
-      {
-        R s = cre_dot(A1h1_0, A1h1_5);
-        s = cre_dot_acc(A1h1_0, A1h1_14, s); s = cre_dot_acc(A1h1_1, A1h1_3, s); s = cre_dot_acc(A1h1_1, A1h1_20, s);
-        s = cre_dot_acc(A1h1_2, A1h1_4, s); s = cre_dot_acc(A1h1_2, A1h1_8, s); s = cre_dot_acc(A1h1_3, A1h1_22, s);
-        s = cre_dot_acc(A1h1_4, A1h1_10, s); s = cre_dot_acc(A1h1_5, A1h1_16, s); s = cre_dot_acc(A1h1_6, A1h1_11, s);
-        s = cre_dot_acc(A1h1_6, A1h1_12, s); s = cre_dot_acc(A1h1_7, A1h1_9, s); s = cre_dot_acc(A1h1_7, A1h1_18, s);
-        s = cre_dot_acc(A1h1_8, A1h1_10, s); s = cre_dot_acc(A1h1_9, A1h1_23, s); s = cre_dot_acc(A1h1_11, A1h1_17, s);
-        s = cre_dot_acc(A1h1_12, A1h1_17, s); s = cre_dot_acc(A1h1_13, A1h1_15, s); s = cre_dot_acc(A1h1_13, A1h1_19, s);
-        s = cre_dot_acc(A1h1_14, A1h1_16, s); s = cre_dot_acc(A1h1_15, A1h1_21, s); s = cre_dot_acc(A1h1_18, A1h1_23, s);
-        s = cre_dot_acc(A1h1_19, A1h1_21, s); s = cre_dot_acc(A1h1_20, A1h1_22, s);
-        total = total + R(160.0) * s;
-      }
-      {
-        R s = cabs2(A1h1_0);
-        s = cabs2_acc(A1h1_1, s); s = cabs2_acc(A1h1_2, s); s = cabs2_acc(A1h1_3, s);
-        s = cabs2_acc(A1h1_4, s); s = cabs2_acc(A1h1_5, s); s = cabs2_acc(A1h1_6, s);
-        s = cabs2_acc(A1h1_7, s); s = cabs2_acc(A1h1_8, s); s = cabs2_acc(A1h1_9, s);
-        s = cabs2_acc(A1h1_10, s); s = cabs2_acc(A1h1_11, s); s = cabs2_acc(A1h1_12, s);
-        s = cabs2_acc(A1h1_13, s); s = cabs2_acc(A1h1_14, s); s = cabs2_acc(A1h1_15, s);
-        s = cabs2_acc(A1h1_16, s); s = cabs2_acc(A1h1_17, s); s = cabs2_acc(A1h1_18, s);
-        s = cabs2_acc(A1h1_19, s); s = cabs2_acc(A1h1_20, s); s = cabs2_acc(A1h1_21, s);
-        s = cabs2_acc(A1h1_22, s); s = cabs2_acc(A1h1_23, s);
-        total = total + R(512.0) * s;
-      }
     }
   }
-  return total * R(1.0 / 54.0);
+  return total * R(2.0 / 54.0);
 }
 }  // namespace mf

@@ -13,6 +13,7 @@
 #include "amp.h"
 #include "gen/me_gg_m2.h"
 #include "gen/me_gg_m3.h"
+#include "gen/me_gg_m3_both.h"
 #include "gen/me_gg_m4.h"
 #include "gen/me_gg_m4_grouped.h"
 #include "qq.h"
@@ -326,7 +327,8 @@ __device__ __forceinline__ RA me_gg(double E, const V4<double>* gl, const V4<RK>
   Sp<RA> UB[2] = {ubar_spinor(t, m_a, -1), ubar_spinor(t, m_a, 1)};
   Sp<RA> VS[2] = {v_spinor(tb, m_a, -1), v_spinor(tb, m_a, 1)};
   if constexpr (m == 2) return me_gg_m2<RA, RK>(K, Ep, UB, VS, atop, mt);
-  else if constexpr (m == 3) return me_gg_m3<RA, RK>(K, Ep, UB, VS, atop, mt);
+  else if constexpr (m == 3 && fp64_amp<RA>::value) return me_gg_m3<RA, RK>(K, Ep, UB, VS, atop, mt);
+  else if constexpr (m == 3) return me_gg_m3_both<RA, RK>(K, Ep, UB, VS, atop, mt);
   else if constexpr (std::is_same<RA, float>::value) return me_gg_m4_grouped<RA, RK>(K, Ep, UB, VS, atop, mt);
   else return me_gg_m4<RA, RK>(K, Ep, UB, VS, atop, mt);
 }

@@ -122,3 +122,28 @@ def test_multi_trace_sum_small_cases():
     assert gen_me.multi_trace_sum([(0,), (0,)]) == 0  # Tr(t^a) = 0
     assert gen_me.multi_trace_sum([(0, 1), (0, 1)]) == 2  # Tr(t^a t^b)^2 = (N^2 - 1)/4
     assert gen_me.multi_trace_sum([(0, 1, 0, 1)]) == gen_me.trace_sum((0, 1, 0, 1)) == Fraction(-2, 3)
+
+
+@pytest.mark.parametrize("n_gluons", [1, 2, 3, 4])
+@pytest.mark.parametrize("lt,la", [(1, 1), (1, -1)])
+def test_flipping_both_top_helicities_conjugates_the_line(n_gluons, lt, la):
+    """ubar(t) J_1-slash (Q_1 + m) J_2-slash ... v(tb) with real vectors J, Q is, up to one sign that does
+    not depend on them, the conjugate of the same line with both helicities flipped (what lets the FP64
+    amplitudes sum over one antitop helicity).  FP64 numpy: a few hundred roundings, tolerance 1e-12."""
+    import oracle
+
+    g = oracle.gamma_matrices() * np.array([1.0, -1.0, -1.0, -1.0])[:, None, None]
+    rng = np.random.default_rng(7 + n_gluons)
+    signs = set()
+    for _ in range(8):
+        m = 1.73
+        p, q = rng.normal(size=3), rng.normal(size=3)
+        p, q = [np.concatenate([[np.sqrt(m * m + k @ k)], k]) for k in (p, q)]
+        mats = [np.einsum("m,mij->ij", rng.normal(size=4), g) + (m * np.eye(4) if i % 2 else 0.0)
+                for i in range(2 * n_gluons - 1)]
+        line = np.linalg.multi_dot(mats) if len(mats) > 1 else mats[0]
+        a = oracle.wavefunction("ubar", p, m, lt) @ line @ oracle.wavefunction("v", q, m, la)
+        b = oracle.wavefunction("ubar", p, m, -lt) @ line @ oracle.wavefunction("v", q, m, -la)
+        assert min(abs(b - a.conj()), abs(b + a.conj())) < 1e-12 * abs(a)
+        signs.add(bool(abs(b - a.conj()) < abs(b + a.conj())))
+    assert len(signs) == 1
