@@ -91,6 +91,7 @@ template <class R, class RK> __device__ __forceinline__ V4<R> cvt4(const V4<RK>&
 // register lifetimes.
 __device__ __forceinline__ void opaque(float& x) { asm volatile("" : "+v"(x)); }
 __device__ __forceinline__ void opaque(double& x) { asm volatile("" : "+v"(x)); }
+__device__ __forceinline__ void opaque(int& x) { asm volatile("" : "+v"(x)); }
 template <class T> __device__ __forceinline__ void opaque(Dual<T>& x) {
   opaque(x.v);
   opaque(x.d);
@@ -254,6 +255,64 @@ template <class R> __device__ __forceinline__ C2<R> ubar_dot(const Sp<R>& u, con
   im = im + u.s3.re * p.s3.im;
   im = im + u.s3.im * p.s3.re;
   return C2<R>{re, im};
+}
+
+// -------------------------------------------------- four lanes per event
+// Values of the lane with the other index in an aligned group of four (lane
+// xor 1, 2 or 3), by quad permutations; every lane of the wave must be active.
+constexpr int QX1 = 0xB1, QX2 = 0x4E, QX3 = 0x1B;
+template <int CTRL> __device__ __forceinline__ int quad1(int x) {
+  return __builtin_amdgcn_mov_dpp(x, CTRL, 0xF, 0xF, true);
+}
+template <int CTRL> __device__ __forceinline__ float quad1(float x) {
+  return __int_as_float(quad1<CTRL>(__float_as_int(x)));
+}
+template <int CTRL> __device__ __forceinline__ double quad1(double x) {
+  return __hiloint2double(quad1<CTRL>(__double2hiint(x)), quad1<CTRL>(__double2loint(x)));
+}
+template <int CTRL, class R> __device__ __forceinline__ C2<R> quad2(const C2<R>& a) {
+  return C2<R>{quad1<CTRL>(a.re), quad1<CTRL>(a.im)};
+}
+template <int CTRL, class R> __device__ __forceinline__ V4<R> quad4(const V4<R>& a) {
+  return V4<R>{quad1<CTRL>(a.t), quad1<CTRL>(a.x), quad1<CTRL>(a.y), quad1<CTRL>(a.z)};
+}
+// Polarisation state hg of four gluons (gluon i is bit 3 - i) in the labels
+// of a lane: bit r is the polarisation of gluon r ^ role.
+__device__ __forceinline__ int quad_roles(int hg, int role) {
+  int b = ((hg & 1) << 3) | ((hg & 2) << 1) | ((hg & 4) >> 1) | ((hg & 8) >> 3);
+  b = (role & 1) ? ((b & 5) << 1) | ((b & 10) >> 1) : b;
+  return (role & 2) ? ((b & 3) << 2) | ((b & 12) >> 2) : b;
+}
+// a[r] becomes a[r ^ role] for four values.
+template <class T> __device__ __forceinline__ void quad_relabel(T& a0, T& a1, T& a2, T& a3, int role) {
+  const T b0 = (role & 1) ? a1 : a0, b1 = (role & 1) ? a0 : a1, b2 = (role & 1) ? a3 : a2, b3 = (role & 1) ? a2 : a3;
+  a0 = (role & 2) ? b2 : b0;
+  a1 = (role & 2) ? b3 : b1;
+  a2 = (role & 2) ? b0 : b2;
+  a3 = (role & 2) ? b1 : b3;
+}
+template <class R> __device__ __forceinline__ void quad_relabel(V4<R>* a, int stride, int role) {
+  quad_relabel(a[0].t, a[stride].t, a[2 * stride].t, a[3 * stride].t, role);
+  quad_relabel(a[0].x, a[stride].x, a[2 * stride].x, a[3 * stride].x, role);
+  quad_relabel(a[0].y, a[stride].y, a[2 * stride].y, a[3 * stride].y, role);
+  quad_relabel(a[0].z, a[stride].z, a[2 * stride].z, a[3 * stride].z, role);
+}
+// A lane's column of a table with W lanes.
+template <int W, class R> __device__ __forceinline__ void quad_put4(R* t, const V4<R>& a) {
+  t[0] = a.t;
+  t[W] = a.x;
+  t[2 * W] = a.y;
+  t[3 * W] = a.z;
+}
+template <int W, class R> __device__ __forceinline__ V4<R> quad_get4(const R* t) {
+  return V4<R>{t[0], t[W], t[2 * W], t[3 * W]};
+}
+template <int W, class R> __device__ __forceinline__ void quad_put_sp(R* t, const Sp<R>& a) {
+  quad_put4<W>(t, V4<R>{a.s0.re, a.s0.im, a.s1.re, a.s1.im});
+  quad_put4<W>(t + 4 * W, V4<R>{a.s2.re, a.s2.im, a.s3.re, a.s3.im});
+}
+template <int W, class R> __device__ __forceinline__ Sp<R> quad_get_sp(const R* t) {
+  return Sp<R>{C2<R>{t[0], t[W]}, C2<R>{t[2 * W], t[3 * W]}, C2<R>{t[4 * W], t[5 * W]}, C2<R>{t[6 * W], t[7 * W]}};
 }
 
 // ------------------------------------------------- external wavefunctions

@@ -62,24 +62,73 @@ __global__ void __launch_bounds__(BLOCK) k_select_points(DevCfg c, const double*
   if (tid == 0) cnt[blockIdx.x] = qn;
 }
 
-template <int NG, int CH, class RA>
+// Running offsets of the selection blocks' lists in LDS: pre[b] is the number
+// of entries of the blocks before b, pre[nblk] the total.  All threads of the
+// block take part.
+__device__ __forceinline__ void list_offsets(const int* __restrict__ cnt, int nblk, int* pre) {
+  constexpr int PER = MAX_BLOCKS / BLOCK;
+  __shared__ int wsum[WAVES];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int v[PER], s = 0;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int b = tid * PER + k;
+    v[k] = b < nblk ? cnt[b] : 0;
+    s += v[k];
+  }
+  int inc = s;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int o = __shfl_up(inc, off);
+    inc += lane >= off ? o : 0;
+  }
+  if (lane == 63) wsum[wave] = inc;
+  __syncthreads();
+  int base = inc - s;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) base += w < wave ? wsum[w] : 0;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int b = tid * PER + k;
+    if (b <= nblk) pre[b] = base;
+    base += v[k];
+  }
+  if (tid == BLOCK - 1 && nblk == MAX_BLOCKS) pre[nblk] = base;
+  __syncthreads();
+}
+// The g-th entry of the lists laid end to end (0 <= g < pre[nblk]).
+__device__ __forceinline__ int list_entry(const int* __restrict__ list, int64_t cap, const int* pre, int nblk, int g) {
+  int lo = 0, hi = nblk;  // pre[lo] <= g < pre[hi]
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (pre[mid] <= g) lo = mid; else hi = mid;
+  }
+  return list[(int64_t)lo * cap + (g - pre[lo])];
+}
+
+// The kept points, numbered through all blocks' lists and dealt out in chunks
+// of BLOCK / LANES, so that every block has full chunks whatever share of its
+// own points passed (a chunk of 256 points keeps 90 to 150 of them).
+template <int NG, int CH, class RA, int LANES>
 __global__ void __launch_bounds__(BLOCK) k_integrand(DevCfg c, const double* __restrict__ u, int64_t n,
                                                      double* __restrict__ w, const int* __restrict__ list,
-                                                     const int* __restrict__ cnt, int64_t cap) {
-  const int* mine_list = list + (int64_t)blockIdx.x * cap;
-  const int nsel = __builtin_amdgcn_readfirstlane(cnt[blockIdx.x]);
-  const int64_t nchunk = (nsel + BLOCK - 1) / BLOCK;
-  for (int64_t it = 0; it < nchunk; ++it) {
-    const int64_t j0 = it * BLOCK + threadIdx.x;
+                                                     const int* __restrict__ cnt, int nblk, int64_t cap) {
+  __shared__ int pre[MAX_BLOCKS + 1];
+  list_offsets(cnt, nblk, pre);
+  const int nsel = __builtin_amdgcn_readfirstlane(pre[nblk]);
+  constexpr int PER = BLOCK / LANES;
+  for (int64_t j = (int64_t)blockIdx.x * PER; j < nsel; j += (int64_t)gridDim.x * PER) {
+    const int64_t j0 = j + threadIdx.x / LANES;
     const bool live = j0 < nsel;
-    const int64_t e = mine_list[live ? j0 : 0];  // idle lanes recompute the block's first point
+    // idle lanes recompute the last point
+    const int64_t e = list_entry(list, cap, pre, nblk, (int)(live ? j0 : nsel - 1));
     double x[MAXD];
 #pragma unroll
-    for (int j = 0; j < MAXD; ++j)
-      if (j < c.ndim) x[j] = u[(int64_t)j * n + e];
-    EventOut<double> r = event_weight<NG, CH, RA, double>(c, x, c.mt, c.pdfc);
+    for (int k = 0; k < MAXD; ++k)
+      if (k < c.ndim) x[k] = u[(int64_t)k * n + e];
+    EventOut<double> r = event_weight<NG, CH, RA, double, LANES>(c, x, c.mt, c.pdfc);
     const double v = isfinite(r.w) ? r.w : 0.0;
-    if (live) w[e] = v;
+    if (live && threadIdx.x % LANES == 0) w[e] = v;
   }
 }
 
@@ -505,23 +554,31 @@ __global__ void __launch_bounds__(BLOCK) k_grad_vegas(DevCfg c, const double* __
 }  // namespace
 
 // Launcher table of one (final gluons, channel, amplitude type) instance;
-// GRAD = 0 leaves the derivative kernels out.
-template <int NG, int CH, class RA, class RD, int GRAD, int FUSED = 1>
+// GRAD = 0 leaves the derivative kernels out, FUSED = 0 the fused iteration;
+// LANES: lanes per event of the integrand at given points.
+template <int NG, int CH, class RA, class RD, int GRAD, int FUSED = 1, int LANES = 1>
 Launchers make_launchers() {
   Launchers L;
   L.fused = FUSED != 0;
   L.integrand = [](const DevCfg& c, const double* u, int64_t n, double* w, int nblk, int* list, int* cnt,
                    int64_t cap, hipStream_t s) {
     hipLaunchKernelGGL((k_select_points<NG>), dim3(nblk), dim3(BLOCK), 0, s, c, u, n, w, list, cnt, cap);
-    hipLaunchKernelGGL((k_integrand<NG, CH, RA>), dim3(nblk), dim3(BLOCK), 0, s, c, u, n, w, list, cnt, cap);
+    // enough blocks for every kept point, in one round of the chip at most
+    // (the kernels hold one or two blocks per compute unit)
+    const int64_t want = (n * LANES + BLOCK - 1) / BLOCK;
+    hipLaunchKernelGGL((k_integrand<NG, CH, RA, LANES>), dim3((unsigned)(want < 512 ? want : 512)), dim3(BLOCK), 0, s, c,
+                       u, n, w, list, cnt, nblk, cap);
   };
-  L.vegas = [](const DevCfg& c, const double* edges, uint64_t iter, int64_t N, uint64_t seed, double* part,
-               int pstride, int nblk, size_t lds, int* list, int* cnt, int64_t cap, double* wk, hipStream_t s) {
-    hipLaunchKernelGGL((k_select<NG>), dim3(nblk), dim3(BLOCK), sizeof(double) * c.ndim * (c.nb + 1), s, c, edges,
-                       iter, N, seed, list, cnt, cap);
-    hipLaunchKernelGGL((k_vegas<NG, CH, RA>), dim3(nblk), dim3(BLOCK), lds, s, c, edges, iter, N, seed, part, pstride,
-                       list, cnt, cap, wk);
-  };
+  L.vegas = nullptr;
+  if constexpr (FUSED != 0) {
+    L.vegas = [](const DevCfg& c, const double* edges, uint64_t iter, int64_t N, uint64_t seed, double* part,
+                 int pstride, int nblk, size_t lds, int* list, int* cnt, int64_t cap, double* wk, hipStream_t s) {
+      hipLaunchKernelGGL((k_select<NG>), dim3(nblk), dim3(BLOCK), sizeof(double) * c.ndim * (c.nb + 1), s, c, edges,
+                         iter, N, seed, list, cnt, cap);
+      hipLaunchKernelGGL((k_vegas<NG, CH, RA>), dim3(nblk), dim3(BLOCK), lds, s, c, edges, iter, N, seed, part, pstride,
+                         list, cnt, cap, wk);
+    };
+  }
   L.observables = [](const DevCfg& c, const double* edges, uint64_t iter, uint64_t seed, const int* list,
                      const int* cnt, int64_t cap, const double* wk, const ObsSpec& o, double* opart, int nblk,
                      hipStream_t s) {

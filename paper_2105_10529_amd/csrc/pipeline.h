@@ -16,6 +16,7 @@
 #include "gen/me_gg_m3_both.h"
 #include "gen/me_gg_m4.h"
 #include "gen/me_gg_m4_grouped.h"
+#include "gen/me_gg_m4_quad.h"
 #include "qq.h"
 
 namespace mf {
@@ -304,8 +305,9 @@ __device__ __forceinline__ Dual<float> to_amp_s(Dual<double> x, Dual<float>*) { 
 // Colour- and polarisation-summed |M|^2 (g = 1) for g g -> t t~ + NG g.
 // E: beam energy; gluons in emission order; top/atop from the phase space.
 // Momenta and per-event invariants stay in the kinematic type RK; the
-// helicity loops run in the amplitude type RA.
-template <int NG, class RA, class RK>
+// helicity loops run in the amplitude type RA.  LANES = 4: called by the four
+// lanes of an aligned group with the same event, which share its work.
+template <int NG, class RA, class RK, int LANES = 1>
 __device__ __forceinline__ RA me_gg(double E, const V4<double>* gl, const V4<RK>& top, const V4<RK>& atop, RK mt) {
   constexpr int m = NG + 2;
   V4<RK> K[m];
@@ -326,7 +328,18 @@ __device__ __forceinline__ RA me_gg(double E, const V4<double>* gl, const V4<RK>
   V4<RA> t = cvt4<RA>(top), tb = cvt4<RA>(atop);
   Sp<RA> UB[2] = {ubar_spinor(t, m_a, -1), ubar_spinor(t, m_a, 1)};
   Sp<RA> VS[2] = {v_spinor(tb, m_a, -1), v_spinor(tb, m_a, 1)};
-  if constexpr (m == 2) return me_gg_m2<RA, RK>(K, Ep, UB, VS, atop, mt);
+  if constexpr (LANES == 4) {
+    static_assert(m == 4 && std::is_same<RA, double>::value && std::is_same<RK, double>::value, "FP64, four gluons");
+    const int role = threadIdx.x & 3;
+    quad_relabel(K, 1, role);
+    quad_relabel(&Ep[0][0], 2, role);
+    quad_relabel(&Ep[0][1], 2, role);
+    // one table per wave of a 256-thread block: its rows are within the reach
+    // of an LDS instruction's 16-bit offset
+    constexpr int W = 64;
+    __shared__ double tab[4][ME_M4_QUAD_TAB * W];
+    return me_gg_m4_quad<RA, W>(K, Ep, UB, VS[0], atop, mt, role, tab[threadIdx.x >> 6] + (threadIdx.x & 63));
+  } else if constexpr (m == 2) return me_gg_m2<RA, RK>(K, Ep, UB, VS, atop, mt);
   else if constexpr (m == 3 && fp64_amp<RA>::value) return me_gg_m3<RA, RK>(K, Ep, UB, VS, atop, mt);
   else if constexpr (m == 3) return me_gg_m3_both<RA, RK>(K, Ep, UB, VS, atop, mt);
   else if constexpr (std::is_same<RA, float>::value) return me_gg_m4_grouped<RA, RK>(K, Ep, UB, VS, atop, mt);
@@ -424,7 +437,7 @@ __device__ __forceinline__ bool event_passes(const DevCfg& c, const double* x) {
 // an event below threshold or outside the cuts is evaluated on safe
 // kinematics and its weight is selected to zero, so the amplitude code never
 // runs under a partial execution mask.
-template <int NG, int CH, class RA, class RK>
+template <int NG, int CH, class RA, class RK, int LANES = 1>
 __device__ __forceinline__ EventOut<RK> event_weight(const DevCfg& c, const double* x, RK mt, const double* pdf) {
   EventOut<RK> out;
   double x1 = x[0], x2 = x[1];
@@ -445,7 +458,7 @@ __device__ __forceinline__ EventOut<RK> event_weight(const DevCfg& c, const doub
   const RK zero = RK(0.0);
   const double tq = c.dyn_scale ? q_position(half_ht<NG>(val(mt), top, atop, gl)) : 0.0;
   if constexpr (CH == 0) {
-    RK me = to_k(me_gg<NG, RA, RK>(E, gl, top, atop, mt), (RK*)nullptr);
+    RK me = to_k(me_gg<NG, RA, RK, LANES>(E, gl, top, atop, mt), (RK*)nullptr);
     RK r1 = pre * me;
     RK w = r1 * RK(pdf_at(c, pdf, 0, out.t1, tq) * pdf_at(c, pdf, 0, out.t2, tq));
     out.r1 = ok ? r1 : zero;

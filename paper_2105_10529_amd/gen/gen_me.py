@@ -591,6 +591,206 @@ def emit_me_per_ordering(m: int, share_antitop: bool = False, pair_orderings=Fal
     return "\n".join(L) + "\n"
 
 
+def quad_imports():
+    """Gluon currents that a lane of a quad takes from another one (see
+    emit_me_quad): {needed roles: (roles computed by that lane, lane xor)},
+    every ordered pair and triple of the four gluons up to reversal."""
+    own = [(0, 1), (0, 2), (0, 3), (0, 1, 2), (1, 0, 2), (0, 2, 1)]
+    out = {}
+    for seq in own:
+        for k in (1, 2, 3):
+            img = tuple(i ^ k for i in seq)
+            if img not in own and img[::-1] not in own and img not in out and img[::-1] not in out:
+                out[img] = (seq, k)
+    return own, out
+
+
+def emit_me_quad() -> str:
+    """g g -> t t~ g g with four lanes per event, for FP64 amplitudes.
+
+    Lane l of an aligned group of four takes the six orderings that end with
+    gluon 3 ^ l: it runs the code of the orderings (x, y, z, 3) with every
+    gluon label ("role") r standing for gluon r ^ l.  A current that lane
+    l ^ k has built from roles (r1, r2, ..) is the current of roles
+    (r1 ^ k, r2 ^ k, ..) in lane l, so each lane builds three of the six
+    two-gluon and three of the twelve three-gluon currents and takes the
+    others from its neighbours by quad permutations; the spinor currents are
+    those of its own orderings and are built nowhere else.  The colour form is
+    split the same way: lane l sums over its own orderings and, with lane
+    l ^ k, over the pairs (i, j) of their six each, i < j taken by one lane
+    with twice the weight and i = j by both.  One antitop helicity and twice
+    the sum, as in emit_me_per_ordering(one_antitop).  The per-event constants
+    but the momenta are read from a column of LDS per lane where they are
+    used, through an offset the compiler cannot see through, so that they
+    neither fill registers across the loop nor cost instructions to fetch from
+    the accumulation registers.
+
+    One lane per event needs 48 FP64 amplitudes at once, spills 1.1 KB and
+    builds most currents twice (an ordering pair at a time); four lanes need
+    12 each, no scratch, and build every current once.  VALU issue bounds it
+    (94 % of the wave cycles): two iterations of 1e6 events (1.5e6 kept)
+    25.8 ms with one lane per event, 14.0 ms with four."""
+    m = 4
+    perms, Z, den = colour_matrix(m)
+    index = {sq: k for k, sq in enumerate(perms)}
+    own, imports = quad_imports()
+    orders = [tuple(q) + (3,) for q in itertools.permutations(range(3))]
+    L = []
+    w = L.append
+    w("// Generated by gen_me.py for g g -> t t~ + 2 g (4 gluons on the top line,")
+    w("// 24 colour orderings, 64 helicity/polarisation states): four lanes per event,")
+    w("// six orderings each. Do not edit.")
+    w("#pragma once")
+    w('#include "amp.h"')
+    w("namespace mf {")
+    masks_g = sorted({_mask(sq) for sq in own} | {15})
+    masks_q = list(range(8, 15))
+    base_u, base_v = 8 * m, 8 * m + 16
+    base_g = base_v + 8
+    base_q = base_g + len(masks_g)
+    w(f"constexpr int ME_M4_QUAD_TAB = {base_q + len(masks_q)};  // table values per lane")
+    w("// Colour- and polarisation-summed |M|^2 with g = 1, summed over the four")
+    w("// lanes of the group (every lane returns it).  K[r], E[r]: outgoing momentum")
+    w("// and polarisation vectors of gluon r ^ role, role = lane & 3; UB: ubar(top)")
+    w("// of both helicities, VS: v(antitop) of helicity 0; tab: LDS, value i of")
+    w("// this lane at tab[i * W].")
+    w("template <class R, int W>")
+    w("__device__ __forceinline__ R me_gg_m4_quad(const V4<R>* K, const V4<R> (*E)[2], const Sp<R>* UB, const Sp<R>& VS,")
+    w("                                           const V4<R>& PTB, R MT, int role, R* tab) {")
+
+    def ksum(s_):
+        return " + ".join(f"K[{i}]" for i in range(m) if s_ >> i & 1)
+
+    w("#pragma unroll")
+    w(f"  for (int i = 0; i < {2 * m}; ++i) quad_put4<W>(tab + 4 * i * W, E[i >> 1][i & 1]);")
+    w(f"  quad_put_sp<W>(tab + {base_u} * W, UB[0]);")
+    w(f"  quad_put_sp<W>(tab + {base_u + 8} * W, UB[1]);")
+    w(f"  quad_put_sp<W>(tab + {base_v} * W, VS);")
+    for n_, s_ in enumerate(masks_g):
+        w(f"  {{ const V4<R> P = {ksum(s_)}; tab[{base_g + n_} * W] = R(-1.0) / mdot(P, P); }}")
+    for n_, s_ in enumerate(masks_q):
+        w(f"  {{ const V4<R> P = {ksum(s_)}; tab[{base_q + n_} * W] = R(-1.0) / (R(2.0) * mdot(PTB, P) + mdot(P, P)); }}")
+    gidx = {s_: base_g + n_ for n_, s_ in enumerate(masks_g)}
+    qidx = {s_: base_q + n_ for n_, s_ in enumerate(masks_q)}
+    w("  R total = R(0.0);")
+    w("#pragma unroll 1")
+    w(f"  for (int hg = 0; hg < {1 << m}; ++hg) {{")
+    w("    // bit r: the polarisation of gluon r ^ role (gluon 0 is bit 3 of hg)")
+    w("    const int hr = quad_roles(hg, role);")
+    ind = "    "
+    for i in range(m):
+        w(f"{ind}const V4<R> E{i} = quad_get4<W>(tab + (4 * ({2 * i} + ((hr >> {i}) & 1))) * W);")
+    for i in range(m):
+        w(f"{ind}V4<R> J{i} = E{i}; opaque4(J{i});")
+        w(f"{ind}V4<R> k{i} = K[{i}]; opaque4(k{i});")
+    w(f"{ind}V4<R> pb = PTB; opaque4(pb);")
+    w(f"{ind}int z_ = 0; opaque(z_);")
+    done = set(f"J{i}" for i in range(m))
+    psum = set()
+
+    def P(sq):
+        s_ = _mask(sq)
+        if len(sq) == 1:
+            return f"k{sq[0]}"
+        if f"p{s_}" not in psum:
+            w(f"{ind}const V4<R> p{s_} = " + " + ".join(f"k{i}" for i in sorted(sq)) + ";")
+            psum.add(f"p{s_}")
+        return f"p{s_}"
+
+    def J(sq):
+        nm = f"J{_name(sq)}"
+        if nm in done:
+            return nm
+        rev = sq[::-1]
+        if f"J{_name(rev)}" in done or (sq not in own and sq not in imports and (rev in own or rev in imports)):
+            r = J(rev)
+            if len(sq) % 2 == 1:
+                return r
+            w(f"{ind}const V4<R> {nm} = R(-1.0) * {r};")
+        elif sq in imports:
+            src, k = imports[sq]
+            w(f"{ind}const V4<R> {nm} = quad4<QX{k}>({J(src)});")
+        else:
+            t3 = [(J(sq[:j]), J(sq[j:]), P(sq[:j]), P(sq[j:])) for j in range(1, len(sq))]
+            t4 = [(J(sq[:j]), J(sq[j:l]), J(sq[l:])) for j in range(1, len(sq) - 1) for l in range(j + 1, len(sq))]
+            const = "" if sq in own else "const "
+            w(f"{ind}{const}V4<R> {nm} = tab[z_ + {gidx[_mask(sq)]} * W] * ({_vsum(t3, t4)});")
+        done.add(nm)
+        return nm
+
+    def S(sq):
+        if not sq:
+            return "S_"
+        nm = f"S_{_name(sq)}"
+        if nm in done:
+            return nm
+        terms = [(J(sq[:j]), S(sq[j:])) for j in range(1, len(sq) + 1)]
+        w(f"{ind}const Sp<R> {nm} = prop_neg(pb + {P(sq)}, MT, tab[z_ + {qidx[_mask(sq)]} * W], {_ssum(terms)});")
+        done.add(nm)
+        return nm
+
+    # the lane's own exchanged currents, which stay for the whole state; what
+    # comes from the other lanes and the sums of momenta are formed again for
+    # each pair of orderings (opaque copies in place), so that they do not
+    # stay in registers
+    for sq in own:
+        J(sq)
+    keep = set(f"J{i}" for i in range(m)) | {f"J{_name(sq)}" for sq in own}
+    w(f"{ind}Sp<R> S_3;")
+    w(f"{ind}C2<R> " + ", ".join(f"A{t}_{q}" for q in range(6) for t in range(2)) + ";")
+    outer = ind
+    for z in range(3):
+        w(f"{outer}{{  // orderings (x, y, {z}, 3)")
+        ind = outer + "  "
+        done = set(keep)
+        psum = set()
+        for v in sorted(keep):
+            w(f"{ind}opaque4({v});")
+        w(f"{ind}" + " ".join(f"opaque4(k{i});" for i in range(m)) + " opaque4(pb); opaque(z_);")
+        w(f"{ind}const Sp<R> S_ = quad_get_sp<W>(tab + z_ + {base_v} * W);")
+        if z == 0:
+            w(f"{ind}S_3 = prop_neg(pb + k3, MT, tab[z_ + {qidx[8]} * W], slash(J3, S_));")
+        else:
+            w(f"{ind}opaque_sp(S_3);")
+        done.add("S_3")
+        for q, sq in enumerate(orders):
+            if sq[2] != z:
+                continue
+            terms = [(J(sq[:j]), S(sq[j:])) for j in range(1, m + 1)]
+            w(f"{ind}const Sp<R> F{q} = {_ssum(terms)};")
+            w(f"{ind}A0_{q} = ubar_dot(quad_get_sp<W>(tab + z_ + {base_u} * W), F{q});")
+            w(f"{ind}A1_{q} = ubar_dot(quad_get_sp<W>(tab + z_ + {base_u + 8} * W), F{q});")
+            w(f"{ind}opaque(z_);")
+        w(f"{outer}}}")
+    ind = outer
+    for k in range(4):
+        groups = {}
+        for i, si in enumerate(orders):
+            for j in range(i, len(orders)):
+                c = Z[index[si]][index[tuple(g ^ k for g in orders[j])]] * (1 if i == j else 2)
+                groups.setdefault(c, []).append((i, j))
+        for t in range(2):
+            w(f"{ind}{{")
+            for j in range(len(orders)):
+                if k:
+                    w(f"{ind}  const C2<R> B{j} = quad2<QX{k}>(A{t}_{j});")
+                else:
+                    w(f"{ind}  const C2<R> B{j} = A{t}_{j};")
+            for c, lst in sorted(groups.items()):
+                e = "R(0.0)"
+                for n_, (i, j) in enumerate(lst):
+                    e = f"cre_dot(A{t}_{i}, B{j})" if n_ == 0 else f"cre_dot_acc(A{t}_{i}, B{j}, {e})"
+                w(f"{ind}  total = total + R({c}.0) * {e};")
+            w(f"{ind}}}")
+    w("  }")
+    w("  total = total + quad1<QX1>(total);")
+    w("  total = total + quad1<QX2>(total);")
+    w(f"  return total * R(2.0 / {den}.0);")
+    w("}")
+    w("}  // namespace mf")
+    return "\n".join(L) + "\n"
+
+
 def emit_amp_store(m: int) -> str:
     """Partial amplitudes of m gluons for a range of gluon polarisation
     states, stored for a separate colour sum (no colour form here): the same
@@ -891,7 +1091,7 @@ def main(outdir: str, ms=(2, 3, 4, 5)) -> None:
     # matrix-core colour sum; the colour matrix of the quark channels
     for name, text in (("me_gg_m3_both.h", emit_me_per_ordering(3, True, "all", "_both")),
                        ("me_gg_m4_grouped.h", emit_me_per_ordering(4, True, "last", "_grouped")),
-                       ("amps_gg_m4.h", emit_amp_store(4)), ("colour_qq.h", emit_colour_qq())):
+                       ("me_gg_m4_quad.h", emit_me_quad()), ("amps_gg_m4.h", emit_amp_store(4)), ("colour_qq.h", emit_colour_qq())):
         path = os.path.join(outdir, name)
         old = open(path).read() if os.path.exists(path) else None
         if old != text:

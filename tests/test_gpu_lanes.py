@@ -1,0 +1,41 @@
+"""Integrands evaluated by several lanes per event, at the sizes where the
+lists of kept points and the groups of lanes have remainders (marker gpu)."""
+import numpy as np
+import pytest
+
+import oracle
+import seeded_inputs as si
+from gpu_util import assert_close, to_dev_soa
+
+import paper_2105_10529_amd as mf
+
+pytestmark = pytest.mark.gpu
+
+
+# one group of lanes, a wave (16 events), a block (64), a selection block (256
+# points) and their neighbours; no point kept (all below threshold)
+@pytest.mark.parametrize("n", [1, 2, 15, 16, 17, 63, 64, 65, 255, 256, 257, 1500])
+def test_ttgg_fp64_four_lanes_match_the_oracle(n):
+    """FP64 on both sides: the tolerance of the other FP64 integrand tests (1e-11 relative, 1e-14 of the
+    largest weight)."""
+    x = si.points_above_threshold(8 * n + 64, 10, 13000.0, 173.0, seed=100 + n)
+    orc = oracle.Oracle(oracle.Config(n_g=2, dr_min=0.4))
+    ref = orc.integrand(x)
+    # n points of which at least one passes, in their drawn order
+    first = int(np.flatnonzero(ref)[0])
+    x, ref = x[first:first + n], ref[first:first + n]
+    p = mf.Process(mf.Config(process="gg>ttxgg", dr_min=0.4))
+    import torch
+
+    u = to_dev_soa(x)
+    w = p.integrand(u)
+    assert_close(w.cpu().numpy(), ref, 1e-11)
+    w2 = torch.empty_like(w)
+    p.integrand_noalloc(u, w2)
+    assert torch.equal(w, w2)
+
+
+def test_ttgg_fp64_no_point_kept():
+    p = mf.Process(mf.Config(process="gg>ttxgg", dr_min=0.4))
+    u = to_dev_soa(np.full((300, 10), 1e-3))  # x1 x2 far below threshold
+    assert float(p.integrand(u).abs().max()) == 0.0
