@@ -371,7 +371,10 @@ template <class R> __device__ __forceinline__ Sp<R> u_spinor(const V4<R>& p, R m
 }
 
 // q(p1) q~(p2) -> t t~: colour- and helicity-summed |M|^2 (g = 1) of the
-// s-channel gluon diagram; colour factor sum Tr(t^a t^b)^2 = 2.
+// s-channel gluon diagram; colour factor sum Tr(t^a t^b)^2 = 2.  The massless
+// line conserves chirality (q and q~ of opposite helicity, the others give
+// exact zeros), and flipping all helicities conjugates the amplitude: one
+// light helicity, twice the sum.
 template <class RA, class RK>
 __device__ __forceinline__ RA me_qqbar(const V4<double>& p1, const V4<double>& p2, const V4<RK>& top,
                                        const V4<RK>& atop, RK mt) {
@@ -382,20 +385,19 @@ __device__ __forceinline__ RA me_qqbar(const V4<double>& p1, const V4<double>& p
   V4<RA> P = a + b;
   RA sh = mdot(P, P);
   RA tot = RA(0.0);
+  C2<RA> ji[4];
+  vcurrent(dbar(v_spinor(b, z, -1)), u_spinor(a, z, 1), ji);
 #pragma unroll 1
-  for (int h = 0; h < 16; ++h) {
-    int l1 = (h & 8) ? 1 : -1, l2 = (h & 4) ? 1 : -1, l3 = (h & 2) ? 1 : -1, l4 = (h & 1) ? 1 : -1;
-    Sp<RA> u1 = u_spinor(a, z, l1);
-    Sp<RA> vb2 = dbar(v_spinor(b, z, l2));
+  for (int h = 0; h < 4; ++h) {
+    int l3 = (h & 2) ? 1 : -1, l4 = (h & 1) ? 1 : -1;
     Sp<RA> ub3 = ubar_spinor(t, m_a, l3);
     Sp<RA> v4 = v_spinor(tb, m_a, l4);
-    C2<RA> ji[4], jo[4];
-    vcurrent(vb2, u1, ji);
+    C2<RA> jo[4];
     vcurrent(ub3, v4, jo);
     C2<RA> amp = cmul(jo[0], ji[0]) - cmul(jo[1], ji[1]) - cmul(jo[2], ji[2]) - cmul(jo[3], ji[3]);
     tot = tot + cabs2(amp);
   }
-  return RA(2.0) * tot / (sh * sh);
+  return RA(4.0) * tot / (sh * sh);
 }
 
 // --------------------------------------------------------- event weight

@@ -78,6 +78,80 @@ template <class R> __device__ __forceinline__ R colour_form5(const C2<R>* K) {
   return t * R(1.0 / QQ_CC_DEN);
 }
 
+// slash(J) psi and row slash(J) for a complex four-vector (contravariant
+// components).
+template <class R> struct SlashC {
+  C2<R> a, b, c, d;  // J0 - J3, J0 + J3, J1 - i J2, J1 + i J2
+  __device__ __forceinline__ explicit SlashC(const CV4<R>& J)
+      : a(J.c[0] - J.c[3]), b(J.c[0] + J.c[3]),
+        c(C2<R>{J.c[1].re + J.c[2].im, J.c[1].im - J.c[2].re}),
+        d(C2<R>{J.c[1].re - J.c[2].im, J.c[1].im + J.c[2].re}) {}
+  __device__ __forceinline__ Sp<R> col(const Sp<R>& p) const {
+    return Sp<R>{cmul(a, p.s2) - cmul(c, p.s3), cmul(b, p.s3) - cmul(d, p.s2), cmul(b, p.s0) + cmul(c, p.s1),
+                 cmul(d, p.s0) + cmul(a, p.s1)};
+  }
+  __device__ __forceinline__ Sp<R> row(const Sp<R>& r) const {
+    return Sp<R>{cmul(r.s2, b) + cmul(r.s3, d), cmul(r.s2, c) + cmul(r.s3, a), cmul(r.s0, a) - cmul(r.s1, d),
+                 cmul(r.s1, b) - cmul(r.s0, c)};
+  }
+};
+
+// Which helicities are summed.  The light quark is massless, so a helicity
+// assignment of its line that does not conserve chirality contributes exact
+// zeros: one helicity of the line fixes the other end.  And with real
+// polarisation vectors flipping every helicity conjugates the four diagrams
+// of the fermion lines and the three-gluon one up to a common sign each,
+// opposite for the two (the factors -i of the former), under which the colour
+// form with its real block and imaginary border is invariant; so the light
+// helicity + stands for both and the sum is doubled: 8 of the 32 helicity
+// states.  What depends on the light line alone is built once per
+// polarisation, what depends on one end of the top line once per end, and the
+// light current is applied to the top spinors once.  VALU-bound, FP64:
+// q g -> t t~ q, two iterations of 1e6 events (1.7e6 kept), 6.17 -> 1.72 ms;
+// u u~ -> t t~ g at 1e5 points 248 -> 38 us, its derivatives 1497 -> 322 us.
+
+// Sum over the top and antitop helicities and the polarisations E of the
+// gluon.  X0, X1[pol]: the light current with the gluon on its incoming or
+// other end, propagators included; JL: without it, times iL at the top line;
+// a3, a4: momenta of the top propagators next to the top and the antitop, f3,
+// f4 their factors; kg: the gluon's incoming momentum, qL that of JL, q34 the
+// top pair's; i5: propagators of the three-gluon diagram.
+template <class R>
+__device__ __forceinline__ R top_line_sum(const CV4<R>* X0, const CV4<R>* X1, const CV4<R>& JL, R iL, const V4<R>* E,
+                                          const V4<R>& pt, const V4<R>& ptb, R mt, const V4<R>& a3, R f3,
+                                          const V4<R>& a4, R f4, const V4<R>& kg, const V4<R>& qL, const V4<R>& q34,
+                                          R i5) {
+  const V4<R> mq34 = R(0.0) * q34 - q34;
+  const SlashC<R> sl(JL);
+  R total = R(0.0);
+#pragma unroll 1
+  for (int h = 0; h < 4; ++h) {
+    const int l3 = (h & 2) ? 1 : -1, l4 = (h & 1) ? 1 : -1;
+    const Sp<R> ub3 = ubar_spinor(pt, mt, l3);
+    const Sp<R> u3 = sbar(ub3);
+    const Sp<R> v4 = v_spinor(ptb, mt, l4);
+    const CV4<R> J34 = vcur(ub3, v4);
+    const Sp<R> y4 = sl.col(v4), z3 = sl.row(ub3);
+#pragma unroll
+    for (int pol = 0; pol < 2; ++pol) {
+      const V4<R> e = E[pol];
+      C2<R> K[5];
+      // the gluon on the light line
+      K[0] = mul_mi(mdotc(X0[pol], J34));
+      K[1] = mul_mi(mdotc(X1[pol], J34));
+      // next to the top, next to the antitop
+      K[2] = mul_mi(cscale(ubar_dot(sbar(prop(a3, mt, f3, slash(e, u3))), y4), iL));
+      K[3] = mul_mi(cscale(ubar_dot(z3, prop(a4, mt, f4, slash(e, v4))), iL));
+      K[4] = cscale(vertex3(e, kg, JL, qL, J34, mq34), i5);
+      total = total + colour_form5(K);
+    }
+  }
+  return R(2.0) * total;
+}
+template <class R> __device__ __forceinline__ CV4<R> cvscale(const CV4<R>& a, R s) {
+  return CV4<R>{{cscale(a.c[0], s), cscale(a.c[1], s), cscale(a.c[2], s), cscale(a.c[3], s)}};
+}
+
 // q(p1) q~(p2) -> t(pt) t~(ptb) g(k): colour- and helicity-summed |M|^2, g = 1.
 template <class R>
 __device__ __forceinline__ R me_qqbar_g(const V4<R>& p1, const V4<R>& p2, const V4<R>& pt, const V4<R>& ptb,
@@ -88,37 +162,19 @@ __device__ __forceinline__ R me_qqbar_g(const V4<R>& p1, const V4<R>& p2, const 
   const V4<R> a1 = p1 - k, a2 = k - p2, a3 = pt + k, a4 = z * k - (ptb + k);
   const R i1 = R(1.0) / (mdot(a1, a1) * s34), i2 = R(1.0) / (mdot(a2, a2) * s34);
   const R f3 = R(1.0) / (mdot(a3, a3) - mt * mt), f4 = R(1.0) / (mdot(a4, a4) - mt * mt);
-  const R i12 = R(1.0) / s12, i5 = R(1.0) / (s12 * s34);
-  const V4<R> mk = z * k - k, mq34 = z * q34 - q34;
   V4<R> E[2];
   lin_pols(k, E);
-  R total = R(0.0);
-#pragma unroll 1
-  for (int h = 0; h < 16; ++h) {
-    const int l1 = (h & 8) ? 1 : -1, l2 = (h & 4) ? 1 : -1, l3 = (h & 2) ? 1 : -1, l4 = (h & 1) ? 1 : -1;
-    const Sp<R> u1 = sbar(ubar_spinor(p1, z, l1));
-    const Sp<R> v2 = v_spinor(p2, z, l2);
-    const Sp<R> vb2 = sbar(v2);
-    const Sp<R> ub3 = ubar_spinor(pt, mt, l3);
-    const Sp<R> u3 = sbar(ub3);
-    const Sp<R> v4 = v_spinor(ptb, mt, l4);
-    const CV4<R> J12 = vcur(vb2, u1), J34 = vcur(ub3, v4);
-#pragma unroll 1
-    for (int pol = 0; pol < 2; ++pol) {
-      const V4<R> e = pol ? E[1] : E[0];
-      C2<R> K[5];
-      // emission from the incoming quark, then from the incoming antiquark
-      K[0] = mul_mi(cscale(mdotc(vcur(vb2, slash(a1, slash(e, u1))), J34), i1));
-      K[1] = mul_mi(cscale(mdotc(vcur(sbar(slash(a2, slash(e, v2))), u1), J34), i2));
-      // emission from the top, then from the antitop
-      K[2] = mul_mi(cscale(mdotc(vcur(sbar(prop(a3, mt, f3, slash(e, u3))), v4), J12), i12));
-      K[3] = mul_mi(cscale(mdotc(vcur(ub3, prop(a4, mt, f4, slash(e, v4))), J12), i12));
-      // three-gluon vertex: (e, -k), (J12, p1 + p2), (J34, -(pt + ptb))
-      K[4] = cscale(vertex3(e, mk, J12, q12, J34, mq34), i5);
-      total = total + colour_form5(K);
-    }
+  const Sp<R> u1 = sbar(ubar_spinor(p1, z, 1)), v2 = v_spinor(p2, z, -1), vb2 = sbar(v2);
+  CV4<R> X0[2], X1[2];
+#pragma unroll
+  for (int pol = 0; pol < 2; ++pol) {
+    // emission from the incoming quark, from the incoming antiquark
+    X0[pol] = cvscale(vcur(vb2, slash(a1, slash(E[pol], u1))), i1);
+    X1[pol] = cvscale(vcur(sbar(slash(a2, slash(E[pol], v2))), u1), i2);
   }
-  return total;
+  // three-gluon vertex: (e, -k), (J12, p1 + p2), (J34, -(pt + ptb))
+  return top_line_sum(X0, X1, vcur(vb2, u1), R(1.0) / s12, E, pt, ptb, mt, a3, f3, a4, f4, z * k - k, q12, q34,
+                      R(1.0) / (s12 * s34));
 }
 
 // q(p1) g(p2) -> t(pt) t~(ptb) q(k): colour- and helicity-summed |M|^2, g = 1.
@@ -131,37 +187,19 @@ __device__ __forceinline__ R me_qg_q(const V4<R>& p1, const V4<R>& p2, const V4<
   const V4<R> a2 = k - p2, a3 = pt - p2, a4 = p2 - ptb;
   const R i0 = R(1.0) / (s12 * s34), i2 = R(1.0) / (mdot(a2, a2) * s34);
   const R f3 = R(1.0) / (mdot(a3, a3) - mt * mt), f4 = R(1.0) / (mdot(a4, a4) - mt * mt);
-  const R i15 = R(1.0) / t15, i5 = R(1.0) / (t15 * s34);
-  const V4<R> mq34 = z * q34 - q34;
   V4<R> E[2];
   lin_pols(p2, E);
-  R total = R(0.0);
-#pragma unroll 1
-  for (int h = 0; h < 16; ++h) {
-    const int l1 = (h & 8) ? 1 : -1, l5 = (h & 4) ? 1 : -1, l3 = (h & 2) ? 1 : -1, l4 = (h & 1) ? 1 : -1;
-    const Sp<R> u1 = sbar(ubar_spinor(p1, z, l1));
-    const Sp<R> ub5 = ubar_spinor(k, z, l5);
-    const Sp<R> u5 = sbar(ub5);
-    const Sp<R> ub3 = ubar_spinor(pt, mt, l3);
-    const Sp<R> u3 = sbar(ub3);
-    const Sp<R> v4 = v_spinor(ptb, mt, l4);
-    const CV4<R> J15 = vcur(ub5, u1), J34 = vcur(ub3, v4);
-#pragma unroll 1
-    for (int pol = 0; pol < 2; ++pol) {
-      const V4<R> e = pol ? E[1] : E[0];
-      C2<R> K[5];
-      // the gluon absorbed by the quark line before / after the top pair leaves it
-      K[0] = mul_mi(cscale(mdotc(vcur(ub5, slash(q12, slash(e, u1))), J34), i0));
-      K[1] = mul_mi(cscale(mdotc(vcur(sbar(slash(a2, slash(e, u5))), u1), J34), i2));
-      // the gluon absorbed by the top line next to the top / the antitop
-      K[2] = mul_mi(cscale(mdotc(vcur(sbar(prop(a3, mt, f3, slash(e, u3))), v4), J15), i15));
-      K[3] = mul_mi(cscale(mdotc(vcur(ub3, prop(a4, mt, f4, slash(e, v4))), J15), i15));
-      // three-gluon vertex: (e, p2), (J15, p1 - k), (J34, -(pt + ptb))
-      K[4] = cscale(vertex3(e, p2, J15, q15, J34, mq34), i5);
-      total = total + colour_form5(K);
-    }
+  const Sp<R> u1 = sbar(ubar_spinor(p1, z, 1)), ub5 = ubar_spinor(k, z, 1), u5 = sbar(ub5);
+  CV4<R> X0[2], X1[2];
+#pragma unroll
+  for (int pol = 0; pol < 2; ++pol) {
+    // the gluon absorbed by the quark line before / after the top pair leaves it
+    X0[pol] = cvscale(vcur(ub5, slash(q12, slash(E[pol], u1))), i0);
+    X1[pol] = cvscale(vcur(sbar(slash(a2, slash(E[pol], u5))), u1), i2);
   }
-  return total;
+  // three-gluon vertex: (e, p2), (J15, p1 - k), (J34, -(pt + ptb))
+  return top_line_sum(X0, X1, vcur(ub5, u1), R(1.0) / t15, E, pt, ptb, mt, a3, f3, a4, f4, p2, q15, q34,
+                      R(1.0) / (t15 * s34));
 }
 
 }  // namespace mf
