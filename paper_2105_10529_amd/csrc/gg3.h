@@ -41,8 +41,15 @@ constexpr int NG = 3;
 constexpr int NF = AMP_M5_NF;          // 120 orderings
 constexpr int NQ = AMP_M5_NQ;          // 32 groups of four (padded to 128)
 constexpr int STATES = AMP_M5_STATES;  // 64 = 2 antitop helicities x 2^5 gluon polarisations
-constexpr int SP = 8;                  // states per amplitude pass
-constexpr int SLICES = SP * 4;         // (state, top helicity, re/im) per pass
+constexpr int GSTATES = STATES / 2;    // gluon polarisation states
+// Antitop helicities of a summed pass: in FP64 the second repeats the first
+// (flipping both top helicities conjugates the amplitudes, whose gluon
+// polarisation vectors are real) and the sum is doubled; FP32 keeps both,
+// each with its own rounding.  g g -> t t~ g g g FP64 at 20000 points:
+// 20.7 -> 3.5 ms with the launches below.
+template <class R> constexpr int NHS = fp64_amp<R>::value ? 1 : 2;
+constexpr int GSP = 4;                 // gluon states per amplitude pass of a full chunk
+constexpr int SLICES = GSP * 2 * 4;    // (gluon state, antitop, top helicity, re/im) of it
 constexpr int AWAVE = 64;              // amplitude kernel block: one wave (LDS tables per wave)
 constexpr int CT = 32;                 // events per colour tile (two 16-column MFMA blocks)
 constexpr int CBLOCK = 256;            // colour kernel block: 4 waves x 8 slices
@@ -50,17 +57,40 @@ constexpr int CMAX_BLOCKS = 512;       // two 65-KB-LDS blocks per CU
 constexpr int64_t NCMAX = 131072;      // passing events per chunk (fills 256 CUs x 2 waves x 4 SIMDs)
 // FP64 amplitudes: half the chunk (the same buffer size)
 template <class R> constexpr int64_t NCMAX_R = std::is_same<R, float>::value ? NCMAX : NCMAX / 2;
+// amplitude blocks the chip holds at once (by their LDS tables: 35 or 70 KB)
+template <class R> constexpr int64_t ARES = std::is_same<R, float>::value ? 1024 : 512;
+
+// Gluon states of one amplitude pass over a chunk of ablk blocks of events
+// (one wave each).  A full chunk fills the chip by itself: GSP states per
+// pass, all in one block.  A smaller one would leave most SIMDs idle, pass
+// after pass, so it takes one block per gluon state and as many states per
+// pass as give the fewest rounds of the chip over all passes, within the same
+// buffer of 2 GiB (the smallest such pass).  FP32, 1.3e4 passing points: 196
+// blocks in each of 8 passes 13.7 ms, 6272 blocks in one pass 4.6 ms.
+template <class R> int pass_states(int64_t ablk, int64_t& rounds) {
+  int best = GSP;
+  rounds = 0;
+  for (int gs = GSP; gs <= GSTATES; gs *= 2) {
+    if (gs > GSP && (int64_t)gs * NHS<R> * ablk * AWAVE > (int64_t)GSP * 2 * NCMAX_R<R>) break;
+    const int64_t r = (GSTATES / gs) * ((ablk * gs + ARES<R> - 1) / ARES<R>);
+    if (rounds == 0 || r < rounds) {
+      rounds = r;
+      best = gs;
+    }
+  }
+  return best;
+}
 
 // Workspace owned by the process handle (grown on demand, freed with it).
 struct Ws {
   int64_t cap_n = 0;  // points: idx, wpre
-  int64_t ld = 0;     // chunk columns of the amplitude buffer (multiple of AWAVE)
+  int64_t ld = 0;     // columns of d_me (multiple of AWAVE)
   size_t amp_bytes = 0;
   int* d_idx = nullptr;
   int* d_count = nullptr;
   double* d_wpre = nullptr;
   double* d_me = nullptr;  // [ld] colour-summed |M|^2 numerators of the chunk
-  void* d_amp = nullptr;   // [SLICES][NQ][ld][4] amplitude type
+  void* d_amp = nullptr;   // [slices of a pass][NQ][ld][4] amplitude type
 };
 
 using st::kinematics;
@@ -122,25 +152,23 @@ __device__ __forceinline__ void spinor_stage(const V4<R> (&J)[5][5], const V4<R>
   }
 }
 
-// Partial amplitudes of states s0 .. s0 + ns - 1 for the passing events
-// idx[0 .. nc-1] of this chunk, written to
+// Partial amplitudes of gluon states g0 .. of this pass (gpb of them per
+// blockIdx.y) for the passing events idx[0 .. nc-1] of this chunk, written to
 //   amp[((slice * NQ + ordering / 4) * ld + j) * 4 + ordering % 4]
-// with slice = ((state - s0) * 2 + top helicity) * 2 + (0: re, 1: im) and
-// j the event's column (orderings 120..127 are written as zeros).  Lanes
+// with slice = (((gluon state - g0) * NHS + antitop) * 2 + top helicity) * 2 +
+// (0: re, 1: im) and j the event's column (orderings 120..127 are written as zeros).  Lanes
 // past nc recompute the last event into columns below ld, never read as
 // results.  The propagator factors of every gluon subset are formed in FP64
 // from the FP64 momenta and kept per lane in LDS, indexed by subset.
-// With c.helicity != 0 each lane evaluates one state k of its own (ns = 1;
-// antitop helicity k / 32, gluon polarisation state k % 32): drawn by Philox
+// With c.helicity != 0 each lane evaluates one state k of its own (antitop
+// helicity k / 32, gluon polarisation state k % 32): drawn by Philox
 // from the point's first two coordinates (mode 1) or the fixed state
-// helicity - 2; the ordering loop stays wave-uniform.  In the summed mode
-// (ns even) pass state s stands for gluon polarisation state s / 2 and
-// antitop helicity s % 2, so that both antitop helicities of a gluon state
-// are evaluated together from one set of gluon currents.
-static_assert(SP % 2 == 0, "summed passes hold both antitop helicities of each gluon state");
+// helicity - 2; the ordering loop stays wave-uniform.  In the summed mode all
+// antitop helicities of a gluon state are evaluated together from one set of
+// gluon currents.
 template <class R>
 __global__ void __launch_bounds__(AWAVE) k_g3_amp(DevCfg c, const double* __restrict__ u, int64_t n,
-                                                  const int* __restrict__ idx, int64_t nc, int s0, int ns,
+                                                  const int* __restrict__ idx, int64_t nc, int g0, int gpb,
                                                   R* __restrict__ amp, int64_t ld) {
   // Per-lane tables (each lane reads only its own column, so no barriers):
   __shared__ R gtab[32][AWAVE];        // -1 / P_S^2 for gluon subsets S (>= 2 gluons)
@@ -284,9 +312,10 @@ __global__ void __launch_bounds__(AWAVE) k_g3_amp(DevCfg c, const double* __rest
   if (own >= 0) {
     orderings(std::integral_constant<int, 1>{}, own & 31, own >> 5, out);
   } else {
-    // pass states s0 .. s0 + ns - 1: gluon state (s0 + q) / 2, antitop helicity q % 2
+    constexpr int NH = NHS<R>;
 #pragma unroll 1
-    for (int q = 0; q < ns; q += 2) orderings(std::integral_constant<int, 2>{}, (s0 + q) >> 1, 0, out + (int64_t)(q * 4) * sstride);
+    for (int q = blockIdx.y * gpb; q < ((int)blockIdx.y + 1) * gpb; ++q)
+      orderings(std::integral_constant<int, NH>{}, g0 + q, 0, out + (int64_t)(q * NH * 4) * sstride);
   }
 }
 
@@ -459,26 +488,32 @@ hipError_t integrand(const DevCfg& c, const double* u, int64_t n, double* w, voi
   G3_TRY(hipStreamSynchronize(s));
   if (count <= 0) return hipSuccess;
   // chunk width: the passing events, up to NCMAX, rounded to the amplitude block
-  int64_t want = count < NCMAX_R<R> ? (int64_t)count : NCMAX_R<R>;
-  want = (want + AWAVE - 1) / AWAVE * AWAVE;
-  if (ws->ld < want) {
+  int64_t ld = count < NCMAX_R<R> ? (int64_t)count : NCMAX_R<R>;
+  ld = (ld + AWAVE - 1) / AWAVE * AWAVE;
+  // all states in passes of gs gluon states, or one state per point in a
+  // single pass
+  const bool own = c.helicity != 0;
+  int64_t rounds = 0;
+  const int gs = own ? 1 : pass_states<R>(ld / AWAVE, rounds);
+  const int NPASS = own ? 1 : GSTATES / gs, nsl = own ? 4 : 4 * NHS<R> * gs;
+  const int gpb = gs == GSP ? GSP : 1;  // gluon states of a block
+  const size_t bytes = sizeof(R) * (size_t)nsl * NQ * (size_t)ld * 4;
+  if (ws->amp_bytes < bytes) {
     (void)hipFree(ws->d_amp);
-    (void)hipFree(ws->d_me);
     ws->d_amp = nullptr;
-    ws->d_me = nullptr;
-    ws->ld = 0;
-    const size_t bytes = sizeof(R) * (size_t)SLICES * NQ * (size_t)want * 4;
+    ws->amp_bytes = 0;
     G3_TRY(hipMalloc(&ws->d_amp, bytes));
-    G3_TRY(hipMalloc(&ws->d_me, sizeof(double) * want));
-    ws->ld = want;
     ws->amp_bytes = bytes;
   }
-  const int64_t ld = ws->ld;
+  if (ws->ld < ld) {
+    (void)hipFree(ws->d_me);
+    ws->d_me = nullptr;
+    ws->ld = 0;
+    G3_TRY(hipMalloc(&ws->d_me, sizeof(double) * ld));
+    ws->ld = ld;
+  }
   R* amp = static_cast<R*>(ws->d_amp);
-  // all states in passes of SP, or one state per point in a single pass
-  const bool own = c.helicity != 0;
-  const int NPASS = own ? 1 : STATES / SP, ns = own ? 1 : SP, nsl = 4 * ns;
-  const double inv_den = (c.helicity == 1 ? (double)STATES : 1.0) / AMP_M5_COLOUR_DEN;
+  const double inv_den = (c.helicity == 1 ? (double)STATES : own ? 1.0 : 2.0 / NHS<R>) / AMP_M5_COLOUR_DEN;
   for (int64_t c0 = 0; c0 < count; c0 += ld) {
     const int64_t nc = (count - c0) < ld ? (count - c0) : ld;
     const int* idx = ws->d_idx + c0;
@@ -487,7 +522,8 @@ hipError_t integrand(const DevCfg& c, const double* u, int64_t n, double* w, voi
                           (std::is_same<R, float>::value ? CT : CT / 2);
     const unsigned cblk = (unsigned)(ntile < CMAX_BLOCKS ? ntile : CMAX_BLOCKS);
     for (int pass = 0; pass < NPASS; ++pass) {
-      hipLaunchKernelGGL((k_g3_amp<R>), dim3(ablk), dim3(AWAVE), 0, s, c, u, n, idx, nc, pass * SP, ns, amp, ld);
+      hipLaunchKernelGGL((k_g3_amp<R>), dim3(ablk, own ? 1 : gs / gpb), dim3(AWAVE), 0, s, c, u, n, idx, nc, pass * gs,
+                         gpb, amp, ld);
       hipLaunchKernelGGL((k_g3_colour<R>), dim3(cblk), dim3(CBLOCK), 0, s, amp, ld, nc, nsl, pass == 0 ? 1 : 0,
                          pass == NPASS - 1 ? 1 : 0, ws->d_me, idx, ws->d_wpre, w, inv_den);
     }

@@ -39,3 +39,23 @@ def test_ttgg_fp64_no_point_kept():
     p = mf.Process(mf.Config(process="gg>ttxgg", dr_min=0.4))
     u = to_dev_soa(np.full((300, 10), 1e-3))  # x1 x2 far below threshold
     assert float(p.integrand(u).abs().max()) == 0.0
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_ttggg_pass_sizes_agree(precision):
+    """Batches that take different numbers of polarisation states per pass give each point the same sum up to
+    its order: at most 256 double additions of positive terms, 256 x 1.1e-16 = 3e-14; tolerance 1e-13."""
+    import torch
+
+    n = 24000
+    x = si.points_above_threshold(n, 13, 13000.0, 173.0, seed=5)
+    p = mf.Process(mf.Config(process="gg>ttxggg", precision=precision, dr_min=0.4))
+    u = to_dev_soa(x)
+    whole = p.integrand(u)
+    assert int((whole != 0).sum()) > 2000
+    a = 0
+    for m in (1, 70, 500, 3000, 9000):
+        part = p.integrand(u[:, a:a + m].contiguous())
+        ref = whole[a:a + m]
+        assert torch.all((part - ref).abs() <= 1e-13 * ref.abs())
+        a += m
