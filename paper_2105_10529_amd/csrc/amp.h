@@ -92,6 +92,7 @@ template <class R, class RK> __device__ __forceinline__ V4<R> cvt4(const V4<RK>&
 __device__ __forceinline__ void opaque(float& x) { asm volatile("" : "+v"(x)); }
 __device__ __forceinline__ void opaque(double& x) { asm volatile("" : "+v"(x)); }
 __device__ __forceinline__ void opaque(int& x) { asm volatile("" : "+v"(x)); }
+__device__ __forceinline__ void opaque_scalar(int& x) { asm volatile("" : "+s"(x)); }
 template <class T> __device__ __forceinline__ void opaque(Dual<T>& x) {
   opaque(x.v);
   opaque(x.d);
@@ -296,6 +297,29 @@ template <class R> __device__ __forceinline__ void quad_relabel(V4<R>* a, int st
   quad_relabel(a[0].x, a[stride].x, a[2 * stride].x, a[3 * stride].x, role);
   quad_relabel(a[0].y, a[stride].y, a[2 * stride].y, a[3 * stride].y, role);
   quad_relabel(a[0].z, a[stride].z, a[2 * stride].z, a[3 * stride].z, role);
+}
+// -------------------------------------------- states dealt out to lanes
+// The value of lane Q of an aligned group of LANES lanes, in all of them:
+// quad permutation, or broadcast within a row of 16 (for groups of 8 into
+// each half of it).
+template <int LANES, int Q> __device__ __forceinline__ float group_bcast(float x) {
+  static_assert(LANES == 4 || LANES == 8 || LANES == 16, "lane groups of a row");
+  const int v = __float_as_int(x);
+  if constexpr (LANES == 4) return __int_as_float(__builtin_amdgcn_mov_dpp(v, 0x55 * Q, 0xF, 0xF, true));
+  const int lo = __builtin_amdgcn_mov_dpp(v, 0x150 + Q, 0xF, 0xF, true);
+  if constexpr (LANES == 16) return __int_as_float(lo);
+  return __int_as_float(__builtin_amdgcn_update_dpp(lo, v, 0x150 + ((8 + Q) & 15), 0xF, 0xC, false));
+}
+// total + sum over the LANES lanes of an aligned group, in lane order, of
+// each lane's F x G sums s[f * G + g] times c[g]: the order, and the fused
+// multiply-adds, of one lane that takes the states one after the other.
+template <int LANES, int F, int G, int Q = 0>
+__device__ __forceinline__ void group_total(const float* s, const float* c, float& total) {
+  if constexpr (Q < LANES) {
+#pragma unroll
+    for (int i = 0; i < F * G; ++i) total = fmaf(c[i % G], group_bcast<LANES, Q>(s[i]), total);
+    group_total<LANES, F, G, Q + 1>(s, c, total);
+  }
 }
 // A lane's column of a table with W lanes.
 template <int W, class R> __device__ __forceinline__ void quad_put4(R* t, const V4<R>& a) {

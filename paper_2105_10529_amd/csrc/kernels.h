@@ -106,6 +106,27 @@ __device__ __forceinline__ int list_entry(const int* __restrict__ list, int64_t 
   return list[(int64_t)lo * cap + (g - pre[lo])];
 }
 
+// Lanes per event of the FP32 g g -> t t~ g g integrand, which deals the 16
+// gluon polarisation states out to them: the number that takes the least
+// time for nsel events on 1024 SIMDs, one wave each at a time.  Measured, one
+// round of the chip takes 25 us for what an event needs once (its
+// kinematics, in every lane) and 41 us per state of a lane (16, 4 and 1 lanes
+// per event: 70, 195 and 700 us).  65536 points (22900 kept): one lane 714
+// us, always four 396, chosen 359; 20000 points 708, 201 and 131 us; 1.5e6
+// points stay 1 % faster with four lanes than with one.
+__device__ __forceinline__ int state_lanes(int nsel) {
+  int best = 4;
+  int64_t cost = -1;
+  for (int l = 4; l <= 16; l *= 2) {
+    const int64_t waves = ((int64_t)nsel * l + 63) / 64, c = (waves + 1023) / 1024 * (25 + 41 * (16 / l));
+    if (cost < 0 || c < cost) {
+      cost = c;
+      best = l;
+    }
+  }
+  return best;
+}
+
 // The kept points, numbered through all blocks' lists and dealt out in chunks
 // of BLOCK / LANES, so that every block has full chunks whatever share of its
 // own points passed (with cuts a chunk of 256 points keeps 90 to 150 of them;
@@ -114,15 +135,12 @@ __device__ __forceinline__ int list_entry(const int* __restrict__ list, int64_t 
 // passes, and each block takes its own list (g g -> t t~ at 1e6 points 114 us
 // against 120 us through the offsets).
 template <int NG, int CH, class RA, int LANES>
-__global__ void __launch_bounds__(BLOCK) k_integrand(DevCfg c, const double* __restrict__ u, int64_t n,
-                                                     double* __restrict__ w, const int* __restrict__ list,
-                                                     const int* __restrict__ cnt, int nblk, int64_t cap) {
+__device__ __forceinline__ void integrand_loop(const DevCfg& c, const double* __restrict__ u, int64_t n,
+                                               double* __restrict__ w, const int* __restrict__ list, int64_t cap,
+                                               const int* pre, int nblk, int nsel) {
   constexpr bool DEALT = NG > 0;
   constexpr int PER = BLOCK / LANES;
-  __shared__ int pre[DEALT ? MAX_BLOCKS + 1 : 1];
   const int* own = list + (int64_t)blockIdx.x * cap;
-  if constexpr (DEALT) list_offsets(cnt, nblk, pre);
-  const int nsel = __builtin_amdgcn_readfirstlane(DEALT ? pre[nblk] : cnt[blockIdx.x]);
   const int64_t step = DEALT ? (int64_t)gridDim.x * PER : PER;
   for (int64_t j = DEALT ? (int64_t)blockIdx.x * PER : 0; j < nsel; j += step) {
     const int64_t j0 = j + threadIdx.x / LANES;
@@ -133,9 +151,26 @@ __global__ void __launch_bounds__(BLOCK) k_integrand(DevCfg c, const double* __r
 #pragma unroll
     for (int k = 0; k < MAXD; ++k)
       if (k < c.ndim) x[k] = u[(int64_t)k * n + e];
-    EventOut<double> r = event_weight<NG, CH, RA, double, LANES>(c, x, c.mt, c.pdfc);
+    EventOut<double> r = event_weight<NG, CH, RA, double, LANES, true>(c, x, c.mt, c.pdfc);
     const double v = isfinite(r.w) ? r.w : 0.0;
     if (live && threadIdx.x % LANES == 0) w[e] = v;
+  }
+}
+// LANES = 0: state_lanes of the number of kept points.
+template <int NG, int CH, class RA, int LANES>
+__global__ void __launch_bounds__(BLOCK) k_integrand(DevCfg c, const double* __restrict__ u, int64_t n,
+                                                     double* __restrict__ w, const int* __restrict__ list,
+                                                     const int* __restrict__ cnt, int nblk, int64_t cap) {
+  __shared__ int pre[NG > 0 ? MAX_BLOCKS + 1 : 1];
+  if constexpr (NG > 0) list_offsets(cnt, nblk, pre);
+  const int nsel = __builtin_amdgcn_readfirstlane(NG > 0 ? pre[nblk] : cnt[blockIdx.x]);
+  if constexpr (LANES != 0) {
+    integrand_loop<NG, CH, RA, LANES>(c, u, n, w, list, cap, pre, nblk, nsel);
+  } else {
+    const int lanes = state_lanes(nsel);
+    if (lanes == 16) integrand_loop<NG, CH, RA, 16>(c, u, n, w, list, cap, pre, nblk, nsel);
+    else if (lanes == 8) integrand_loop<NG, CH, RA, 8>(c, u, n, w, list, cap, pre, nblk, nsel);
+    else integrand_loop<NG, CH, RA, 4>(c, u, n, w, list, cap, pre, nblk, nsel);
   }
 }
 
@@ -337,7 +372,7 @@ __global__ void __launch_bounds__(BLOCK) k_vegas(DevCfg c, const double* __restr
 #pragma unroll
     for (int j = 0; j < MAXD; ++j)
       if (j < d) x[j] = xs[j * BLOCK + tid];
-    EventOut<double> r = event_weight<NG, CH, RA, double>(cl, x, c.mt, pdf);
+    EventOut<double> r = event_weight<NG, CH, RA, double, 1, true>(cl, x, c.mt, pdf);
     asm volatile("" ::: "memory");
     double w = r.w * jac_s[tid];
     const bool finite = isfinite(w);
@@ -562,17 +597,21 @@ __global__ void __launch_bounds__(BLOCK) k_grad_vegas(DevCfg c, const double* __
 
 // Launcher table of one (final gluons, channel, amplitude type) instance;
 // GRAD = 0 leaves the derivative kernels out, FUSED = 0 the fused iteration;
-// LANES: lanes per event of the integrand at given points.
+// LANES: lanes per event of the integrand at given points (0: state_lanes).
 template <int NG, int CH, class RA, class RD, int GRAD, int FUSED = 1, int LANES = 1>
 Launchers make_launchers() {
   Launchers L;
   L.fused = FUSED != 0;
+  // one lane per event leaves part of the chip's 65536 lanes idle (FP32
+  // g g -> t t~ g g, two iterations of 2000 events 1.66 -> 0.43 ms, of 1e5
+  // events 3.16 -> 2.29 ms; from 1.4e5 events the fused kernel is as fast)
+  L.staged_events = LANES == 0 ? 1 << 17 : 0;
   L.integrand = [](const DevCfg& c, const double* u, int64_t n, double* w, int nblk, int* list, int* cnt,
                    int64_t cap, hipStream_t s) {
     hipLaunchKernelGGL((k_select_points<NG>), dim3(nblk), dim3(BLOCK), 0, s, c, u, n, w, list, cnt, cap);
     // enough blocks for every kept point, four per compute unit at most (the
     // kernels hold one to three; more would only repeat the offsets)
-    const int64_t want = (n * LANES + BLOCK - 1) / BLOCK;
+    const int64_t want = (n * (LANES ? LANES : 16) + BLOCK - 1) / BLOCK;
     const unsigned grid = NG == 0 ? (unsigned)nblk : (unsigned)(want < 1024 ? want : 1024);
     hipLaunchKernelGGL((k_integrand<NG, CH, RA, LANES>), dim3(grid), dim3(BLOCK), 0, s, c, u, n, w, list, cnt, nblk,
                        cap);

@@ -78,6 +78,10 @@ struct Launchers {
   // false: VEGAS iterations go through the staged path (points kernel ->
   // integrand kernel -> accumulation kernel) instead of the fused kernel
   bool fused;
+  // of a fused instance: iterations of up to this many events take the staged
+  // path all the same (0: none), where the integrand splits an event over
+  // lanes
+  int64_t staged_events = 0;
   // selection (k_select_points) then the weights of the kept points
   // (k_integrand); list/cnt/cap as for vegas
   void (*integrand)(const DevCfg&, const double*, int64_t, double*, int, int*, int*, int64_t, hipStream_t);

@@ -978,11 +978,13 @@ mf_status mf_integrate(mf_process* p, const mf_integrate_opts* o, mf_result* r) 
   if (!(o->fallback_rel_var >= 0.0) || !std::isfinite(o->fallback_rel_var))
     return fail(MF_EINVAL, "fallback_rel_var must be finite and >= 0");
   const bool can_fallback = o->flow && o->fallback_rel_var > 0.0;
-  if (!p->L.fused || o->flow) {
+  // the observables' kernel reads the fused iteration's lists
+  const bool fused = p->L.fused && (o->obs || o->n_events > p->L.staged_events);
+  if (!fused || o->flow) {
     mf_status st = ensure_stage(p, o->n_events, s);
     if (st != MF_OK) return st;
   }
-  if (p->L.fused && (!o->flow || can_fallback)) {
+  if (fused && (!o->flow || can_fallback)) {
     mf_status st = ensure_select(p, o->n_events, nblk, s);
     if (st != MF_OK) return st;
   }
@@ -1047,7 +1049,7 @@ mf_status mf_integrate(mf_process* p, const mf_integrate_opts* o, mf_result* r) 
       if (sst != MF_OK) return sst;
       hipLaunchKernelGGL(k_stage_accumulate, dim3(nblk), dim3(256), 0, s, p->d_sw, p->d_sjac, p->d_sbins, d, nb, N,
                          p->d_part, p->pstride);
-    } else if (p->L.fused) {
+    } else if (fused) {
       p->L.vegas(p->dc, p->d_edges, iter, o->n_events, p->cfg.seed, p->d_part, p->pstride, nblk, lds, p->d_sel,
                  p->d_selcnt, p->sel_cap, o->obs ? p->d_selw : nullptr, s);
       if (o->obs && it >= o->warmup_iters_discarded) {

@@ -16,6 +16,7 @@
 #include "gen/me_gg_m3_both.h"
 #include "gen/me_gg_m4.h"
 #include "gen/me_gg_m4_grouped.h"
+#include "gen/me_gg_m4_lanes.h"
 #include "gen/me_gg_m4_quad.h"
 #include "qq.h"
 
@@ -200,6 +201,21 @@ __device__ __forceinline__ double solve_mass_ratio(int N, double r) {
   return v;
 }
 
+// sin and cos of the azimuth 2 pi x.  The bound, far above any x in (0, 1),
+// tells the compiler that the library's reduction of large arguments is not
+// needed, which leaves no divergent branch in an event's code: the values and
+// bits are those of sincos(2 pi x).  Besides the instructions this matters for
+// correctness: in kernels that fill the register file the compiler moved a
+// live value (the thread index among them) to an accumulation register at the
+// join of that branch, under the execution mask of one of its sides, and the
+// other lanes read a stale one afterwards.
+__device__ __forceinline__ void azimuth(double x, double* sp, double* cp) {
+  const double ph = 2.0 * M_PI * x;
+  double s;
+  sincos(fmin(fabs(ph), 1024.0), &s, cp);
+  *sp = ph < 0.0 ? -s : s;
+}
+
 // Final state from x[2..] in the partonic centre-of-mass frame: the gluons
 // are emitted one by one from the massless n-body recursion (Platzer,
 // "RAMBO on diet"), the top pair is split last; returns V_n(s) * beta or 0
@@ -216,10 +232,9 @@ __device__ __forceinline__ R phase_space(int ng, const double* x, double shat, R
     double Mi = Mprev * sqrt(v);
     double q = (Mprev * Mprev - Mi * Mi) / (2.0 * Mprev);
     double ct = 2.0 * x[2 + (n - 2) + 2 * (i - 1)] - 1.0;
-    double ph = 2.0 * M_PI * x[2 + (n - 2) + 2 * (i - 1) + 1];
     double st = sqrt(fmax(0.0, 1.0 - ct * ct));
     double sp, cp;
-    sincos(ph, &sp, &cp);
+    azimuth(x[2 + (n - 2) + 2 * (i - 1) + 1], &sp, &cp);
     V4<double> g{q, q * st * cp, q * st * sp, q * ct};
     V4<double> rest{sqrt(Mi * Mi + q * q), -g.x, -g.y, -g.z};
     gl[i - 1] = boost_from_rest(g, Q, Mprev);
@@ -234,10 +249,9 @@ __device__ __forceinline__ R phase_space(int ng, const double* x, double shat, R
   R beta = dsqrt(R(1.0) - R(4.0) * mt * mt / (Mtt * Mtt));
   R q = Mtt * beta * R(0.5);
   double ct = 2.0 * x[2 + (n - 2) + 2 * (n - 2)] - 1.0;
-  double ph = 2.0 * M_PI * x[2 + (n - 2) + 2 * (n - 2) + 1];
   double st = sqrt(fmax(0.0, 1.0 - ct * ct));
   double sp, cp;
-  sincos(ph, &sp, &cp);
+  azimuth(x[2 + (n - 2) + 2 * (n - 2) + 1], &sp, &cp);
   R E = Mtt * R(0.5);
   V4<R> t{E, q * R(st * cp), q * R(st * sp), q * R(ct)};
   V4<R> tb{E, R(0.0) - t.x, R(0.0) - t.y, R(0.0) - t.z};
@@ -305,8 +319,8 @@ __device__ __forceinline__ Dual<float> to_amp_s(Dual<double> x, Dual<float>*) { 
 // Colour- and polarisation-summed |M|^2 (g = 1) for g g -> t t~ + NG g.
 // E: beam energy; gluons in emission order; top/atop from the phase space.
 // Momenta and per-event invariants stay in the kinematic type RK; the
-// helicity loops run in the amplitude type RA.  LANES = 4: called by the four
-// lanes of an aligned group with the same event, which share its work.
+// helicity loops run in the amplitude type RA.  LANES > 1: called by the lanes
+// of an aligned group with the same event, which share its work.
 template <int NG, class RA, class RK, int LANES = 1>
 __device__ __forceinline__ RA me_gg(double E, const V4<double>* gl, const V4<RK>& top, const V4<RK>& atop, RK mt) {
   constexpr int m = NG + 2;
@@ -328,8 +342,8 @@ __device__ __forceinline__ RA me_gg(double E, const V4<double>* gl, const V4<RK>
   V4<RA> t = cvt4<RA>(top), tb = cvt4<RA>(atop);
   Sp<RA> UB[2] = {ubar_spinor(t, m_a, -1), ubar_spinor(t, m_a, 1)};
   Sp<RA> VS[2] = {v_spinor(tb, m_a, -1), v_spinor(tb, m_a, 1)};
-  if constexpr (LANES == 4) {
-    static_assert(m == 4 && std::is_same<RA, double>::value && std::is_same<RK, double>::value, "FP64, four gluons");
+  if constexpr (LANES > 1 && fp64_amp<RA>::value) {
+    static_assert(m == 4 && LANES == 4 && std::is_same<RK, double>::value, "one lane per last gluon");
     const int role = threadIdx.x & 3;
     quad_relabel(K, 1, role);
     quad_relabel(&Ep[0][0], 2, role);
@@ -339,6 +353,9 @@ __device__ __forceinline__ RA me_gg(double E, const V4<double>* gl, const V4<RK>
     constexpr int W = 64;
     __shared__ double tab[4][ME_M4_QUAD_TAB * W];
     return me_gg_m4_quad<RA, W>(K, Ep, UB, VS[0], atop, mt, role, tab[threadIdx.x >> 6] + (threadIdx.x & 63));
+  } else if constexpr (LANES > 1) {
+    static_assert(m == 4, "16 gluon polarisation states");
+    return me_gg_m4_lanes<LANES, RA, RK>(K, Ep, UB, VS, atop, mt);
   } else if constexpr (m == 2) return me_gg_m2<RA, RK>(K, Ep, UB, VS, atop, mt);
   else if constexpr (m == 3 && fp64_amp<RA>::value) return me_gg_m3<RA, RK>(K, Ep, UB, VS, atop, mt);
   else if constexpr (m == 3) return me_gg_m3_both<RA, RK>(K, Ep, UB, VS, atop, mt);
@@ -439,7 +456,9 @@ __device__ __forceinline__ bool event_passes(const DevCfg& c, const double* x) {
 // an event below threshold or outside the cuts is evaluated on safe
 // kinematics and its weight is selected to zero, so the amplitude code never
 // runs under a partial execution mask.
-template <int NG, int CH, class RA, class RK, int LANES = 1>
+// KEPT: the event is known to pass the cuts (it comes from a selection's list,
+// which took the decision of event_passes), so they are not evaluated again.
+template <int NG, int CH, class RA, class RK, int LANES = 1, bool KEPT = false>
 __device__ __forceinline__ EventOut<RK> event_weight(const DevCfg& c, const double* x, RK mt, const double* pdf) {
   EventOut<RK> out;
   double x1 = x[0], x2 = x[1];
@@ -451,7 +470,7 @@ __device__ __forceinline__ EventOut<RK> event_weight(const DevCfg& c, const doub
   V4<RK> top, atop;
   RK wps = phase_space<RK>(NG, x, shat_k, mt, gl, top, atop);
   ok = ok && (val(wps) > 0.0);
-  ok = ok && pass_cuts(c, NG, gl, 0.5 * log(x1 / x2));
+  if constexpr (!KEPT) ok = ok && pass_cuts(c, NG, gl, 0.5 * log(x1 / x2));
   out.pass = ok ? 1 : 0;
   double E = 0.5 * sqrt(shat_k);
   out.t1 = x_position(c, x1);

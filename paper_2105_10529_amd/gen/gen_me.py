@@ -215,11 +215,12 @@ def _ssum(terms):
     return e
 
 
-def _colour_lines(w, ind, groups, name):
+def _colour_lines(w, ind, groups, name, store=None):
     """total += sum over coefficient groups c * (sum of |A_i|^2 or
     Re(A_i^* A_j)); each group's sum is one chain of fused multiply-adds.
-    name(i) is the amplitude variable of ordering i."""
-    for c, lst in sorted(groups.items()):
+    name(i) is the amplitude variable of ordering i.  store: keep the groups'
+    sums in s_[store ..] instead of adding them."""
+    for g_, (c, lst) in enumerate(sorted(groups.items())):
         calls = []
         for k_, (i, j) in enumerate(lst):
             if k_ == 0:
@@ -230,7 +231,7 @@ def _colour_lines(w, ind, groups, name):
         w(f"{ind}  R s = {first};")
         for q in range(0, len(calls), 3):
             w(f"{ind}  " + " ".join(calls[q:q + 3]))
-        w(f"{ind}  total = total + R({c}.0) * s;")
+        w(f"{ind}  total = total + R({c}.0) * s;" if store is None else f"{ind}  s_[{store + g_}] = s;")
         w(f"{ind}}}")
 
 
@@ -400,7 +401,7 @@ def emit_me(m: int, with_cost: bool = False):
 
 
 def emit_me_per_ordering(m: int, share_antitop: bool = False, pair_orderings=False, suffix: str = "",
-                         one_antitop: bool = False) -> str:
+                         one_antitop: bool = False, lanes: bool = False) -> str:
     """Lower-register schedule: each colour ordering builds its own currents.
 
     Only per-event scalars (propagator factors, formed in the kinematic type),
@@ -428,6 +429,13 @@ def emit_me_per_ordering(m: int, share_antitop: bool = False, pair_orderings=Fal
     (scratch 2004 -> 1132 B per lane); derivatives of g g -> t t~ g at 1e5
     points 1.34 -> 0.89 ms.  Only for amplitudes in FP64: the two halves agree to
     rounding, not bit for bit, which in FP32 would show in the weights.
+    lanes: the polarisation states dealt out to the 4, 8 or 16 lanes of an
+    aligned group, with the arithmetic of the one-lane form; the group sums
+    of the colour form are then added up in the order of the states by every
+    lane of the group (lane broadcasts), so the result is the same bit for
+    bit.  The loop over a lane's states has a bound the compiler cannot see:
+    with one known to be 1 it would drop the loop and fill the registers with
+    the per-event constants (1.1 KB of scratch against 0.6).
     """
     perms, Z, den = colour_matrix(m)
     nf = len(perms)
@@ -446,9 +454,11 @@ def emit_me_per_ordering(m: int, share_antitop: bool = False, pair_orderings=Fal
         w(f"constexpr double ME_M{m}_COLOUR_DEN = {den}.0;")
     w("// Colour- and polarisation-summed |M|^2 with g = 1 (argument meaning as in")
     w("// the shared-current schedule).")
-    w("template <class R, class RK>")
+    w("template <" + ("int LANES, " if lanes else "") + "class R, class RK>")
     w(f"__device__ __forceinline__ R me_gg_m{m}{suffix}(const V4<RK>* K, const V4<R> (*E)[2], const Sp<R>* UB,")
     w("                                         const Sp<R>* VS, const V4<RK>& PTB, RK MTK) {")
+    if lanes:
+        assert m == 4 and share_antitop
     w("  const R MT = cvt<R>(MTK);")
     subsets = list(range(1, 1 << m))
     full = (1 << m) - 1
@@ -476,8 +486,15 @@ def emit_me_per_ordering(m: int, share_antitop: bool = False, pair_orderings=Fal
         w("    const Sp<R> V = VS[ht];")
     else:
         w("  {")
-    w("#pragma unroll 1")
-    w(f"    for (int hg = 0; hg < {1 << m}; ++hg) {{")
+    if lanes:
+        w(f"    int rounds = {1 << m} / LANES;")
+        w("    opaque_scalar(rounds);")
+        w("#pragma unroll 1")
+        w("    for (int round = 0; round < rounds; ++round) {")
+        w("      const int hg = round * LANES + (threadIdx.x & (LANES - 1));")
+    else:
+        w("#pragma unroll 1")
+        w(f"    for (int hg = 0; hg < {1 << m}; ++hg) {{")
     ind = "      "
     for i in range(m):
         w(f"{ind}const V4<R> E{i} = ((hg >> {m - 1 - i}) & 1) ? E[{i}][1] : E[{i}][0];")
@@ -579,10 +596,14 @@ def emit_me_per_ordering(m: int, share_antitop: bool = False, pair_orderings=Fal
         for j in range(i, nf):
             c = Z[i][j] * (1 if i == j else 2)
             groups.setdefault(c, []).append((i, j))
-    for h in hts:
-        hs = "" if h is None else f"h{h}"
-        for t in range(2):
-            _colour_lines(w, ind, groups, lambda i, t=t, hs=hs: f"A{t}{hs}_{i}")
+    forms = [(t, "" if h is None else f"h{h}") for h in hts for t in range(2)]
+    if lanes:
+        w(f"{ind}R s_[{len(forms) * len(groups)}];")
+    for f_, (t, hs) in enumerate(forms):
+        _colour_lines(w, ind, groups, lambda i, t=t, hs=hs: f"A{t}{hs}_{i}", f_ * len(groups) if lanes else None)
+    if lanes:
+        w(f"{ind}const R c_[{len(groups)}] = {{" + ", ".join(f"R({c}.0)" for c in sorted(groups)) + "};")
+        w(f"{ind}group_total<LANES, {len(forms)}, {len(groups)}>(s_, c_, total);")
     w("    }")
     w("  }")
     w(f"  return total * R({2 if one_antitop else 1}.0 / {den}.0);")
@@ -1091,6 +1112,7 @@ def main(outdir: str, ms=(2, 3, 4, 5)) -> None:
     # matrix-core colour sum; the colour matrix of the quark channels
     for name, text in (("me_gg_m3_both.h", emit_me_per_ordering(3, True, "all", "_both")),
                        ("me_gg_m4_grouped.h", emit_me_per_ordering(4, True, "last", "_grouped")),
+                       ("me_gg_m4_lanes.h", emit_me_per_ordering(4, True, "last", "_lanes", lanes=True)),
                        ("me_gg_m4_quad.h", emit_me_quad()), ("amps_gg_m4.h", emit_amp_store(4)), ("colour_qq.h", emit_colour_qq())):
         path = os.path.join(outdir, name)
         old = open(path).read() if os.path.exists(path) else None

@@ -59,3 +59,35 @@ def test_ttggg_pass_sizes_agree(precision):
         ref = whole[a:a + m]
         assert torch.all((part - ref).abs() <= 1e-13 * ref.abs())
         a += m
+
+
+def test_ttgg_fp32_lane_counts_give_the_same_bits():
+    """Batches whose kept points are evaluated by 16, 8 and 4 lanes each agree bit for bit (the lanes add the
+    states' sums in the order of one lane), and with the oracle to the FP32 tolerance of 1e-5."""
+    import torch
+
+    n = 90000
+    x = si.points_above_threshold(n, 10, 13000.0, 173.0, seed=9)
+    p = mf.Process(mf.Config(process="gg>ttxgg", precision="fp32", dr_min=0.4))
+    u = to_dev_soa(x)
+    whole = p.integrand(u)
+    a = 0
+    for m in (1, 17, 300, 1000, 9000, 24000, 45000):
+        part = p.integrand(u[:, a:a + m].contiguous())
+        assert torch.equal(part, whole[a:a + m]), m
+        a += m
+    ref = oracle.Oracle(oracle.Config(n_g=2, dr_min=0.4)).integrand(x[:3000])
+    got = whole[:3000].cpu().numpy()
+    assert np.all(np.abs(got - ref) <= 1e-5 * np.abs(ref))
+
+
+@pytest.mark.parametrize("n", [2, 4000, 1 << 17])
+def test_ttgg_fp32_staged_and_fused_iterations_agree(n):
+    """With observables a small iteration stays in the fused kernel; both sum the same weights in double-double,
+    so the estimates agree to FP64 rounding (1e-12, as the oracle's iteration tests)."""
+    p = mf.Process(mf.Config(process="gg>ttxgg", precision="fp32", dr_min=0.4))
+    a = p.integrate(1, n, adapt=False)
+    b = p.integrate(1, n, adapt=False, observables={"nbins": 8, "lo": (0, 0, 0), "hi": (1000, 2000, 1000)})
+    assert a.n_nonzero == b.n_nonzero
+    assert abs(a.integral - b.integral) <= 1e-12 * abs(b.integral)
+    assert abs(a.error - b.error) <= 1e-12 * abs(b.error)
