@@ -7,15 +7,15 @@
 //                   dense layers as BF16 MFMA products (v_mfma_f32_16x16x32_bf16,
 //                   FP32 accumulation) with the hidden activations resident in
 //                   LDS, then the FP32 piecewise-quadratic CDF (or its inverse)
-//                   of each transformed coordinate; optionally writes the
-//                   activations needed by the backward pass
-//   k_pq_backward   derivatives of the PQ transform with respect to its input
-//                   and its 2K+1 logits (per event and transformed coordinate)
-//   k_gemm          LDS-staged BF16 MFMA product with split-K for the weight
-//                   gradients and a LeakyReLU-derivative epilogue for the
-//                   activation gradients
-//   k_reduce_grad   ordered reduction of the split-K partials into the FP32
-//                   gradient
+//                   of each transformed coordinate; optionally keeps the layer
+//                   input for the backward pass
+//   k_layer_backward  one layer of the backward pass for a tile of 64 events:
+//                   the forward products again, the derivatives of the PQ
+//                   transforms, and the activation-gradient products; writes
+//                   the operands of the weight gradients
+//   k_wgrad         the three weight-gradient products of a layer, split over
+//                   events
+//   k_reduce_layer  ordered reduction of their partials into the FP32 gradient
 //   k_adam          Adam on the FP32 masters and refresh of the BF16 copies
 #include <hip/hip_runtime.h>
 
@@ -36,7 +36,8 @@ namespace flow {
 constexpr int H = 256;        // hidden width
 constexpr int KB = 32;        // PQ bins
 constexpr int NO = 2 * KB + 1;  // logits per transformed coordinate
-constexpr int NOP = 80;       // NO padded to five 16-column MFMA tiles
+constexpr int NOP = 80;       // NO padded: stride of a coordinate's output biases and of its k range in W3q
+constexpr int NOG = 72;       // NO padded to 16-byte chunks: logit gradients of one coordinate
 constexpr int KA = 32;        // first-layer k width: inputs split as BF16 hi (k < 16) + lo (k >= 16)
 constexpr int KLO = 16;       // offset of the low parts
 constexpr int T = 64;         // events per workgroup of the layer kernel
@@ -73,22 +74,16 @@ struct LayerDev {
   const bf16* W2p;   // [H][H]
   const bf16* W3p;   // [dB][64][H]
   const bf16* W3L;   // [16][H]
-  // The backward products' B operands with k contiguous: W2 [in][out] and
-  // W3 [in][dB*NOP] in their own orientation (zero-padded outputs)
-  const bf16* W2n;   // [H][H]
-  const bf16* W3n;   // [H][dB*NOP]
-};
-
-// Training caches of one layer.  The activations are kept event-contiguous
-// ([feature][ldn], ldn = the batch rounded up to 8) because their only
-// consumers are the weight-gradient products, which reduce over events.
-struct LayerCache {
-  bf16* xa;     // [KA][ldn] inputs of the first dense layer (hi | lo)
-  bf16* h1;     // [H][ldn]
-  bf16* h2;     // [H][ldn]
-  float* o;     // [n][dB][NOP] logits
-  float* lin;   // [d][n]   layer input
-  int64_t ldn;  // leading dimension of the event-contiguous caches
+  // The backward products' A fragments, packed in the same way with the roles
+  // of inputs and outputs exchanged:
+  //   W2q[((w * 8 + ks) * 4 + jt) * 64 + lane][8]:  W2[j][k], j = 64 w + 16 jt + (lane & 15),
+  //                                                 k = 32 ks + 8 (lane >> 4) + e
+  //   W3q[((ks * 4 + w) * 4 + jt) * 64 + lane][8]: column k of W3 with NOP columns per coordinate,
+  //                                                 c NOP + r (zero for r >= NO), same j and k
+  //   W1q[ks * 64 + lane][8]:                       W1[lane & 15][k] (zero rows past d_A)
+  const bf16* W2q;   // [H][H]
+  const bf16* W3q;   // [dB NOP rounded up to 32][H]
+  const bf16* W1q;   // [16][H]
 };
 
 __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
@@ -123,59 +118,6 @@ __device__ __forceinline__ float max_nc(float a, float b) {
 }
 
 // ------------------------------------------------------------ PQ transform
-// Softmax widths and normalised vertex heights from the 2K+1 logits.
-__device__ __forceinline__ void pq_params(const float* o, float* W, float* V) {
-  float mw = o[0];
-#pragma unroll
-  for (int k = 1; k < KB; ++k) mw = fmaxf(mw, o[k]);
-  float sw = 0.0f;
-#pragma unroll
-  for (int k = 0; k < KB; ++k) {
-    W[k] = __expf(o[k] - mw);
-    sw += W[k];
-  }
-  const float isw = 1.0f / sw;
-#pragma unroll
-  for (int k = 0; k < KB; ++k) W[k] *= isw;
-  float mv = o[KB];
-#pragma unroll
-  for (int k = 1; k <= KB; ++k) mv = fmaxf(mv, o[KB + k]);
-#pragma unroll
-  for (int k = 0; k <= KB; ++k) V[k] = __expf(o[KB + k] - mv);
-  float N = 0.0f;
-#pragma unroll
-  for (int k = 0; k < KB; ++k) N += 0.5f * (V[k] + V[k + 1]) * W[k];
-  const float iN = 1.0f / N;
-#pragma unroll
-  for (int k = 0; k <= KB; ++k) V[k] *= iN;
-}
-
-// Bin b of a point: the largest k >= 1 with edge_k <= t (else 0), where
-// edge_k is the running sum of W (by_area = 0) or of the bin areas
-// (by_area = 1).  Returns the bin's left edge S_b, its area offset A_b,
-// W_b, V_b, V_b+1 through static register indices only.
-struct Bin {
-  int b;
-  float S, A, Wb, Vb, Vb1;
-};
-__device__ __forceinline__ Bin find_bin(const float* W, const float* V, float t, bool by_area) {
-  Bin r{0, 0.0f, 0.0f, W[0], V[0], V[1]};
-  float S = W[0], A = 0.5f * (V[0] + V[1]) * W[0];
-#pragma unroll
-  for (int k = 1; k < KB; ++k) {
-    const bool take = (by_area ? A : S) <= t;
-    r.b = take ? k : r.b;
-    r.S = take ? S : r.S;
-    r.A = take ? A : r.A;
-    r.Wb = take ? W[k] : r.Wb;
-    r.Vb = take ? V[k] : r.Vb;
-    r.Vb1 = take ? V[k + 1] : r.Vb1;
-    S += W[k];
-    A += 0.5f * (V[k] + V[k + 1]) * W[k];
-  }
-  return r;
-}
-
 // Epilogue of a transposed dense layer: acc[jt][mt][i] is feature
 // 64 wave + 16 jt + 4 quad + i of event 16 mt + row, bias included (it is
 // the accumulator's initial value); applies the LeakyReLU, rounds to BF16 and
@@ -325,30 +267,10 @@ __device__ __forceinline__ void pq_quad(const float* o, float vlast, float t, in
 }
 
 // --------------------------------------------------------- coupling layer
-// Copy of the [T][H] activation tile into an event-contiguous cache: eight
-// events of one feature per 16-byte store.
-__device__ __forceinline__ void cache_hidden(const bf16* h, bf16* __restrict__ dst, int64_t ldn, int64_t e0,
-                                             int64_t n, int tid) {
-  for (int idx = tid; idx < H * (T / 8); idx += 256) {
-    const int ch = idx % (T / 8), f = idx / (T / 8);
-    const int m0 = 8 * ch;
-    const int64_t e = e0 + m0;
-    if (e >= n) continue;
-    bf16x8 v;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = h[hs(m0 + i, f)];
-    if (e + 8 <= n) {
-      *reinterpret_cast<bf16x8*>(dst + (int64_t)f * ldn + e) = v;
-    } else {
-      for (int i = 0; e + i < n; ++i) dst[(int64_t)f * ldn + e + i] = v[i];
-    }
-  }
-}
-
 // One layer for events [64 blockIdx.x, +64): y is [d][ld] (n <= ld events
 // used) and is transformed in place (the kept coordinates are only read).
 // INVERSE selects the sampling direction.  logq[e] is set (first layer) or
-// accumulated.  The caches use row length n.
+// accumulated.  CACHE keeps the layer's input points in lin [d][n].
 //
 // LDS: one [T][H] BF16 tile that holds the first hidden layer and then the
 // second (written over the first once every wave has read it), and one
@@ -357,8 +279,8 @@ __device__ __forceinline__ void cache_hidden(const bf16* h, bf16* __restrict__ d
 // of the transformed coordinates (2 KiB): 51.0 KiB, so that three
 // workgroups share a compute unit.
 template <bool INVERSE, bool CACHE>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CACHE ? 2 : 3))) k_coupling(LayerDev L, float* __restrict__ y, int64_t n, int64_t ld,
-                                                  float* __restrict__ logq, int first, LayerCache C, int d) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k_coupling(LayerDev L, float* __restrict__ y, int64_t n, int64_t ld,
+                                                  float* __restrict__ logq, int first, float* __restrict__ lin, int d) {
   __shared__ __attribute__((aligned(16))) bf16 h[T * H];
   __shared__ __attribute__((aligned(16))) float out[T * LDO];
   __shared__ float tb[TBMAX * T];
@@ -401,10 +323,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CACHE 
       const int il = i + KLO;
       xa[m * KA + (((i >> 3) ^ (m & 3)) << 3) + (i & 7)] = hi;
       xa[m * KA + (((il >> 3) ^ (m & 3)) << 3) + (il & 7)] = lo;
-      if (CACHE && ev) {
-        C.xa[i * C.ldn + e] = hi;
-        C.xa[il * C.ldn + e] = lo;
-      }
     }
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
@@ -416,7 +334,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CACHE 
     for (int idx = tid; idx < T * d; idx += 256) {
       const int m = idx % T, j = idx / T;
       const int64_t e = e0 + m;
-      if (e < n) C.lin[(int64_t)j * n + e] = y[(int64_t)j * ld + e];
+      if (e < n) lin[(int64_t)j * n + e] = y[(int64_t)j * ld + e];
     }
   }
   __syncthreads();
@@ -446,7 +364,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CACHE 
     store_features(h, acc, wave, row, quad);
   }
   __syncthreads();
-  if (CACHE) cache_hidden(h, C.h1, C.ldn, e0, n, tid);
   {
     f32x4 acc[4][4];
 #pragma unroll
@@ -481,13 +398,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CACHE 
         for (int mt = 0; mt < 4; ++mt) acc[jt][mt] = mfma16(a[ks % 3][jt], b[mt], acc[jt][mt]);
       __builtin_amdgcn_sched_barrier(0);
     }
-    // every wave has read the first layer (and the cache copy is done)
-    // before the second overwrites it
+    // every wave has read the first layer before the second overwrites it
     __syncthreads();
     store_features(h, acc, wave, row, quad);
   }
   __syncthreads();
-  if (CACHE) cache_hidden(h, C.h2, C.ldn, e0, n, tid);
 
   // The 65th logit of every transformed coordinate at once: one more MFMA
   // tile per wave, D[coordinate][event] for the wave's 16 events, with the
@@ -555,14 +470,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CACHE 
     const float lsel = ci == 0 ? lastv[0] : ci == 1 ? lastv[1] : ci == 2 ? lastv[2] : lastv[3];
     const float vlast = __shfl(lsel, (lane >> 2) + 16 * (c >> 2)) + L.b3p[c * NOP + 2 * KB];
     __syncthreads();
-    if (CACHE) {
-      for (int idx = tid; idx < T * 2 * KB; idx += 256) {
-        const int mm = idx / (2 * KB), col = idx % (2 * KB);
-        const int64_t e = e0 + mm;
-        if (e < n) C.o[(e * L.dB + c) * NOP + col] = out[mm * LDO + col];
-      }
-      if (live && part == 3) C.o[(em * L.dB + c) * NOP + 2 * KB] = vlast;
-    }
     {
       float* yp = y + (int64_t)L.b_idx[c] * ld + (live ? em : e0);
       const float t = tb[c * T + m];
@@ -581,407 +488,725 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CACHE 
   }
 }
 
-// ------------------------------------------------------------ PQ backward
-// For event e = 256 blockIdx.x + threadIdx.x and transformed coordinate
-// c = blockIdx.y: given the gradient gz of the loss with respect to the layer
-// output at that coordinate (g[j][e]) and glp = dL/dlog q = -w_e / sum w,
-// replaces g[j][e] by the gradient with respect to the layer input and writes
-// the gradient with respect to the 2K+1 logits (BF16, padded to NOP with
-// zeros), row-major per event and event-contiguous per logit (through an LDS
-// tile, 16-byte stores).
-__global__ void __launch_bounds__(256) k_pq_backward(LayerDev L, LayerCache C, int64_t n, float* __restrict__ g,
-                                                     const float* __restrict__ w, const float* __restrict__ wsum,
-                                                     bf16* __restrict__ go, bf16* __restrict__ goT) {
-  __shared__ __attribute__((aligned(16))) bf16 tile[NOP][256 + 8];
-  const int c = blockIdx.y;
-  const int64_t eb = (int64_t)blockIdx.x * 256;
-  const int64_t e = eb + threadIdx.x;
-  const bool live = e < n;
-  if (live) {
-  const int j = L.b_idx[c];
-  const float* o = C.o + (e * L.dB + c) * NOP;
-  float ol[NO];
+// -------------------------------------------------------- backward layer
+// Operands of the weight gradients of one layer, event-major.
+struct Operands {
+  bf16* xa;   // [n][KA]  inputs of the first dense layer (hi | lo)
+  bf16* h1;   // [n][H]   hidden activations
+  bf16* h2;   // [n][H]
+  bf16* go;   // [n][dB*NOG] gradients of the logits (zero-padded per coordinate)
+  bf16* ga2;  // [n][H]   gradients before the second activation
+  bf16* ga1;  // [n][H]   and before the first
+};
+
+// Sign bits of a lane's 64 features of a hidden layer, in the order of
+// store_features: bit (jt 4 + mt) 4 + i.
+struct Signs {
+  unsigned b[2];
+};
+// store_features that also returns which rounded activations are positive.
+__device__ __forceinline__ Signs store_features_signs(bf16* h, const f32x4 (&acc)[4][4], int wave, int row, int quad) {
+  Signs s{{0u, 0u}};
 #pragma unroll
-  for (int k = 0; k < NO; ++k) ol[k] = o[k];
-  float W[KB], V[KB + 1];
-  pq_params(ol, W, V);
-  const float yv = C.lin[(int64_t)j * n + e];
-  const Bin B = find_bin(W, V, yv, false);
-  const float al = fminf(fmaxf((yv - B.S) / B.Wb, 0.0f), 1.0f);
-  const float dV = B.Vb1 - B.Vb;
-  const float pdf = B.Vb + al * dV;
-  const float gz = g[(int64_t)j * n + e];
-  const float glp = -w[e] / wsum[0];
-  const float gp = glp / pdf;
-  // d/dW_k and d/dV_k of (gz z + glp log pdf) at fixed logits of other bins
-  float GW[KB], GV[KB + 1];
+  for (int jt = 0; jt < 4; ++jt) {
+    const int f0 = 64 * wave + 16 * jt + 4 * quad;
 #pragma unroll
-  for (int k = 0; k <= KB; ++k) GV[k] = 0.0f;
+    for (int mt = 0; mt < 4; ++mt) {
+      bf16x4 v;
 #pragma unroll
-  for (int k = 0; k < KB; ++k) {
-    const bool below = k < B.b, at = k == B.b;
-    const float dz = below ? 0.5f * (V[k] + V[k + 1]) - B.Vb - al * dV : (at ? -0.5f * al * al * dV : 0.0f);
-    const float dp = below ? -dV / B.Wb : (at ? -al * dV / B.Wb : 0.0f);
-    GW[k] = gz * dz + gp * dp;
-    // area terms of z: A_b = sum_{k<b} W_k (V_k + V_k+1)/2
-    if (below) {
-      GV[k] += gz * 0.5f * W[k];
-      GV[k + 1] += gz * 0.5f * W[k];
+      for (int i = 0; i < 4; ++i) {
+        v[i] = (bf16)leaky(acc[jt][mt][i]);
+        s.b[jt >> 1] |= (float)v[i] > 0.0f ? 1u << ((jt & 1) * 16 + mt * 4 + i) : 0u;
+      }
+      *reinterpret_cast<bf16x4*>(h + hs(16 * mt + row, f0)) = v;
     }
   }
+  // the bits now, not the activations until the bits are used
+  asm volatile("" : "+v"(s.b[0]), "+v"(s.b[1]));
+  return s;
+}
+// The gradient before an activation from the one after it, rounded to BF16
+// and stored as store_features does.
+__device__ __forceinline__ void store_gradients(bf16* h, const f32x4 (&acc)[4][4], Signs s, int wave, int row, int quad) {
 #pragma unroll
-  for (int k = 0; k <= KB; ++k) {
-    const bool at = k == B.b, next = k == B.b + 1;
-    GV[k] += at ? gz * B.Wb * (al - 0.5f * al * al) + gp * (1.0f - al) : 0.0f;
-    GV[k] += next ? gz * B.Wb * 0.5f * al * al + gp * al : 0.0f;
+  for (int jt = 0; jt < 4; ++jt) {
+    const int f0 = 64 * wave + 16 * jt + 4 * quad;
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+      bf16x4 v;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        v[i] = (bf16)(acc[jt][mt][i] * ((s.b[jt >> 1] >> ((jt & 1) * 16 + mt * 4 + i)) & 1u ? 1.0f : SLOPE));
+      *reinterpret_cast<bf16x4*>(h + hs(16 * mt + row, f0)) = v;
+    }
   }
-  g[(int64_t)j * n + e] = gz * pdf + glp * (dV / B.Wb) / pdf;
+}
+// A copy of x whose value the compiler does not follow: LDS offsets derived
+// from it are computed where they are used instead of being kept in registers
+// from one phase of the kernel to the next (123 spilled registers otherwise).
+__device__ __forceinline__ int fresh(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+// The [T][H] tile to rows e0.. of an event-major matrix: 512 consecutive
+// bytes per event.
+__device__ __forceinline__ void copy_tile(const bf16* h, bf16* __restrict__ dst, int64_t e0, int64_t n, int tid) {
+#pragma unroll
+  for (int r = 0; r < T * H / 8 / 256; ++r) {
+    const int idx = tid + 256 * r, m = idx >> 5, k = 8 * (idx & 31);
+    if (e0 + m < n) *reinterpret_cast<bf16x8*>(dst + (e0 + m) * H + k) = *reinterpret_cast<const bf16x8*>(h + hs(m, k));
+  }
+}
+// Logit-gradient tile of one coordinate: [T][64] bf16, the eight 16-byte
+// chunks of a row permuted so that the 16 rows of a fragment load fall in
+// different banks.
+__device__ __forceinline__ int gs(int m, int chunk) { return m * 64 + ((chunk ^ ((m ^ (m >> 3)) & 7)) << 3); }
+// After it, a chunk per event for the last logit of an even and of an odd
+// coordinate (the other seven elements stay zero), and one chunk of zeros.
+__device__ __forceinline__ int gs_last(int m, int odd) { return T * 64 + (odd * T + m) * 8; }
+constexpr int GS_ZERO = T * 64 + 2 * T * 8;
+constexpr int GT_CHUNKS = GS_ZERO / 8 + 1;
+
+// Value of lane S of each aligned group of four.
+template <int S> __device__ __forceinline__ float qlane(float x) { return qdpp<0x55 * S>(x); }
+// Sum over the four lanes' terms in order (lane 0's first), each lane adding
+// its terms one by one with f(running sum); every lane returns the total,
+// and start receives the sum before this lane's terms.
+template <class F> __device__ __forceinline__ float ordered_sum(int p, float& start, F f) {
+  float t = 0.0f;
+  start = 0.0f;
+  t = qlane<0>(f(t));
+  start = p == 1 ? t : start;
+  t = qlane<1>(f(t));
+  start = p == 2 ? t : start;
+  t = qlane<2>(f(t));
+  start = p == 3 ? t : start;
+  return qlane<3>(f(t));
+}
+
+// Derivatives of the PQ transform of one coordinate (density direction), four
+// lanes per event as in pq_quad, lane part p holding bins and vertices
+// [8p, 8p+8): from the gradient gz of the loss with respect to the
+// transform's output and glp with respect to its log density, the gradients
+// gw[k] and gv[k] of the part's width and vertex logits, glast of the last
+// vertex logit (p = 3), and the gradient with respect to the input yv.  Sums
+// over bins run in bin order, and the products that are added use one rounding.
+__device__ __forceinline__ void pq_quad_backward(const float* o, float vlast, float yv, int p, float gz, float glp,
+                                                 float (&gw)[KB / 4], float (&gv)[KB / 4], float& glast, float& gy) {
+  constexpr int KP = KB / 4;
+  float W[KP], V[KP + 1], start;
+#pragma unroll
+  for (int k = 0; k < KP; ++k) W[k] = o[KP * p + k];
+#pragma unroll
+  for (int k = 0; k < KP; ++k) V[k] = o[KB + KP * p + k];
+  {
+    const float vn = o[KB + KP * p + (p < 3 ? KP : 0)];
+    V[KP] = p < 3 ? vn : vlast;
+  }
+  float mw = W[0];
+#pragma unroll
+  for (int k = 1; k < KP; ++k) mw = fmaxf(mw, W[k]);
+  mw = max_nc(mw, qdpp<QX1>(mw));
+  mw = max_nc(mw, qdpp<QX2>(mw));
+#pragma unroll
+  for (int k = 0; k < KP; ++k) W[k] = __expf(W[k] - mw);
+  const float sw = ordered_sum(p, start, [&](float t) {
+#pragma unroll
+    for (int k = 0; k < KP; ++k) t += W[k];
+    return t;
+  });
+  const float isw = 1.0f / sw;
+  // bin b of the point: the largest k >= 1 whose left edge is <= yv, else 0;
+  // the edges are running sums of the widths, each product and sum one rounding
+  (void)ordered_sum(p, start, [&](float t) {
+#pragma unroll
+    for (int k = 0; k < KP; ++k) t = __builtin_fmaf(W[k], isw, t);
+    return t;
+  });
+  int b = p == 0 || start <= yv ? KP * p : -1;
+  float S = start, Sb = S;
+#pragma unroll
+  for (int k = 0; k < KP; ++k) {
+    const bool take = k > 0 && S <= yv;
+    b = take ? KP * p + k : b;
+    Sb = take ? S : Sb;
+    S = __builtin_fmaf(W[k], isw, S);
+  }
+  b = max(b, qdpp<QX1>(b));
+  b = max(b, qdpp<QX2>(b));
+#pragma unroll
+  for (int k = 0; k < KP; ++k) W[k] *= isw;
+  float mv = V[0];
+#pragma unroll
+  for (int k = 1; k <= KP; ++k) mv = fmaxf(mv, V[k]);
+  mv = max_nc(mv, qdpp<QX1>(mv));
+  mv = max_nc(mv, qdpp<QX2>(mv));
+#pragma unroll
+  for (int k = 0; k <= KP; ++k) V[k] = __expf(V[k] - mv);
+  const float N = ordered_sum(p, start, [&](float t) {
+#pragma unroll
+    for (int k = 0; k < KP; ++k) t = __builtin_fmaf(0.5f * (V[k] + V[k + 1]), W[k], t);
+    return t;
+  });
+  const float iN = 1.0f / N;
+#pragma unroll
+  for (int k = 0; k <= KP; ++k) V[k] *= iN;
+  float Wb = W[0], Vb = V[0], Vb1 = V[1];
+#pragma unroll
+  for (int k = 1; k < KP; ++k) {
+    const bool at = KP * p + k == b;
+    Wb = at ? W[k] : Wb;
+    Vb = at ? V[k] : Vb;
+    Vb1 = at ? V[k + 1] : Vb1;
+  }
+  {
+    const bool own = (b >> 3) == p;
+    auto bcast = [&](float v) {
+      float x = own ? v : 0.0f;
+      x += qdpp<QX1>(x);
+      return x + qdpp<QX2>(x);
+    };
+    Sb = bcast(Sb);
+    Wb = bcast(Wb);
+    Vb = bcast(Vb);
+    Vb1 = bcast(Vb1);
+  }
+  const float al = fminf(fmaxf((yv - Sb) / Wb, 0.0f), 1.0f);
+  const float dV = Vb1 - Vb;
+  const float pdf = __builtin_fmaf(al, dV, Vb);
+  const float gp = glp / pdf, slope = dV / Wb;
+  // d/dW_k and d/dV_k of (gz z + glp log pdf) at fixed logits of other bins
+  const float wl0 = qdpp<0x90>(W[KP - 1]);  // the width before the part's first (lane p - 1)
+  const float vat = __builtin_fmaf(gz * Wb, __builtin_fmaf(al, -0.5f * al, al), gp * (1.0f - al));
+  const float vnext = __builtin_fmaf(gz * Wb * 0.5f * al, al, gp * al);
+#pragma unroll
+  for (int k = 0; k < KP; ++k) {
+    const int kk = KP * p + k;
+    const bool below = kk < b, at = kk == b;
+    const float dz = below ? __builtin_fmaf(-al, dV, __builtin_fmaf(0.5f, V[k] + V[k + 1], -Vb))
+                           : (at ? -0.5f * al * al * dV : 0.0f);
+    const float dp = below ? -slope : (at ? -al * dV / Wb : 0.0f);
+    gw[k] = __builtin_fmaf(gz, dz, gp * dp);
+    // area terms of z: A_b = sum_{k<b} W_k (V_k + V_k+1)/2
+    const float wl = k > 0 ? W[k - 1] : wl0;
+    float g = kk >= 1 && kk - 1 < b ? gz * 0.5f * wl : 0.0f;
+    g = below ? __builtin_fmaf(gz * 0.5f, W[k], g) : g;
+    g += at ? vat : 0.0f;
+    g += kk == b + 1 ? vnext : 0.0f;
+    gv[k] = g;
+  }
+  glast = KB - 1 < b ? gz * 0.5f * W[KP - 1] : 0.0f;
+  glast += b + 1 == KB ? vnext : 0.0f;
+  gy = __builtin_fmaf(gz, pdf, glp * slope / pdf);
   // through V = exp(v) / N, N = sum_k W_k (exp(v_k) + exp(v_k+1)) / 2, and W = softmax
-  float SG = 0.0f;
+  const float sg = ordered_sum(p, start, [&](float t) {
 #pragma unroll
-  for (int k = 0; k <= KB; ++k) SG += GV[k] * V[k];
-  float SW = 0.0f;
+    for (int k = 0; k < KP; ++k) t = __builtin_fmaf(gv[k], V[k], t);
+    return t;
+  });
+  const float SG = qlane<3>(__builtin_fmaf(glast, V[KP], sg));
 #pragma unroll
-  for (int k = 0; k < KB; ++k) {
-    GW[k] -= SG * 0.5f * (V[k] + V[k + 1]);
-    SW += W[k] * GW[k];
+  for (int k = 0; k < KP; ++k) gw[k] = __builtin_fmaf(-(V[k] + V[k + 1]), SG * 0.5f, gw[k]);
+  const float SW = ordered_sum(p, start, [&](float t) {
+#pragma unroll
+    for (int k = 0; k < KP; ++k) t = __builtin_fmaf(W[k], gw[k], t);
+    return t;
+  });
+#pragma unroll
+  for (int k = 0; k < KP; ++k) {
+    gw[k] = W[k] * (gw[k] - SW);
+    const float wl = k > 0 ? W[k - 1] : (p > 0 ? wl0 : 0.0f);
+    gv[k] = V[k] * __builtin_fmaf(-(wl + W[k]), SG * 0.5f, gv[k]);
   }
-  // row-major for the activation-gradient product, event-contiguous for the
-  // weight-gradient product
-  bf16* dst = go + e * ((int64_t)L.dB * NOP) + (int64_t)c * NOP;
+  glast = V[KP] * __builtin_fmaf(-W[KP - 1], SG * 0.5f, glast);
+}
+
+// One layer of the backward pass for events [64 blockIdx.x, +64), in one
+// kernel: the hidden layers and the logits are computed again from the layer
+// input lin ([d][n]; the same products as in k_coupling, cheaper than keeping
+// 2.4 KB per event and layer), each coordinate's logits give the gradients of
+// its PQ transform, which are multiplied into the gradient of the second
+// hidden layer at once, and so on to the kept inputs.  g ([d][n]) holds the
+// gradient with respect to the layer's output and receives the one with
+// respect to its input; glp = dL/dlog q = -w_e / sum w.  Written to memory:
+// only the operands of the weight gradients, in rows of 64 to 576 bytes per
+// event.  The products run transposed, D[feature][event], so that a lane's
+// gradients are the features whose activations it computed and their signs
+// stay in two registers per layer.
+//
+// LDS: the [T][H] tile holds the first hidden layer, the second, the gradient
+// before the second activation and that before the first; the logits of the
+// current coordinate (before that, the first layer's inputs); its logit
+// gradients; the last logits' gradients of all coordinates; the transformed
+// inputs: 60 KiB, two workgroups per compute unit.
+//
+// Sums over bins, and over k in the products, keep one fixed order: a BF16
+// rounding that falls the other way changes an event's gradient by 2^-9.
+//
+// Bound by vector instructions (51 % of the time; the matrix instructions take
+// 20 %) at two waves per SIMD.  65536 points of 10 dimensions, per layer: 96
+// us.  As separate kernels over cached activations and logits the same work
+// took 285 us: PQ derivatives 67, two products with BF16 epilogues 76 each,
+// the input product 17, its addition 6, and 43 for writing the caches in the
+// forward pass.
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+k_layer_backward(LayerDev L, const float* __restrict__ lin, int64_t n, float* __restrict__ g,
+                 const float* __restrict__ w, const float* __restrict__ wsum, Operands out_op) {
+  __shared__ __attribute__((aligned(16))) bf16 h[T * H];
+  __shared__ __attribute__((aligned(16))) float out[T * LDO];
+  __shared__ __attribute__((aligned(16))) bf16 gt[GT_CHUNKS * 8];
+  __shared__ float tb[TBMAX * T];
+  bf16* xa = reinterpret_cast<bf16*>(out);  // [T][KA]
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t e0 = (int64_t)blockIdx.x * T;
+  const int row = lane & 15, quad = lane >> 4;
+  // inputs as in k_coupling
+  {
+    const int m = lane;
+    const int64_t e = e0 + m;
+    const bool ev = e < n;
+    float v[4], tv[2];
 #pragma unroll
-  for (int k = 0; k < KB; ++k) {
-    const bf16 v = (bf16)(W[k] * (GW[k] - SW));
-    dst[k] = v;
-    tile[k][threadIdx.x] = v;
-  }
+    for (int r = 0; r < 4; ++r) {
+      const int i = wave + 4 * r;
+      v[r] = (i < L.dA && ev) ? lin[(int64_t)L.a_idx[i] * n + e] : 0.0f;
+    }
 #pragma unroll
-  for (int k = 0; k <= KB; ++k) {
-    const float wl = k > 0 ? W[k - 1] : 0.0f, wr = k < KB ? W[k] : 0.0f;
-    const bf16 v = (bf16)(V[k] * (GV[k] - SG * 0.5f * (wl + wr)));
-    dst[KB + k] = v;
-    tile[KB + k][threadIdx.x] = v;
-  }
+    for (int r = 0; r < 2; ++r) {
+      const int j = wave + 4 * r;
+      tv[r] = (j < L.dB && ev) ? lin[(int64_t)L.b_idx[j] * n + e] : 0.5f;
+    }
 #pragma unroll
-  for (int k = NO; k < NOP; ++k) {
-    dst[k] = (bf16)0.0f;
-    tile[k][threadIdx.x] = (bf16)0.0f;
-  }
+    for (int r = 0; r < 4; ++r) {
+      const int i = wave + 4 * r;
+      const bf16 hi = (bf16)v[r];
+      const bf16 lo = (bf16)(v[r] - (float)hi);
+      const int il = i + KLO;
+      xa[m * KA + (((i >> 3) ^ (m & 3)) << 3) + (i & 7)] = hi;
+      xa[m * KA + (((il >> 3) ^ (m & 3)) << 3) + (il & 7)] = lo;
+    }
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const int j = wave + 4 * r;
+      if (j < L.dB) tb[j * T + m] = tv[r];
+    }
+    for (int i = T * 64 + tid; i < GT_CHUNKS * 8; i += 256) gt[i] = (bf16)0.0f;
   }
   __syncthreads();
-  // event-contiguous copy: 8 events of one logit per 16-byte store
-  bf16* dstT = goT + (int64_t)c * NOP * C.ldn;
-  for (int ch = threadIdx.x; ch < NOP * 32; ch += 256) {
-    const int k = ch / 32, e8 = 8 * (ch % 32);
-    const int64_t ee = eb + e8;
-    if (ee >= n) continue;
-    const bf16x8 v = *reinterpret_cast<const bf16x8*>(&tile[k][e8]);
-    if (ee + 8 <= n) {
-      *reinterpret_cast<bf16x8*>(dstT + (int64_t)k * C.ldn + ee) = v;
-    } else {
-      for (int i = 0; ee + i < n; ++i) dstT[(int64_t)k * C.ldn + ee + i] = v[i];
+  {
+    const int m = tid >> 2, k = tid & 3;  // one 16-byte chunk of the inputs per thread
+    if (e0 + m < n)
+      *reinterpret_cast<bf16x8*>(out_op.xa + (e0 + m) * KA + 8 * k) =
+          *reinterpret_cast<const bf16x8*>(xa + m * KA + ((k ^ (m & 3)) << 3));
+  }
+  Signs s1, s2;
+  {
+    f32x4 acc[4][4];
+    bf16x8 a[4], b[4];
+#pragma unroll
+    for (int jt = 0; jt < 4; ++jt)
+      a[jt] = *reinterpret_cast<const bf16x8*>(L.W1t + (64 * wave + 16 * jt + row) * KA + 8 * quad);
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+      const int m = 16 * mt + row;
+      b[mt] = *reinterpret_cast<const bf16x8*>(xa + m * KA + ((quad ^ (m & 3)) << 3));
+    }
+#pragma unroll
+    for (int jt = 0; jt < 4; ++jt) {
+      const f32x4 bias = bias4(L.b1, wave, jt, quad);
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt) acc[jt][mt] = mfma16(a[jt], b[mt], bias);
+    }
+    s1 = store_features_signs(h, acc, wave, fresh(row), quad);
+  }
+  __syncthreads();
+  copy_tile(h, out_op.h1, e0, n, fresh(tid));
+  // [H x H] product with the tile: fragments of packed rows W, as in k_coupling
+  auto dense = [&](const bf16* Wp, f32x4 (&acc)[4][4]) {
+    const bf16* W2 = Wp + (int64_t)wave * 8 * 4 * 512 + lane * 8;
+    const int rb = fresh(row);
+    bf16x8 a[3][4];
+#pragma unroll
+    for (int st = 0; st < 2; ++st)
+#pragma unroll
+      for (int jt = 0; jt < 4; ++jt) a[st][jt] = *reinterpret_cast<const bf16x8*>(W2 + (st * 4 + jt) * 512);
+#pragma unroll
+    for (int ks = 0; ks < H / 32; ++ks) {
+      if (ks + 2 < H / 32) {
+#pragma unroll
+        for (int jt = 0; jt < 4; ++jt)
+          a[(ks + 2) % 3][jt] = *reinterpret_cast<const bf16x8*>(W2 + ((ks + 2) * 4 + jt) * 512);
+      }
+      bf16x8 b[4];
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt)
+        b[mt] = *reinterpret_cast<const bf16x8*>(h + hs(16 * mt + rb, 32 * ks + 8 * quad));
+#pragma unroll
+      for (int jt = 0; jt < 4; ++jt)
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) acc[jt][mt] = mfma16(a[ks % 3][jt], b[mt], acc[jt][mt]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  {
+    f32x4 acc[4][4];
+#pragma unroll
+    for (int jt = 0; jt < 4; ++jt) {
+      const f32x4 bias = bias4(L.b2, wave, jt, quad);
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt) acc[jt][mt] = bias;
+    }
+    dense(L.W2p, acc);
+    __syncthreads();  // every wave has read the first layer
+    s2 = store_features_signs(h, acc, wave, fresh(row), quad);
+  }
+  __syncthreads();
+  copy_tile(h, out_op.h2, e0, n, fresh(tid));
+  f32x4 lastv = {0.0f, 0.0f, 0.0f, 0.0f};
+  {
+    const bf16* wl = L.W3L + lane * 8;
+#pragma unroll
+    for (int ks = 0; ks < H / 32; ++ks) {
+      const bf16x8 a = *reinterpret_cast<const bf16x8*>(wl + ks * 512);
+      const bf16x8 b = *reinterpret_cast<const bf16x8*>(h + hs(16 * wave + row, 32 * ks + 8 * quad));
+      lastv = mfma16(a, b, lastv);
+    }
+  }
+  // gradient after the second activation, accumulated over the coordinates
+  f32x4 acc[4][4];
+#pragma unroll
+  for (int jt = 0; jt < 4; ++jt)
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) acc[jt][mt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  const int m = tid >> 2, part = tid & 3;
+  const int64_t em = e0 + m;
+  const bool live = em < n;
+  const float glp = live ? -w[em] / wsum[0] : 0.0f;
+  const int NB = L.dB * NOG;
+  for (int c = 0; c < L.dB; ++c) {
+    {
+      const bf16* W3 = L.W3p + (((int64_t)c * 4 + wave) * 8) * 512 + lane * 8;
+      const int col = 16 * wave + row;
+      const float bias = L.b3p[c * NOP + col];
+      f32x4 lg[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) lg[r] = f32x4{bias, bias, bias, bias};
+#pragma unroll
+      for (int ks = 0; ks < H / 32; ++ks) {
+        const bf16x8 bw = *reinterpret_cast<const bf16x8*>(W3 + ks * 512);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const bf16x8 a = *reinterpret_cast<const bf16x8*>(h + hs(16 * r + row, 32 * ks + 8 * quad));
+          lg[r] = mfma16(a, bw, lg[r]);
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) out[(16 * r + 4 * quad + i) * LDO + col] = lg[r][i];
+    }
+    const int ci = c & 3;
+    const float lsel = ci == 0 ? lastv[0] : ci == 1 ? lastv[1] : ci == 2 ? lastv[2] : lastv[3];
+    const float vlast = __shfl(lsel, (lane >> 2) + 16 * (c >> 2)) + L.b3p[c * NOP + 2 * KB];
+    float* gp = g + (int64_t)L.b_idx[c] * n + (live ? em : e0);
+    const float gz = live ? *gp : 0.0f;
+    // this coordinate's fragments for the gradient, requested before the PQ
+    // derivatives
+    const int odd = c & 1;
+    const bf16* wqc = L.W3q + ((int64_t)((c >> 1) * 5 + 2 * odd) * 16 + wave * 4) * 512 + lane * 8;
+    bf16x8 wq[2][4];
+#pragma unroll
+    for (int st = 0; st < 2; ++st)
+#pragma unroll
+      for (int jt = 0; jt < 4; ++jt) wq[st][jt] = *reinterpret_cast<const bf16x8*>(wqc + (st * 16 + jt) * 512);
+    __syncthreads();  // logits complete; the previous coordinate's gradients have been read
+    {
+      float gw[KB / 4], gv[KB / 4], gl, gy;
+      pq_quad_backward(out + m * LDO, vlast, tb[c * T + m], part, gz, glp, gw, gv, gl, gy);
+      if (live && part == 0) *gp = gy;
+      bf16x8 a, b;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        a[k] = (bf16)gw[k];
+        b[k] = (bf16)gv[k];
+      }
+      bf16x8 l8;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) l8[k] = k == 0 ? (bf16)gl : (bf16)0.0f;
+      *reinterpret_cast<bf16x8*>(gt + gs(m, part)) = a;
+      *reinterpret_cast<bf16x8*>(gt + gs(m, 4 + part)) = b;
+      if (part == 3) gt[gs_last(m, odd)] = (bf16)gl;
+      if (live) {
+        bf16* dst = out_op.go + em * NB + c * NOG;
+        *reinterpret_cast<bf16x8*>(dst + 8 * part) = a;
+        *reinterpret_cast<bf16x8*>(dst + KB + 8 * part) = b;
+        if (part == 3) *reinterpret_cast<bf16x8*>(dst + 2 * KB) = l8;
+      }
+    }
+    __syncthreads();
+    // k steps of 32 over NOP columns per coordinate: two for an even
+    // coordinate; three for an odd one, the first beginning with the last
+    // logit of the one before, the third ending with its own.  An even last
+    // coordinate ends with a step of its last logit.
+    auto step = [&](const bf16x8 (&aw)[4], int chunk) {
+      bf16x8 b[4];
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt) {
+        const int mm = 16 * mt + row;
+        int at = gs(mm, chunk & 7);
+        at = chunk < 0 || chunk > 8 ? GS_ZERO : at;
+        at = chunk == -2 || chunk == 8 ? gs_last(mm, chunk == 8 ? odd : 0) : at;
+        b[mt] = *reinterpret_cast<const bf16x8*>(gt + at);
+      }
+#pragma unroll
+      for (int jt = 0; jt < 4; ++jt)
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) acc[jt][mt] = mfma16(aw[jt], b[mt], acc[jt][mt]);
+    };
+    step(wq[0], quad - 2 * odd);
+    step(wq[1], quad + 4 - 2 * odd);
+    if (odd || c + 1 == L.dB) {
+#pragma unroll
+      for (int jt = 0; jt < 4; ++jt) wq[0][jt] = *reinterpret_cast<const bf16x8*>(wqc + (32 + jt) * 512);
+      step(wq[0], quad + 8 - 2 * odd);
+    }
+  }
+  // every wave read the second layer before the barriers of the last coordinate
+  store_gradients(h, acc, s2, wave, fresh(row), quad);
+  __syncthreads();
+  copy_tile(h, out_op.ga2, e0, n, fresh(tid));
+#pragma unroll
+  for (int jt = 0; jt < 4; ++jt)
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) acc[jt][mt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  dense(L.W2q, acc);
+  __syncthreads();
+  store_gradients(h, acc, s1, wave, fresh(row), quad);
+  __syncthreads();
+  copy_tile(h, out_op.ga1, e0, n, fresh(tid));
+  // gradient reaching the kept coordinates: D[coordinate][event], the wave's
+  // 16 events
+  f32x4 gx = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int ks = 0; ks < H / 32; ++ks) {
+    const bf16x8 a = *reinterpret_cast<const bf16x8*>(L.W1q + ks * 512 + lane * 8);
+    const bf16x8 b = *reinterpret_cast<const bf16x8*>(h + hs(16 * wave + row, 32 * ks + 8 * quad));
+    gx = mfma16(a, b, gx);
+  }
+  const int64_t eg = e0 + 16 * wave + row;
+  if (eg < n) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int ci = 4 * quad + i;
+      if (ci < L.dA) g[(int64_t)L.a_idx[ci] * n + eg] += gx[i];
     }
   }
 }
 
-// ------------------------------------------------------------------ GEMM
-// C[M x N] = sum over k in the z-th chunk of A(m,k) B(k,n), BF16 operands,
-// FP32 accumulation, tile 64 x 64 per workgroup, k-step 32 staged in LDS.
-//   A_KC: A(m,k) = A[m lda + k] (1) or A[k lda + m] (0)
-//   B_NC: B(k,n) = B[k ldb + n] (1) or B[n ldb + k] (0)
-//   EPI 0: FP32 store to Cf + z zs + m ldc + n (split-K partials); with
-//          colsum set, row M of the partial receives the column sums of B
-//          over the chunk (one more MFMA per k-step with an all-ones A
-//          fragment in the first row of blocks)
-//   EPI 1: BF16 store to Cb[m ldc + n] of acc * (ref[m + n ref_cs] > 0 ? 1 : slope),
-//          and of the same values to CbT[n ldt + m] (event-contiguous copy);
-//          the references are event-contiguous (ref_rs = 1), and Cb, CbT and
-//          ref rows are 16-byte aligned
-struct GemmArgs {
-  const bf16* A;
-  int64_t lda;
-  const bf16* B;
-  int64_t ldb;
-  int M, N;
-  int64_t K, kchunk;
-  float* Cf;
-  int64_t zs;
-  bf16* Cb;
-  const bf16* ref;
-  int64_t ldc, ref_rs, ref_cs;
-  bf16* CbT;
-  int64_t ldt;
-  int colsum;
+// ------------------------------------------------------ weight gradients
+// dW[m][j] = sum over events of X[e][m] G[e][j] for the three dense layers of
+// one coupling layer (X = h2, h1, xa and G = go, ga2, ga1), with the column
+// sums of G (the bias gradients) as row M, in partials over chunks of events:
+// part[z zs + off + m N + j].  All three products are one launch, numbered so
+// that the tiles of one chunk run on one XCD and share their operands in its
+// L2.  A workgroup takes a 128 x 128 tile, each of its four waves 64 x 64: a
+// fragment read from LDS then serves four matrix instructions (two for the
+// 32 x 32 of a 64 x 64 tile, which is bound by LDS reads).  The operands are
+// event-major and the events are the contraction, so the fragments come from
+// LDS transposed (ds_read_b64_tr_b16): a group of 16 lanes reads 4 events x 16
+// features, lane i receiving feature i of the four events.  Per k step of 32
+// events lane group q takes events 4q..4q+3 and 16+4q..16+4q+3 for both
+// operands; with rows of 288 bytes the 8 rows of half a wave fall in different
+// banks (no conflicts counted).  Bound by memory: 65536 points of 10
+// dimensions, per layer, read and write 212 MB in 57 us (3.7 TB/s, a copy
+// reaches 4.7) and the reduction takes 16 us; three launches of 64 x 64 tiles
+// on event-contiguous copies and three reductions took 250 us.
+constexpr int WT = 128;        // tile edge
+constexpr int WK = 64;         // events per staged slice: two k steps
+constexpr int WLD = WT + 16;   // LDS row stride (bf16)
+struct WgradArgs {
+  const bf16* X[3];
+  const bf16* G[3];
+  int M[3], N[3];
+  int tiles_n[3], first[3];  // column tiles; first tile number of the product
+  int tiles;                 // of all products
+  int64_t off[3], zs;        // partial offsets and stride
+  int64_t n, chunk;
+  float* part;
 };
-
-constexpr int GK = 64;        // k depth of one staged slice
-constexpr int GLD = GK + 8;   // LDS row stride (bf16) of a staged slice
-
-// C = A B over k in [kchunk z, kchunk (z+1)) for the 64 x 64 output tile of
-// the workgroup; four waves of 32 x 32, v_mfma_f32_16x16x32_bf16.  A is
-// staged from k-contiguous rows A[m lda + k]; B from B[n ldb + k] (B_NC = 0)
-// or B[k ldb + n] (B_NC = 1, transposed into LDS).  The k slices are double
-// buffered: the next slice's global loads are issued into registers before
-// the current slice's products, and each slice costs one barrier.
-template <int A_KC, int B_NC, int EPI>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k_gemm(GemmArgs g) {
-  static_assert(A_KC == 1, "A is staged from k-contiguous rows");
-  // the two double-buffered slices; after the k loop the same memory holds
-  // the FP32 output tile of the BF16 epilogue
-  __shared__ __attribute__((aligned(16))) bf16 smem[4 * 64 * GLD];
-  bf16(*As)[64 * GLD] = reinterpret_cast<bf16(*)[64 * GLD]>(smem);
-  bf16(*Bs)[64 * GLD] = reinterpret_cast<bf16(*)[64 * GLD]>(smem + 2 * 64 * GLD);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ bf16x8 tr_fragment(const bf16* base, int k, int f, int lane) {
+  // events k + 4q + (0..3) and k + 16 + 4q + (0..3), feature f + (lane & 15)
+  typedef __attribute__((address_space(3))) s16x4* P;
+  const int q = lane >> 4, i = lane & 15;
+  const bf16* p = base + (k + 4 * q + (i >> 2)) * WLD + f + 4 * (i & 3);
+  union {
+    s16x4 s[2];
+    bf16x8 v;
+  } u;
+  u.s[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((P)p);
+  u.s[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((P)(p + 16 * WLD));
+  return u.v;
+}
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_wgrad(WgradArgs a) {
+  __shared__ __attribute__((aligned(16))) bf16 Xs[2][WK * WLD];
+  __shared__ __attribute__((aligned(16))) bf16 Gs[2][WK * WLD];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int row = lane & 15, quad = lane >> 4;
-  // XCD-aware tile order: workgroup b runs on XCD b mod 8, so the tiles are
-  // numbered XCD by XCD; consecutive tiles (the column tiles of one row
-  // tile, the tiles of one event chunk) then share an XCD and its L2, and
-  // their common operand rows are read from HBM once
-  int tx, ty, tz;
-  {
-    const int gx = gridDim.x, gy = gridDim.y;
-    const int G = gx * gy * gridDim.z;
-    const int b = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
-    const int xcd = b & 7, slot = b >> 3, per = G >> 3, rem = G & 7;
-    const int t = xcd * per + (xcd < rem ? xcd : rem) + slot;
-    tx = t % gx;
-    ty = (t / gx) % gy;
-    tz = t / (gx * gy);
+  // workgroup b runs on XCD b mod 8: tiles are numbered XCD by XCD
+  const int G = gridDim.x, xcd = blockIdx.x & 7, per = G >> 3, rem = G & 7;
+  const int t = xcd * per + (xcd < rem ? xcd : rem) + (int)(blockIdx.x >> 3);
+  const int z = t / a.tiles, tl = t % a.tiles;
+  const int pr = tl >= a.first[2] ? 2 : (tl >= a.first[1] ? 1 : 0);
+  const bf16* X = pr == 2 ? a.X[2] : (pr == 1 ? a.X[1] : a.X[0]);
+  const bf16* Gp = pr == 2 ? a.G[2] : (pr == 1 ? a.G[1] : a.G[0]);
+  const int M = pr == 2 ? a.M[2] : (pr == 1 ? a.M[1] : a.M[0]);
+  const int N = pr == 2 ? a.N[2] : (pr == 1 ? a.N[1] : a.N[0]);
+  const int tn = pr == 2 ? a.tiles_n[2] : (pr == 1 ? a.tiles_n[1] : a.tiles_n[0]);
+  const int tp = tl - (pr == 2 ? a.first[2] : (pr == 1 ? a.first[1] : a.first[0]));
+  const int m0 = tp / tn * WT, n0 = tp % tn * WT;
+  const int64_t kb = (int64_t)z * a.chunk, ke = kb + a.chunk < a.n ? kb + a.chunk : a.n;
+  const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
+  f32x4 acc[4][4], accs[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    accs[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   }
-  const int m0 = ty * 64, n0 = tx * 64;
-  const int64_t kb = (int64_t)tz * g.kchunk;
-  const int64_t ke = kb + g.kchunk < g.K ? kb + g.kchunk : g.K;
-  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-  f32x4 acc[2][2];
+  const bool sums = m0 == 0 && wm == 0;
+  const bool work = m0 + wm < M;  // the wave's rows exist (the first layer has 32)
+  bf16x8 ones, zero;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < 8; ++i) {
+    ones[i] = (bf16)1.0f;
+    zero[i] = (bf16)0.0f;
+  }
+  // this thread's share of a slice: rows r0 + 16 r, eight features from c8;
+  // rows past the chunk and columns past the matrix are loaded from an
+  // in-range place and stored as zeros (M and N are multiples of 8)
+  const int r0 = tid >> 4, c8 = (tid & 15) * 8;
+  const bool vx = m0 + c8 < M, vg = n0 + c8 < N;
+  const bf16* Xc = X + (vx ? m0 + c8 : 0);
+  const bf16* Gc = Gp + (vg ? n0 + c8 : 0);
+  // two register stages: the slices k + 1 and k + 2 are in flight while slice
+  // k is multiplied
+  bf16x8 rx[2][4], rg[2][4];
+  auto load = [&](int64_t k0, bf16x8 (&x)[4], bf16x8 (&g)[4]) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  f32x4 accs[2] = {f32x4{0.0f, 0.0f, 0.0f, 0.0f}, f32x4{0.0f, 0.0f, 0.0f, 0.0f}};
-  const bool sums = EPI == 0 && g.colsum && ty == 0 && wm == 0;
-  bf16x8 ones;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) ones[i] = (bf16)1.0f;
-  // this thread's share of a slice: rows (or k) r0 and r0 + 32, eight
-  // consecutive elements from c8, one 16-byte load each.  The loads have no
-  // branches (so that the waits for a slice do not wait for the next one):
-  // rows and chunks outside the operand read an in-range chunk instead, and
-  // the number of valid elements of each chunk (0-8) zeroes the rest when
-  // the slice is stored.  The caller guarantees 16-byte aligned rows: base
-  // and leading dimension multiples of 8 elements, so a chunk that starts
-  // inside a row ends inside it.
-  const int r0 = tid >> 3, c8 = (tid & 7) * 8;
-  // two register stages: the slices k + 1 and k + 2 are in flight while
-  // slice k is multiplied
-  bf16x8 ra0[2], rb0[2], ra1[2], rb1[2];
-  // valid elements of this thread's A and B chunks h of the slice at k0
-  auto nvalid = [](int64_t lim, int64_t j) -> int {
-    const int64_t r = lim - j;
-    return r <= 0 ? 0 : (r >= 8 ? 8 : (int)r);
-  };
-  auto va = [&](int64_t k0, int h) -> int { return m0 + r0 + 32 * h < g.M ? nvalid(ke, k0 + c8) : 0; };
-  auto vb = [&](int64_t k0, int h) -> int {
-    if (B_NC) return k0 + r0 + 32 * h < ke ? nvalid(g.N, n0 + c8) : 0;
-    return n0 + r0 + 32 * h < g.N ? nvalid(ke, k0 + c8) : 0;
-  };
-  auto load = [&](int64_t k0, bf16x8 (&ra)[2], bf16x8 (&rb)[2]) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int gm = m0 + r0 + 32 * h;
-      ra[h] = *reinterpret_cast<const bf16x8*>(g.A + (int64_t)(gm < g.M ? gm : 0) * g.lda + (va(k0, h) > 0 ? k0 + c8 : kb));
-      if (B_NC) {
-        const int64_t gk = k0 + r0 + 32 * h;
-        rb[h] = *reinterpret_cast<const bf16x8*>(g.B + (gk < ke ? gk : kb) * g.ldb + (vb(k0, h) > 0 ? n0 + c8 : 0));
-      } else {
-        const int gn = n0 + r0 + 32 * h;
-        rb[h] = *reinterpret_cast<const bf16x8*>(g.B + (int64_t)(gn < g.N ? gn : 0) * g.ldb + (vb(k0, h) > 0 ? k0 + c8 : kb));
-      }
+    for (int r = 0; r < 4; ++r) {
+      const int64_t e = k0 + r0 + 16 * r, ec = e < ke ? e : kb;
+      x[r] = *reinterpret_cast<const bf16x8*>(Xc + ec * M);
+      g[r] = *reinterpret_cast<const bf16x8*>(Gc + ec * N);
     }
   };
-  // A rows m-major, B rows n-major in LDS, each row GK consecutive k
-  auto store = [&](int buf, bf16x8 (&ra)[2], bf16x8 (&rb)[2], int64_t k0) {
+  auto store = [&](int buf, int64_t k0, const bf16x8 (&x)[4], const bf16x8 (&g)[4]) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int na = va(k0, h), nb = vb(k0, h);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        ra[h][i] = i < na ? ra[h][i] : (bf16)0.0f;
-        rb[h][i] = i < nb ? rb[h][i] : (bf16)0.0f;
-      }
-      *reinterpret_cast<bf16x8*>(&As[buf][(r0 + 32 * h) * GLD + c8]) = ra[h];
-      if (B_NC) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) Bs[buf][(c8 + i) * GLD + r0 + 32 * h] = rb[h][i];
-      } else {
-        *reinterpret_cast<bf16x8*>(&Bs[buf][(r0 + 32 * h) * GLD + c8]) = rb[h];
-      }
+    for (int r = 0; r < 4; ++r) {
+      const bool ok = k0 + r0 + 16 * r < ke;
+      *reinterpret_cast<bf16x8*>(&Xs[buf][(r0 + 16 * r) * WLD + c8]) = ok && vx ? x[r] : zero;
+      *reinterpret_cast<bf16x8*>(&Gs[buf][(r0 + 16 * r) * WLD + c8]) = ok && vg ? g[r] : zero;
     }
   };
   auto products = [&](int buf) {
+    if (!work) return;
 #pragma unroll
-    for (int kk = 0; kk < GK; kk += 32) {
-      bf16x8 a[2], b[2];
+    for (int kk = 0; kk < WK; kk += 32) {
+      bf16x8 x[4], y[4];
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-        a[i] = *reinterpret_cast<const bf16x8*>(&As[buf][(wm + 16 * i + row) * GLD + kk + 8 * quad]);
+      for (int i = 0; i < 4; ++i) x[i] = tr_fragment(Xs[buf], kk, wm + 16 * i, lane);
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
-        b[j] = *reinterpret_cast<const bf16x8*>(&Bs[buf][(wn + 16 * j + row) * GLD + kk + 8 * quad]);
+      for (int j = 0; j < 4; ++j) y[j] = tr_fragment(Gs[buf], kk, wn + 16 * j, lane);
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = mfma16(a[i], b[j], acc[i][j]);
+        for (int j = 0; j < 4; ++j) acc[i][j] = mfma16(x[i], y[j], acc[i][j]);
       if (sums) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) accs[j] = mfma16(ones, b[j], accs[j]);
+        for (int j = 0; j < 4; ++j) accs[j] = mfma16(ones, y[j], accs[j]);
       }
     }
   };
-  // slices alternate between the register stages and the LDS buffers; the
-  // buffer written for a slice was last read two slices before, ahead of the
-  // previous slice's barrier.  Each iteration takes two slices and issues the
-  // loads of the two after them (empty past the chunk, reading its first
-  // columns), so that every iteration has the same loads in flight; an odd
-  // last slice follows the loop.
-  load(kb, ra0, rb0);
-  load(kb + GK, ra1, rb1);
+  // slice k is stored to buffer k mod 2, which was last read two slices
+  // before, ahead of the previous slice's barrier; loads past the chunk read
+  // its first event
+  load(kb, rx[0], rg[0]);
+  load(kb + WK, rx[1], rg[1]);
   int64_t k0 = kb;
-  for (; k0 + GK < ke; k0 += 2 * GK) {
-    store(0, ra0, rb0, k0);
+  for (; k0 + WK < ke; k0 += 2 * WK) {
+    store(0, k0, rx[0], rg[0]);
     __syncthreads();
-    load(k0 + 2 * GK, ra0, rb0);
+    load(k0 + 2 * WK, rx[0], rg[0]);
     products(0);
-    store(1, ra1, rb1, k0 + GK);
+    store(1, k0 + WK, rx[1], rg[1]);
     __syncthreads();
-    load(k0 + 3 * GK, ra1, rb1);
+    load(k0 + 3 * WK, rx[1], rg[1]);
     products(1);
   }
   if (k0 < ke) {
-    store(0, ra0, rb0, k0);
+    store(0, k0, rx[0], rg[0]);
     __syncthreads();
     products(0);
   }
-  if (sums && quad == 0) {
+  float* P = a.part + (int64_t)z * a.zs + (pr == 2 ? a.off[2] : (pr == 1 ? a.off[1] : a.off[0]));
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int gn = n0 + wn + 16 * j + row;
-      if (gn < g.N) g.Cf[(int64_t)tz * g.zs + (int64_t)g.M * g.ldc + gn] = accs[j][0];
-    }
-  }
-  if (EPI == 0) {
+  for (int j = 0; j < 4; ++j) {
+    const int gn = n0 + wn + 16 * j + row;
+    if (gn >= N) continue;
+    if (sums && quad == 0) P[(int64_t)M * N + gn] = accs[j][0];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 4; ++i) {
+      const int gm = m0 + wm + 16 * i + 4 * quad;
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int gn = n0 + wn + 16 * j + row;
-        if (gn >= g.N) continue;
-        const int gm0 = m0 + wm + 16 * i + 4 * quad;
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (gm0 + r < g.M) g.Cf[(int64_t)tz * g.zs + (int64_t)(gm0 + r) * g.ldc + gn] = acc[i][j][r];
-      }
-  } else {
-    // The tile goes through LDS (FP32, row stride LDT: the fragment stores
-    // at most two-way bank conflicts, the column reads none), so that the
-    // sign references are read and both BF16 copies written with 16-byte
-    // accesses: first eight consecutive events of one feature per thread
-    // (references, scaling, the event-contiguous copy; the rounded values go
-    // back to the tile), then eight consecutive features of one event (the
-    // row-major copy).  The references are event-contiguous (ref_rs = 1).
-    constexpr int LDT = 73;
-    static_assert(64 * LDT * sizeof(float) <= sizeof(smem), "the output tile must fit the slice buffers");
-    float* Ts = reinterpret_cast<float*>(smem);
-    __syncthreads();  // every wave is done with the slices
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) Ts[(wm + 16 * i + 4 * quad + r) * LDT + wn + 16 * j + row] = acc[i][j][r];
-    __syncthreads();
-    for (int q = tid; q < 64 * 8; q += 256) {
-      const int c = q & 7, nn = q >> 3;
-      const int gm = m0 + 8 * c, gn = n0 + nn;
-      if (gm >= g.M || gn >= g.N) continue;
-      const bool full = gm + 8 <= g.M;
-      const bf16* rp = g.ref + (int64_t)gn * g.ref_cs + gm;
-      bf16x8 rv;
-      if (full) {
-        rv = *reinterpret_cast<const bf16x8*>(rp);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) rv[e] = gm + e < g.M ? rp[e] : (bf16)0.0f;
-      }
-      bf16x8 t;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        float* tp = Ts + (8 * c + e) * LDT + nn;
-        t[e] = (bf16)(*tp * ((float)rv[e] > 0.0f ? 1.0f : SLOPE));
-        *tp = (float)t[e];
-      }
-      bf16* dp = g.CbT + (int64_t)gn * g.ldt + gm;
-      if (full) {
-        *reinterpret_cast<bf16x8*>(dp) = t;
-      } else {
-        for (int e = 0; gm + e < g.M; ++e) dp[e] = t[e];
-      }
-    }
-    __syncthreads();
-    for (int q = tid; q < 64 * 8; q += 256) {
-      const int k = q & 7, mm = q >> 3;
-      const int gm = m0 + mm, gn = n0 + 8 * k;
-      if (gm >= g.M || gn >= g.N) continue;
-      bf16x8 t;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) t[e] = (bf16)Ts[mm * LDT + 8 * k + e];
-      bf16* dp = g.Cb + (int64_t)gm * g.ldc + gn;
-      if (gn + 8 <= g.N) {
-        *reinterpret_cast<bf16x8*>(dp) = t;
-      } else {
-        for (int e = 0; gn + e < g.N; ++e) dp[e] = t[e];
-      }
+      for (int r = 0; r < 4; ++r)
+        if (gm + r < M) P[(int64_t)(gm + r) * N + gn] = acc[i][j][r];
     }
   }
 }
 
-// out[m ldo + map(n)] = sum_z part[z][m][n] (+ part[z][m + fold][n] when
-// fold > 0: the two halves of a split input) for m < m_real, and
-// bias[map(n)] = sum_z part[z][M][n] (the column-sum row); partials have
-// M + 1 rows.  The column map drops the padding of groups of gpad columns to
-// greal (gpad = 0: identity).  Sums run over z in order.
-__global__ void k_reduce_grad(const float* __restrict__ part, int Z, int M, int N, int m_real, int gpad, int greal,
-                              float* __restrict__ out, int ldo, int fold, float* __restrict__ bias) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)(m_real + 1) * N) return;
-  const int m = (int)(idx / N);
-  const int nn = (int)(idx % N);
-  int col = nn;
-  if (gpad) {
-    if (nn % gpad >= greal) return;
-    col = (nn / gpad) * greal + nn % gpad;
-  }
-  const int64_t zs = (int64_t)(M + 1) * N;
-  if (m == m_real) {
-    float s = 0.0f;
-    for (int z = 0; z < Z; ++z) s += part[z * zs + (int64_t)M * N + nn];
-    bias[col] = s;
-    return;
+// The gradients of one layer from the partials, summed over the chunks in
+// order: W3 and b3 without the padding of each coordinate's columns, W2 and
+// b2, W1 (the sum of the products with the high and the low input parts) and
+// b1.  grad: the layer's slice of the gradient.
+__global__ void __launch_bounds__(256) k_reduce_layer(const float* __restrict__ part, int Z, int64_t zs, int dA, int dB,
+                                                      float* __restrict__ grad) {
+  const int N3 = dB * NOG, nO = dB * NO;
+  const int64_t n3 = (int64_t)(H + 1) * N3, n2 = (int64_t)(H + 1) * H, n1 = (int64_t)(dA + 1) * H;
+  int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n3 + n2 + n1) return;
+  float* gW1 = grad;
+  float* gb1 = gW1 + (int64_t)dA * H;
+  float* gW2 = gb1 + H;
+  float* gb2 = gW2 + (int64_t)H * H;
+  float* gW3 = gb2 + H;
+  const float* p = part + i;
+  const float* q = nullptr;
+  float* dst;
+  if (i < n3) {
+    const int m = (int)(i / N3), j = (int)(i % N3), c = j / NOG, r = j % NOG;
+    if (r >= NO) return;
+    dst = gW3 + (int64_t)m * nO + c * NO + r;  // row H: the bias gradients follow the weights
+  } else if (i < n3 + n2) {
+    dst = gW2 + (i - n3);
+  } else {
+    // rows 0..dA-1 and KLO.. of the KA input rows, and the sums in row KA
+    i -= n3 + n2;
+    const int m = (int)(i / H), j = (int)(i % H);
+    p = part + n3 + n2 + (int64_t)(m < dA ? m : KA) * H + j;
+    q = m < dA ? p + (int64_t)KLO * H : nullptr;
+    dst = gW1 + i;
   }
   float s = 0.0f;
-  for (int z = 0; z < Z; ++z) {
-    s += part[z * zs + (int64_t)m * N + nn];
-    if (fold) s += part[z * zs + (int64_t)(m + fold) * N + nn];
+  if (q) {
+    for (int z = 0; z < Z; ++z) {
+      s += p[z * zs];
+      s += q[z * zs];
+    }
+  } else {
+#pragma unroll 8
+    for (int z = 0; z < Z; ++z) s += p[z * zs];
   }
-  out[(int64_t)m * ldo + col] = s;
-}
-
-// g[a_idx[i]][e] += gx[e][i] (gradient reaching the kept coordinates)
-__global__ void k_add_gx(LayerDev L, const float* __restrict__ gx, int64_t n, float* __restrict__ g) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= n * L.dA) return;
-  const int i = (int)(idx / n);
-  const int64_t e = idx % n;
-  g[(int64_t)L.a_idx[i] * n + e] += gx[e * KA + i];
+  *dst = s;
 }
 
 // sum of w over the batch (one block, fixed order) and the loss
@@ -1050,8 +1275,9 @@ struct SegLayer {
   bf16* W2p;
   bf16* W3p;
   bf16* W3L;
-  bf16* W2n;
-  bf16* W3n;
+  bf16* W2q;
+  bf16* W3q;
+  bf16* W1q;
 };
 struct SegTable {
   int nl;
@@ -1083,30 +1309,35 @@ __global__ void k_adam(float* __restrict__ p, const float* __restrict__ gr, floa
     const int a = (int)(r / H), j = (int)(r % H);
     s.W1t[j * KA + a] = (bf16)v;
     s.W1t[j * KA + KLO + a] = (bf16)v;
+    s.W1q[((j >> 5) * 64 + a + 16 * ((j >> 3) & 3)) * 8 + (j & 7)] = (bf16)v;
     return;
   }
   r -= nW1 + H;  // b1 is used in FP32 from the master array
   if (r < 0) return;
   if (r < nW2) {
     const int a = (int)(r / H), j = (int)(r % H);
-    s.W2n[r] = (bf16)v;
     // wave j >> 6, fragment (j >> 4) & 3, row j & 15
     s.W2p[(((int64_t)(j >> 6) * 8 + (a >> 5)) * 4 + ((j >> 4) & 3)) * 512 + ((j & 15) + 16 * ((a >> 3) & 3)) * 8 +
           (a & 7)] = (bf16)v;
+    s.W2q[(((int64_t)(a >> 6) * 8 + (j >> 5)) * 4 + ((a >> 4) & 3)) * 512 + ((a & 15) + 16 * ((j >> 3) & 3)) * 8 +
+          (j & 7)] = (bf16)v;
     return;
   }
   r -= nW2 + H;
   if (r < 0) return;
   if (r < H * nO) {
     const int a = (int)(r / nO), o = (int)(r % nO);
-    s.W3n[(int64_t)a * s.dB * NOP + (o / NO) * NOP + o % NO] = (bf16)v;
     const int c = o / NO, col = o % NO;
     // coordinate c, wave col >> 4, row col & 15; the 65th logit in row c of W3L
-    if (col < 64)
+    const int kq = c * NOP + col;
+    s.W3q[(((int64_t)(kq >> 5) * 4 + (a >> 6)) * 4 + ((a >> 4) & 3)) * 512 + ((a & 15) + 16 * ((kq >> 3) & 3)) * 8 +
+          (kq & 7)] = (bf16)v;
+    if (col < 64) {
       s.W3p[(((int64_t)c * 4 + (col >> 4)) * 8 + (a >> 5)) * 512 + ((col & 15) + 16 * ((a >> 3) & 3)) * 8 + (a & 7)] =
           (bf16)v;
-    else if (col == 2 * KB)
+    } else {
       s.W3L[((a >> 5) * 64 + c + 16 * ((a >> 3) & 3)) * 8 + (a & 7)] = (bf16)v;
+    }
     return;
   }
   r -= H * nO;
@@ -1156,40 +1387,39 @@ struct mf_flow {
   bf16* d_w16 = nullptr;  // BF16 weight copies of every layer
   float* d_b3p = nullptr;
   int64_t step = 0;
-  // training caches and work buffers (max_batch events)
+  // training work buffers (max_batch events)
   int64_t cap = 0;
-  LayerCache cache[MAXL];
-  void* d_cachemem = nullptr;
+  float* d_lin = nullptr;   // [nl][d][cap] layer inputs
   float* d_y = nullptr;     // [d][cap]
   float* d_gy = nullptr;    // [d][cap]
   float* d_lq = nullptr;    // [cap]
   float* d_weff = nullptr;  // [cap] per-point loss weights of the variance loss
-  bf16* d_go = nullptr;     // [cap][dBmax*NOP]
-  bf16* d_ga2 = nullptr;    // [cap][H]
-  bf16* d_ga1 = nullptr;    // [cap][H]
-  bf16* d_goT = nullptr;    // [dBmax*NOP][capp]  event-contiguous copies
-  bf16* d_ga2T = nullptr;   // [H][capp]
-  bf16* d_ga1T = nullptr;   // [H][capp]
-  float* d_gx = nullptr;    // [cap][KA]
-  float* d_part = nullptr;  // split-K partials
-  size_t part_cap = 0;
+  // operands of the weight gradients, two sets: one layer's are read on the
+  // side stream while the next layer's are written
+  Operands op[2];
+  bf16* d_op = nullptr;
+  float* d_part = nullptr;  // partials of the weight gradients, split over events
+  size_t part_cap = 0;      // floats
   float* d_scal = nullptr;  // wsum, loss
   std::vector<float*> d_losses;
   // the backward pass runs the weight-gradient products on a second stream
   // (default priority) beside the activation-gradient chain; events order
   // the two
   hipStream_t side = nullptr;
-  hipEvent_t ev[6] = {};
+  hipEvent_t ev[4] = {};  // operands written and read, per set
 };
 
 namespace {
 
-constexpr int64_t SPLITK_BLOCKS = 512;
-constexpr int64_t SPLITK_MIN = 256;
-// at most this many chunks: the ordered reduction sums them sequentially per
-// output, which for the narrow first-layer gradient (four output tiles) would
-// otherwise take 128 partials
-constexpr int64_t SPLITK_MAX = 32;
+// Chunks of events of a layer's weight gradients: at most two workgroups per
+// compute unit over the tiles of the three products, so that all run at once
+// (43 chunks of 12 tiles, four workgroups more, took 69 us instead of 57),
+// whole slices per chunk, and at most WGRAD_MAX chunks, which the reduction
+// adds up in turn.
+constexpr int64_t WGRAD_BLOCKS = 512;
+constexpr int64_t WGRAD_MAX = 64;
+// floats of one chunk's partials: (inputs + 1) x outputs of the three layers
+int64_t wgrad_outputs(int dB) { return (int64_t)(H + 1) * dB * NOG + (int64_t)(H + 1) * H + (int64_t)(KA + 1) * H; }
 
 mf_status launch_err(const char* what) {
   hipError_t e = hipGetLastError();
@@ -1197,52 +1427,42 @@ mf_status launch_err(const char* what) {
   return MF_OK;
 }
 
-template <int A_KC, int B_NC, int EPI>
-void gemm(const GemmArgs& a, int Z, hipStream_t s) {
-  dim3 grid((a.N + 63) / 64, (a.M + 63) / 64, Z);
-  hipLaunchKernelGGL((k_gemm<A_KC, B_NC, EPI>), grid, dim3(256), 0, s, a);
+
+WgradArgs wgrad_args(const Operands& o, int dB, int64_t n) {
+  WgradArgs a{};
+  const bf16* X[3] = {o.h2, o.h1, o.xa};
+  const bf16* G[3] = {o.go, o.ga2, o.ga1};
+  const int M[3] = {H, H, KA}, N[3] = {dB * NOG, H, H};
+  for (int p = 0; p < 3; ++p) {
+    a.X[p] = X[p];
+    a.G[p] = G[p];
+    a.M[p] = M[p];
+    a.N[p] = N[p];
+    a.tiles_n[p] = (N[p] + WT - 1) / WT;
+    a.first[p] = a.tiles;
+    a.tiles += a.tiles_n[p] * ((M[p] + WT - 1) / WT);
+    a.off[p] = a.zs;
+    a.zs += (int64_t)(M[p] + 1) * N[p];
+  }
+  a.n = n;
+  int64_t z = WGRAD_BLOCKS / a.tiles;
+  z = z < WGRAD_MAX ? z : WGRAD_MAX;
+  a.chunk = ((n + z - 1) / z + WK - 1) / WK * WK;
+  return a;
 }
 
-// Number of event chunks of a weight-gradient product over n events with an
-// M x N output: enough workgroups to fill the chip (about SPLITK_BLOCKS),
-// chunks of at least SPLITK_MIN events, at most SPLITK_MAX chunks.
-// Non-decreasing in n.
-int64_t splitk(int64_t n, int M, int N) {
-  const int64_t tiles = (int64_t)((M + 63) / 64) * ((N + 63) / 64);
-  int64_t z = (SPLITK_BLOCKS + tiles - 1) / tiles;
-  z = z < SPLITK_MAX ? z : SPLITK_MAX;
-  const int64_t zmax = (n + SPLITK_MIN - 1) / SPLITK_MIN;
-  z = z < zmax ? z : zmax;
-  return z < 1 ? 1 : z;
-}
-
-// Weight and bias gradients over the batch: dW[in][out] = X^T G and
-// db[out] = column sums of G, from the event-contiguous BF16 copies
-// XT [M][ldn] and GT [N][ldn], split over events.
-bool weight_grad(mf_flow* f, const bf16* XT, int64_t ldn, int M, int m_real, const bf16* GT, int N, int gpad,
-                 int greal, int64_t n, float* out, int ldo, float* bias, hipStream_t s, int fold = 0) {
-  const int64_t Z = splitk(n, M, N);
-  const int64_t chunk = ((n + Z - 1) / Z + 31) / 32 * 32;
-  const int Zl = (int)((n + chunk - 1) / chunk);
+// Weight and bias gradients of layer l over n events from the operands o.
+bool weight_grads(mf_flow* f, int l, const Operands& o, int64_t n, hipStream_t s) {
+  const LayerDev& L = f->L[l];
+  WgradArgs a = wgrad_args(o, L.dB, n);
+  const int64_t Z = (n + a.chunk - 1) / a.chunk;
   // the partials of all chunks must fit the buffer sized at creation
-  if ((size_t)Zl * (size_t)(M + 1) * (size_t)N > f->part_cap) return false;
-  GemmArgs a{};
-  a.A = XT;  // A(m, k) = XT[m ldn + k]
-  a.lda = ldn;
-  a.B = GT;  // B(k, n) = GT[n ldn + k]
-  a.ldb = ldn;
-  a.M = M;
-  a.N = N;
-  a.K = n;
-  a.kchunk = chunk;
-  a.Cf = f->d_part;
-  a.zs = (int64_t)(M + 1) * N;
-  a.ldc = N;
-  a.colsum = 1;
-  gemm<1, 0, 0>(a, Zl, s);
-  const int64_t tot = (int64_t)(m_real + 1) * N;
-  hipLaunchKernelGGL(k_reduce_grad, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, f->d_part, Zl, M, N, m_real,
-                     gpad, greal, out, ldo, fold, bias);
+  if ((size_t)(Z * a.zs) > f->part_cap) return false;
+  a.part = f->d_part;
+  hipLaunchKernelGGL(k_wgrad, dim3((unsigned)(a.tiles * Z)), dim3(256), 0, s, a);
+  const int64_t tot = a.off[2] + (int64_t)(L.dA + 1) * H;
+  hipLaunchKernelGGL(k_reduce_layer, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, f->d_part, (int)Z, a.zs,
+                     L.dA, L.dB, f->d_g + f->loff[l]);
   return true;
 }
 
@@ -1250,16 +1470,16 @@ void run_layers(mf_flow* f, float* y, int64_t n, int64_t ld, float* logq, bool i
   const unsigned nblk = (unsigned)((n + T - 1) / T);
   for (int k = 0; k < f->nl; ++k) {
     const int l = inverse ? f->nl - 1 - k : k;
-    LayerCache C = cache ? f->cache[l] : LayerCache{};
+    float* lin = cache ? f->d_lin + (int64_t)l * f->d * f->cap : nullptr;
     if (inverse)
       hipLaunchKernelGGL((k_coupling<true, false>), dim3(nblk), dim3(256), 0, s, f->L[l], y, n, ld, logq,
-                         k == 0 ? 1 : 0, C, f->d);
+                         k == 0 ? 1 : 0, lin, f->d);
     else if (cache)
       hipLaunchKernelGGL((k_coupling<false, true>), dim3(nblk), dim3(256), 0, s, f->L[l], y, n, ld, logq,
-                         k == 0 ? 1 : 0, C, f->d);
+                         k == 0 ? 1 : 0, lin, f->d);
     else
       hipLaunchKernelGGL((k_coupling<false, false>), dim3(nblk), dim3(256), 0, s, f->L[l], y, n, ld, logq,
-                         k == 0 ? 1 : 0, C, f->d);
+                         k == 0 ? 1 : 0, lin, f->d);
   }
 }
 
@@ -1282,8 +1502,6 @@ mf_status loss_grad_impl(mf_flow* f, const float* y, int64_t ldy, const float* w
   hipError_t e = hipMemcpy2DAsync(f->d_y, sizeof(float) * n, y, sizeof(float) * ldy, sizeof(float) * n, d,
                                   hipMemcpyDeviceToDevice, s);
   if (e != hipSuccess) return set_error(MF_EDEVICE, "batch copy: %s", hipGetErrorString(e));
-  const int64_t ldn = (n + 7) / 8 * 8;
-  for (int l = 0; l < f->nl; ++l) f->cache[l].ldn = ldn;
   run_layers(f, f->d_y, n, n, f->d_lq, false, true, s);
   const float* w = w_in;
   if (kind == MF_FLOW_LOSS_VARIANCE) {
@@ -1295,98 +1513,31 @@ mf_status loss_grad_impl(mf_flow* f, const float* y, int64_t ldy, const float* w
   hipLaunchKernelGGL(k_wsum, dim3(1), dim3(RB), 0, s, w, n, f->d_scal);
   if (kind != MF_FLOW_LOSS_VARIANCE)
     hipLaunchKernelGGL(k_loss, dim3(1), dim3(RB), 0, s, w, f->d_lq, n, f->d_scal, loss_dev);
+
   e = hipMemsetAsync(f->d_gy, 0, sizeof(float) * d * n, s);
   if (e != hipSuccess) return set_error(MF_EDEVICE, "gradient clear: %s", hipGetErrorString(e));
-  // Per layer the activation-gradient chain (PQ backward, ga2, ga1, gx) runs
-  // on s and the three weight-gradient products on the side stream, each
-  // started once its input exists on s; before a layer's kernels overwrite
-  // go/goT, ga2/ga2T or ga1/ga1T, s waits until the previous layer's product
-  // that reads them has run.  All split-K partials are on the side stream.
+  // Per layer the backward kernel runs on s and the weight gradients on the
+  // side stream, started once their operands exist; before a set of operands
+  // is written again, s waits for the products that read it.  All partials are
+  // on the side stream.
   hipStream_t s2 = f->side;
-  enum { E_PQ, E_GA2, E_GA1, E_W3, E_W2, E_W1 };
   bool ok = true;
   auto rec = [&](int k, hipStream_t from) { ok = ok && hipEventRecord(f->ev[k], from) == hipSuccess; };
   auto wait = [&](int k, hipStream_t on) { ok = ok && hipStreamWaitEvent(on, f->ev[k], 0) == hipSuccess; };
   for (int l = f->nl - 1; l >= 0; --l) {
-    const LayerDev& L = f->L[l];
-    const LayerCache& C = f->cache[l];
-    const int NB = L.dB * NOP, nO = L.dB * NO;
-    const bool later = l < f->nl - 1;  // a previous layer's products exist
-    float* gW1 = f->d_g + f->loff[l];
-    float* gb1 = gW1 + (int64_t)L.dA * H;
-    float* gW2 = gb1 + H;
-    float* gb2 = gW2 + (int64_t)H * H;
-    float* gW3 = gb2 + H;
-    float* gb3 = gW3 + (int64_t)H * nO;
-    if (later) wait(E_W3, s);
-    hipLaunchKernelGGL(k_pq_backward, dim3((unsigned)((n + 255) / 256), L.dB), dim3(256), 0, s, L, C, n, f->d_gy, w,
-                       f->d_scal, f->d_go, f->d_goT);
-    rec(E_PQ, s);
-    wait(E_PQ, s2);
-    if (!weight_grad(f, C.h2, ldn, H, H, f->d_goT, NB, NOP, NO, n, gW3, nO, gb3, s2))
+    const int set = l & 1;
+    if (l + 2 <= f->nl - 1) wait(2 + set, s);
+    hipLaunchKernelGGL(k_layer_backward, dim3((unsigned)((n + T - 1) / T)), dim3(256), 0, s, f->L[l],
+                       f->d_lin + (int64_t)l * d * f->cap, n, f->d_gy, w, f->d_scal, f->op[set]);
+    rec(set, s);
+    wait(set, s2);
+    if (!weight_grads(f, l, f->op[set], n, s2))
       return set_error(MF_EINVAL, "weight-gradient partials exceed the flow's buffer");
-    rec(E_W3, s2);
-    // ga2 = (go W3^T) * leaky'(h2): A = go [n][NB], B(k=o, n=j) = W3n[j][o]
-    GemmArgs a{};
-    a.A = f->d_go;
-    a.lda = NB;
-    a.B = L.W3n;
-    a.ldb = NB;
-    a.M = (int)n;
-    a.N = H;
-    a.K = NB;
-    a.kchunk = NB;
-    a.Cb = f->d_ga2;
-    a.CbT = f->d_ga2T;
-    a.ldt = ldn;
-    a.ref = C.h2;
-    a.ref_rs = 1;
-    a.ref_cs = ldn;
-    a.ldc = H;
-    if (later) wait(E_W2, s);
-    gemm<1, 0, 1>(a, 1, s);
-    rec(E_GA2, s);
-    wait(E_GA2, s2);
-    if (!weight_grad(f, C.h1, ldn, H, H, f->d_ga2T, H, 0, 0, n, gW2, H, gb2, s2))
-      return set_error(MF_EINVAL, "weight-gradient partials exceed the flow's buffer");
-    rec(E_W2, s2);
-    // ga1 = (ga2 W2^T) * leaky'(h1): B(k=j2, n=j1) = W2[j1][j2] = W2n[j1][j2]
-    a.A = f->d_ga2;
-    a.lda = H;
-    a.B = L.W2n;
-    a.ldb = H;
-    a.K = H;
-    a.kchunk = H;
-    a.Cb = f->d_ga1;
-    a.CbT = f->d_ga1T;
-    a.ref = C.h1;
-    if (later) wait(E_W1, s);
-    gemm<1, 0, 1>(a, 1, s);
-    rec(E_GA1, s);
-    wait(E_GA1, s2);
-    if (!weight_grad(f, C.xa, ldn, KA, L.dA, f->d_ga1T, H, 0, 0, n, gW1, H, gb1, s2, KLO))
-      return set_error(MF_EINVAL, "weight-gradient partials exceed the flow's buffer");
-    rec(E_W1, s2);
-    // gx = ga1 W1^T: B(k=j, n=i) = W1[i][j] = W1t[j][i]
-    GemmArgs b{};
-    b.A = f->d_ga1;
-    b.lda = H;
-    b.B = L.W1t;
-    b.ldb = KA;
-    b.M = (int)n;
-    b.N = KA;
-    b.K = H;
-    b.kchunk = H;
-    b.Cf = f->d_gx;
-    b.zs = 0;
-    b.ldc = KA;
-    gemm<1, 1, 0>(b, 1, s);
-    const int64_t ta = n * L.dA;
-    if (ta > 0)
-      hipLaunchKernelGGL(k_add_gx, dim3((unsigned)((ta + 255) / 256)), dim3(256), 0, s, L, f->d_gx, n, f->d_gy);
+    rec(2 + set, s2);
   }
   // the gradient is complete on s once the side stream's last product is
-  wait(E_W1, s);
+  // (layer 0, set 0)
+  wait(2, s);
   if (!ok) return set_error(MF_EDEVICE, "backward stream ordering failed");
   return launch_err("flow backward");
 }
@@ -1448,7 +1599,7 @@ mf_status mf_flow_create(const mf_flow_config* cfg, mf_flow** out) {
     f->seg.l[l].dB = L.dB;
     off += (int64_t)L.dA * H + H + (int64_t)H * H + H + (int64_t)H * L.dB * NO + L.dB * NO;
     w16 += (int64_t)H * KA + (int64_t)H * H + (int64_t)L.dB * 64 * H + (int64_t)16 * H + (int64_t)H * H +
-           (int64_t)H * L.dB * NOP;
+           (int64_t)(L.dB * NOP + 31) / 32 * 32 * H + (int64_t)16 * H;
     b3 += (int64_t)L.dB * NOP;
     if (L.dB > dBmax) dBmax = L.dB;
   }
@@ -1462,30 +1613,26 @@ mf_status mf_flow_create(const mf_flow_config* cfg, mf_flow** out) {
   if (dBmax > TBMAX) return cleanup(set_error(MF_EINVAL, "a layer transforms more than %d coordinates", TBMAX));
   const int64_t cap = cfg->max_batch;
   f->cap = cap;
-  // caches: xa, h1, h2, o, lin per layer
-  const int64_t capp = (cap + 7) / 8 * 8;
-  size_t per_layer = sizeof(bf16) * (size_t)capp * (KA + 2 * H) + sizeof(float) * (size_t)cap * (dBmax * NOP + d);
-  per_layer = (per_layer + 255) / 256 * 256;  // every layer's caches start 256-byte aligned
-  // the chunk count depends on the output tiles, so a narrower output could
-  // need more partials than the widest one: the maximum over every width
-  int64_t pc = std::max(splitk(cap, H, H) * (H + 1) * H, splitk(cap, KA, H) * (KA + 1) * H);
-  for (int dB = 1; dB <= dBmax; ++dB) pc = std::max(pc, splitk(cap, H, dB * NOP) * (H + 1) * dB * NOP);
+
+  // operands of the weight gradients of one layer
+  const size_t per_set = ((size_t)cap * (4 * H + KA + dBmax * NOG) + 127) / 128 * 128;
+  // the chunks depend on the tiles and so on d_B: the maximum over every one
+  int64_t pc = 0;
+  for (int dB = 1; dB <= dBmax; ++dB) {
+    const WgradArgs a = wgrad_args(Operands{}, dB, cap);
+    const int64_t z = WGRAD_BLOCKS / a.tiles;
+    pc = std::max(pc, std::min(z, (cap + WK - 1) / WK) * a.zs);
+  }
   f->part_cap = (size_t)pc;
   if (hipMalloc(&f->d_p, sizeof(float) * off) != hipSuccess || hipMalloc(&f->d_g, sizeof(float) * off) != hipSuccess ||
       hipMalloc(&f->d_m1, sizeof(float) * off) != hipSuccess || hipMalloc(&f->d_m2, sizeof(float) * off) != hipSuccess ||
       hipMalloc(&f->d_w16, sizeof(bf16) * w16) != hipSuccess || hipMalloc(&f->d_b3p, sizeof(float) * b3) != hipSuccess ||
-      hipMalloc(&f->d_cachemem, per_layer * f->nl) != hipSuccess ||
+      hipMalloc(&f->d_lin, sizeof(float) * f->nl * d * cap) != hipSuccess ||
       hipMalloc(&f->d_y, sizeof(float) * d * cap) != hipSuccess ||
       hipMalloc(&f->d_gy, sizeof(float) * d * cap) != hipSuccess ||
       hipMalloc(&f->d_lq, sizeof(float) * cap) != hipSuccess ||
       hipMalloc(&f->d_weff, sizeof(float) * cap) != hipSuccess ||
-      hipMalloc(&f->d_go, sizeof(bf16) * cap * dBmax * NOP) != hipSuccess ||
-      hipMalloc(&f->d_ga2, sizeof(bf16) * cap * H) != hipSuccess ||
-      hipMalloc(&f->d_ga1, sizeof(bf16) * cap * H) != hipSuccess ||
-      hipMalloc(&f->d_goT, sizeof(bf16) * capp * dBmax * NOP) != hipSuccess ||
-      hipMalloc(&f->d_ga2T, sizeof(bf16) * capp * H) != hipSuccess ||
-      hipMalloc(&f->d_ga1T, sizeof(bf16) * capp * H) != hipSuccess ||
-      hipMalloc(&f->d_gx, sizeof(float) * cap * KA) != hipSuccess ||
+      hipMalloc(&f->d_op, sizeof(bf16) * 2 * per_set) != hipSuccess ||
       hipMalloc(&f->d_part, sizeof(float) * f->part_cap) != hipSuccess ||
       hipMalloc(&f->d_scal, sizeof(float) * 4) != hipSuccess) {
     hipGetLastError();
@@ -1510,7 +1657,16 @@ mf_status mf_flow_create(const mf_flow_config* cfg, mf_flow** out) {
     }
   bf16* wp = f->d_w16;
   float* bp = f->d_b3p;
-  char* cm = (char*)f->d_cachemem;
+  for (int k = 0; k < 2; ++k) {
+    bf16* q = f->d_op + k * per_set;
+    Operands& o = f->op[k];
+    o.h1 = q;
+    o.h2 = o.h1 + cap * H;
+    o.ga1 = o.h2 + cap * H;
+    o.ga2 = o.ga1 + cap * H;
+    o.xa = o.ga2 + cap * H;
+    o.go = o.xa + cap * KA;
+  }
   for (int l = 0; l < f->nl; ++l) {
     LayerDev& L = f->L[l];
     L.W1t = wp;
@@ -1525,29 +1681,20 @@ mf_status mf_flow_create(const mf_flow_config* cfg, mf_flow** out) {
     L.W3L = wp;
     f->seg.l[l].W3L = wp;
     wp += (int64_t)16 * H;
-    L.W2n = wp;
-    f->seg.l[l].W2n = wp;
+    L.W2q = wp;
+    f->seg.l[l].W2q = wp;
     wp += (int64_t)H * H;
-    L.W3n = wp;
-    f->seg.l[l].W3n = wp;
-    wp += (int64_t)H * L.dB * NOP;
+    L.W3q = wp;
+    f->seg.l[l].W3q = wp;
+    wp += (int64_t)(L.dB * NOP + 31) / 32 * 32 * H;
+    L.W1q = wp;
+    f->seg.l[l].W1q = wp;
+    wp += (int64_t)16 * H;
     L.b3p = bp;
     f->seg.l[l].b3p = bp;
     bp += (int64_t)L.dB * NOP;
     L.b1 = f->d_p + f->loff[l] + (int64_t)L.dA * H;
     L.b2 = L.b1 + H + (int64_t)H * H;
-    LayerCache& C = f->cache[l];
-    C.xa = (bf16*)cm;
-    cm += sizeof(bf16) * capp * KA;
-    C.h1 = (bf16*)cm;
-    cm += sizeof(bf16) * capp * H;
-    C.h2 = (bf16*)cm;
-    cm += sizeof(bf16) * capp * H;
-    C.ldn = capp;
-    C.o = (float*)cm;
-    cm += sizeof(float) * cap * dBmax * NOP;
-    C.lin = (float*)cm;
-    cm = (char*)f->d_cachemem + per_layer * (size_t)(l + 1);
   }
   hipLaunchKernelGGL(k_init_params, dim3((unsigned)((off + 255) / 256)), dim3(256), 0, 0, f->d_p, off, cfg->seed,
                      f->seg);
@@ -1565,18 +1712,12 @@ void mf_flow_destroy(mf_flow* f) {
   hipFree(f->d_m2);
   hipFree(f->d_w16);
   hipFree(f->d_b3p);
-  hipFree(f->d_cachemem);
+  hipFree(f->d_lin);
   hipFree(f->d_y);
   hipFree(f->d_gy);
   hipFree(f->d_lq);
   hipFree(f->d_weff);
-  hipFree(f->d_go);
-  hipFree(f->d_ga2);
-  hipFree(f->d_ga1);
-  hipFree(f->d_goT);
-  hipFree(f->d_ga2T);
-  hipFree(f->d_ga1T);
-  hipFree(f->d_gx);
+  hipFree(f->d_op);
   hipFree(f->d_part);
   hipFree(f->d_scal);
   for (float* p : f->d_losses) hipFree(p);

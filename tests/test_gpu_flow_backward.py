@@ -1,0 +1,71 @@
+"""Loss gradient of the flow at the edges of its kernels: tiles of 64 events,
+event chunks of the weight gradients, one to eight transformed coordinates."""
+import numpy as np
+import pytest
+
+import seeded_inputs as si
+from gpu_util import cosine_rel_l2
+from oracle import flow as oflow
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no HIP device", allow_module_level=True)
+
+import paper_2105_10529_amd as mf  # noqa: E402
+
+K = 32
+
+
+def _dev32(x):
+    return torch.from_numpy(np.ascontiguousarray(np.asarray(x, dtype=np.float32).T)).to("cuda")
+
+
+@pytest.mark.parametrize("d,n", [(2, 1), (3, 63), (4, 64), (7, 65), (10, 129), (13, 1500), (16, 4000)])
+def test_gradient_is_the_mean_of_single_event_gradients(d, n):
+    """With weights 1 for a power of two of the events and 0 for the rest, an
+    event's weight relative to the sum is a power of two: every rounding of its
+    gradient, also to BF16, is that of the event alone, and zero weights add
+    exact zeros.  What is left are the FP32 sums over events, at most k + 2
+    additions in a row, a product's high and low parts, and the same for the
+    single events: below 4 (k + 2) 2^-24 times the sum of the magnitudes."""
+    f = mf.Flow(d, max_batch=4096)
+    rng = np.random.default_rng(40 + d)
+    shapes = [(int((~m).sum()), 256, int(m.sum()) * (2 * K + 1)) for m in oflow.masks(d, 6)]
+    f.set_params(mf.Flow.flatten(si.flow_params(shapes, seed=40 + d, scale_out=0.1)))
+    y = _dev32(si.unit_points(n, d, seed=41))
+    k = min(32, 1 << (n.bit_length() - 1))
+    at = np.r_[n - 1, rng.permutation(n - 1)[: k - 1]]
+    w = np.zeros(n, np.float32)
+    w[at] = 1.0
+    _, g = f.loss_grad(y, torch.from_numpy(w).cuda())
+    one = torch.ones(1, dtype=torch.float32, device="cuda")
+    s, a = np.zeros(g.numel()), np.zeros(g.numel())
+    for e in at:
+        v = f.loss_grad(y[:, e:e + 1].contiguous(), one)[1].cpu().numpy().astype(np.float64) / k
+        s += v
+        a += np.abs(v)
+    assert np.any(s != 0.0)
+    assert np.all(np.abs(g.cpu().numpy() - s) <= 4.0 * (k + 2) * 2.0 ** -24 * a)
+
+
+@pytest.mark.parametrize("d,n", [(3, 65), (13, 200), (16, 64)])
+def test_gradient_of_odd_and_full_coordinate_counts_matches_oracle(d, n):
+    """One, six and eight transformed coordinates with BF16-exact forward
+    arithmetic; the backward pass rounds activations and gradients to BF16
+    (2^-9 relative, independent signs), as for the sizes tested elsewhere."""
+    f = mf.Flow(d, n_layers=1, max_batch=256)
+    mk = oflow.masks(d, 1)
+    shapes = [(int((~m).sum()), 256, int(m.sum()) * (2 * K + 1)) for m in mk]
+    params = si.flow_params_dyadic(shapes, seed=80 + d)
+    f.set_params(mf.Flow.flatten(params))
+    y = si.grid_points(n, d, seed=81)
+    w = np.random.default_rng(82).exponential(size=n)
+    _, _, caches = oflow.forward(params, mk, y, K)
+    g_ref = oflow.backward(params, mk, caches, w, K)
+    _, g = f.loss_grad(_dev32(y), torch.from_numpy(w.astype(np.float32)).cuda())
+    g = f.unflatten(g.cpu().numpy())
+    for name in ("W1", "b1", "W2", "b2", "W3", "b3"):
+        cos, rl2 = cosine_rel_l2(g[0][name], g_ref[0][name])
+        assert cos >= 0.9999 and rl2 <= 5e-3, (name, cos, rl2)
