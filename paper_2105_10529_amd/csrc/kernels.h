@@ -177,9 +177,10 @@ __global__ void __launch_bounds__(BLOCK) k_integrand(DevCfg c, const double* __r
 // Derivatives of the event weight: m_t by a dual number through phase space
 // and amplitudes, plus the scale derivative of the PDFs when mu = m_t; PDF
 // parameters through the collapsed derivative tables.
-template <int NG, int CH, class RA>
+// KEPT: the point is known to pass the cuts.
+template <int NG, int CH, class RA, bool KEPT>
 __device__ __forceinline__ void grad_event(const DevCfg& c, const double* x, double& w, double* dw) {
-  EventOut<Dual<double>> r = event_weight<NG, CH, RA, Dual<double>>(c, x, Dual<double>(c.mt, 1.0), c.pdfc);
+  EventOut<Dual<double>> r = event_weight<NG, CH, RA, Dual<double>, 1, KEPT>(c, x, Dual<double>(c.mt, 1.0), c.pdfc);
   w = r.w.v;
   for (int k = 0; k < 9; ++k) dw[k] = 0.0;
   dw[0] = r.w.d;  // r1, r2 and w are zero for an event that fails, so every term below is 0
@@ -233,25 +234,94 @@ __device__ __forceinline__ void grad_event(const DevCfg& c, const double* x, dou
   }
 }
 
+// One derivative event per lane; writes its weight and nine derivatives.
+template <int NG, int CH, class RA, bool KEPT>
+__device__ __forceinline__ void grad_point(const DevCfg& c, const double* __restrict__ u, int64_t n, int64_t e, bool live,
+                                           double* __restrict__ w, double* __restrict__ dw) {
+  double x[MAXD];
+#pragma unroll
+  for (int j = 0; j < MAXD; ++j)
+    if (j < c.ndim) x[j] = u[(int64_t)j * n + e];
+  double ww, d[9];
+  grad_event<NG, CH, RA, KEPT>(c, x, ww, d);
+  bool ok = isfinite(ww);
+  for (int k = 0; k < 9; ++k) ok = ok && isfinite(d[k]);
+  if (live) {
+    if (w) w[e] = ok ? ww : 0.0;
+    for (int k = 0; k < 9; ++k) dw[(int64_t)k * n + e] = ok ? d[k] : 0.0;
+  }
+}
+
+// Derivatives at given points.  The dual numbers fill the register file (one
+// wave per SIMD) and an event costs the same whether it passes the cuts or
+// not, so with cuts each block compacts: it tests its share of the points
+// (kinematics only), writes zeros for those that fail and queues the others in
+// LDS, and evaluates them a full block at a time.  The queue is the block's
+// own: the call needs no memory and shares none with others.  GRAD_BLOCKS
+// blocks, one per compute unit, with equal contiguous shares: 1e5 points of
+// g g -> t t~ g (54 % pass) are one pass of 211 events per block, 366 us
+// against 710 us in two rounds of 391 blocks.  Shares have 64 points or more
+// and waves without events skip the evaluation: what spills goes through
+// memory, and 1000 points take 194 us on 16 waves, 354 us on 1024.  Without
+// final-state partons nearly every point passes and the points are taken as
+// they come.
+constexpr int GRAD_BLOCKS = 256;
 template <int NG, int CH, class RA>
 __global__ void __launch_bounds__(BLOCK) k_integrand_grad(DevCfg c, const double* __restrict__ u, int64_t n,
                                                           double* __restrict__ w, double* __restrict__ dw) {
-  const int64_t nchunk = chunks_of_block(n);
-  for (int64_t it = 0; it < nchunk; ++it) {
-    const int64_t e0 = chunk_base(it) + threadIdx.x;
-    const bool live = e0 < n;
-    const int64_t e = live ? e0 : n - 1;
-    double x[MAXD];
+  if constexpr (NG == 0) {
+    const int64_t nchunk = chunks_of_block(n);
+    for (int64_t it = 0; it < nchunk; ++it) {
+      const int64_t e0 = chunk_base(it) + threadIdx.x;
+      const bool live = e0 < n;
+      grad_point<NG, CH, RA, false>(c, u, n, live ? e0 : n - 1, live, w, dw);
+    }
+  } else {
+    __shared__ int queue[2 * BLOCK];  // points that passed, relative to the share
+    __shared__ int wcount[WAVES];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t b0 = n * blockIdx.x / gridDim.x, b1 = n * (blockIdx.x + 1) / gridDim.x;
+    int have = 0;
+    for (int64_t next = b0;;) {
+      for (; have < BLOCK && next < b1; next += BLOCK) {
+        const int64_t e0 = next + tid;
+        const bool live = e0 < b1;
+        const int64_t e = live ? e0 : b1 - 1;
+        double x[MAXD];
 #pragma unroll
-    for (int j = 0; j < MAXD; ++j)
-      if (j < c.ndim) x[j] = u[(int64_t)j * n + e];
-    double ww, d[9];
-    grad_event<NG, CH, RA>(c, x, ww, d);
-    bool ok = isfinite(ww);
-    for (int k = 0; k < 9; ++k) ok = ok && isfinite(d[k]);
-    if (live) {
-      if (w) w[e] = ok ? ww : 0.0;
-      for (int k = 0; k < 9; ++k) dw[(int64_t)k * n + e] = ok ? d[k] : 0.0;
+        for (int j = 0; j < MAXD; ++j)
+          if (j < c.ndim) x[j] = u[(int64_t)j * n + e];
+        const bool pass = event_passes<NG>(c, x) && live;
+        if (live && !pass) {
+          if (w) w[e] = 0.0;
+          for (int k = 0; k < 9; ++k) dw[(int64_t)k * n + e] = 0.0;
+        }
+        const unsigned long long ball = __ballot(pass);
+        if (lane == 0) wcount[wave] = __popcll(ball);
+        __syncthreads();
+        int off = have, total = 0;
+#pragma unroll
+        for (int v = 0; v < WAVES; ++v) {
+          const int cv = wcount[v];
+          off += v < wave ? cv : 0;
+          total += cv;
+        }
+        if (pass) queue[off + __popcll(ball & ((1ull << lane) - 1ull))] = (int)(e0 - b0);
+        __syncthreads();
+        have = __builtin_amdgcn_readfirstlane(have + total);
+      }
+      if (have == 0) break;
+      if (64 * wave < have) {
+        const bool live = tid < have;
+        grad_point<NG, CH, RA, true>(c, u, n, b0 + queue[live ? tid : 0], live, w, dw);
+      }
+      // the events of the next pass move to the front
+      const int rest = have > BLOCK ? have - BLOCK : 0;
+      const int v = queue[BLOCK + (tid < rest ? tid : 0)];
+      __syncthreads();
+      if (tid < rest) queue[tid] = v;
+      __syncthreads();
+      have = rest;
     }
   }
 }
@@ -563,7 +633,7 @@ __global__ void __launch_bounds__(BLOCK) k_grad_vegas(DevCfg c, const double* __
     for (int j = 0; j < MAXD; ++j)
       if (j < d) x[j] = vegas_map_dim(edges + j * (nb + 1), nb, y[j], bins[j], jac);
     double v[GV];
-    grad_event<NG, CH, RA>(c, x, v[0], v + 1);
+    grad_event<NG, CH, RA, false>(c, x, v[0], v + 1);
     bool ok = live;
     for (int k = 0; k < GV; ++k) ok = ok && isfinite(v[k]);
     for (int k = 0; k < GV; ++k) {
@@ -641,7 +711,8 @@ Launchers make_launchers() {
   if constexpr (GRAD != 0) {
     L.integrand_grad = [](const DevCfg& c, const double* u, int64_t n, double* w, double* dw, int nblk,
                           hipStream_t s) {
-      hipLaunchKernelGGL((k_integrand_grad<NG, CH, RD>), dim3(nblk), dim3(BLOCK), 0, s, c, u, n, w, dw);
+      const unsigned grid = NG == 0 ? (unsigned)nblk : (unsigned)((n + 63) / 64 < GRAD_BLOCKS ? (n + 63) / 64 : GRAD_BLOCKS);
+      hipLaunchKernelGGL((k_integrand_grad<NG, CH, RD>), dim3(grid), dim3(BLOCK), 0, s, c, u, n, w, dw);
     };
     L.grad_vegas = [](const DevCfg& c, const double* edges, uint64_t iter, int64_t N, uint64_t seed, double* part,
                       int nblk, size_t lds, int* list, int* cnt, int64_t cap, hipStream_t s) {
