@@ -27,6 +27,9 @@ template <class T> __device__ __forceinline__ Dual<T> operator-(Dual<T> a) { ret
 template <class T> __device__ __forceinline__ Dual<T> operator*(Dual<T> a, Dual<T> b) {
   return Dual<T>(a.v * b.v, fma(a.d, b.v, a.v * b.d));
 }
+// with a constant
+template <class T> __device__ __forceinline__ Dual<T> operator+(Dual<T> a, T b) { return Dual<T>(a.v + b, a.d); }
+template <class T> __device__ __forceinline__ Dual<T> operator*(T a, Dual<T> b) { return Dual<T>(a * b.v, a * b.d); }
 template <class T> __device__ __forceinline__ Dual<T> operator/(Dual<T> a, Dual<T> b) {
   T iv = T(1) / b.v;
   T q = a.v * iv;
@@ -81,6 +84,13 @@ template <class R> __device__ __forceinline__ R mdot(const V4<R>& a, const V4<R>
   return a.t * b.t - a.x * b.x - a.y * b.y - a.z * b.z;
 }
 
+// with a constant vector
+template <class T> __device__ __forceinline__ V4<Dual<T>> operator+(const V4<Dual<T>>& a, const V4<T>& b) {
+  return V4<Dual<T>>{a.t + b.t, a.x + b.x, a.y + b.y, a.z + b.z};
+}
+template <class T> __device__ __forceinline__ Dual<T> mdot(const V4<Dual<T>>& a, const V4<T>& b) {
+  return b.t * a.t - b.x * a.x - b.y * a.y - b.z * a.z;
+}
 template <class R, class RK> __device__ __forceinline__ V4<R> cvt4(const V4<RK>& p) {
   return V4<R>{cvt<R>(p.t), cvt<R>(p.x), cvt<R>(p.y), cvt<R>(p.z)};
 }
@@ -176,11 +186,11 @@ template <class R> struct Sp {
 template <class R> __device__ __forceinline__ Sp<R> operator+(const Sp<R>& a, const Sp<R>& b) {
   return Sp<R>{a.s0 + b.s0, a.s1 + b.s1, a.s2 + b.s2, a.s3 + b.s3};
 }
-// slash(J) psi for a real four-vector J.
+// slash(J) psi for a real four-vector J (RJ: the type of J, R or its constants).
 //   out0 = (J0-J3) p2 - (J1 - i J2) p3     out2 = (J0+J3) p0 + (J1 - i J2) p1
 //   out1 = -(J1 + i J2) p2 + (J0+J3) p3    out3 = (J1 + i J2) p0 + (J0-J3) p1
-template <class R> __device__ __forceinline__ Sp<R> slash(const V4<R>& J, const Sp<R>& p) {
-  R a = J.t - J.z, b = J.t + J.z, c = J.x, d = J.y;
+template <class RJ, class R> __device__ __forceinline__ Sp<R> slash(const V4<RJ>& J, const Sp<R>& p) {
+  RJ a = J.t - J.z, b = J.t + J.z, c = J.x, d = J.y;
   Sp<R> o;
   // (c - i d)(x + i y) = (c x + d y) + i (c y - d x);  (c + i d)(x + i y) = (c x - d y) + i (c y + d x)
   o.s0 = C2<R>{a * p.s2.re - (c * p.s3.re + d * p.s3.im), a * p.s2.im - (c * p.s3.im - d * p.s3.re)};
@@ -190,8 +200,8 @@ template <class R> __device__ __forceinline__ Sp<R> slash(const V4<R>& J, const 
   return o;
 }
 // o + slash(J) psi, each component one chain of fused multiply-adds.
-template <class R> __device__ __forceinline__ Sp<R> slash_acc(const V4<R>& J, const Sp<R>& p, Sp<R> o) {
-  R a = J.t - J.z, b = J.t + J.z, c = J.x, d = J.y;
+template <class RJ, class R> __device__ __forceinline__ Sp<R> slash_acc(const V4<RJ>& J, const Sp<R>& p, Sp<R> o) {
+  RJ a = J.t - J.z, b = J.t + J.z, c = J.x, d = J.y;
   o.s0.re = ((o.s0.re + a * p.s2.re) - c * p.s3.re) - d * p.s3.im;
   o.s0.im = ((o.s0.im + a * p.s2.im) - c * p.s3.im) + d * p.s3.re;
   o.s1.re = ((o.s1.re + b * p.s3.re) - c * p.s2.re) + d * p.s2.im;

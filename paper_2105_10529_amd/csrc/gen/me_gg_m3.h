@@ -8,41 +8,41 @@ constexpr int ME_M3_NF = 6;
 constexpr double ME_M3_COLOUR_DEN = 9.0;
 // Colour- and polarisation-summed |M|^2 with g = 1 (argument meaning as in
 // the shared-current schedule).
-template <class R, class RK>
-__device__ __forceinline__ R me_gg_m3(const V4<RK>* K, const V4<R> (*E)[2], const Sp<R>* UB,
+template <class R, class RK, class RG, class KG>
+__device__ __forceinline__ R me_gg_m3(const V4<KG>* K, const V4<RG> (*E)[2], const Sp<R>* UB,
                                          const Sp<R>* VS, const V4<RK>& PTB, RK MTK) {
   const R MT = cvt<R>(MTK);
-  R G3;
-  { const V4<RK> P = K[0] + K[1]; G3 = cvt<R>(RK(-1.0) / mdot(P, P)); }
-  R G5;
-  { const V4<RK> P = K[0] + K[2]; G5 = cvt<R>(RK(-1.0) / mdot(P, P)); }
-  R G6;
-  { const V4<RK> P = K[1] + K[2]; G6 = cvt<R>(RK(-1.0) / mdot(P, P)); }
-  R G7;
-  { const V4<RK> P = K[0] + K[1] + K[2]; G7 = cvt<R>(RK(-1.0) / mdot(P, P)); }
+  RG G3;
+  { const V4<KG> P = K[0] + K[1]; G3 = cvt<RG>(KG(-1.0) / mdot(P, P)); }
+  RG G5;
+  { const V4<KG> P = K[0] + K[2]; G5 = cvt<RG>(KG(-1.0) / mdot(P, P)); }
+  RG G6;
+  { const V4<KG> P = K[1] + K[2]; G6 = cvt<RG>(KG(-1.0) / mdot(P, P)); }
+  RG G7;
+  { const V4<KG> P = K[0] + K[1] + K[2]; G7 = cvt<RG>(KG(-1.0) / mdot(P, P)); }
   R IQ1;
-  { const V4<RK> P = K[0]; IQ1 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
+  { const V4<KG> P = K[0]; IQ1 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
   R IQ2;
-  { const V4<RK> P = K[1]; IQ2 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
+  { const V4<KG> P = K[1]; IQ2 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
   R IQ3;
-  { const V4<RK> P = K[0] + K[1]; IQ3 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
+  { const V4<KG> P = K[0] + K[1]; IQ3 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
   R IQ4;
-  { const V4<RK> P = K[2]; IQ4 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
+  { const V4<KG> P = K[2]; IQ4 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
   R IQ5;
-  { const V4<RK> P = K[0] + K[2]; IQ5 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
+  { const V4<KG> P = K[0] + K[2]; IQ5 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
   R IQ6;
-  { const V4<RK> P = K[1] + K[2]; IQ6 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
-  const V4<R> K0 = cvt4<R>(K[0]);
-  const V4<R> K1 = cvt4<R>(K[1]);
-  const V4<R> K2 = cvt4<R>(K[2]);
+  { const V4<KG> P = K[1] + K[2]; IQ6 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
+  const V4<RG> K0 = cvt4<RG>(K[0]);
+  const V4<RG> K1 = cvt4<RG>(K[1]);
+  const V4<RG> K2 = cvt4<RG>(K[2]);
   const V4<R> PB = cvt4<R>(PTB);
   R total = R(0.0);
   {
 #pragma unroll 1
     for (int hg = 0; hg < 8; ++hg) {
-      const V4<R> E0 = ((hg >> 2) & 1) ? E[0][1] : E[0][0];
-      const V4<R> E1 = ((hg >> 1) & 1) ? E[1][1] : E[1][0];
-      const V4<R> E2 = ((hg >> 0) & 1) ? E[2][1] : E[2][0];
+      const V4<RG> E0 = ((hg >> 2) & 1) ? E[0][1] : E[0][0];
+      const V4<RG> E1 = ((hg >> 1) & 1) ? E[1][1] : E[1][0];
+      const V4<RG> E2 = ((hg >> 0) & 1) ? E[2][1] : E[2][0];
       C2<R> A0h0_0, A1h0_0;
       C2<R> A0h0_1, A1h0_1;
       C2<R> A0h0_2, A1h0_2;
@@ -50,25 +50,25 @@ __device__ __forceinline__ R me_gg_m3(const V4<RK>* K, const V4<R> (*E)[2], cons
       C2<R> A0h0_4, A1h0_4;
       C2<R> A0h0_5, A1h0_5;
       {  // orderings (0, 1, 2), (0, 2, 1), (1, 0, 2), (1, 2, 0), (2, 0, 1), (2, 1, 0)
-        V4<R> J0 = E0; opaque4(J0);
-        V4<R> k0 = K0; opaque4(k0);
-        V4<R> J1 = E1; opaque4(J1);
-        V4<R> k1 = K1; opaque4(k1);
-        V4<R> J2 = E2; opaque4(J2);
-        V4<R> k2 = K2; opaque4(k2);
+        V4<RG> J0 = E0; opaque4(J0);
+        V4<RG> k0 = K0; opaque4(k0);
+        V4<RG> J1 = E1; opaque4(J1);
+        V4<RG> k1 = K1; opaque4(k1);
+        V4<RG> J2 = E2; opaque4(J2);
+        V4<RG> k2 = K2; opaque4(k2);
         V4<R> pb = PB; opaque4(pb);
-        const V4<R> J01 = G3 * (v3(J0, J1, k0, k1));
-        const V4<R> J12 = G6 * (v3(J1, J2, k1, k2));
-        const V4<R> p6 = k1 + k2;
-        const V4<R> p3 = k0 + k1;
-        const V4<R> J012 = G7 * (w4_sub(J0, J1, J2, v3_acc(J01, J2, p3, k2, v3(J0, J12, k0, p6))));
-        const V4<R> J02 = G5 * (v3(J0, J2, k0, k2));
-        const V4<R> J21 = R(-1.0) * J12;
-        const V4<R> p5 = k0 + k2;
-        const V4<R> J021 = G7 * (w4_sub(J0, J2, J1, v3_acc(J02, J1, p5, k1, v3(J0, J21, k0, p6))));
-        const V4<R> J10 = R(-1.0) * J01;
-        const V4<R> J102 = G7 * (w4_sub(J1, J0, J2, v3_acc(J10, J2, p3, k2, v3(J1, J02, k1, p5))));
-        const V4<R> J20 = R(-1.0) * J02;
+        const V4<RG> J01 = G3 * (v3(J0, J1, k0, k1));
+        const V4<RG> J12 = G6 * (v3(J1, J2, k1, k2));
+        const V4<RG> p6 = k1 + k2;
+        const V4<RG> p3 = k0 + k1;
+        const V4<RG> J012 = G7 * (w4_sub(J0, J1, J2, v3_acc(J01, J2, p3, k2, v3(J0, J12, k0, p6))));
+        const V4<RG> J02 = G5 * (v3(J0, J2, k0, k2));
+        const V4<RG> J21 = RG(-1.0) * J12;
+        const V4<RG> p5 = k0 + k2;
+        const V4<RG> J021 = G7 * (w4_sub(J0, J2, J1, v3_acc(J02, J1, p5, k1, v3(J0, J21, k0, p6))));
+        const V4<RG> J10 = RG(-1.0) * J01;
+        const V4<RG> J102 = G7 * (w4_sub(J1, J0, J2, v3_acc(J10, J2, p3, k2, v3(J1, J02, k1, p5))));
+        const V4<RG> J20 = RG(-1.0) * J02;
         Sp<R> Sh0_ = VS[0]; opaque_sp(Sh0_);
         const Sp<R> Sh0_2 = prop_neg(pb + k2, MT, IQ4, slash(J2, Sh0_));
         const Sp<R> Sh0_12 = prop_neg(pb + p6, MT, IQ6, slash_acc(J12, Sh0_, slash(J1, Sh0_2)));

@@ -8,103 +8,103 @@ constexpr int ME_M4_NF = 24;
 constexpr double ME_M4_COLOUR_DEN = 54.0;
 // Colour- and polarisation-summed |M|^2 with g = 1 (argument meaning as in
 // the shared-current schedule).
-template <class R, class RK>
-__device__ __forceinline__ R me_gg_m4(const V4<RK>* K, const V4<R> (*E)[2], const Sp<R>* UB,
+template <class R, class RK, class RG, class KG>
+__device__ __forceinline__ R me_gg_m4(const V4<KG>* K, const V4<RG> (*E)[2], const Sp<R>* UB,
                                          const Sp<R>* VS, const V4<RK>& PTB, RK MTK) {
   const R MT = cvt<R>(MTK);
-  R G3;
-  { const V4<RK> P = K[0] + K[1]; G3 = cvt<R>(RK(-1.0) / mdot(P, P)); }
-  R G5;
-  { const V4<RK> P = K[0] + K[2]; G5 = cvt<R>(RK(-1.0) / mdot(P, P)); }
-  R G6;
-  { const V4<RK> P = K[1] + K[2]; G6 = cvt<R>(RK(-1.0) / mdot(P, P)); }
-  R G7;
-  { const V4<RK> P = K[0] + K[1] + K[2]; G7 = cvt<R>(RK(-1.0) / mdot(P, P)); }
-  R G9;
-  { const V4<RK> P = K[0] + K[3]; G9 = cvt<R>(RK(-1.0) / mdot(P, P)); }
-  R G10;
-  { const V4<RK> P = K[1] + K[3]; G10 = cvt<R>(RK(-1.0) / mdot(P, P)); }
-  R G11;
-  { const V4<RK> P = K[0] + K[1] + K[3]; G11 = cvt<R>(RK(-1.0) / mdot(P, P)); }
-  R G12;
-  { const V4<RK> P = K[2] + K[3]; G12 = cvt<R>(RK(-1.0) / mdot(P, P)); }
-  R G13;
-  { const V4<RK> P = K[0] + K[2] + K[3]; G13 = cvt<R>(RK(-1.0) / mdot(P, P)); }
-  R G14;
-  { const V4<RK> P = K[1] + K[2] + K[3]; G14 = cvt<R>(RK(-1.0) / mdot(P, P)); }
-  R G15;
-  { const V4<RK> P = K[0] + K[1] + K[2] + K[3]; G15 = cvt<R>(RK(-1.0) / mdot(P, P)); }
+  RG G3;
+  { const V4<KG> P = K[0] + K[1]; G3 = cvt<RG>(KG(-1.0) / mdot(P, P)); }
+  RG G5;
+  { const V4<KG> P = K[0] + K[2]; G5 = cvt<RG>(KG(-1.0) / mdot(P, P)); }
+  RG G6;
+  { const V4<KG> P = K[1] + K[2]; G6 = cvt<RG>(KG(-1.0) / mdot(P, P)); }
+  RG G7;
+  { const V4<KG> P = K[0] + K[1] + K[2]; G7 = cvt<RG>(KG(-1.0) / mdot(P, P)); }
+  RG G9;
+  { const V4<KG> P = K[0] + K[3]; G9 = cvt<RG>(KG(-1.0) / mdot(P, P)); }
+  RG G10;
+  { const V4<KG> P = K[1] + K[3]; G10 = cvt<RG>(KG(-1.0) / mdot(P, P)); }
+  RG G11;
+  { const V4<KG> P = K[0] + K[1] + K[3]; G11 = cvt<RG>(KG(-1.0) / mdot(P, P)); }
+  RG G12;
+  { const V4<KG> P = K[2] + K[3]; G12 = cvt<RG>(KG(-1.0) / mdot(P, P)); }
+  RG G13;
+  { const V4<KG> P = K[0] + K[2] + K[3]; G13 = cvt<RG>(KG(-1.0) / mdot(P, P)); }
+  RG G14;
+  { const V4<KG> P = K[1] + K[2] + K[3]; G14 = cvt<RG>(KG(-1.0) / mdot(P, P)); }
+  RG G15;
+  { const V4<KG> P = K[0] + K[1] + K[2] + K[3]; G15 = cvt<RG>(KG(-1.0) / mdot(P, P)); }
   R IQ1;
-  { const V4<RK> P = K[0]; IQ1 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
+  { const V4<KG> P = K[0]; IQ1 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
   R IQ2;
-  { const V4<RK> P = K[1]; IQ2 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
+  { const V4<KG> P = K[1]; IQ2 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
   R IQ3;
-  { const V4<RK> P = K[0] + K[1]; IQ3 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
+  { const V4<KG> P = K[0] + K[1]; IQ3 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
   R IQ4;
-  { const V4<RK> P = K[2]; IQ4 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
+  { const V4<KG> P = K[2]; IQ4 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
   R IQ5;
-  { const V4<RK> P = K[0] + K[2]; IQ5 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
+  { const V4<KG> P = K[0] + K[2]; IQ5 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
   R IQ6;
-  { const V4<RK> P = K[1] + K[2]; IQ6 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
+  { const V4<KG> P = K[1] + K[2]; IQ6 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
   R IQ7;
-  { const V4<RK> P = K[0] + K[1] + K[2]; IQ7 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
+  { const V4<KG> P = K[0] + K[1] + K[2]; IQ7 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
   R IQ8;
-  { const V4<RK> P = K[3]; IQ8 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
+  { const V4<KG> P = K[3]; IQ8 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
   R IQ9;
-  { const V4<RK> P = K[0] + K[3]; IQ9 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
+  { const V4<KG> P = K[0] + K[3]; IQ9 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
   R IQ10;
-  { const V4<RK> P = K[1] + K[3]; IQ10 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
+  { const V4<KG> P = K[1] + K[3]; IQ10 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
   R IQ11;
-  { const V4<RK> P = K[0] + K[1] + K[3]; IQ11 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
+  { const V4<KG> P = K[0] + K[1] + K[3]; IQ11 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
   R IQ12;
-  { const V4<RK> P = K[2] + K[3]; IQ12 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
+  { const V4<KG> P = K[2] + K[3]; IQ12 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
   R IQ13;
-  { const V4<RK> P = K[0] + K[2] + K[3]; IQ13 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
+  { const V4<KG> P = K[0] + K[2] + K[3]; IQ13 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
   R IQ14;
-  { const V4<RK> P = K[1] + K[2] + K[3]; IQ14 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
-  const V4<R> K0 = cvt4<R>(K[0]);
-  const V4<R> K1 = cvt4<R>(K[1]);
-  const V4<R> K2 = cvt4<R>(K[2]);
-  const V4<R> K3 = cvt4<R>(K[3]);
+  { const V4<KG> P = K[1] + K[2] + K[3]; IQ14 = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }
+  const V4<RG> K0 = cvt4<RG>(K[0]);
+  const V4<RG> K1 = cvt4<RG>(K[1]);
+  const V4<RG> K2 = cvt4<RG>(K[2]);
+  const V4<RG> K3 = cvt4<RG>(K[3]);
   const V4<R> PB = cvt4<R>(PTB);
   R total = R(0.0);
   {
 #pragma unroll 1
     for (int hg = 0; hg < 16; ++hg) {
-      const V4<R> E0 = ((hg >> 3) & 1) ? E[0][1] : E[0][0];
-      const V4<R> E1 = ((hg >> 2) & 1) ? E[1][1] : E[1][0];
-      const V4<R> E2 = ((hg >> 1) & 1) ? E[2][1] : E[2][0];
-      const V4<R> E3 = ((hg >> 0) & 1) ? E[3][1] : E[3][0];
+      const V4<RG> E0 = ((hg >> 3) & 1) ? E[0][1] : E[0][0];
+      const V4<RG> E1 = ((hg >> 2) & 1) ? E[1][1] : E[1][0];
+      const V4<RG> E2 = ((hg >> 1) & 1) ? E[2][1] : E[2][0];
+      const V4<RG> E3 = ((hg >> 0) & 1) ? E[3][1] : E[3][0];
       C2<R> A0h0_0, A1h0_0;
       C2<R> A0h0_6, A1h0_6;
       {  // orderings (0, 1, 2, 3), (1, 0, 2, 3)
-        V4<R> J0 = E0; opaque4(J0);
-        V4<R> k0 = K0; opaque4(k0);
-        V4<R> J1 = E1; opaque4(J1);
-        V4<R> k1 = K1; opaque4(k1);
-        V4<R> J2 = E2; opaque4(J2);
-        V4<R> k2 = K2; opaque4(k2);
-        V4<R> J3 = E3; opaque4(J3);
-        V4<R> k3 = K3; opaque4(k3);
+        V4<RG> J0 = E0; opaque4(J0);
+        V4<RG> k0 = K0; opaque4(k0);
+        V4<RG> J1 = E1; opaque4(J1);
+        V4<RG> k1 = K1; opaque4(k1);
+        V4<RG> J2 = E2; opaque4(J2);
+        V4<RG> k2 = K2; opaque4(k2);
+        V4<RG> J3 = E3; opaque4(J3);
+        V4<RG> k3 = K3; opaque4(k3);
         V4<R> pb = PB; opaque4(pb);
-        const V4<R> J01 = G3 * (v3(J0, J1, k0, k1));
-        const V4<R> J12 = G6 * (v3(J1, J2, k1, k2));
-        const V4<R> p6 = k1 + k2;
-        const V4<R> p3 = k0 + k1;
-        const V4<R> J012 = G7 * (w4_sub(J0, J1, J2, v3_acc(J01, J2, p3, k2, v3(J0, J12, k0, p6))));
-        const V4<R> J23 = G12 * (v3(J2, J3, k2, k3));
-        const V4<R> p12 = k2 + k3;
-        const V4<R> J123 = G14 * (w4_sub(J1, J2, J3, v3_acc(J12, J3, p6, k3, v3(J1, J23, k1, p12))));
-        const V4<R> p14 = k1 + k2 + k3;
-        const V4<R> p7 = k0 + k1 + k2;
-        const V4<R> J0123 = G15 * (w4_sub(J01, J2, J3, w4_sub(J0, J12, J3, w4_sub(J0, J1, J23, v3_acc(J012, J3, p7, k3, v3_acc(J01, J23, p3, p12, v3(J0, J123, k0, p14)))))));
-        const V4<R> J10 = R(-1.0) * J01;
-        const V4<R> J02 = G5 * (v3(J0, J2, k0, k2));
-        const V4<R> p5 = k0 + k2;
-        const V4<R> J102 = G7 * (w4_sub(J1, J0, J2, v3_acc(J10, J2, p3, k2, v3(J1, J02, k1, p5))));
-        const V4<R> J023 = G13 * (w4_sub(J0, J2, J3, v3_acc(J02, J3, p5, k3, v3(J0, J23, k0, p12))));
-        const V4<R> p13 = k0 + k2 + k3;
-        const V4<R> J1023 = G15 * (w4_sub(J10, J2, J3, w4_sub(J1, J02, J3, w4_sub(J1, J0, J23, v3_acc(J102, J3, p7, k3, v3_acc(J10, J23, p3, p12, v3(J1, J023, k1, p13)))))));
+        const V4<RG> J01 = G3 * (v3(J0, J1, k0, k1));
+        const V4<RG> J12 = G6 * (v3(J1, J2, k1, k2));
+        const V4<RG> p6 = k1 + k2;
+        const V4<RG> p3 = k0 + k1;
+        const V4<RG> J012 = G7 * (w4_sub(J0, J1, J2, v3_acc(J01, J2, p3, k2, v3(J0, J12, k0, p6))));
+        const V4<RG> J23 = G12 * (v3(J2, J3, k2, k3));
+        const V4<RG> p12 = k2 + k3;
+        const V4<RG> J123 = G14 * (w4_sub(J1, J2, J3, v3_acc(J12, J3, p6, k3, v3(J1, J23, k1, p12))));
+        const V4<RG> p14 = k1 + k2 + k3;
+        const V4<RG> p7 = k0 + k1 + k2;
+        const V4<RG> J0123 = G15 * (w4_sub(J01, J2, J3, w4_sub(J0, J12, J3, w4_sub(J0, J1, J23, v3_acc(J012, J3, p7, k3, v3_acc(J01, J23, p3, p12, v3(J0, J123, k0, p14)))))));
+        const V4<RG> J10 = RG(-1.0) * J01;
+        const V4<RG> J02 = G5 * (v3(J0, J2, k0, k2));
+        const V4<RG> p5 = k0 + k2;
+        const V4<RG> J102 = G7 * (w4_sub(J1, J0, J2, v3_acc(J10, J2, p3, k2, v3(J1, J02, k1, p5))));
+        const V4<RG> J023 = G13 * (w4_sub(J0, J2, J3, v3_acc(J02, J3, p5, k3, v3(J0, J23, k0, p12))));
+        const V4<RG> p13 = k0 + k2 + k3;
+        const V4<RG> J1023 = G15 * (w4_sub(J10, J2, J3, w4_sub(J1, J02, J3, w4_sub(J1, J0, J23, v3_acc(J102, J3, p7, k3, v3_acc(J10, J23, p3, p12, v3(J1, J023, k1, p13)))))));
         Sp<R> Sh0_ = VS[0]; opaque_sp(Sh0_);
         const Sp<R> Sh0_3 = prop_neg(pb + k3, MT, IQ8, slash(J3, Sh0_));
         const Sp<R> Sh0_23 = prop_neg(pb + p12, MT, IQ12, slash_acc(J23, Sh0_, slash(J2, Sh0_3)));
@@ -120,33 +120,33 @@ __device__ __forceinline__ R me_gg_m4(const V4<RK>* K, const V4<R> (*E)[2], cons
       C2<R> A0h0_1, A1h0_1;
       C2<R> A0h0_7, A1h0_7;
       {  // orderings (0, 1, 3, 2), (1, 0, 3, 2)
-        V4<R> J0 = E0; opaque4(J0);
-        V4<R> k0 = K0; opaque4(k0);
-        V4<R> J1 = E1; opaque4(J1);
-        V4<R> k1 = K1; opaque4(k1);
-        V4<R> J2 = E2; opaque4(J2);
-        V4<R> k2 = K2; opaque4(k2);
-        V4<R> J3 = E3; opaque4(J3);
-        V4<R> k3 = K3; opaque4(k3);
+        V4<RG> J0 = E0; opaque4(J0);
+        V4<RG> k0 = K0; opaque4(k0);
+        V4<RG> J1 = E1; opaque4(J1);
+        V4<RG> k1 = K1; opaque4(k1);
+        V4<RG> J2 = E2; opaque4(J2);
+        V4<RG> k2 = K2; opaque4(k2);
+        V4<RG> J3 = E3; opaque4(J3);
+        V4<RG> k3 = K3; opaque4(k3);
         V4<R> pb = PB; opaque4(pb);
-        const V4<R> J01 = G3 * (v3(J0, J1, k0, k1));
-        const V4<R> J13 = G10 * (v3(J1, J3, k1, k3));
-        const V4<R> p10 = k1 + k3;
-        const V4<R> p3 = k0 + k1;
-        const V4<R> J013 = G11 * (w4_sub(J0, J1, J3, v3_acc(J01, J3, p3, k3, v3(J0, J13, k0, p10))));
-        const V4<R> J32 = G12 * (v3(J3, J2, k3, k2));
-        const V4<R> p12 = k2 + k3;
-        const V4<R> J132 = G14 * (w4_sub(J1, J3, J2, v3_acc(J13, J2, p10, k2, v3(J1, J32, k1, p12))));
-        const V4<R> p14 = k1 + k2 + k3;
-        const V4<R> p11 = k0 + k1 + k3;
-        const V4<R> J0132 = G15 * (w4_sub(J01, J3, J2, w4_sub(J0, J13, J2, w4_sub(J0, J1, J32, v3_acc(J013, J2, p11, k2, v3_acc(J01, J32, p3, p12, v3(J0, J132, k0, p14)))))));
-        const V4<R> J10 = R(-1.0) * J01;
-        const V4<R> J03 = G9 * (v3(J0, J3, k0, k3));
-        const V4<R> p9 = k0 + k3;
-        const V4<R> J103 = G11 * (w4_sub(J1, J0, J3, v3_acc(J10, J3, p3, k3, v3(J1, J03, k1, p9))));
-        const V4<R> J032 = G13 * (w4_sub(J0, J3, J2, v3_acc(J03, J2, p9, k2, v3(J0, J32, k0, p12))));
-        const V4<R> p13 = k0 + k2 + k3;
-        const V4<R> J1032 = G15 * (w4_sub(J10, J3, J2, w4_sub(J1, J03, J2, w4_sub(J1, J0, J32, v3_acc(J103, J2, p11, k2, v3_acc(J10, J32, p3, p12, v3(J1, J032, k1, p13)))))));
+        const V4<RG> J01 = G3 * (v3(J0, J1, k0, k1));
+        const V4<RG> J13 = G10 * (v3(J1, J3, k1, k3));
+        const V4<RG> p10 = k1 + k3;
+        const V4<RG> p3 = k0 + k1;
+        const V4<RG> J013 = G11 * (w4_sub(J0, J1, J3, v3_acc(J01, J3, p3, k3, v3(J0, J13, k0, p10))));
+        const V4<RG> J32 = G12 * (v3(J3, J2, k3, k2));
+        const V4<RG> p12 = k2 + k3;
+        const V4<RG> J132 = G14 * (w4_sub(J1, J3, J2, v3_acc(J13, J2, p10, k2, v3(J1, J32, k1, p12))));
+        const V4<RG> p14 = k1 + k2 + k3;
+        const V4<RG> p11 = k0 + k1 + k3;
+        const V4<RG> J0132 = G15 * (w4_sub(J01, J3, J2, w4_sub(J0, J13, J2, w4_sub(J0, J1, J32, v3_acc(J013, J2, p11, k2, v3_acc(J01, J32, p3, p12, v3(J0, J132, k0, p14)))))));
+        const V4<RG> J10 = RG(-1.0) * J01;
+        const V4<RG> J03 = G9 * (v3(J0, J3, k0, k3));
+        const V4<RG> p9 = k0 + k3;
+        const V4<RG> J103 = G11 * (w4_sub(J1, J0, J3, v3_acc(J10, J3, p3, k3, v3(J1, J03, k1, p9))));
+        const V4<RG> J032 = G13 * (w4_sub(J0, J3, J2, v3_acc(J03, J2, p9, k2, v3(J0, J32, k0, p12))));
+        const V4<RG> p13 = k0 + k2 + k3;
+        const V4<RG> J1032 = G15 * (w4_sub(J10, J3, J2, w4_sub(J1, J03, J2, w4_sub(J1, J0, J32, v3_acc(J103, J2, p11, k2, v3_acc(J10, J32, p3, p12, v3(J1, J032, k1, p13)))))));
         Sp<R> Sh0_ = VS[0]; opaque_sp(Sh0_);
         const Sp<R> Sh0_2 = prop_neg(pb + k2, MT, IQ4, slash(J2, Sh0_));
         const Sp<R> Sh0_32 = prop_neg(pb + p12, MT, IQ12, slash_acc(J32, Sh0_, slash(J3, Sh0_2)));
@@ -162,33 +162,33 @@ __device__ __forceinline__ R me_gg_m4(const V4<RK>* K, const V4<R> (*E)[2], cons
       C2<R> A0h0_2, A1h0_2;
       C2<R> A0h0_12, A1h0_12;
       {  // orderings (0, 2, 1, 3), (2, 0, 1, 3)
-        V4<R> J0 = E0; opaque4(J0);
-        V4<R> k0 = K0; opaque4(k0);
-        V4<R> J1 = E1; opaque4(J1);
-        V4<R> k1 = K1; opaque4(k1);
-        V4<R> J2 = E2; opaque4(J2);
-        V4<R> k2 = K2; opaque4(k2);
-        V4<R> J3 = E3; opaque4(J3);
-        V4<R> k3 = K3; opaque4(k3);
+        V4<RG> J0 = E0; opaque4(J0);
+        V4<RG> k0 = K0; opaque4(k0);
+        V4<RG> J1 = E1; opaque4(J1);
+        V4<RG> k1 = K1; opaque4(k1);
+        V4<RG> J2 = E2; opaque4(J2);
+        V4<RG> k2 = K2; opaque4(k2);
+        V4<RG> J3 = E3; opaque4(J3);
+        V4<RG> k3 = K3; opaque4(k3);
         V4<R> pb = PB; opaque4(pb);
-        const V4<R> J02 = G5 * (v3(J0, J2, k0, k2));
-        const V4<R> J21 = G6 * (v3(J2, J1, k2, k1));
-        const V4<R> p6 = k1 + k2;
-        const V4<R> p5 = k0 + k2;
-        const V4<R> J021 = G7 * (w4_sub(J0, J2, J1, v3_acc(J02, J1, p5, k1, v3(J0, J21, k0, p6))));
-        const V4<R> J13 = G10 * (v3(J1, J3, k1, k3));
-        const V4<R> p10 = k1 + k3;
-        const V4<R> J213 = G14 * (w4_sub(J2, J1, J3, v3_acc(J21, J3, p6, k3, v3(J2, J13, k2, p10))));
-        const V4<R> p14 = k1 + k2 + k3;
-        const V4<R> p7 = k0 + k1 + k2;
-        const V4<R> J0213 = G15 * (w4_sub(J02, J1, J3, w4_sub(J0, J21, J3, w4_sub(J0, J2, J13, v3_acc(J021, J3, p7, k3, v3_acc(J02, J13, p5, p10, v3(J0, J213, k0, p14)))))));
-        const V4<R> J20 = R(-1.0) * J02;
-        const V4<R> J01 = G3 * (v3(J0, J1, k0, k1));
-        const V4<R> p3 = k0 + k1;
-        const V4<R> J201 = G7 * (w4_sub(J2, J0, J1, v3_acc(J20, J1, p5, k1, v3(J2, J01, k2, p3))));
-        const V4<R> J013 = G11 * (w4_sub(J0, J1, J3, v3_acc(J01, J3, p3, k3, v3(J0, J13, k0, p10))));
-        const V4<R> p11 = k0 + k1 + k3;
-        const V4<R> J2013 = G15 * (w4_sub(J20, J1, J3, w4_sub(J2, J01, J3, w4_sub(J2, J0, J13, v3_acc(J201, J3, p7, k3, v3_acc(J20, J13, p5, p10, v3(J2, J013, k2, p11)))))));
+        const V4<RG> J02 = G5 * (v3(J0, J2, k0, k2));
+        const V4<RG> J21 = G6 * (v3(J2, J1, k2, k1));
+        const V4<RG> p6 = k1 + k2;
+        const V4<RG> p5 = k0 + k2;
+        const V4<RG> J021 = G7 * (w4_sub(J0, J2, J1, v3_acc(J02, J1, p5, k1, v3(J0, J21, k0, p6))));
+        const V4<RG> J13 = G10 * (v3(J1, J3, k1, k3));
+        const V4<RG> p10 = k1 + k3;
+        const V4<RG> J213 = G14 * (w4_sub(J2, J1, J3, v3_acc(J21, J3, p6, k3, v3(J2, J13, k2, p10))));
+        const V4<RG> p14 = k1 + k2 + k3;
+        const V4<RG> p7 = k0 + k1 + k2;
+        const V4<RG> J0213 = G15 * (w4_sub(J02, J1, J3, w4_sub(J0, J21, J3, w4_sub(J0, J2, J13, v3_acc(J021, J3, p7, k3, v3_acc(J02, J13, p5, p10, v3(J0, J213, k0, p14)))))));
+        const V4<RG> J20 = RG(-1.0) * J02;
+        const V4<RG> J01 = G3 * (v3(J0, J1, k0, k1));
+        const V4<RG> p3 = k0 + k1;
+        const V4<RG> J201 = G7 * (w4_sub(J2, J0, J1, v3_acc(J20, J1, p5, k1, v3(J2, J01, k2, p3))));
+        const V4<RG> J013 = G11 * (w4_sub(J0, J1, J3, v3_acc(J01, J3, p3, k3, v3(J0, J13, k0, p10))));
+        const V4<RG> p11 = k0 + k1 + k3;
+        const V4<RG> J2013 = G15 * (w4_sub(J20, J1, J3, w4_sub(J2, J01, J3, w4_sub(J2, J0, J13, v3_acc(J201, J3, p7, k3, v3_acc(J20, J13, p5, p10, v3(J2, J013, k2, p11)))))));
         Sp<R> Sh0_ = VS[0]; opaque_sp(Sh0_);
         const Sp<R> Sh0_3 = prop_neg(pb + k3, MT, IQ8, slash(J3, Sh0_));
         const Sp<R> Sh0_13 = prop_neg(pb + p10, MT, IQ10, slash_acc(J13, Sh0_, slash(J1, Sh0_3)));
@@ -204,33 +204,33 @@ __device__ __forceinline__ R me_gg_m4(const V4<RK>* K, const V4<R> (*E)[2], cons
       C2<R> A0h0_3, A1h0_3;
       C2<R> A0h0_13, A1h0_13;
       {  // orderings (0, 2, 3, 1), (2, 0, 3, 1)
-        V4<R> J0 = E0; opaque4(J0);
-        V4<R> k0 = K0; opaque4(k0);
-        V4<R> J1 = E1; opaque4(J1);
-        V4<R> k1 = K1; opaque4(k1);
-        V4<R> J2 = E2; opaque4(J2);
-        V4<R> k2 = K2; opaque4(k2);
-        V4<R> J3 = E3; opaque4(J3);
-        V4<R> k3 = K3; opaque4(k3);
+        V4<RG> J0 = E0; opaque4(J0);
+        V4<RG> k0 = K0; opaque4(k0);
+        V4<RG> J1 = E1; opaque4(J1);
+        V4<RG> k1 = K1; opaque4(k1);
+        V4<RG> J2 = E2; opaque4(J2);
+        V4<RG> k2 = K2; opaque4(k2);
+        V4<RG> J3 = E3; opaque4(J3);
+        V4<RG> k3 = K3; opaque4(k3);
         V4<R> pb = PB; opaque4(pb);
-        const V4<R> J02 = G5 * (v3(J0, J2, k0, k2));
-        const V4<R> J23 = G12 * (v3(J2, J3, k2, k3));
-        const V4<R> p12 = k2 + k3;
-        const V4<R> p5 = k0 + k2;
-        const V4<R> J023 = G13 * (w4_sub(J0, J2, J3, v3_acc(J02, J3, p5, k3, v3(J0, J23, k0, p12))));
-        const V4<R> J31 = G10 * (v3(J3, J1, k3, k1));
-        const V4<R> p10 = k1 + k3;
-        const V4<R> J231 = G14 * (w4_sub(J2, J3, J1, v3_acc(J23, J1, p12, k1, v3(J2, J31, k2, p10))));
-        const V4<R> p14 = k1 + k2 + k3;
-        const V4<R> p13 = k0 + k2 + k3;
-        const V4<R> J0231 = G15 * (w4_sub(J02, J3, J1, w4_sub(J0, J23, J1, w4_sub(J0, J2, J31, v3_acc(J023, J1, p13, k1, v3_acc(J02, J31, p5, p10, v3(J0, J231, k0, p14)))))));
-        const V4<R> J20 = R(-1.0) * J02;
-        const V4<R> J03 = G9 * (v3(J0, J3, k0, k3));
-        const V4<R> p9 = k0 + k3;
-        const V4<R> J203 = G13 * (w4_sub(J2, J0, J3, v3_acc(J20, J3, p5, k3, v3(J2, J03, k2, p9))));
-        const V4<R> J031 = G11 * (w4_sub(J0, J3, J1, v3_acc(J03, J1, p9, k1, v3(J0, J31, k0, p10))));
-        const V4<R> p11 = k0 + k1 + k3;
-        const V4<R> J2031 = G15 * (w4_sub(J20, J3, J1, w4_sub(J2, J03, J1, w4_sub(J2, J0, J31, v3_acc(J203, J1, p13, k1, v3_acc(J20, J31, p5, p10, v3(J2, J031, k2, p11)))))));
+        const V4<RG> J02 = G5 * (v3(J0, J2, k0, k2));
+        const V4<RG> J23 = G12 * (v3(J2, J3, k2, k3));
+        const V4<RG> p12 = k2 + k3;
+        const V4<RG> p5 = k0 + k2;
+        const V4<RG> J023 = G13 * (w4_sub(J0, J2, J3, v3_acc(J02, J3, p5, k3, v3(J0, J23, k0, p12))));
+        const V4<RG> J31 = G10 * (v3(J3, J1, k3, k1));
+        const V4<RG> p10 = k1 + k3;
+        const V4<RG> J231 = G14 * (w4_sub(J2, J3, J1, v3_acc(J23, J1, p12, k1, v3(J2, J31, k2, p10))));
+        const V4<RG> p14 = k1 + k2 + k3;
+        const V4<RG> p13 = k0 + k2 + k3;
+        const V4<RG> J0231 = G15 * (w4_sub(J02, J3, J1, w4_sub(J0, J23, J1, w4_sub(J0, J2, J31, v3_acc(J023, J1, p13, k1, v3_acc(J02, J31, p5, p10, v3(J0, J231, k0, p14)))))));
+        const V4<RG> J20 = RG(-1.0) * J02;
+        const V4<RG> J03 = G9 * (v3(J0, J3, k0, k3));
+        const V4<RG> p9 = k0 + k3;
+        const V4<RG> J203 = G13 * (w4_sub(J2, J0, J3, v3_acc(J20, J3, p5, k3, v3(J2, J03, k2, p9))));
+        const V4<RG> J031 = G11 * (w4_sub(J0, J3, J1, v3_acc(J03, J1, p9, k1, v3(J0, J31, k0, p10))));
+        const V4<RG> p11 = k0 + k1 + k3;
+        const V4<RG> J2031 = G15 * (w4_sub(J20, J3, J1, w4_sub(J2, J03, J1, w4_sub(J2, J0, J31, v3_acc(J203, J1, p13, k1, v3_acc(J20, J31, p5, p10, v3(J2, J031, k2, p11)))))));
         Sp<R> Sh0_ = VS[0]; opaque_sp(Sh0_);
         const Sp<R> Sh0_1 = prop_neg(pb + k1, MT, IQ2, slash(J1, Sh0_));
         const Sp<R> Sh0_31 = prop_neg(pb + p10, MT, IQ10, slash_acc(J31, Sh0_, slash(J3, Sh0_1)));
@@ -246,33 +246,33 @@ __device__ __forceinline__ R me_gg_m4(const V4<RK>* K, const V4<R> (*E)[2], cons
       C2<R> A0h0_4, A1h0_4;
       C2<R> A0h0_18, A1h0_18;
       {  // orderings (0, 3, 1, 2), (3, 0, 1, 2)
-        V4<R> J0 = E0; opaque4(J0);
-        V4<R> k0 = K0; opaque4(k0);
-        V4<R> J1 = E1; opaque4(J1);
-        V4<R> k1 = K1; opaque4(k1);
-        V4<R> J2 = E2; opaque4(J2);
-        V4<R> k2 = K2; opaque4(k2);
-        V4<R> J3 = E3; opaque4(J3);
-        V4<R> k3 = K3; opaque4(k3);
+        V4<RG> J0 = E0; opaque4(J0);
+        V4<RG> k0 = K0; opaque4(k0);
+        V4<RG> J1 = E1; opaque4(J1);
+        V4<RG> k1 = K1; opaque4(k1);
+        V4<RG> J2 = E2; opaque4(J2);
+        V4<RG> k2 = K2; opaque4(k2);
+        V4<RG> J3 = E3; opaque4(J3);
+        V4<RG> k3 = K3; opaque4(k3);
         V4<R> pb = PB; opaque4(pb);
-        const V4<R> J03 = G9 * (v3(J0, J3, k0, k3));
-        const V4<R> J31 = G10 * (v3(J3, J1, k3, k1));
-        const V4<R> p10 = k1 + k3;
-        const V4<R> p9 = k0 + k3;
-        const V4<R> J031 = G11 * (w4_sub(J0, J3, J1, v3_acc(J03, J1, p9, k1, v3(J0, J31, k0, p10))));
-        const V4<R> J12 = G6 * (v3(J1, J2, k1, k2));
-        const V4<R> p6 = k1 + k2;
-        const V4<R> J312 = G14 * (w4_sub(J3, J1, J2, v3_acc(J31, J2, p10, k2, v3(J3, J12, k3, p6))));
-        const V4<R> p14 = k1 + k2 + k3;
-        const V4<R> p11 = k0 + k1 + k3;
-        const V4<R> J0312 = G15 * (w4_sub(J03, J1, J2, w4_sub(J0, J31, J2, w4_sub(J0, J3, J12, v3_acc(J031, J2, p11, k2, v3_acc(J03, J12, p9, p6, v3(J0, J312, k0, p14)))))));
-        const V4<R> J30 = R(-1.0) * J03;
-        const V4<R> J01 = G3 * (v3(J0, J1, k0, k1));
-        const V4<R> p3 = k0 + k1;
-        const V4<R> J301 = G11 * (w4_sub(J3, J0, J1, v3_acc(J30, J1, p9, k1, v3(J3, J01, k3, p3))));
-        const V4<R> J012 = G7 * (w4_sub(J0, J1, J2, v3_acc(J01, J2, p3, k2, v3(J0, J12, k0, p6))));
-        const V4<R> p7 = k0 + k1 + k2;
-        const V4<R> J3012 = G15 * (w4_sub(J30, J1, J2, w4_sub(J3, J01, J2, w4_sub(J3, J0, J12, v3_acc(J301, J2, p11, k2, v3_acc(J30, J12, p9, p6, v3(J3, J012, k3, p7)))))));
+        const V4<RG> J03 = G9 * (v3(J0, J3, k0, k3));
+        const V4<RG> J31 = G10 * (v3(J3, J1, k3, k1));
+        const V4<RG> p10 = k1 + k3;
+        const V4<RG> p9 = k0 + k3;
+        const V4<RG> J031 = G11 * (w4_sub(J0, J3, J1, v3_acc(J03, J1, p9, k1, v3(J0, J31, k0, p10))));
+        const V4<RG> J12 = G6 * (v3(J1, J2, k1, k2));
+        const V4<RG> p6 = k1 + k2;
+        const V4<RG> J312 = G14 * (w4_sub(J3, J1, J2, v3_acc(J31, J2, p10, k2, v3(J3, J12, k3, p6))));
+        const V4<RG> p14 = k1 + k2 + k3;
+        const V4<RG> p11 = k0 + k1 + k3;
+        const V4<RG> J0312 = G15 * (w4_sub(J03, J1, J2, w4_sub(J0, J31, J2, w4_sub(J0, J3, J12, v3_acc(J031, J2, p11, k2, v3_acc(J03, J12, p9, p6, v3(J0, J312, k0, p14)))))));
+        const V4<RG> J30 = RG(-1.0) * J03;
+        const V4<RG> J01 = G3 * (v3(J0, J1, k0, k1));
+        const V4<RG> p3 = k0 + k1;
+        const V4<RG> J301 = G11 * (w4_sub(J3, J0, J1, v3_acc(J30, J1, p9, k1, v3(J3, J01, k3, p3))));
+        const V4<RG> J012 = G7 * (w4_sub(J0, J1, J2, v3_acc(J01, J2, p3, k2, v3(J0, J12, k0, p6))));
+        const V4<RG> p7 = k0 + k1 + k2;
+        const V4<RG> J3012 = G15 * (w4_sub(J30, J1, J2, w4_sub(J3, J01, J2, w4_sub(J3, J0, J12, v3_acc(J301, J2, p11, k2, v3_acc(J30, J12, p9, p6, v3(J3, J012, k3, p7)))))));
         Sp<R> Sh0_ = VS[0]; opaque_sp(Sh0_);
         const Sp<R> Sh0_2 = prop_neg(pb + k2, MT, IQ4, slash(J2, Sh0_));
         const Sp<R> Sh0_12 = prop_neg(pb + p6, MT, IQ6, slash_acc(J12, Sh0_, slash(J1, Sh0_2)));
@@ -288,33 +288,33 @@ __device__ __forceinline__ R me_gg_m4(const V4<RK>* K, const V4<R> (*E)[2], cons
       C2<R> A0h0_5, A1h0_5;
       C2<R> A0h0_19, A1h0_19;
       {  // orderings (0, 3, 2, 1), (3, 0, 2, 1)
-        V4<R> J0 = E0; opaque4(J0);
-        V4<R> k0 = K0; opaque4(k0);
-        V4<R> J1 = E1; opaque4(J1);
-        V4<R> k1 = K1; opaque4(k1);
-        V4<R> J2 = E2; opaque4(J2);
-        V4<R> k2 = K2; opaque4(k2);
-        V4<R> J3 = E3; opaque4(J3);
-        V4<R> k3 = K3; opaque4(k3);
+        V4<RG> J0 = E0; opaque4(J0);
+        V4<RG> k0 = K0; opaque4(k0);
+        V4<RG> J1 = E1; opaque4(J1);
+        V4<RG> k1 = K1; opaque4(k1);
+        V4<RG> J2 = E2; opaque4(J2);
+        V4<RG> k2 = K2; opaque4(k2);
+        V4<RG> J3 = E3; opaque4(J3);
+        V4<RG> k3 = K3; opaque4(k3);
         V4<R> pb = PB; opaque4(pb);
-        const V4<R> J03 = G9 * (v3(J0, J3, k0, k3));
-        const V4<R> J32 = G12 * (v3(J3, J2, k3, k2));
-        const V4<R> p12 = k2 + k3;
-        const V4<R> p9 = k0 + k3;
-        const V4<R> J032 = G13 * (w4_sub(J0, J3, J2, v3_acc(J03, J2, p9, k2, v3(J0, J32, k0, p12))));
-        const V4<R> J21 = G6 * (v3(J2, J1, k2, k1));
-        const V4<R> p6 = k1 + k2;
-        const V4<R> J321 = G14 * (w4_sub(J3, J2, J1, v3_acc(J32, J1, p12, k1, v3(J3, J21, k3, p6))));
-        const V4<R> p14 = k1 + k2 + k3;
-        const V4<R> p13 = k0 + k2 + k3;
-        const V4<R> J0321 = G15 * (w4_sub(J03, J2, J1, w4_sub(J0, J32, J1, w4_sub(J0, J3, J21, v3_acc(J032, J1, p13, k1, v3_acc(J03, J21, p9, p6, v3(J0, J321, k0, p14)))))));
-        const V4<R> J30 = R(-1.0) * J03;
-        const V4<R> J02 = G5 * (v3(J0, J2, k0, k2));
-        const V4<R> p5 = k0 + k2;
-        const V4<R> J302 = G13 * (w4_sub(J3, J0, J2, v3_acc(J30, J2, p9, k2, v3(J3, J02, k3, p5))));
-        const V4<R> J021 = G7 * (w4_sub(J0, J2, J1, v3_acc(J02, J1, p5, k1, v3(J0, J21, k0, p6))));
-        const V4<R> p7 = k0 + k1 + k2;
-        const V4<R> J3021 = G15 * (w4_sub(J30, J2, J1, w4_sub(J3, J02, J1, w4_sub(J3, J0, J21, v3_acc(J302, J1, p13, k1, v3_acc(J30, J21, p9, p6, v3(J3, J021, k3, p7)))))));
+        const V4<RG> J03 = G9 * (v3(J0, J3, k0, k3));
+        const V4<RG> J32 = G12 * (v3(J3, J2, k3, k2));
+        const V4<RG> p12 = k2 + k3;
+        const V4<RG> p9 = k0 + k3;
+        const V4<RG> J032 = G13 * (w4_sub(J0, J3, J2, v3_acc(J03, J2, p9, k2, v3(J0, J32, k0, p12))));
+        const V4<RG> J21 = G6 * (v3(J2, J1, k2, k1));
+        const V4<RG> p6 = k1 + k2;
+        const V4<RG> J321 = G14 * (w4_sub(J3, J2, J1, v3_acc(J32, J1, p12, k1, v3(J3, J21, k3, p6))));
+        const V4<RG> p14 = k1 + k2 + k3;
+        const V4<RG> p13 = k0 + k2 + k3;
+        const V4<RG> J0321 = G15 * (w4_sub(J03, J2, J1, w4_sub(J0, J32, J1, w4_sub(J0, J3, J21, v3_acc(J032, J1, p13, k1, v3_acc(J03, J21, p9, p6, v3(J0, J321, k0, p14)))))));
+        const V4<RG> J30 = RG(-1.0) * J03;
+        const V4<RG> J02 = G5 * (v3(J0, J2, k0, k2));
+        const V4<RG> p5 = k0 + k2;
+        const V4<RG> J302 = G13 * (w4_sub(J3, J0, J2, v3_acc(J30, J2, p9, k2, v3(J3, J02, k3, p5))));
+        const V4<RG> J021 = G7 * (w4_sub(J0, J2, J1, v3_acc(J02, J1, p5, k1, v3(J0, J21, k0, p6))));
+        const V4<RG> p7 = k0 + k1 + k2;
+        const V4<RG> J3021 = G15 * (w4_sub(J30, J2, J1, w4_sub(J3, J02, J1, w4_sub(J3, J0, J21, v3_acc(J302, J1, p13, k1, v3_acc(J30, J21, p9, p6, v3(J3, J021, k3, p7)))))));
         Sp<R> Sh0_ = VS[0]; opaque_sp(Sh0_);
         const Sp<R> Sh0_1 = prop_neg(pb + k1, MT, IQ2, slash(J1, Sh0_));
         const Sp<R> Sh0_21 = prop_neg(pb + p6, MT, IQ6, slash_acc(J21, Sh0_, slash(J2, Sh0_1)));
@@ -330,33 +330,33 @@ __device__ __forceinline__ R me_gg_m4(const V4<RK>* K, const V4<R> (*E)[2], cons
       C2<R> A0h0_8, A1h0_8;
       C2<R> A0h0_14, A1h0_14;
       {  // orderings (1, 2, 0, 3), (2, 1, 0, 3)
-        V4<R> J0 = E0; opaque4(J0);
-        V4<R> k0 = K0; opaque4(k0);
-        V4<R> J1 = E1; opaque4(J1);
-        V4<R> k1 = K1; opaque4(k1);
-        V4<R> J2 = E2; opaque4(J2);
-        V4<R> k2 = K2; opaque4(k2);
-        V4<R> J3 = E3; opaque4(J3);
-        V4<R> k3 = K3; opaque4(k3);
+        V4<RG> J0 = E0; opaque4(J0);
+        V4<RG> k0 = K0; opaque4(k0);
+        V4<RG> J1 = E1; opaque4(J1);
+        V4<RG> k1 = K1; opaque4(k1);
+        V4<RG> J2 = E2; opaque4(J2);
+        V4<RG> k2 = K2; opaque4(k2);
+        V4<RG> J3 = E3; opaque4(J3);
+        V4<RG> k3 = K3; opaque4(k3);
         V4<R> pb = PB; opaque4(pb);
-        const V4<R> J12 = G6 * (v3(J1, J2, k1, k2));
-        const V4<R> J20 = G5 * (v3(J2, J0, k2, k0));
-        const V4<R> p5 = k0 + k2;
-        const V4<R> p6 = k1 + k2;
-        const V4<R> J120 = G7 * (w4_sub(J1, J2, J0, v3_acc(J12, J0, p6, k0, v3(J1, J20, k1, p5))));
-        const V4<R> J03 = G9 * (v3(J0, J3, k0, k3));
-        const V4<R> p9 = k0 + k3;
-        const V4<R> J203 = G13 * (w4_sub(J2, J0, J3, v3_acc(J20, J3, p5, k3, v3(J2, J03, k2, p9))));
-        const V4<R> p13 = k0 + k2 + k3;
-        const V4<R> p7 = k0 + k1 + k2;
-        const V4<R> J1203 = G15 * (w4_sub(J12, J0, J3, w4_sub(J1, J20, J3, w4_sub(J1, J2, J03, v3_acc(J120, J3, p7, k3, v3_acc(J12, J03, p6, p9, v3(J1, J203, k1, p13)))))));
-        const V4<R> J21 = R(-1.0) * J12;
-        const V4<R> J10 = G3 * (v3(J1, J0, k1, k0));
-        const V4<R> p3 = k0 + k1;
-        const V4<R> J210 = G7 * (w4_sub(J2, J1, J0, v3_acc(J21, J0, p6, k0, v3(J2, J10, k2, p3))));
-        const V4<R> J103 = G11 * (w4_sub(J1, J0, J3, v3_acc(J10, J3, p3, k3, v3(J1, J03, k1, p9))));
-        const V4<R> p11 = k0 + k1 + k3;
-        const V4<R> J2103 = G15 * (w4_sub(J21, J0, J3, w4_sub(J2, J10, J3, w4_sub(J2, J1, J03, v3_acc(J210, J3, p7, k3, v3_acc(J21, J03, p6, p9, v3(J2, J103, k2, p11)))))));
+        const V4<RG> J12 = G6 * (v3(J1, J2, k1, k2));
+        const V4<RG> J20 = G5 * (v3(J2, J0, k2, k0));
+        const V4<RG> p5 = k0 + k2;
+        const V4<RG> p6 = k1 + k2;
+        const V4<RG> J120 = G7 * (w4_sub(J1, J2, J0, v3_acc(J12, J0, p6, k0, v3(J1, J20, k1, p5))));
+        const V4<RG> J03 = G9 * (v3(J0, J3, k0, k3));
+        const V4<RG> p9 = k0 + k3;
+        const V4<RG> J203 = G13 * (w4_sub(J2, J0, J3, v3_acc(J20, J3, p5, k3, v3(J2, J03, k2, p9))));
+        const V4<RG> p13 = k0 + k2 + k3;
+        const V4<RG> p7 = k0 + k1 + k2;
+        const V4<RG> J1203 = G15 * (w4_sub(J12, J0, J3, w4_sub(J1, J20, J3, w4_sub(J1, J2, J03, v3_acc(J120, J3, p7, k3, v3_acc(J12, J03, p6, p9, v3(J1, J203, k1, p13)))))));
+        const V4<RG> J21 = RG(-1.0) * J12;
+        const V4<RG> J10 = G3 * (v3(J1, J0, k1, k0));
+        const V4<RG> p3 = k0 + k1;
+        const V4<RG> J210 = G7 * (w4_sub(J2, J1, J0, v3_acc(J21, J0, p6, k0, v3(J2, J10, k2, p3))));
+        const V4<RG> J103 = G11 * (w4_sub(J1, J0, J3, v3_acc(J10, J3, p3, k3, v3(J1, J03, k1, p9))));
+        const V4<RG> p11 = k0 + k1 + k3;
+        const V4<RG> J2103 = G15 * (w4_sub(J21, J0, J3, w4_sub(J2, J10, J3, w4_sub(J2, J1, J03, v3_acc(J210, J3, p7, k3, v3_acc(J21, J03, p6, p9, v3(J2, J103, k2, p11)))))));
         Sp<R> Sh0_ = VS[0]; opaque_sp(Sh0_);
         const Sp<R> Sh0_3 = prop_neg(pb + k3, MT, IQ8, slash(J3, Sh0_));
         const Sp<R> Sh0_03 = prop_neg(pb + p9, MT, IQ9, slash_acc(J03, Sh0_, slash(J0, Sh0_3)));
@@ -372,33 +372,33 @@ __device__ __forceinline__ R me_gg_m4(const V4<RK>* K, const V4<R> (*E)[2], cons
       C2<R> A0h0_9, A1h0_9;
       C2<R> A0h0_15, A1h0_15;
       {  // orderings (1, 2, 3, 0), (2, 1, 3, 0)
-        V4<R> J0 = E0; opaque4(J0);
-        V4<R> k0 = K0; opaque4(k0);
-        V4<R> J1 = E1; opaque4(J1);
-        V4<R> k1 = K1; opaque4(k1);
-        V4<R> J2 = E2; opaque4(J2);
-        V4<R> k2 = K2; opaque4(k2);
-        V4<R> J3 = E3; opaque4(J3);
-        V4<R> k3 = K3; opaque4(k3);
+        V4<RG> J0 = E0; opaque4(J0);
+        V4<RG> k0 = K0; opaque4(k0);
+        V4<RG> J1 = E1; opaque4(J1);
+        V4<RG> k1 = K1; opaque4(k1);
+        V4<RG> J2 = E2; opaque4(J2);
+        V4<RG> k2 = K2; opaque4(k2);
+        V4<RG> J3 = E3; opaque4(J3);
+        V4<RG> k3 = K3; opaque4(k3);
         V4<R> pb = PB; opaque4(pb);
-        const V4<R> J12 = G6 * (v3(J1, J2, k1, k2));
-        const V4<R> J23 = G12 * (v3(J2, J3, k2, k3));
-        const V4<R> p12 = k2 + k3;
-        const V4<R> p6 = k1 + k2;
-        const V4<R> J123 = G14 * (w4_sub(J1, J2, J3, v3_acc(J12, J3, p6, k3, v3(J1, J23, k1, p12))));
-        const V4<R> J30 = G9 * (v3(J3, J0, k3, k0));
-        const V4<R> p9 = k0 + k3;
-        const V4<R> J230 = G13 * (w4_sub(J2, J3, J0, v3_acc(J23, J0, p12, k0, v3(J2, J30, k2, p9))));
-        const V4<R> p13 = k0 + k2 + k3;
-        const V4<R> p14 = k1 + k2 + k3;
-        const V4<R> J1230 = G15 * (w4_sub(J12, J3, J0, w4_sub(J1, J23, J0, w4_sub(J1, J2, J30, v3_acc(J123, J0, p14, k0, v3_acc(J12, J30, p6, p9, v3(J1, J230, k1, p13)))))));
-        const V4<R> J21 = R(-1.0) * J12;
-        const V4<R> J13 = G10 * (v3(J1, J3, k1, k3));
-        const V4<R> p10 = k1 + k3;
-        const V4<R> J213 = G14 * (w4_sub(J2, J1, J3, v3_acc(J21, J3, p6, k3, v3(J2, J13, k2, p10))));
-        const V4<R> J130 = G11 * (w4_sub(J1, J3, J0, v3_acc(J13, J0, p10, k0, v3(J1, J30, k1, p9))));
-        const V4<R> p11 = k0 + k1 + k3;
-        const V4<R> J2130 = G15 * (w4_sub(J21, J3, J0, w4_sub(J2, J13, J0, w4_sub(J2, J1, J30, v3_acc(J213, J0, p14, k0, v3_acc(J21, J30, p6, p9, v3(J2, J130, k2, p11)))))));
+        const V4<RG> J12 = G6 * (v3(J1, J2, k1, k2));
+        const V4<RG> J23 = G12 * (v3(J2, J3, k2, k3));
+        const V4<RG> p12 = k2 + k3;
+        const V4<RG> p6 = k1 + k2;
+        const V4<RG> J123 = G14 * (w4_sub(J1, J2, J3, v3_acc(J12, J3, p6, k3, v3(J1, J23, k1, p12))));
+        const V4<RG> J30 = G9 * (v3(J3, J0, k3, k0));
+        const V4<RG> p9 = k0 + k3;
+        const V4<RG> J230 = G13 * (w4_sub(J2, J3, J0, v3_acc(J23, J0, p12, k0, v3(J2, J30, k2, p9))));
+        const V4<RG> p13 = k0 + k2 + k3;
+        const V4<RG> p14 = k1 + k2 + k3;
+        const V4<RG> J1230 = G15 * (w4_sub(J12, J3, J0, w4_sub(J1, J23, J0, w4_sub(J1, J2, J30, v3_acc(J123, J0, p14, k0, v3_acc(J12, J30, p6, p9, v3(J1, J230, k1, p13)))))));
+        const V4<RG> J21 = RG(-1.0) * J12;
+        const V4<RG> J13 = G10 * (v3(J1, J3, k1, k3));
+        const V4<RG> p10 = k1 + k3;
+        const V4<RG> J213 = G14 * (w4_sub(J2, J1, J3, v3_acc(J21, J3, p6, k3, v3(J2, J13, k2, p10))));
+        const V4<RG> J130 = G11 * (w4_sub(J1, J3, J0, v3_acc(J13, J0, p10, k0, v3(J1, J30, k1, p9))));
+        const V4<RG> p11 = k0 + k1 + k3;
+        const V4<RG> J2130 = G15 * (w4_sub(J21, J3, J0, w4_sub(J2, J13, J0, w4_sub(J2, J1, J30, v3_acc(J213, J0, p14, k0, v3_acc(J21, J30, p6, p9, v3(J2, J130, k2, p11)))))));
         Sp<R> Sh0_ = VS[0]; opaque_sp(Sh0_);
         const Sp<R> Sh0_0 = prop_neg(pb + k0, MT, IQ1, slash(J0, Sh0_));
         const Sp<R> Sh0_30 = prop_neg(pb + p9, MT, IQ9, slash_acc(J30, Sh0_, slash(J3, Sh0_0)));
@@ -414,33 +414,33 @@ __device__ __forceinline__ R me_gg_m4(const V4<RK>* K, const V4<R> (*E)[2], cons
       C2<R> A0h0_10, A1h0_10;
       C2<R> A0h0_20, A1h0_20;
       {  // orderings (1, 3, 0, 2), (3, 1, 0, 2)
-        V4<R> J0 = E0; opaque4(J0);
-        V4<R> k0 = K0; opaque4(k0);
-        V4<R> J1 = E1; opaque4(J1);
-        V4<R> k1 = K1; opaque4(k1);
-        V4<R> J2 = E2; opaque4(J2);
-        V4<R> k2 = K2; opaque4(k2);
-        V4<R> J3 = E3; opaque4(J3);
-        V4<R> k3 = K3; opaque4(k3);
+        V4<RG> J0 = E0; opaque4(J0);
+        V4<RG> k0 = K0; opaque4(k0);
+        V4<RG> J1 = E1; opaque4(J1);
+        V4<RG> k1 = K1; opaque4(k1);
+        V4<RG> J2 = E2; opaque4(J2);
+        V4<RG> k2 = K2; opaque4(k2);
+        V4<RG> J3 = E3; opaque4(J3);
+        V4<RG> k3 = K3; opaque4(k3);
         V4<R> pb = PB; opaque4(pb);
-        const V4<R> J13 = G10 * (v3(J1, J3, k1, k3));
-        const V4<R> J30 = G9 * (v3(J3, J0, k3, k0));
-        const V4<R> p9 = k0 + k3;
-        const V4<R> p10 = k1 + k3;
-        const V4<R> J130 = G11 * (w4_sub(J1, J3, J0, v3_acc(J13, J0, p10, k0, v3(J1, J30, k1, p9))));
-        const V4<R> J02 = G5 * (v3(J0, J2, k0, k2));
-        const V4<R> p5 = k0 + k2;
-        const V4<R> J302 = G13 * (w4_sub(J3, J0, J2, v3_acc(J30, J2, p9, k2, v3(J3, J02, k3, p5))));
-        const V4<R> p13 = k0 + k2 + k3;
-        const V4<R> p11 = k0 + k1 + k3;
-        const V4<R> J1302 = G15 * (w4_sub(J13, J0, J2, w4_sub(J1, J30, J2, w4_sub(J1, J3, J02, v3_acc(J130, J2, p11, k2, v3_acc(J13, J02, p10, p5, v3(J1, J302, k1, p13)))))));
-        const V4<R> J31 = R(-1.0) * J13;
-        const V4<R> J10 = G3 * (v3(J1, J0, k1, k0));
-        const V4<R> p3 = k0 + k1;
-        const V4<R> J310 = G11 * (w4_sub(J3, J1, J0, v3_acc(J31, J0, p10, k0, v3(J3, J10, k3, p3))));
-        const V4<R> J102 = G7 * (w4_sub(J1, J0, J2, v3_acc(J10, J2, p3, k2, v3(J1, J02, k1, p5))));
-        const V4<R> p7 = k0 + k1 + k2;
-        const V4<R> J3102 = G15 * (w4_sub(J31, J0, J2, w4_sub(J3, J10, J2, w4_sub(J3, J1, J02, v3_acc(J310, J2, p11, k2, v3_acc(J31, J02, p10, p5, v3(J3, J102, k3, p7)))))));
+        const V4<RG> J13 = G10 * (v3(J1, J3, k1, k3));
+        const V4<RG> J30 = G9 * (v3(J3, J0, k3, k0));
+        const V4<RG> p9 = k0 + k3;
+        const V4<RG> p10 = k1 + k3;
+        const V4<RG> J130 = G11 * (w4_sub(J1, J3, J0, v3_acc(J13, J0, p10, k0, v3(J1, J30, k1, p9))));
+        const V4<RG> J02 = G5 * (v3(J0, J2, k0, k2));
+        const V4<RG> p5 = k0 + k2;
+        const V4<RG> J302 = G13 * (w4_sub(J3, J0, J2, v3_acc(J30, J2, p9, k2, v3(J3, J02, k3, p5))));
+        const V4<RG> p13 = k0 + k2 + k3;
+        const V4<RG> p11 = k0 + k1 + k3;
+        const V4<RG> J1302 = G15 * (w4_sub(J13, J0, J2, w4_sub(J1, J30, J2, w4_sub(J1, J3, J02, v3_acc(J130, J2, p11, k2, v3_acc(J13, J02, p10, p5, v3(J1, J302, k1, p13)))))));
+        const V4<RG> J31 = RG(-1.0) * J13;
+        const V4<RG> J10 = G3 * (v3(J1, J0, k1, k0));
+        const V4<RG> p3 = k0 + k1;
+        const V4<RG> J310 = G11 * (w4_sub(J3, J1, J0, v3_acc(J31, J0, p10, k0, v3(J3, J10, k3, p3))));
+        const V4<RG> J102 = G7 * (w4_sub(J1, J0, J2, v3_acc(J10, J2, p3, k2, v3(J1, J02, k1, p5))));
+        const V4<RG> p7 = k0 + k1 + k2;
+        const V4<RG> J3102 = G15 * (w4_sub(J31, J0, J2, w4_sub(J3, J10, J2, w4_sub(J3, J1, J02, v3_acc(J310, J2, p11, k2, v3_acc(J31, J02, p10, p5, v3(J3, J102, k3, p7)))))));
         Sp<R> Sh0_ = VS[0]; opaque_sp(Sh0_);
         const Sp<R> Sh0_2 = prop_neg(pb + k2, MT, IQ4, slash(J2, Sh0_));
         const Sp<R> Sh0_02 = prop_neg(pb + p5, MT, IQ5, slash_acc(J02, Sh0_, slash(J0, Sh0_2)));
@@ -456,33 +456,33 @@ __device__ __forceinline__ R me_gg_m4(const V4<RK>* K, const V4<R> (*E)[2], cons
       C2<R> A0h0_11, A1h0_11;
       C2<R> A0h0_21, A1h0_21;
       {  // orderings (1, 3, 2, 0), (3, 1, 2, 0)
-        V4<R> J0 = E0; opaque4(J0);
-        V4<R> k0 = K0; opaque4(k0);
-        V4<R> J1 = E1; opaque4(J1);
-        V4<R> k1 = K1; opaque4(k1);
-        V4<R> J2 = E2; opaque4(J2);
-        V4<R> k2 = K2; opaque4(k2);
-        V4<R> J3 = E3; opaque4(J3);
-        V4<R> k3 = K3; opaque4(k3);
+        V4<RG> J0 = E0; opaque4(J0);
+        V4<RG> k0 = K0; opaque4(k0);
+        V4<RG> J1 = E1; opaque4(J1);
+        V4<RG> k1 = K1; opaque4(k1);
+        V4<RG> J2 = E2; opaque4(J2);
+        V4<RG> k2 = K2; opaque4(k2);
+        V4<RG> J3 = E3; opaque4(J3);
+        V4<RG> k3 = K3; opaque4(k3);
         V4<R> pb = PB; opaque4(pb);
-        const V4<R> J13 = G10 * (v3(J1, J3, k1, k3));
-        const V4<R> J32 = G12 * (v3(J3, J2, k3, k2));
-        const V4<R> p12 = k2 + k3;
-        const V4<R> p10 = k1 + k3;
-        const V4<R> J132 = G14 * (w4_sub(J1, J3, J2, v3_acc(J13, J2, p10, k2, v3(J1, J32, k1, p12))));
-        const V4<R> J20 = G5 * (v3(J2, J0, k2, k0));
-        const V4<R> p5 = k0 + k2;
-        const V4<R> J320 = G13 * (w4_sub(J3, J2, J0, v3_acc(J32, J0, p12, k0, v3(J3, J20, k3, p5))));
-        const V4<R> p13 = k0 + k2 + k3;
-        const V4<R> p14 = k1 + k2 + k3;
-        const V4<R> J1320 = G15 * (w4_sub(J13, J2, J0, w4_sub(J1, J32, J0, w4_sub(J1, J3, J20, v3_acc(J132, J0, p14, k0, v3_acc(J13, J20, p10, p5, v3(J1, J320, k1, p13)))))));
-        const V4<R> J31 = R(-1.0) * J13;
-        const V4<R> J12 = G6 * (v3(J1, J2, k1, k2));
-        const V4<R> p6 = k1 + k2;
-        const V4<R> J312 = G14 * (w4_sub(J3, J1, J2, v3_acc(J31, J2, p10, k2, v3(J3, J12, k3, p6))));
-        const V4<R> J120 = G7 * (w4_sub(J1, J2, J0, v3_acc(J12, J0, p6, k0, v3(J1, J20, k1, p5))));
-        const V4<R> p7 = k0 + k1 + k2;
-        const V4<R> J3120 = G15 * (w4_sub(J31, J2, J0, w4_sub(J3, J12, J0, w4_sub(J3, J1, J20, v3_acc(J312, J0, p14, k0, v3_acc(J31, J20, p10, p5, v3(J3, J120, k3, p7)))))));
+        const V4<RG> J13 = G10 * (v3(J1, J3, k1, k3));
+        const V4<RG> J32 = G12 * (v3(J3, J2, k3, k2));
+        const V4<RG> p12 = k2 + k3;
+        const V4<RG> p10 = k1 + k3;
+        const V4<RG> J132 = G14 * (w4_sub(J1, J3, J2, v3_acc(J13, J2, p10, k2, v3(J1, J32, k1, p12))));
+        const V4<RG> J20 = G5 * (v3(J2, J0, k2, k0));
+        const V4<RG> p5 = k0 + k2;
+        const V4<RG> J320 = G13 * (w4_sub(J3, J2, J0, v3_acc(J32, J0, p12, k0, v3(J3, J20, k3, p5))));
+        const V4<RG> p13 = k0 + k2 + k3;
+        const V4<RG> p14 = k1 + k2 + k3;
+        const V4<RG> J1320 = G15 * (w4_sub(J13, J2, J0, w4_sub(J1, J32, J0, w4_sub(J1, J3, J20, v3_acc(J132, J0, p14, k0, v3_acc(J13, J20, p10, p5, v3(J1, J320, k1, p13)))))));
+        const V4<RG> J31 = RG(-1.0) * J13;
+        const V4<RG> J12 = G6 * (v3(J1, J2, k1, k2));
+        const V4<RG> p6 = k1 + k2;
+        const V4<RG> J312 = G14 * (w4_sub(J3, J1, J2, v3_acc(J31, J2, p10, k2, v3(J3, J12, k3, p6))));
+        const V4<RG> J120 = G7 * (w4_sub(J1, J2, J0, v3_acc(J12, J0, p6, k0, v3(J1, J20, k1, p5))));
+        const V4<RG> p7 = k0 + k1 + k2;
+        const V4<RG> J3120 = G15 * (w4_sub(J31, J2, J0, w4_sub(J3, J12, J0, w4_sub(J3, J1, J20, v3_acc(J312, J0, p14, k0, v3_acc(J31, J20, p10, p5, v3(J3, J120, k3, p7)))))));
         Sp<R> Sh0_ = VS[0]; opaque_sp(Sh0_);
         const Sp<R> Sh0_0 = prop_neg(pb + k0, MT, IQ1, slash(J0, Sh0_));
         const Sp<R> Sh0_20 = prop_neg(pb + p5, MT, IQ5, slash_acc(J20, Sh0_, slash(J2, Sh0_0)));
@@ -498,33 +498,33 @@ __device__ __forceinline__ R me_gg_m4(const V4<RK>* K, const V4<R> (*E)[2], cons
       C2<R> A0h0_16, A1h0_16;
       C2<R> A0h0_22, A1h0_22;
       {  // orderings (2, 3, 0, 1), (3, 2, 0, 1)
-        V4<R> J0 = E0; opaque4(J0);
-        V4<R> k0 = K0; opaque4(k0);
-        V4<R> J1 = E1; opaque4(J1);
-        V4<R> k1 = K1; opaque4(k1);
-        V4<R> J2 = E2; opaque4(J2);
-        V4<R> k2 = K2; opaque4(k2);
-        V4<R> J3 = E3; opaque4(J3);
-        V4<R> k3 = K3; opaque4(k3);
+        V4<RG> J0 = E0; opaque4(J0);
+        V4<RG> k0 = K0; opaque4(k0);
+        V4<RG> J1 = E1; opaque4(J1);
+        V4<RG> k1 = K1; opaque4(k1);
+        V4<RG> J2 = E2; opaque4(J2);
+        V4<RG> k2 = K2; opaque4(k2);
+        V4<RG> J3 = E3; opaque4(J3);
+        V4<RG> k3 = K3; opaque4(k3);
         V4<R> pb = PB; opaque4(pb);
-        const V4<R> J23 = G12 * (v3(J2, J3, k2, k3));
-        const V4<R> J30 = G9 * (v3(J3, J0, k3, k0));
-        const V4<R> p9 = k0 + k3;
-        const V4<R> p12 = k2 + k3;
-        const V4<R> J230 = G13 * (w4_sub(J2, J3, J0, v3_acc(J23, J0, p12, k0, v3(J2, J30, k2, p9))));
-        const V4<R> J01 = G3 * (v3(J0, J1, k0, k1));
-        const V4<R> p3 = k0 + k1;
-        const V4<R> J301 = G11 * (w4_sub(J3, J0, J1, v3_acc(J30, J1, p9, k1, v3(J3, J01, k3, p3))));
-        const V4<R> p11 = k0 + k1 + k3;
-        const V4<R> p13 = k0 + k2 + k3;
-        const V4<R> J2301 = G15 * (w4_sub(J23, J0, J1, w4_sub(J2, J30, J1, w4_sub(J2, J3, J01, v3_acc(J230, J1, p13, k1, v3_acc(J23, J01, p12, p3, v3(J2, J301, k2, p11)))))));
-        const V4<R> J32 = R(-1.0) * J23;
-        const V4<R> J20 = G5 * (v3(J2, J0, k2, k0));
-        const V4<R> p5 = k0 + k2;
-        const V4<R> J320 = G13 * (w4_sub(J3, J2, J0, v3_acc(J32, J0, p12, k0, v3(J3, J20, k3, p5))));
-        const V4<R> J201 = G7 * (w4_sub(J2, J0, J1, v3_acc(J20, J1, p5, k1, v3(J2, J01, k2, p3))));
-        const V4<R> p7 = k0 + k1 + k2;
-        const V4<R> J3201 = G15 * (w4_sub(J32, J0, J1, w4_sub(J3, J20, J1, w4_sub(J3, J2, J01, v3_acc(J320, J1, p13, k1, v3_acc(J32, J01, p12, p3, v3(J3, J201, k3, p7)))))));
+        const V4<RG> J23 = G12 * (v3(J2, J3, k2, k3));
+        const V4<RG> J30 = G9 * (v3(J3, J0, k3, k0));
+        const V4<RG> p9 = k0 + k3;
+        const V4<RG> p12 = k2 + k3;
+        const V4<RG> J230 = G13 * (w4_sub(J2, J3, J0, v3_acc(J23, J0, p12, k0, v3(J2, J30, k2, p9))));
+        const V4<RG> J01 = G3 * (v3(J0, J1, k0, k1));
+        const V4<RG> p3 = k0 + k1;
+        const V4<RG> J301 = G11 * (w4_sub(J3, J0, J1, v3_acc(J30, J1, p9, k1, v3(J3, J01, k3, p3))));
+        const V4<RG> p11 = k0 + k1 + k3;
+        const V4<RG> p13 = k0 + k2 + k3;
+        const V4<RG> J2301 = G15 * (w4_sub(J23, J0, J1, w4_sub(J2, J30, J1, w4_sub(J2, J3, J01, v3_acc(J230, J1, p13, k1, v3_acc(J23, J01, p12, p3, v3(J2, J301, k2, p11)))))));
+        const V4<RG> J32 = RG(-1.0) * J23;
+        const V4<RG> J20 = G5 * (v3(J2, J0, k2, k0));
+        const V4<RG> p5 = k0 + k2;
+        const V4<RG> J320 = G13 * (w4_sub(J3, J2, J0, v3_acc(J32, J0, p12, k0, v3(J3, J20, k3, p5))));
+        const V4<RG> J201 = G7 * (w4_sub(J2, J0, J1, v3_acc(J20, J1, p5, k1, v3(J2, J01, k2, p3))));
+        const V4<RG> p7 = k0 + k1 + k2;
+        const V4<RG> J3201 = G15 * (w4_sub(J32, J0, J1, w4_sub(J3, J20, J1, w4_sub(J3, J2, J01, v3_acc(J320, J1, p13, k1, v3_acc(J32, J01, p12, p3, v3(J3, J201, k3, p7)))))));
         Sp<R> Sh0_ = VS[0]; opaque_sp(Sh0_);
         const Sp<R> Sh0_1 = prop_neg(pb + k1, MT, IQ2, slash(J1, Sh0_));
         const Sp<R> Sh0_01 = prop_neg(pb + p3, MT, IQ3, slash_acc(J01, Sh0_, slash(J0, Sh0_1)));
@@ -540,33 +540,33 @@ __device__ __forceinline__ R me_gg_m4(const V4<RK>* K, const V4<R> (*E)[2], cons
       C2<R> A0h0_17, A1h0_17;
       C2<R> A0h0_23, A1h0_23;
       {  // orderings (2, 3, 1, 0), (3, 2, 1, 0)
-        V4<R> J0 = E0; opaque4(J0);
-        V4<R> k0 = K0; opaque4(k0);
-        V4<R> J1 = E1; opaque4(J1);
-        V4<R> k1 = K1; opaque4(k1);
-        V4<R> J2 = E2; opaque4(J2);
-        V4<R> k2 = K2; opaque4(k2);
-        V4<R> J3 = E3; opaque4(J3);
-        V4<R> k3 = K3; opaque4(k3);
+        V4<RG> J0 = E0; opaque4(J0);
+        V4<RG> k0 = K0; opaque4(k0);
+        V4<RG> J1 = E1; opaque4(J1);
+        V4<RG> k1 = K1; opaque4(k1);
+        V4<RG> J2 = E2; opaque4(J2);
+        V4<RG> k2 = K2; opaque4(k2);
+        V4<RG> J3 = E3; opaque4(J3);
+        V4<RG> k3 = K3; opaque4(k3);
         V4<R> pb = PB; opaque4(pb);
-        const V4<R> J23 = G12 * (v3(J2, J3, k2, k3));
-        const V4<R> J31 = G10 * (v3(J3, J1, k3, k1));
-        const V4<R> p10 = k1 + k3;
-        const V4<R> p12 = k2 + k3;
-        const V4<R> J231 = G14 * (w4_sub(J2, J3, J1, v3_acc(J23, J1, p12, k1, v3(J2, J31, k2, p10))));
-        const V4<R> J10 = G3 * (v3(J1, J0, k1, k0));
-        const V4<R> p3 = k0 + k1;
-        const V4<R> J310 = G11 * (w4_sub(J3, J1, J0, v3_acc(J31, J0, p10, k0, v3(J3, J10, k3, p3))));
-        const V4<R> p11 = k0 + k1 + k3;
-        const V4<R> p14 = k1 + k2 + k3;
-        const V4<R> J2310 = G15 * (w4_sub(J23, J1, J0, w4_sub(J2, J31, J0, w4_sub(J2, J3, J10, v3_acc(J231, J0, p14, k0, v3_acc(J23, J10, p12, p3, v3(J2, J310, k2, p11)))))));
-        const V4<R> J32 = R(-1.0) * J23;
-        const V4<R> J21 = G6 * (v3(J2, J1, k2, k1));
-        const V4<R> p6 = k1 + k2;
-        const V4<R> J321 = G14 * (w4_sub(J3, J2, J1, v3_acc(J32, J1, p12, k1, v3(J3, J21, k3, p6))));
-        const V4<R> J210 = G7 * (w4_sub(J2, J1, J0, v3_acc(J21, J0, p6, k0, v3(J2, J10, k2, p3))));
-        const V4<R> p7 = k0 + k1 + k2;
-        const V4<R> J3210 = G15 * (w4_sub(J32, J1, J0, w4_sub(J3, J21, J0, w4_sub(J3, J2, J10, v3_acc(J321, J0, p14, k0, v3_acc(J32, J10, p12, p3, v3(J3, J210, k3, p7)))))));
+        const V4<RG> J23 = G12 * (v3(J2, J3, k2, k3));
+        const V4<RG> J31 = G10 * (v3(J3, J1, k3, k1));
+        const V4<RG> p10 = k1 + k3;
+        const V4<RG> p12 = k2 + k3;
+        const V4<RG> J231 = G14 * (w4_sub(J2, J3, J1, v3_acc(J23, J1, p12, k1, v3(J2, J31, k2, p10))));
+        const V4<RG> J10 = G3 * (v3(J1, J0, k1, k0));
+        const V4<RG> p3 = k0 + k1;
+        const V4<RG> J310 = G11 * (w4_sub(J3, J1, J0, v3_acc(J31, J0, p10, k0, v3(J3, J10, k3, p3))));
+        const V4<RG> p11 = k0 + k1 + k3;
+        const V4<RG> p14 = k1 + k2 + k3;
+        const V4<RG> J2310 = G15 * (w4_sub(J23, J1, J0, w4_sub(J2, J31, J0, w4_sub(J2, J3, J10, v3_acc(J231, J0, p14, k0, v3_acc(J23, J10, p12, p3, v3(J2, J310, k2, p11)))))));
+        const V4<RG> J32 = RG(-1.0) * J23;
+        const V4<RG> J21 = G6 * (v3(J2, J1, k2, k1));
+        const V4<RG> p6 = k1 + k2;
+        const V4<RG> J321 = G14 * (w4_sub(J3, J2, J1, v3_acc(J32, J1, p12, k1, v3(J3, J21, k3, p6))));
+        const V4<RG> J210 = G7 * (w4_sub(J2, J1, J0, v3_acc(J21, J0, p6, k0, v3(J2, J10, k2, p3))));
+        const V4<RG> p7 = k0 + k1 + k2;
+        const V4<RG> J3210 = G15 * (w4_sub(J32, J1, J0, w4_sub(J3, J21, J0, w4_sub(J3, J2, J10, v3_acc(J321, J0, p14, k0, v3_acc(J32, J10, p12, p3, v3(J3, J210, k3, p7)))))));
         Sp<R> Sh0_ = VS[0]; opaque_sp(Sh0_);
         const Sp<R> Sh0_0 = prop_neg(pb + k0, MT, IQ1, slash(J0, Sh0_));
         const Sp<R> Sh0_10 = prop_neg(pb + p3, MT, IQ3, slash_acc(J10, Sh0_, slash(J1, Sh0_0)));

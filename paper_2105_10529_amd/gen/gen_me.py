@@ -429,6 +429,9 @@ def emit_me_per_ordering(m: int, share_antitop: bool = False, pair_orderings=Fal
     (scratch 2004 -> 1132 B per lane); derivatives of g g -> t t~ g at 1e5
     points 1.34 -> 0.89 ms.  Only for amplitudes in FP64: the two halves agree to
     rounding, not bit for bit, which in FP32 would show in the weights.
+    RG, KG: the types of the gluons' currents and momenta.  The final gluons'
+    momenta do not depend on the top mass, so with R dual in FP64 the whole
+    gluon part is plain FP64 and only the top line carries derivatives.
     lanes: the polarisation states dealt out to the 4, 8 or 16 lanes of an
     aligned group, with the arithmetic of the one-lane form; the group sums
     of the colour form are then added up in the order of the states by every
@@ -454,8 +457,8 @@ def emit_me_per_ordering(m: int, share_antitop: bool = False, pair_orderings=Fal
         w(f"constexpr double ME_M{m}_COLOUR_DEN = {den}.0;")
     w("// Colour- and polarisation-summed |M|^2 with g = 1 (argument meaning as in")
     w("// the shared-current schedule).")
-    w("template <" + ("int LANES, " if lanes else "") + "class R, class RK>")
-    w(f"__device__ __forceinline__ R me_gg_m{m}{suffix}(const V4<RK>* K, const V4<R> (*E)[2], const Sp<R>* UB,")
+    w("template <" + ("int LANES, " if lanes else "") + "class R, class RK, class RG, class KG>")
+    w(f"__device__ __forceinline__ R me_gg_m{m}{suffix}(const V4<KG>* K, const V4<RG> (*E)[2], const Sp<R>* UB,")
     w("                                         const Sp<R>* VS, const V4<RK>& PTB, RK MTK) {")
     if lanes:
         assert m == 4 and share_antitop
@@ -469,14 +472,14 @@ def emit_me_per_ordering(m: int, share_antitop: bool = False, pair_orderings=Fal
 
     for s_ in subsets:
         if bin(s_).count("1") >= 2:
-            w(f"  R G{s_};")
-            w(f"  {{ const V4<RK> P = {ksum(s_)}; G{s_} = cvt<R>(RK(-1.0) / mdot(P, P)); }}")
+            w(f"  RG G{s_};")
+            w(f"  {{ const V4<KG> P = {ksum(s_)}; G{s_} = cvt<RG>(KG(-1.0) / mdot(P, P)); }}")
     for s_ in subsets:
         if s_ != full:
             w(f"  R IQ{s_};")
-            w(f"  {{ const V4<RK> P = {ksum(s_)}; IQ{s_} = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }}")
+            w(f"  {{ const V4<KG> P = {ksum(s_)}; IQ{s_} = cvt<R>(RK(-1.0) / (RK(2.0) * mdot(PTB, P) + mdot(P, P))); }}")
     for i in range(m):
-        w(f"  const V4<R> K{i} = cvt4<R>(K[{i}]);")
+        w(f"  const V4<RG> K{i} = cvt4<RG>(K[{i}]);")
     w("  const V4<R> PB = cvt4<R>(PTB);")
     w("  R total = R(0.0);")
     hts = ((0,) if one_antitop else (0, 1)) if share_antitop else (None,)
@@ -497,7 +500,7 @@ def emit_me_per_ordering(m: int, share_antitop: bool = False, pair_orderings=Fal
         w(f"    for (int hg = 0; hg < {1 << m}; ++hg) {{")
     ind = "      "
     for i in range(m):
-        w(f"{ind}const V4<R> E{i} = ((hg >> {m - 1 - i}) & 1) ? E[{i}][1] : E[{i}][0];")
+        w(f"{ind}const V4<RG> E{i} = ((hg >> {m - 1 - i}) & 1) ? E[{i}][1] : E[{i}][0];")
     # orderings handled together: pairs that differ by the swap of their
     # first two gluons share the currents of positions 2.. (gluon and top-line
     # spinor currents), and their leading two-gluon currents differ in sign
@@ -525,8 +528,8 @@ def emit_me_per_ordering(m: int, share_antitop: bool = False, pair_orderings=Fal
         w(f"{ind}{{  // ordering" + ("s " if len(grp) > 1 else " ") + ", ".join(str(perms[k]) for k in grp))
         ii = ind + "  "
         for i in range(m):
-            w(f"{ii}V4<R> J{i} = E{i}; opaque4(J{i});")
-            w(f"{ii}V4<R> k{i} = K{i}; opaque4(k{i});")
+            w(f"{ii}V4<RG> J{i} = E{i}; opaque4(J{i});")
+            w(f"{ii}V4<RG> k{i} = K{i}; opaque4(k{i});")
         if not share_antitop:
             w(f"{ii}Sp<R> S_ = V; opaque_sp(S_);")
         w(f"{ii}V4<R> pb = PB; opaque4(pb);")
@@ -539,7 +542,7 @@ def emit_me_per_ordering(m: int, share_antitop: bool = False, pair_orderings=Fal
             if len(sq) == 1:
                 return f"k{sq[0]}"
             if nm not in psum:
-                w(f"{ii}const V4<R> {nm} = " + " + ".join(f"k{i}" for i in sorted(sq)) + ";")
+                w(f"{ii}const V4<RG> {nm} = " + " + ".join(f"k{i}" for i in sorted(sq)) + ";")
                 psum.add(nm)
             return nm
 
@@ -551,14 +554,14 @@ def emit_me_per_ordering(m: int, share_antitop: bool = False, pair_orderings=Fal
             if rev in done:
                 # reflection of a colour-ordered current: J(n..1) = (-1)^(n+1) J(1..n)
                 if len(sq) % 2 == 0:
-                    w(f"{ii}const V4<R> {nm} = R(-1.0) * {rev};")
+                    w(f"{ii}const V4<RG> {nm} = RG(-1.0) * {rev};")
                     done.add(nm)
                     return nm
                 return rev
             t3 = [(J(sq[:j]), J(sq[j:]), P(sq[:j]), P(sq[j:])) for j in range(1, len(sq))]
             t4 = [(J(sq[:j]), J(sq[j:l]), J(sq[l:])) for j in range(1, len(sq) - 1)
                   for l in range(j + 1, len(sq))]
-            w(f"{ii}const V4<R> {nm} = G{_mask(sq)} * ({_vsum(t3, t4)});")
+            w(f"{ii}const V4<RG> {nm} = G{_mask(sq)} * ({_vsum(t3, t4)});")
             done.add(nm)
             return nm
 
