@@ -3,8 +3,8 @@
 // and the flow part of the C ABI.
 //
 // Kernels:
-//   k_coupling      one coupling layer for a tile of 64 events: the three
-//                   dense layers as BF16 MFMA products (v_mfma_f32_16x16x32_bf16,
+//   k_coupling      all coupling layers for a tile of 64 events; of each the
+//                   three dense layers as BF16 MFMA products (v_mfma_f32_16x16x32_bf16,
 //                   FP32 accumulation) with the hidden activations resident in
 //                   LDS, then the FP32 piecewise-quadratic CDF (or its inverse)
 //                   of each transformed coordinate; optionally keeps the layer
@@ -84,6 +84,10 @@ struct LayerDev {
   const bf16* W2q;   // [H][H]
   const bf16* W3q;   // [dB NOP rounded up to 32][H]
   const bf16* W1q;   // [16][H]
+};
+
+struct Layers {
+  LayerDev L[MAXL];
 };
 
 __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
@@ -266,11 +270,27 @@ __device__ __forceinline__ void pq_quad(const float* o, float vlast, float t, in
   pdf = qq + qdpp<QX2>(qq);
 }
 
-// --------------------------------------------------------- coupling layer
-// One layer for events [64 blockIdx.x, +64): y is [d][ld] (n <= ld events
-// used) and is transformed in place (the kept coordinates are only read).
-// INVERSE selects the sampling direction.  logq[e] is set (first layer) or
-// accumulated.  CACHE keeps the layer's input points in lin [d][n].
+// A copy of x whose value the compiler does not follow: LDS offsets derived
+// from it are computed where they are used instead of being kept in registers
+// from one phase of a kernel to the next (9 spilled registers otherwise in
+// k_coupling, 123 in k_layer_backward).
+__device__ __forceinline__ int fresh(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+// -------------------------------------------------------- coupling layers
+// All nl layers for events [64 blockIdx.x, +64): y is [d][ld] (n <= ld events
+// used) and is transformed in place (a layer's kept coordinates are only
+// read).  INVERSE selects the sampling direction, in which the last layer
+// comes first.  logq[e] is set to the sum over the layers.  CACHE keeps the
+// input points of layer l in lin + l lstride, [d][n].
+//
+// A tile needs no other tile between its layers, so one launch runs them all:
+// a layer of few events is a chain of latencies, and of many events has a last
+// round of tiles that is not full.  6 layers, one launch per layer and one for
+// all: 700 points of 7 dimensions 68 and 60 us of kernels, 1e6 points of 10
+// dimensions 2.25 and 2.21 ms.
 //
 // LDS: one [T][H] BF16 tile that holds the first hidden layer and then the
 // second (written over the first once every wave has read it), and one
@@ -279,8 +299,8 @@ __device__ __forceinline__ void pq_quad(const float* o, float vlast, float t, in
 // of the transformed coordinates (2 KiB): 51.0 KiB, so that three
 // workgroups share a compute unit.
 template <bool INVERSE, bool CACHE>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k_coupling(LayerDev L, float* __restrict__ y, int64_t n, int64_t ld,
-                                                  float* __restrict__ logq, int first, float* __restrict__ lin, int d) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k_coupling(Layers layers, int nl, float* __restrict__ y, int64_t n, int64_t ld,
+                                                  float* __restrict__ logq, float* __restrict__ lin, int64_t lstride, int d) {
   __shared__ __attribute__((aligned(16))) bf16 h[T * H];
   __shared__ __attribute__((aligned(16))) float out[T * LDO];
   __shared__ float tb[TBMAX * T];
@@ -288,203 +308,211 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
   bf16* xa = reinterpret_cast<bf16*>(out);  // [T][KA]
   // the wave index is uniform across the wave: held in a scalar register, the
   // per-wave weight and index addresses are scalar arithmetic
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid0 = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid0 >> 6);
   const int64_t e0 = (int64_t)blockIdx.x * T;
-  const int row = lane & 15, quad = lane >> 4;
 
-  // inputs of the first dense layer (events fastest, so the reads coalesce):
-  // each kept coordinate as a BF16 pair hi + lo (about 16 significant bits),
-  // multiplied by the same weight column
-  {
-    // all of this thread's HBM reads are issued before the first is used
-    // (one latency instead of several): kept coordinates w, w + 4, w + 8,
-    // w + 12 and transformed coordinates w, w + 4 of event m (w = wave); the
-    // transformed ones wait in LDS for their PQ transforms
-    static_assert(KLO == 16 && TBMAX == 8, "four kept and two transformed coordinates per thread");
-    const int m = lane;
-    const int64_t e = e0 + m;
-    const bool ev = e < n;
-    float v[4], tv[2];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int i = wave + 4 * r;
-      v[r] = (i < L.dA && ev) ? y[(int64_t)L.a_idx[i] * ld + e] : 0.0f;
-    }
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const int j = wave + 4 * r;
-      tv[r] = (j < L.dB && ev) ? y[(int64_t)L.b_idx[j] * ld + e] : 0.5f;
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int i = wave + 4 * r;
-      const bf16 hi = (bf16)v[r];
-      const bf16 lo = (bf16)(v[r] - (float)hi);
-      const int il = i + KLO;
-      xa[m * KA + (((i >> 3) ^ (m & 3)) << 3) + (i & 7)] = hi;
-      xa[m * KA + (((il >> 3) ^ (m & 3)) << 3) + (il & 7)] = lo;
-    }
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const int j = wave + 4 * r;
-      if (j < L.dB) tb[j * T + m] = tv[r];
-    }
-  }
-  if (CACHE) {
-    for (int idx = tid; idx < T * d; idx += 256) {
-      const int m = idx % T, j = idx / T;
+  float logs = 0.0f;
+#pragma unroll 1
+  for (int k = 0; k < nl; ++k) {
+    const int l = INVERSE ? nl - 1 - k : k;
+    const LayerDev& L = layers.L[l];
+    const int tid = fresh(tid0), lane = tid & 63, row = lane & 15, quad = lane >> 4;
+
+    // inputs of the first dense layer (events fastest, so the reads coalesce):
+    // each kept coordinate as a BF16 pair hi + lo (about 16 significant bits),
+    // multiplied by the same weight column
+    {
+      // all of this thread's HBM reads are issued before the first is used
+      // (one latency instead of several): kept coordinates w, w + 4, w + 8,
+      // w + 12 and transformed coordinates w, w + 4 of event m (w = wave); the
+      // transformed ones wait in LDS for their PQ transforms
+      static_assert(KLO == 16 && TBMAX == 8, "four kept and two transformed coordinates per thread");
+      const int m = lane;
       const int64_t e = e0 + m;
-      if (e < n) lin[(int64_t)j * n + e] = y[(int64_t)j * ld + e];
-    }
-  }
-  __syncthreads();
-
-  // Dense layers 1 and 2 are computed transposed, D[feature][event] =
-  // W^T X^T: the weight rows are the A fragments (16-byte loads from the
-  // [out][in] copies), the activations in LDS the B fragments, and each lane
-  // ends with four consecutive features of one event, stored as one 8-byte
-  // LDS write after bias and activation.  Wave w owns features [64w, 64w+64).
-  {
-    f32x4 acc[4][4];
-    bf16x8 a[4], b[4];
+      const bool ev = e < n;
+      float v[4], tv[2];
 #pragma unroll
-    for (int jt = 0; jt < 4; ++jt)
-      a[jt] = *reinterpret_cast<const bf16x8*>(L.W1t + (64 * wave + 16 * jt + row) * KA + 8 * quad);
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-      const int m = 16 * mt + row;
-      b[mt] = *reinterpret_cast<const bf16x8*>(xa + m * KA + ((quad ^ (m & 3)) << 3));
-    }
-#pragma unroll
-    for (int jt = 0; jt < 4; ++jt) {
-      const f32x4 bias = bias4(L.b1, wave, jt, quad);
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt) acc[jt][mt] = mfma16(a[jt], b[mt], bias);
-    }
-    store_features(h, acc, wave, row, quad);
-  }
-  __syncthreads();
-  {
-    f32x4 acc[4][4];
-#pragma unroll
-    for (int jt = 0; jt < 4; ++jt) {
-      const f32x4 bias = bias4(L.b2, wave, jt, quad);
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt) acc[jt][mt] = bias;
-    }
-    // this wave's fragments in packed order: step ks, fragment jt at
-    // ((wave 8 + ks) 4 + jt) KB; a step's fragments are requested two steps
-    // ahead (a ring of three) and kept in their step by a scheduling barrier
-    const bf16* W2 = L.W2p + (int64_t)wave * 8 * 4 * 512 + lane * 8;
-    bf16x8 a[3][4];
-#pragma unroll
-    for (int st = 0; st < 2; ++st)
-#pragma unroll
-      for (int jt = 0; jt < 4; ++jt) a[st][jt] = *reinterpret_cast<const bf16x8*>(W2 + (st * 4 + jt) * 512);
-#pragma unroll
-    for (int ks = 0; ks < H / 32; ++ks) {
-      if (ks + 2 < H / 32) {
-#pragma unroll
-        for (int jt = 0; jt < 4; ++jt)
-          a[(ks + 2) % 3][jt] = *reinterpret_cast<const bf16x8*>(W2 + ((ks + 2) * 4 + jt) * 512);
+      for (int r = 0; r < 4; ++r) {
+        const int i = wave + 4 * r;
+        v[r] = (i < L.dA && ev) ? y[(int64_t)L.a_idx[i] * ld + e] : 0.0f;
       }
-      bf16x8 b[4];
 #pragma unroll
-      for (int mt = 0; mt < 4; ++mt)
-        b[mt] = *reinterpret_cast<const bf16x8*>(h + hs(16 * mt + row, 32 * ks + 8 * quad));
+      for (int r = 0; r < 2; ++r) {
+        const int j = wave + 4 * r;
+        tv[r] = (j < L.dB && ev) ? y[(int64_t)L.b_idx[j] * ld + e] : 0.5f;
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = wave + 4 * r;
+        const bf16 hi = (bf16)v[r];
+        const bf16 lo = (bf16)(v[r] - (float)hi);
+        const int il = i + KLO;
+        xa[m * KA + (((i >> 3) ^ (m & 3)) << 3) + (i & 7)] = hi;
+        xa[m * KA + (((il >> 3) ^ (m & 3)) << 3) + (il & 7)] = lo;
+      }
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        const int j = wave + 4 * r;
+        if (j < L.dB) tb[j * T + m] = tv[r];
+      }
+    }
+    if (CACHE) {
+      for (int idx = tid; idx < T * d; idx += 256) {
+        const int m = idx % T, j = idx / T;
+        const int64_t e = e0 + m;
+        if (e < n) lin[l * lstride + (int64_t)j * n + e] = y[(int64_t)j * ld + e];
+      }
+    }
+    __syncthreads();
+
+    // Dense layers 1 and 2 are computed transposed, D[feature][event] =
+    // W^T X^T: the weight rows are the A fragments (16-byte loads from the
+    // [out][in] copies), the activations in LDS the B fragments, and each lane
+    // ends with four consecutive features of one event, stored as one 8-byte
+    // LDS write after bias and activation.  Wave w owns features [64w, 64w+64).
+    {
+      f32x4 acc[4][4];
+      bf16x8 a[4], b[4];
 #pragma unroll
       for (int jt = 0; jt < 4; ++jt)
+        a[jt] = *reinterpret_cast<const bf16x8*>(L.W1t + (64 * wave + 16 * jt + row) * KA + 8 * quad);
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) acc[jt][mt] = mfma16(a[ks % 3][jt], b[mt], acc[jt][mt]);
-      __builtin_amdgcn_sched_barrier(0);
+      for (int mt = 0; mt < 4; ++mt) {
+        const int m = 16 * mt + row;
+        b[mt] = *reinterpret_cast<const bf16x8*>(xa + m * KA + ((quad ^ (m & 3)) << 3));
+      }
+#pragma unroll
+      for (int jt = 0; jt < 4; ++jt) {
+        const f32x4 bias = bias4(L.b1, wave, jt, quad);
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) acc[jt][mt] = mfma16(a[jt], b[mt], bias);
+      }
+      store_features(h, acc, wave, row, quad);
     }
-    // every wave has read the first layer before the second overwrites it
     __syncthreads();
-    store_features(h, acc, wave, row, quad);
-  }
-  __syncthreads();
-
-  // The 65th logit of every transformed coordinate at once: one more MFMA
-  // tile per wave, D[coordinate][event] for the wave's 16 events, with the
-  // weight rows of the coordinates' last outputs as A fragments (packed;
-  // rows past d_B are zero and never read).  Lane l keeps coordinates
-  // 4 (l >> 4) + i of event 16 wave + (l & 15) in registers until their PQ
-  // transforms.
-  f32x4 lastv = {0.0f, 0.0f, 0.0f, 0.0f};
-  {
-    const bf16* wl = L.W3L + lane * 8;
-#pragma unroll
-    for (int ks = 0; ks < H / 32; ++ks) {
-      const bf16x8 a = *reinterpret_cast<const bf16x8*>(wl + ks * 512);
-      const bf16x8 b = *reinterpret_cast<const bf16x8*>(h + hs(16 * wave + row, 32 * ks + 8 * quad));
-      lastv = mfma16(a, b, lastv);
-    }
-  }
-
-  // dense layer 3 and the PQ transform, one transformed coordinate at a time:
-  // the 64 leading logits of a coordinate are four 16-column MFMA tiles, one
-  // per wave over all 64 events (each wave streams only its own weight
-  // columns).
-  float lq = 0.0f;
-  // the eight weight fragments of this wave's columns of coordinate c; those
-  // of coordinate c + 1 are requested before the PQ transform of c, so their
-  // L2 latency overlaps it
-  bf16x8 bw[H / 32];
-  {
-    const bf16* W3 = L.W3p + (int64_t)wave * 8 * 512 + lane * 8;
-#pragma unroll
-    for (int ks = 0; ks < H / 32; ++ks) bw[ks] = *reinterpret_cast<const bf16x8*>(W3 + ks * 512);
-  }
-  // the PQ transform's event (16 per wave, four lanes each) and part
-  const int m = tid >> 2, part = tid & 3;
-  const int64_t em = e0 + m;
-  const bool live = em < n;
-  for (int c = 0; c < L.dB; ++c) {
     {
-      const int col = 16 * wave + row;
-      const float bias = L.b3p[c * NOP + col];
-      f32x4 acc[4];
+      f32x4 acc[4][4];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) acc[r] = f32x4{bias, bias, bias, bias};
+      for (int jt = 0; jt < 4; ++jt) {
+        const f32x4 bias = bias4(L.b2, wave, jt, quad);
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) acc[jt][mt] = bias;
+      }
+      // this wave's fragments in packed order: step ks, fragment jt at
+      // ((wave 8 + ks) 4 + jt) KB; a step's fragments are requested two steps
+      // ahead (a ring of three) and kept in their step by a scheduling barrier
+      const bf16* W2 = L.W2p + (int64_t)wave * 8 * 4 * 512 + lane * 8;
+      bf16x8 a[3][4];
+#pragma unroll
+      for (int st = 0; st < 2; ++st)
+#pragma unroll
+        for (int jt = 0; jt < 4; ++jt) a[st][jt] = *reinterpret_cast<const bf16x8*>(W2 + (st * 4 + jt) * 512);
 #pragma unroll
       for (int ks = 0; ks < H / 32; ++ks) {
+        if (ks + 2 < H / 32) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const bf16x8 a = *reinterpret_cast<const bf16x8*>(h + hs(16 * r + row, 32 * ks + 8 * quad));
-          acc[r] = mfma16(a, bw[ks], acc[r]);
+          for (int jt = 0; jt < 4; ++jt)
+            a[(ks + 2) % 3][jt] = *reinterpret_cast<const bf16x8*>(W2 + ((ks + 2) * 4 + jt) * 512);
+        }
+        bf16x8 b[4];
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt)
+          b[mt] = *reinterpret_cast<const bf16x8*>(h + hs(16 * mt + row, 32 * ks + 8 * quad));
+#pragma unroll
+        for (int jt = 0; jt < 4; ++jt)
+#pragma unroll
+          for (int mt = 0; mt < 4; ++mt) acc[jt][mt] = mfma16(a[ks % 3][jt], b[mt], acc[jt][mt]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // every wave has read the first layer before the second overwrites it
+      __syncthreads();
+      store_features(h, acc, wave, row, quad);
+    }
+    __syncthreads();
+
+    // The 65th logit of every transformed coordinate at once: one more MFMA
+    // tile per wave, D[coordinate][event] for the wave's 16 events, with the
+    // weight rows of the coordinates' last outputs as A fragments (packed;
+    // rows past d_B are zero and never read).  Lane l keeps coordinates
+    // 4 (l >> 4) + i of event 16 wave + (l & 15) in registers until their PQ
+    // transforms.
+    f32x4 lastv = {0.0f, 0.0f, 0.0f, 0.0f};
+    {
+      const bf16* wl = L.W3L + lane * 8;
+#pragma unroll
+      for (int ks = 0; ks < H / 32; ++ks) {
+        const bf16x8 a = *reinterpret_cast<const bf16x8*>(wl + ks * 512);
+        const bf16x8 b = *reinterpret_cast<const bf16x8*>(h + hs(16 * wave + row, 32 * ks + 8 * quad));
+        lastv = mfma16(a, b, lastv);
+      }
+    }
+
+    // dense layer 3 and the PQ transform, one transformed coordinate at a time:
+    // the 64 leading logits of a coordinate are four 16-column MFMA tiles, one
+    // per wave over all 64 events (each wave streams only its own weight
+    // columns).
+    float lq = 0.0f;
+    // the eight weight fragments of this wave's columns of coordinate c; those
+    // of coordinate c + 1 are requested before the PQ transform of c, so their
+    // L2 latency overlaps it
+    bf16x8 bw[H / 32];
+    {
+      const bf16* W3 = L.W3p + (int64_t)wave * 8 * 512 + lane * 8;
+#pragma unroll
+      for (int ks = 0; ks < H / 32; ++ks) bw[ks] = *reinterpret_cast<const bf16x8*>(W3 + ks * 512);
+    }
+    // the PQ transform's event (16 per wave, four lanes each) and part
+    const int m = tid >> 2, part = tid & 3;
+    const int64_t em = e0 + m;
+    const bool live = em < n;
+    for (int c = 0; c < L.dB; ++c) {
+      {
+        const int col = 16 * wave + row;
+        const float bias = L.b3p[c * NOP + col];
+        f32x4 acc[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[r] = f32x4{bias, bias, bias, bias};
+#pragma unroll
+        for (int ks = 0; ks < H / 32; ++ks) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const bf16x8 a = *reinterpret_cast<const bf16x8*>(h + hs(16 * r + row, 32 * ks + 8 * quad));
+            acc[r] = mfma16(a, bw[ks], acc[r]);
+          }
+        }
+        if (c + 1 < L.dB) {
+          const bf16* W3 = L.W3p + (((int64_t)(c + 1) * 4 + wave) * 8) * 512 + lane * 8;
+#pragma unroll
+          for (int ks = 0; ks < H / 32; ++ks) bw[ks] = *reinterpret_cast<const bf16x8*>(W3 + ks * 512);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) out[(16 * r + 4 * quad + i) * LDO + col] = acc[r][i];
+      }
+      // the 65th logit of (event m, coordinate c) from the lane of this wave
+      // that holds it
+      const int ci = c & 3;
+      const float lsel = ci == 0 ? lastv[0] : ci == 1 ? lastv[1] : ci == 2 ? lastv[2] : lastv[3];
+      const float vlast = __shfl(lsel, (lane >> 2) + 16 * (c >> 2)) + L.b3p[c * NOP + 2 * KB];
+      __syncthreads();
+      {
+        float* yp = y + (int64_t)L.b_idx[c] * ld + (live ? em : e0);
+        const float t = tb[c * T + m];
+        float res, pdf;
+        pq_quad<INVERSE>(out + m * LDO, vlast, t, part, res, pdf);
+        if (live && part == 0) {
+          *yp = res;
+          lq += __logf(pdf);
         }
       }
-      if (c + 1 < L.dB) {
-        const bf16* W3 = L.W3p + (((int64_t)(c + 1) * 4 + wave) * 8) * 512 + lane * 8;
-#pragma unroll
-        for (int ks = 0; ks < H / 32; ++ks) bw[ks] = *reinterpret_cast<const bf16x8*>(W3 + ks * 512);
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) out[(16 * r + 4 * quad + i) * LDO + col] = acc[r][i];
+      __syncthreads();
     }
-    // the 65th logit of (event m, coordinate c) from the lane of this wave
-    // that holds it
-    const int ci = c & 3;
-    const float lsel = ci == 0 ? lastv[0] : ci == 1 ? lastv[1] : ci == 2 ? lastv[2] : lastv[3];
-    const float vlast = __shfl(lsel, (lane >> 2) + 16 * (c >> 2)) + L.b3p[c * NOP + 2 * KB];
-    __syncthreads();
-    {
-      float* yp = y + (int64_t)L.b_idx[c] * ld + (live ? em : e0);
-      const float t = tb[c * T + m];
-      float res, pdf;
-      pq_quad<INVERSE>(out + m * LDO, vlast, t, part, res, pdf);
-      if (live && part == 0) {
-        *yp = res;
-        lq += __logf(pdf);
-      }
-    }
-    __syncthreads();
+    logs = k == 0 ? lq : logs + lq;
   }
-  if ((tid & 3) == 0) {
-    const int64_t e = e0 + (tid >> 2);
-    if (e < n) logq[e] = first ? lq : logq[e] + lq;
+  if ((tid0 & 3) == 0) {
+    const int64_t e = e0 + (tid0 >> 2);
+    if (e < n) logq[e] = logs;
   }
 }
 
@@ -540,13 +568,6 @@ __device__ __forceinline__ void store_gradients(bf16* h, const f32x4 (&acc)[4][4
       *reinterpret_cast<bf16x4*>(h + hs(16 * mt + row, f0)) = v;
     }
   }
-}
-// A copy of x whose value the compiler does not follow: LDS offsets derived
-// from it are computed where they are used instead of being kept in registers
-// from one phase of the kernel to the next (123 spilled registers otherwise).
-__device__ __forceinline__ int fresh(int x) {
-  asm volatile("" : "+v"(x));
-  return x;
 }
 // The [T][H] tile to rows e0.. of an event-major matrix: 512 consecutive
 // bytes per event.
@@ -1377,7 +1398,7 @@ struct mf_flow {
   int d, nl;
   int64_t count = 0;
   std::vector<std::vector<uint8_t>> mask;
-  LayerDev L[MAXL];
+  Layers L;
   SegTable seg;
   int64_t loff[MAXL];
   float* d_p = nullptr;   // masters
@@ -1453,7 +1474,7 @@ WgradArgs wgrad_args(const Operands& o, int dB, int64_t n) {
 
 // Weight and bias gradients of layer l over n events from the operands o.
 bool weight_grads(mf_flow* f, int l, const Operands& o, int64_t n, hipStream_t s) {
-  const LayerDev& L = f->L[l];
+  const LayerDev& L = f->L.L[l];
   WgradArgs a = wgrad_args(o, L.dB, n);
   const int64_t Z = (n + a.chunk - 1) / a.chunk;
   // the partials of all chunks must fit the buffer sized at creation
@@ -1468,19 +1489,16 @@ bool weight_grads(mf_flow* f, int l, const Operands& o, int64_t n, hipStream_t s
 
 void run_layers(mf_flow* f, float* y, int64_t n, int64_t ld, float* logq, bool inverse, bool cache, hipStream_t s) {
   const unsigned nblk = (unsigned)((n + T - 1) / T);
-  for (int k = 0; k < f->nl; ++k) {
-    const int l = inverse ? f->nl - 1 - k : k;
-    float* lin = cache ? f->d_lin + (int64_t)l * f->d * f->cap : nullptr;
-    if (inverse)
-      hipLaunchKernelGGL((k_coupling<true, false>), dim3(nblk), dim3(256), 0, s, f->L[l], y, n, ld, logq,
-                         k == 0 ? 1 : 0, lin, f->d);
-    else if (cache)
-      hipLaunchKernelGGL((k_coupling<false, true>), dim3(nblk), dim3(256), 0, s, f->L[l], y, n, ld, logq,
-                         k == 0 ? 1 : 0, lin, f->d);
-    else
-      hipLaunchKernelGGL((k_coupling<false, false>), dim3(nblk), dim3(256), 0, s, f->L[l], y, n, ld, logq,
-                         k == 0 ? 1 : 0, lin, f->d);
-  }
+  const int64_t ls = (int64_t)f->d * f->cap;
+  if (inverse)
+    hipLaunchKernelGGL((k_coupling<true, false>), dim3(nblk), dim3(256), 0, s, f->L, f->nl, y, n, ld, logq, f->d_lin, ls,
+                       f->d);
+  else if (cache)
+    hipLaunchKernelGGL((k_coupling<false, true>), dim3(nblk), dim3(256), 0, s, f->L, f->nl, y, n, ld, logq, f->d_lin, ls,
+                       f->d);
+  else
+    hipLaunchKernelGGL((k_coupling<false, false>), dim3(nblk), dim3(256), 0, s, f->L, f->nl, y, n, ld, logq, f->d_lin, ls,
+                       f->d);
 }
 
 mf_status refresh(mf_flow* f, hipStream_t s, int do_adam, float lr, float c1, float c2) {
@@ -1527,7 +1545,7 @@ mf_status loss_grad_impl(mf_flow* f, const float* y, int64_t ldy, const float* w
   for (int l = f->nl - 1; l >= 0; --l) {
     const int set = l & 1;
     if (l + 2 <= f->nl - 1) wait(2 + set, s);
-    hipLaunchKernelGGL(k_layer_backward, dim3((unsigned)((n + T - 1) / T)), dim3(256), 0, s, f->L[l],
+    hipLaunchKernelGGL(k_layer_backward, dim3((unsigned)((n + T - 1) / T)), dim3(256), 0, s, f->L.L[l],
                        f->d_lin + (int64_t)l * d * f->cap, n, f->d_gy, w, f->d_scal, f->op[set]);
     rec(set, s);
     wait(set, s2);
@@ -1584,7 +1602,7 @@ mf_status mf_flow_create(const mf_flow_config* cfg, mf_flow** out) {
   f->seg.nl = f->nl;
   for (int l = 0; l < f->nl; ++l) {
     std::vector<uint8_t> m(d);
-    LayerDev& L = f->L[l];
+    LayerDev& L = f->L.L[l];
     L.dA = L.dB = 0;
     for (int j = 0; j < d; ++j) {
       const int bit = (j >> (l % nb)) & 1;
@@ -1668,7 +1686,7 @@ mf_status mf_flow_create(const mf_flow_config* cfg, mf_flow** out) {
     o.go = o.xa + cap * KA;
   }
   for (int l = 0; l < f->nl; ++l) {
-    LayerDev& L = f->L[l];
+    LayerDev& L = f->L.L[l];
     L.W1t = wp;
     f->seg.l[l].W1t = wp;
     wp += (int64_t)H * KA;

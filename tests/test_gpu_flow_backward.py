@@ -1,4 +1,4 @@
-"""Loss gradient of the flow at the edges of its kernels: tiles of 64 events,
+"""Flow and its loss gradient at the edges of their kernels: tiles of 64 events,
 event chunks of the weight gradients, one to eight transformed coordinates."""
 import numpy as np
 import pytest
@@ -69,3 +69,31 @@ def test_gradient_of_odd_and_full_coordinate_counts_matches_oracle(d, n):
     for name in ("W1", "b1", "W2", "b2", "W3", "b3"):
         cos, rl2 = cosine_rel_l2(g[0][name], g_ref[0][name])
         assert cos >= 0.9999 and rl2 <= 5e-3, (name, cos, rl2)
+
+
+@pytest.mark.parametrize("layers,d,n", [(1, 16, 65), (2, 2, 1), (3, 4, 64), (8, 16, 129)])
+def test_all_layers_in_one_launch_are_the_layers_in_turn(layers, d, n):
+    """With a power of two of coordinates every layer keeps and transforms half
+    of them, so that it is the layer of a one-layer flow on coordinates
+    renamed in order: both directions bit for bit, the log density being the
+    FP32 sum over the layers in the order they are applied."""
+    f, one = mf.Flow(d, n_layers=layers, max_batch=64), mf.Flow(d, n_layers=1, max_batch=64)
+    mk = oflow.masks(d, layers)
+    shapes = [(d // 2, 256, d // 2 * (2 * K + 1))] * layers
+    params = si.flow_params(shapes, seed=90 + d, scale_out=0.5)
+    f.set_params(mf.Flow.flatten(params))
+    y = _dev32(np.clip(si.unit_points(n, d, seed=91), 1e-6, 1 - 1e-6))
+    for direction in ("forward", "inverse"):
+        z, lq = getattr(f, direction)(y)
+        x, s = y.clone(), None
+        for l in range(layers) if direction == "forward" else reversed(range(layers)):
+            one.set_params(mf.Flow.flatten([params[l]]))
+            here = np.r_[np.flatnonzero(~mk[l]), np.flatnonzero(mk[l])]
+            there = np.r_[np.flatnonzero(~mk[0]), np.flatnonzero(mk[0])]
+            u = torch.empty_like(x)
+            u[there] = x[here]
+            v, q = getattr(one, direction)(u)
+            x = torch.empty_like(x)
+            x[here] = v[there]
+            s = q if s is None else s + q
+        assert torch.equal(z, x) and torch.equal(lq, s)
