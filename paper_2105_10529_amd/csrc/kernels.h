@@ -462,15 +462,7 @@ __global__ void __launch_bounds__(BLOCK) k_vegas(DevCfg c, const double* __restr
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    {
-      // every lane runs the binning loop (no divergent region in the event
-      // loop); lanes >= d update a scratch row of their wave
-      const bool mine = lane < d;
-      const unsigned char* bj = bins_s + (mine ? lane : 0) * BLOCK + wave * 64;
-      const double* ws = w2s + wave * 64;
-      double* hj = mine ? my_hist + lane * nb : dummy + wave * nb;
-      for (int k = 0; k < 64; ++k) hj[bj[k]] += ws[k];
-    }
+    bin_wave(bins_s + wave * 64, BLOCK, w2s + wave * 64, my_hist, dummy + wave * nb, d, nb);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");

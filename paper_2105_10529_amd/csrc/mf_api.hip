@@ -300,6 +300,8 @@ __global__ void __launch_bounds__(256) k_stage_accumulate(const double* __restri
                                                           int64_t N, double* __restrict__ partials, int pstride) {
   __shared__ double hist[WAVES][MAXD * MAX_BINS];
   __shared__ double wacc[WAVES][4];
+  __shared__ double w2s[WAVES][64], spare[WAVES][MAX_BINS];
+  __shared__ __attribute__((aligned(8))) unsigned char bins_s[WAVES][MAXD][64];
   __shared__ unsigned long long cnt[2 * WAVES];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   for (int i = lane; i < d * nb; i += 64) hist[wave][i] = 0.0;
@@ -322,13 +324,19 @@ __global__ void __launch_bounds__(256) k_stage_accumulate(const double* __restri
     lds_dd_accumulate(wacc[wave], h, l);
     wave_sum_dd(w * w, h, l);
     lds_dd_accumulate(wacc[wave] + 2, h, l);
-    // bin in event order: lane j < d walks the wave's 64 events of dimension j
-    const double w2 = w * w;
-    for (int k = 0; k < 64; ++k) {
-      const double wk = __shfl(w2, k);
-      const int64_t ek = __shfl(e, k);
-      if (lane < d) hist[wave][lane * nb + bins[(int64_t)lane * N + ek]] += wk;
-    }
+    // the wave's bins, one coalesced read per dimension, and its squares to
+    // LDS, then the histograms in event order
+    w2s[wave][lane] = w * w;
+#pragma unroll
+    for (int j = 0; j < MAXD; ++j)
+      if (j < d) bins_s[wave][j][lane] = bins[(int64_t)j * N + e];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    bin_wave(&bins_s[wave][0][0], 64, w2s[wave], hist[wave], spare[wave], d, nb);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
   __syncthreads();
   double* p = partials + (int64_t)blockIdx.x * pstride;

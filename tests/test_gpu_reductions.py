@@ -45,3 +45,23 @@ def test_weight_statistics_at_block_edges(n):
         assert r["quantile"] == np.sort(w)[rank - 1]
         assert r["max"] == w.max() and r["nonzero"] == np.count_nonzero(w)
         assert abs(r["mean"] - w.mean()) <= n * 2.0 ** -52 * np.abs(w).mean()
+
+
+@pytest.mark.parametrize("ng,n,nb", [(0, 1025, 64), (0, 63, 1), (1, 4097, 31), (1, 300, 32), (2, 2049, 64), (2, 129, 2)])
+def test_iteration_histograms_at_bin_counts(ng, n, nb):
+    """Histograms of few and of the most bins, ragged waves, one kernel per
+    iteration (ng = 0, 1) and staged (ng = 2): the estimate to FP64 rounding and
+    the refined edges, which follow from the histograms, to 1e-10, the bounds
+    that full iterations are held to."""
+    from test_gpu_parity import _oracle
+
+    d = si.ndim(ng)
+    p = mf.Process(mf.Config(process="gg>ttx" + "g" * ng, n_bins=nb, dr_min=0.4 if ng >= 2 else 0.0))
+    edges = si.random_grid(d, nb, seed=nb)
+    out = torch.empty((d, nb + 1), dtype=torch.float64, device="cuda")
+    r = p.integrate(1, n, adapt=True, iter_offset=2, edges_in=torch.from_numpy(edges).to("cuda"), edges_out=out)
+    S1, S2, hist, nnz, nbad = _oracle(ng).vegas_iteration(edges, 2, n, p.cfg.seed, purpose=0)
+    I, s = oracle.iteration_estimate(S1, S2, n)
+    assert r.n_nonzero == nnz > 0 and r.n_nonfinite == nbad == 0
+    assert abs(r.iter_integral[0] / I - 1) < 1e-12 and abs(r.iter_error[0] / s - 1) < 1e-9
+    assert np.max(np.abs(out.cpu().numpy() - oracle.vegas_refine(edges, hist, 1.5))) < 1e-10
