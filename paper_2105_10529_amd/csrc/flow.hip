@@ -9,13 +9,12 @@
 //                   LDS, then the FP32 piecewise-quadratic CDF (or its inverse)
 //                   of each transformed coordinate; optionally keeps the layer
 //                   input for the backward pass
-//   k_layer_backward  one layer of the backward pass for a tile of 64 events:
-//                   the forward products again, the derivatives of the PQ
-//                   transforms, and the activation-gradient products; writes
-//                   the operands of the weight gradients
-//   k_wgrad         the three weight-gradient products of a layer, split over
-//                   events
-//   k_reduce_layer  ordered reduction of their partials into the FP32 gradient
+//   k_backward      the backward pass through all layers for a tile of 64
+//                   events; of each the forward products again, the derivatives
+//                   of the PQ transforms, and the activation-gradient products;
+//                   writes the operands of the weight gradients
+//   k_wgrad         the weight-gradient products of all layers, split over events
+//   k_reduce_grad   ordered reduction of their partials into the FP32 gradient
 //   k_adam          Adam on the FP32 masters and refresh of the BF16 copies
 #include <hip/hip_runtime.h>
 
@@ -273,7 +272,7 @@ __device__ __forceinline__ void pq_quad(const float* o, float vlast, float t, in
 // A copy of x whose value the compiler does not follow: LDS offsets derived
 // from it are computed where they are used instead of being kept in registers
 // from one phase of a kernel to the next (9 spilled registers otherwise in
-// k_coupling, 123 in k_layer_backward).
+// k_coupling, 123 in k_backward).
 __device__ __forceinline__ int fresh(int x) {
   asm volatile("" : "+v"(x));
   return x;
@@ -517,7 +516,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
 }
 
 // -------------------------------------------------------- backward layer
-// Operands of the weight gradients of one layer, event-major.
+// Operands of the weight gradients, event-major; layer l's are l stride
+// elements further.
 struct Operands {
   bf16* xa;   // [n][KA]  inputs of the first dense layer (hi | lo)
   bf16* h1;   // [n][H]   hidden activations
@@ -525,6 +525,7 @@ struct Operands {
   bf16* go;   // [n][dB*NOG] gradients of the logits (zero-padded per coordinate)
   bf16* ga2;  // [n][H]   gradients before the second activation
   bf16* ga1;  // [n][H]   and before the first
+  int64_t stride;
 };
 
 // Sign bits of a lane's 64 features of a hidden layer, in the order of
@@ -570,12 +571,14 @@ __device__ __forceinline__ void store_gradients(bf16* h, const f32x4 (&acc)[4][4
   }
 }
 // The [T][H] tile to rows e0.. of an event-major matrix: 512 consecutive
-// bytes per event.
+// bytes per event, past the caches.
 __device__ __forceinline__ void copy_tile(const bf16* h, bf16* __restrict__ dst, int64_t e0, int64_t n, int tid) {
 #pragma unroll
   for (int r = 0; r < T * H / 8 / 256; ++r) {
     const int idx = tid + 256 * r, m = idx >> 5, k = 8 * (idx & 31);
-    if (e0 + m < n) *reinterpret_cast<bf16x8*>(dst + (e0 + m) * H + k) = *reinterpret_cast<const bf16x8*>(h + hs(m, k));
+    if (e0 + m < n)
+      __builtin_nontemporal_store(*reinterpret_cast<const bf16x8*>(h + hs(m, k)),
+                                  reinterpret_cast<bf16x8*>(dst + (e0 + m) * H + k));
   }
 }
 // Logit-gradient tile of one coordinate: [T][64] bf16, the eight 16-byte
@@ -742,317 +745,342 @@ __device__ __forceinline__ void pq_quad_backward(const float* o, float vlast, fl
   glast = V[KP] * __builtin_fmaf(-W[KP - 1], SG * 0.5f, glast);
 }
 
-// One layer of the backward pass for events [64 blockIdx.x, +64), in one
-// kernel: the hidden layers and the logits are computed again from the layer
-// input lin ([d][n]; the same products as in k_coupling, cheaper than keeping
-// 2.4 KB per event and layer), each coordinate's logits give the gradients of
-// its PQ transform, which are multiplied into the gradient of the second
-// hidden layer at once, and so on to the kept inputs.  g ([d][n]) holds the
-// gradient with respect to the layer's output and receives the one with
-// respect to its input; glp = dL/dlog q = -w_e / sum w.  Written to memory:
-// only the operands of the weight gradients, in rows of 64 to 576 bytes per
-// event.  The products run transposed, D[feature][event], so that a lane's
-// gradients are the features whose activations it computed and their signs
-// stay in two registers per layer.
+// The backward pass through all nl layers for events [64 blockIdx.x, +64); as
+// in the forward pass a tile needs no other.  Of each layer, the last first,
+// the hidden layers and the logits are computed again from the layer's input
+// lin + l lstride ([d][n]; the same products as in k_coupling, cheaper than
+// keeping 2.4 KB per event and layer), each coordinate's logits give the
+// gradients of its PQ transform, which are multiplied into the gradient of the
+// second hidden layer at once, and so on to the kept inputs.  g ([d][n]) holds
+// the gradient with respect to the current layer's output, zero at the start,
+// and receives the one with respect to its input; glp = dL/dlog q =
+// -w_e / sum w.  Written besides: the operands of the weight gradients, in rows
+// of 64 to 1152 bytes per event.  The products run transposed,
+// D[feature][event], so that a lane's gradients are the features whose
+// activations it computed and their signs stay in two registers per layer.
 //
 // LDS: the [T][H] tile holds the first hidden layer, the second, the gradient
 // before the second activation and that before the first; the logits of the
 // current coordinate (before that, the first layer's inputs); its logit
-// gradients; the last logits' gradients of all coordinates; the transformed
-// inputs: 60 KiB, two workgroups per compute unit.
+// gradients; the transformed inputs: 61 KiB, two workgroups per compute unit.
 //
 // Sums over bins, and over k in the products, keep one fixed order: a BF16
 // rounding that falls the other way changes an event's gradient by 2^-9.
 //
+// The operands are stored past the caches: they are read by the next launch
+// only, 1.1 GB for 65536 points of 10 dimensions, and would push the weights
+// of six layers (4.5 MB) out of the L2 (735 us, with these stores 590).
+//
 // Bound by vector instructions (51 % of the time; the matrix instructions take
-// 20 %) at two waves per SIMD.  65536 points of 10 dimensions, per layer: 96
-// us.  As separate kernels over cached activations and logits the same work
-// took 285 us: PQ derivatives 67, two products with BF16 epilogues 76 each,
-// the input product 17, its addition 6, and 43 for writing the caches in the
-// forward pass.
+// 20 %) at two waves per SIMD.  As separate kernels over cached activations and
+// logits the same work took 285 us per layer: PQ derivatives 67, two products
+// with BF16 epilogues 76 each, the input product 17, its addition 6, and 43 for
+// writing the caches in the forward pass.
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
-k_layer_backward(LayerDev L, const float* __restrict__ lin, int64_t n, float* __restrict__ g,
-                 const float* __restrict__ w, const float* __restrict__ wsum, Operands out_op) {
+k_backward(Layers layers, int nl, const float* __restrict__ lin_all, int64_t lstride, int64_t n, float* __restrict__ g,
+           const float* __restrict__ w, const float* __restrict__ wsum, Operands op, int d) {
   __shared__ __attribute__((aligned(16))) bf16 h[T * H];
   __shared__ __attribute__((aligned(16))) float out[T * LDO];
   __shared__ __attribute__((aligned(16))) bf16 gt[GT_CHUNKS * 8];
   __shared__ float tb[TBMAX * T];
   bf16* xa = reinterpret_cast<bf16*>(out);  // [T][KA]
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid0 = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid0 >> 6);
   const int64_t e0 = (int64_t)blockIdx.x * T;
-  const int row = lane & 15, quad = lane >> 4;
-  // inputs as in k_coupling
-  {
-    const int m = lane;
-    const int64_t e = e0 + m;
-    const bool ev = e < n;
-    float v[4], tv[2];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int i = wave + 4 * r;
-      v[r] = (i < L.dA && ev) ? lin[(int64_t)L.a_idx[i] * n + e] : 0.0f;
-    }
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const int j = wave + 4 * r;
-      tv[r] = (j < L.dB && ev) ? lin[(int64_t)L.b_idx[j] * n + e] : 0.5f;
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int i = wave + 4 * r;
-      const bf16 hi = (bf16)v[r];
-      const bf16 lo = (bf16)(v[r] - (float)hi);
-      const int il = i + KLO;
-      xa[m * KA + (((i >> 3) ^ (m & 3)) << 3) + (i & 7)] = hi;
-      xa[m * KA + (((il >> 3) ^ (m & 3)) << 3) + (il & 7)] = lo;
-    }
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const int j = wave + 4 * r;
-      if (j < L.dB) tb[j * T + m] = tv[r];
-    }
-    for (int i = T * 64 + tid; i < GT_CHUNKS * 8; i += 256) gt[i] = (bf16)0.0f;
-  }
-  __syncthreads();
-  {
-    const int m = tid >> 2, k = tid & 3;  // one 16-byte chunk of the inputs per thread
-    if (e0 + m < n)
-      *reinterpret_cast<bf16x8*>(out_op.xa + (e0 + m) * KA + 8 * k) =
-          *reinterpret_cast<const bf16x8*>(xa + m * KA + ((k ^ (m & 3)) << 3));
-  }
-  Signs s1, s2;
-  {
-    f32x4 acc[4][4];
-    bf16x8 a[4], b[4];
-#pragma unroll
-    for (int jt = 0; jt < 4; ++jt)
-      a[jt] = *reinterpret_cast<const bf16x8*>(L.W1t + (64 * wave + 16 * jt + row) * KA + 8 * quad);
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-      const int m = 16 * mt + row;
-      b[mt] = *reinterpret_cast<const bf16x8*>(xa + m * KA + ((quad ^ (m & 3)) << 3));
-    }
-#pragma unroll
-    for (int jt = 0; jt < 4; ++jt) {
-      const f32x4 bias = bias4(L.b1, wave, jt, quad);
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt) acc[jt][mt] = mfma16(a[jt], b[mt], bias);
-    }
-    s1 = store_features_signs(h, acc, wave, fresh(row), quad);
-  }
-  __syncthreads();
-  copy_tile(h, out_op.h1, e0, n, fresh(tid));
-  // [H x H] product with the tile: fragments of packed rows W, as in k_coupling
-  auto dense = [&](const bf16* Wp, f32x4 (&acc)[4][4]) {
-    const bf16* W2 = Wp + (int64_t)wave * 8 * 4 * 512 + lane * 8;
-    const int rb = fresh(row);
-    bf16x8 a[3][4];
-#pragma unroll
-    for (int st = 0; st < 2; ++st)
-#pragma unroll
-      for (int jt = 0; jt < 4; ++jt) a[st][jt] = *reinterpret_cast<const bf16x8*>(W2 + (st * 4 + jt) * 512);
-#pragma unroll
-    for (int ks = 0; ks < H / 32; ++ks) {
-      if (ks + 2 < H / 32) {
-#pragma unroll
-        for (int jt = 0; jt < 4; ++jt)
-          a[(ks + 2) % 3][jt] = *reinterpret_cast<const bf16x8*>(W2 + ((ks + 2) * 4 + jt) * 512);
-      }
-      bf16x8 b[4];
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt)
-        b[mt] = *reinterpret_cast<const bf16x8*>(h + hs(16 * mt + rb, 32 * ks + 8 * quad));
-#pragma unroll
-      for (int jt = 0; jt < 4; ++jt)
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt) acc[jt][mt] = mfma16(a[ks % 3][jt], b[mt], acc[jt][mt]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-  {
-    f32x4 acc[4][4];
-#pragma unroll
-    for (int jt = 0; jt < 4; ++jt) {
-      const f32x4 bias = bias4(L.b2, wave, jt, quad);
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt) acc[jt][mt] = bias;
-    }
-    dense(L.W2p, acc);
-    __syncthreads();  // every wave has read the first layer
-    s2 = store_features_signs(h, acc, wave, fresh(row), quad);
-  }
-  __syncthreads();
-  copy_tile(h, out_op.h2, e0, n, fresh(tid));
-  f32x4 lastv = {0.0f, 0.0f, 0.0f, 0.0f};
-  {
-    const bf16* wl = L.W3L + lane * 8;
-#pragma unroll
-    for (int ks = 0; ks < H / 32; ++ks) {
-      const bf16x8 a = *reinterpret_cast<const bf16x8*>(wl + ks * 512);
-      const bf16x8 b = *reinterpret_cast<const bf16x8*>(h + hs(16 * wave + row, 32 * ks + 8 * quad));
-      lastv = mfma16(a, b, lastv);
-    }
-  }
-  // gradient after the second activation, accumulated over the coordinates
-  f32x4 acc[4][4];
-#pragma unroll
-  for (int jt = 0; jt < 4; ++jt)
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) acc[jt][mt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  const int m = tid >> 2, part = tid & 3;
-  const int64_t em = e0 + m;
-  const bool live = em < n;
-  const float glp = live ? -w[em] / wsum[0] : 0.0f;
-  const int NB = L.dB * NOG;
-  for (int c = 0; c < L.dB; ++c) {
+  for (int idx = tid0; idx < T * d; idx += 256)
+    if (e0 + idx % T < n) g[(int64_t)(idx / T) * n + e0 + idx % T] = 0.0f;
+#pragma unroll 1
+  for (int l = nl - 1; l >= 0; --l) {
+    const LayerDev& L = layers.L[l];
+    const float* lin = lin_all + l * lstride;
+    Operands out_op = op;
+    out_op.xa += l * op.stride;
+    out_op.h1 += l * op.stride;
+    out_op.h2 += l * op.stride;
+    out_op.go += l * op.stride;
+    out_op.ga2 += l * op.stride;
+    out_op.ga1 += l * op.stride;
+    const int tid = fresh(tid0), lane = tid & 63, row = lane & 15, quad = lane >> 4;
+    // inputs as in k_coupling
     {
-      const bf16* W3 = L.W3p + (((int64_t)c * 4 + wave) * 8) * 512 + lane * 8;
-      const int col = 16 * wave + row;
-      const float bias = L.b3p[c * NOP + col];
-      f32x4 lg[4];
+      const int m = lane;
+      const int64_t e = e0 + m;
+      const bool ev = e < n;
+      float v[4], tv[2];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) lg[r] = f32x4{bias, bias, bias, bias};
-#pragma unroll
-      for (int ks = 0; ks < H / 32; ++ks) {
-        const bf16x8 bw = *reinterpret_cast<const bf16x8*>(W3 + ks * 512);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const bf16x8 a = *reinterpret_cast<const bf16x8*>(h + hs(16 * r + row, 32 * ks + 8 * quad));
-          lg[r] = mfma16(a, bw, lg[r]);
-        }
+      for (int r = 0; r < 4; ++r) {
+        const int i = wave + 4 * r;
+        v[r] = (i < L.dA && ev) ? lin[(int64_t)L.a_idx[i] * n + e] : 0.0f;
       }
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) out[(16 * r + 4 * quad + i) * LDO + col] = lg[r][i];
-    }
-    const int ci = c & 3;
-    const float lsel = ci == 0 ? lastv[0] : ci == 1 ? lastv[1] : ci == 2 ? lastv[2] : lastv[3];
-    const float vlast = __shfl(lsel, (lane >> 2) + 16 * (c >> 2)) + L.b3p[c * NOP + 2 * KB];
-    float* gp = g + (int64_t)L.b_idx[c] * n + (live ? em : e0);
-    const float gz = live ? *gp : 0.0f;
-    // this coordinate's fragments for the gradient, requested before the PQ
-    // derivatives
-    const int odd = c & 1;
-    const bf16* wqc = L.W3q + ((int64_t)((c >> 1) * 5 + 2 * odd) * 16 + wave * 4) * 512 + lane * 8;
-    bf16x8 wq[2][4];
-#pragma unroll
-    for (int st = 0; st < 2; ++st)
-#pragma unroll
-      for (int jt = 0; jt < 4; ++jt) wq[st][jt] = *reinterpret_cast<const bf16x8*>(wqc + (st * 16 + jt) * 512);
-    __syncthreads();  // logits complete; the previous coordinate's gradients have been read
-    {
-      float gw[KB / 4], gv[KB / 4], gl, gy;
-      pq_quad_backward(out + m * LDO, vlast, tb[c * T + m], part, gz, glp, gw, gv, gl, gy);
-      if (live && part == 0) *gp = gy;
-      bf16x8 a, b;
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        a[k] = (bf16)gw[k];
-        b[k] = (bf16)gv[k];
+      for (int r = 0; r < 2; ++r) {
+        const int j = wave + 4 * r;
+        tv[r] = (j < L.dB && ev) ? lin[(int64_t)L.b_idx[j] * n + e] : 0.5f;
       }
-      bf16x8 l8;
 #pragma unroll
-      for (int k = 0; k < 8; ++k) l8[k] = k == 0 ? (bf16)gl : (bf16)0.0f;
-      *reinterpret_cast<bf16x8*>(gt + gs(m, part)) = a;
-      *reinterpret_cast<bf16x8*>(gt + gs(m, 4 + part)) = b;
-      if (part == 3) gt[gs_last(m, odd)] = (bf16)gl;
-      if (live) {
-        bf16* dst = out_op.go + em * NB + c * NOG;
-        *reinterpret_cast<bf16x8*>(dst + 8 * part) = a;
-        *reinterpret_cast<bf16x8*>(dst + KB + 8 * part) = b;
-        if (part == 3) *reinterpret_cast<bf16x8*>(dst + 2 * KB) = l8;
+      for (int r = 0; r < 4; ++r) {
+        const int i = wave + 4 * r;
+        const bf16 hi = (bf16)v[r];
+        const bf16 lo = (bf16)(v[r] - (float)hi);
+        const int il = i + KLO;
+        xa[m * KA + (((i >> 3) ^ (m & 3)) << 3) + (i & 7)] = hi;
+        xa[m * KA + (((il >> 3) ^ (m & 3)) << 3) + (il & 7)] = lo;
       }
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        const int j = wave + 4 * r;
+        if (j < L.dB) tb[j * T + m] = tv[r];
+      }
+      for (int i = T * 64 + tid; i < GT_CHUNKS * 8; i += 256) gt[i] = (bf16)0.0f;
     }
     __syncthreads();
-    // k steps of 32 over NOP columns per coordinate: two for an even
-    // coordinate; three for an odd one, the first beginning with the last
-    // logit of the one before, the third ending with its own.  An even last
-    // coordinate ends with a step of its last logit.
-    auto step = [&](const bf16x8 (&aw)[4], int chunk) {
-      bf16x8 b[4];
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt) {
-        const int mm = 16 * mt + row;
-        int at = gs(mm, chunk & 7);
-        at = chunk < 0 || chunk > 8 ? GS_ZERO : at;
-        at = chunk == -2 || chunk == 8 ? gs_last(mm, chunk == 8 ? odd : 0) : at;
-        b[mt] = *reinterpret_cast<const bf16x8*>(gt + at);
-      }
+    {
+      const int m = tid >> 2, k = tid & 3;  // one 16-byte chunk of the inputs per thread
+      if (e0 + m < n)
+        *reinterpret_cast<bf16x8*>(out_op.xa + (e0 + m) * KA + 8 * k) =
+            *reinterpret_cast<const bf16x8*>(xa + m * KA + ((k ^ (m & 3)) << 3));
+    }
+    Signs s1, s2;
+    {
+      f32x4 acc[4][4];
+      bf16x8 a[4], b[4];
 #pragma unroll
       for (int jt = 0; jt < 4; ++jt)
+        a[jt] = *reinterpret_cast<const bf16x8*>(L.W1t + (64 * wave + 16 * jt + row) * KA + 8 * quad);
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) acc[jt][mt] = mfma16(aw[jt], b[mt], acc[jt][mt]);
+      for (int mt = 0; mt < 4; ++mt) {
+        const int m = 16 * mt + row;
+        b[mt] = *reinterpret_cast<const bf16x8*>(xa + m * KA + ((quad ^ (m & 3)) << 3));
+      }
+#pragma unroll
+      for (int jt = 0; jt < 4; ++jt) {
+        const f32x4 bias = bias4(L.b1, wave, jt, quad);
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) acc[jt][mt] = mfma16(a[jt], b[mt], bias);
+      }
+      s1 = store_features_signs(h, acc, wave, fresh(row), quad);
+    }
+    __syncthreads();
+    copy_tile(h, out_op.h1, e0, n, fresh(tid));
+    // [H x H] product with the tile: fragments of packed rows W, as in k_coupling
+    auto dense = [&](const bf16* Wp, f32x4 (&acc)[4][4]) {
+      const bf16* W2 = Wp + (int64_t)wave * 8 * 4 * 512 + lane * 8;
+      const int rb = fresh(row);
+      bf16x8 a[3][4];
+#pragma unroll
+      for (int st = 0; st < 2; ++st)
+#pragma unroll
+        for (int jt = 0; jt < 4; ++jt) a[st][jt] = *reinterpret_cast<const bf16x8*>(W2 + (st * 4 + jt) * 512);
+#pragma unroll
+      for (int ks = 0; ks < H / 32; ++ks) {
+        if (ks + 2 < H / 32) {
+#pragma unroll
+          for (int jt = 0; jt < 4; ++jt)
+            a[(ks + 2) % 3][jt] = *reinterpret_cast<const bf16x8*>(W2 + ((ks + 2) * 4 + jt) * 512);
+        }
+        bf16x8 b[4];
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt)
+          b[mt] = *reinterpret_cast<const bf16x8*>(h + hs(16 * mt + rb, 32 * ks + 8 * quad));
+#pragma unroll
+        for (int jt = 0; jt < 4; ++jt)
+#pragma unroll
+          for (int mt = 0; mt < 4; ++mt) acc[jt][mt] = mfma16(a[ks % 3][jt], b[mt], acc[jt][mt]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
     };
-    step(wq[0], quad - 2 * odd);
-    step(wq[1], quad + 4 - 2 * odd);
-    if (odd || c + 1 == L.dB) {
+    {
+      f32x4 acc[4][4];
 #pragma unroll
-      for (int jt = 0; jt < 4; ++jt) wq[0][jt] = *reinterpret_cast<const bf16x8*>(wqc + (32 + jt) * 512);
-      step(wq[0], quad + 8 - 2 * odd);
+      for (int jt = 0; jt < 4; ++jt) {
+        const f32x4 bias = bias4(L.b2, wave, jt, quad);
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) acc[jt][mt] = bias;
+      }
+      dense(L.W2p, acc);
+      __syncthreads();  // every wave has read the first layer
+      s2 = store_features_signs(h, acc, wave, fresh(row), quad);
     }
-  }
-  // every wave read the second layer before the barriers of the last coordinate
-  store_gradients(h, acc, s2, wave, fresh(row), quad);
-  __syncthreads();
-  copy_tile(h, out_op.ga2, e0, n, fresh(tid));
+    __syncthreads();
+    copy_tile(h, out_op.h2, e0, n, fresh(tid));
+    f32x4 lastv = {0.0f, 0.0f, 0.0f, 0.0f};
+    {
+      const bf16* wl = L.W3L + lane * 8;
 #pragma unroll
-  for (int jt = 0; jt < 4; ++jt)
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) acc[jt][mt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  dense(L.W2q, acc);
-  __syncthreads();
-  store_gradients(h, acc, s1, wave, fresh(row), quad);
-  __syncthreads();
-  copy_tile(h, out_op.ga1, e0, n, fresh(tid));
-  // gradient reaching the kept coordinates: D[coordinate][event], the wave's
-  // 16 events
-  f32x4 gx = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-  for (int ks = 0; ks < H / 32; ++ks) {
-    const bf16x8 a = *reinterpret_cast<const bf16x8*>(L.W1q + ks * 512 + lane * 8);
-    const bf16x8 b = *reinterpret_cast<const bf16x8*>(h + hs(16 * wave + row, 32 * ks + 8 * quad));
-    gx = mfma16(a, b, gx);
-  }
-  const int64_t eg = e0 + 16 * wave + row;
-  if (eg < n) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int ci = 4 * quad + i;
-      if (ci < L.dA) g[(int64_t)L.a_idx[ci] * n + eg] += gx[i];
+      for (int ks = 0; ks < H / 32; ++ks) {
+        const bf16x8 a = *reinterpret_cast<const bf16x8*>(wl + ks * 512);
+        const bf16x8 b = *reinterpret_cast<const bf16x8*>(h + hs(16 * wave + row, 32 * ks + 8 * quad));
+        lastv = mfma16(a, b, lastv);
+      }
     }
+    // gradient after the second activation, accumulated over the coordinates
+    f32x4 acc[4][4];
+#pragma unroll
+    for (int jt = 0; jt < 4; ++jt)
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt) acc[jt][mt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    const int m = tid >> 2, part = tid & 3;
+    const int64_t em = e0 + m;
+    const bool live = em < n;
+    const float glp = live ? -w[em] / wsum[0] : 0.0f;
+    const int NB = L.dB * NOG;
+    for (int c = 0; c < L.dB; ++c) {
+      {
+        const bf16* W3 = L.W3p + (((int64_t)c * 4 + wave) * 8) * 512 + lane * 8;
+        const int col = 16 * wave + row;
+        const float bias = L.b3p[c * NOP + col];
+        f32x4 lg[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) lg[r] = f32x4{bias, bias, bias, bias};
+#pragma unroll
+        for (int ks = 0; ks < H / 32; ++ks) {
+          const bf16x8 bw = *reinterpret_cast<const bf16x8*>(W3 + ks * 512);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const bf16x8 a = *reinterpret_cast<const bf16x8*>(h + hs(16 * r + row, 32 * ks + 8 * quad));
+            lg[r] = mfma16(a, bw, lg[r]);
+          }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) out[(16 * r + 4 * quad + i) * LDO + col] = lg[r][i];
+      }
+      const int ci = c & 3;
+      const float lsel = ci == 0 ? lastv[0] : ci == 1 ? lastv[1] : ci == 2 ? lastv[2] : lastv[3];
+      const float vlast = __shfl(lsel, (lane >> 2) + 16 * (c >> 2)) + L.b3p[c * NOP + 2 * KB];
+      float* gp = g + (int64_t)L.b_idx[c] * n + (live ? em : e0);
+      const float gz = live ? *gp : 0.0f;
+      // this coordinate's fragments for the gradient, requested before the PQ
+      // derivatives
+      const int odd = c & 1;
+      const bf16* wqc = L.W3q + ((int64_t)((c >> 1) * 5 + 2 * odd) * 16 + wave * 4) * 512 + lane * 8;
+      bf16x8 wq[2][4];
+#pragma unroll
+      for (int st = 0; st < 2; ++st)
+#pragma unroll
+        for (int jt = 0; jt < 4; ++jt) wq[st][jt] = *reinterpret_cast<const bf16x8*>(wqc + (st * 16 + jt) * 512);
+      __syncthreads();  // logits complete; the previous coordinate's gradients have been read
+      {
+        float gw[KB / 4], gv[KB / 4], gl, gy;
+        pq_quad_backward(out + m * LDO, vlast, tb[c * T + m], part, gz, glp, gw, gv, gl, gy);
+        if (live && part == 0) *gp = gy;
+        bf16x8 a, b;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          a[k] = (bf16)gw[k];
+          b[k] = (bf16)gv[k];
+        }
+        bf16x8 l8;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) l8[k] = k == 0 ? (bf16)gl : (bf16)0.0f;
+        *reinterpret_cast<bf16x8*>(gt + gs(m, part)) = a;
+        *reinterpret_cast<bf16x8*>(gt + gs(m, 4 + part)) = b;
+        if (part == 3) gt[gs_last(m, odd)] = (bf16)gl;
+        if (live) {
+          bf16* dst = out_op.go + em * NB + c * NOG;
+          __builtin_nontemporal_store(a, reinterpret_cast<bf16x8*>(dst + 8 * part));
+          __builtin_nontemporal_store(b, reinterpret_cast<bf16x8*>(dst + KB + 8 * part));
+          if (part == 3) __builtin_nontemporal_store(l8, reinterpret_cast<bf16x8*>(dst + 2 * KB));
+        }
+      }
+      __syncthreads();
+      // k steps of 32 over NOP columns per coordinate: two for an even
+      // coordinate; three for an odd one, the first beginning with the last
+      // logit of the one before, the third ending with its own.  An even last
+      // coordinate ends with a step of its last logit.
+      auto step = [&](const bf16x8 (&aw)[4], int chunk) {
+        bf16x8 b[4];
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) {
+          const int mm = 16 * mt + row;
+          int at = gs(mm, chunk & 7);
+          at = chunk < 0 || chunk > 8 ? GS_ZERO : at;
+          at = chunk == -2 || chunk == 8 ? gs_last(mm, chunk == 8 ? odd : 0) : at;
+          b[mt] = *reinterpret_cast<const bf16x8*>(gt + at);
+        }
+#pragma unroll
+        for (int jt = 0; jt < 4; ++jt)
+#pragma unroll
+          for (int mt = 0; mt < 4; ++mt) acc[jt][mt] = mfma16(aw[jt], b[mt], acc[jt][mt]);
+      };
+      step(wq[0], quad - 2 * odd);
+      step(wq[1], quad + 4 - 2 * odd);
+      if (odd || c + 1 == L.dB) {
+#pragma unroll
+        for (int jt = 0; jt < 4; ++jt) wq[0][jt] = *reinterpret_cast<const bf16x8*>(wqc + (32 + jt) * 512);
+        step(wq[0], quad + 8 - 2 * odd);
+      }
+    }
+    // every wave read the second layer before the barriers of the last coordinate
+    store_gradients(h, acc, s2, wave, fresh(row), quad);
+    __syncthreads();
+    copy_tile(h, out_op.ga2, e0, n, fresh(tid));
+#pragma unroll
+    for (int jt = 0; jt < 4; ++jt)
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt) acc[jt][mt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    dense(L.W2q, acc);
+    __syncthreads();
+    store_gradients(h, acc, s1, wave, fresh(row), quad);
+    __syncthreads();
+    copy_tile(h, out_op.ga1, e0, n, fresh(tid));
+    // gradient reaching the kept coordinates: D[coordinate][event], the wave's
+    // 16 events
+    f32x4 gx = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int ks = 0; ks < H / 32; ++ks) {
+      const bf16x8 a = *reinterpret_cast<const bf16x8*>(L.W1q + ks * 512 + lane * 8);
+      const bf16x8 b = *reinterpret_cast<const bf16x8*>(h + hs(16 * wave + row, 32 * ks + 8 * quad));
+      gx = mfma16(a, b, gx);
+    }
+    const int64_t eg = e0 + 16 * wave + row;
+    if (eg < n) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int ci = 4 * quad + i;
+        if (ci < L.dA) g[(int64_t)L.a_idx[ci] * n + eg] += gx[i];
+      }
+    }
+    __syncthreads();  // the layer's gradients are written and its tiles read
   }
 }
 
 // ------------------------------------------------------ weight gradients
 // dW[m][j] = sum over events of X[e][m] G[e][j] for the three dense layers of
-// one coupling layer (X = h2, h1, xa and G = go, ga2, ga1), with the column
+// every coupling layer (X = h2, h1, xa and G = go, ga2, ga1), with the column
 // sums of G (the bias gradients) as row M, in partials over chunks of events:
-// part[z zs + off + m N + j].  All three products are one launch, numbered so
-// that the tiles of one chunk run on one XCD and share their operands in its
-// L2.  A workgroup takes a 128 x 128 tile, each of its four waves 64 x 64: a
-// fragment read from LDS then serves four matrix instructions (two for the
-// 32 x 32 of a 64 x 64 tile, which is bound by LDS reads).  The operands are
-// event-major and the events are the contraction, so the fragments come from
-// LDS transposed (ds_read_b64_tr_b16): a group of 16 lanes reads 4 events x 16
-// features, lane i receiving feature i of the four events.  Per k step of 32
-// events lane group q takes events 4q..4q+3 and 16+4q..16+4q+3 for both
-// operands; with rows of 288 bytes the 8 rows of half a wave fall in different
-// banks (no conflicts counted).  Bound by memory: 65536 points of 10
-// dimensions, per layer, read and write 212 MB in 57 us (3.7 TB/s, a copy
-// reaches 4.7) and the reduction takes 16 us; three launches of 64 x 64 tiles
-// on event-contiguous copies and three reductions took 250 us.
+// part[z zs + off + m N + j].  All products are one launch, numbered so that the
+// tiles of one chunk run on one XCD, those of one layer together, and share
+// their operands in its L2.  A workgroup takes a 128 x 128 tile, each of its
+// four waves 64 x 64: a fragment read from LDS then serves four matrix
+// instructions (two for the 32 x 32 of a 64 x 64 tile, which is bound by LDS
+// reads).  The operands are event-major and the events are the contraction, so
+// the fragments come from LDS transposed (ds_read_b64_tr_b16): a group of 16
+// lanes reads 4 events x 16 features, lane i receiving feature i of the four
+// events.  Per k step of 32 events lane group q takes events 4q..4q+3 and
+// 16+4q..16+4q+3 for both operands; with rows of 288 bytes the 8 rows of half a
+// wave fall in different banks (no conflicts counted).  Bound by memory: six
+// layers of 65536 points of 10 dimensions have 1.1 GB of operands, read 1.5
+// times: 285 us, and 11 us for the reduction.  Launched layer by layer beside
+// the backward pass, with six times the partials, the whole gradient took 1.42
+// ms instead of 1.11; three launches per layer of 64 x 64 tiles on
+// event-contiguous copies and three reductions took 250 us per layer.
 constexpr int WT = 128;        // tile edge
 constexpr int WK = 64;         // events per staged slice: two k steps
 constexpr int WLD = WT + 16;   // LDS row stride (bf16)
+struct Product {
+  const bf16* X;
+  const bf16* G;
+  int M, N;
+  int tiles_n, first;  // column tiles; first tile number
+  int64_t off;         // of its partials
+};
 struct WgradArgs {
-  const bf16* X[3];
-  const bf16* G[3];
-  int M[3], N[3];
-  int tiles_n[3], first[3];  // column tiles; first tile number of the product
-  int tiles;                 // of all products
-  int64_t off[3], zs;        // partial offsets and stride
+  Product p[3 * MAXL];
+  int np, tiles;  // products and their tiles
+  int64_t zs;     // floats of one chunk's partials
   int64_t n, chunk;
+  int64_t zmax;   // chunks at most, whatever n
   float* part;
 };
 typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -1078,14 +1106,13 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
   const int G = gridDim.x, xcd = blockIdx.x & 7, per = G >> 3, rem = G & 7;
   const int t = xcd * per + (xcd < rem ? xcd : rem) + (int)(blockIdx.x >> 3);
   const int z = t / a.tiles, tl = t % a.tiles;
-  const int pr = tl >= a.first[2] ? 2 : (tl >= a.first[1] ? 1 : 0);
-  const bf16* X = pr == 2 ? a.X[2] : (pr == 1 ? a.X[1] : a.X[0]);
-  const bf16* Gp = pr == 2 ? a.G[2] : (pr == 1 ? a.G[1] : a.G[0]);
-  const int M = pr == 2 ? a.M[2] : (pr == 1 ? a.M[1] : a.M[0]);
-  const int N = pr == 2 ? a.N[2] : (pr == 1 ? a.N[1] : a.N[0]);
-  const int tn = pr == 2 ? a.tiles_n[2] : (pr == 1 ? a.tiles_n[1] : a.tiles_n[0]);
-  const int tp = tl - (pr == 2 ? a.first[2] : (pr == 1 ? a.first[1] : a.first[0]));
-  const int m0 = tp / tn * WT, n0 = tp % tn * WT;
+  int pr = 0;
+  for (int i = 1; i < a.np; ++i) pr = tl >= a.p[i].first ? i : pr;
+  const Product& D = a.p[pr];
+  const bf16* X = D.X;
+  const bf16* Gp = D.G;
+  const int M = D.M, N = D.N, tp = tl - D.first;
+  const int m0 = tp / D.tiles_n * WT, n0 = tp % D.tiles_n * WT;
   const int64_t kb = (int64_t)z * a.chunk, ke = kb + a.chunk < a.n ? kb + a.chunk : a.n;
   const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
   f32x4 acc[4][4], accs[4];
@@ -1169,7 +1196,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
     __syncthreads();
     products(0);
   }
-  float* P = a.part + (int64_t)z * a.zs + (pr == 2 ? a.off[2] : (pr == 1 ? a.off[1] : a.off[0]));
+  float* P = a.part + (int64_t)z * a.zs + D.off;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int gn = n0 + wn + 16 * j + row;
@@ -1185,12 +1212,19 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
   }
 }
 
-// The gradients of one layer from the partials, summed over the chunks in
-// order: W3 and b3 without the padding of each coordinate's columns, W2 and
+// The gradients of layer blockIdx.y from the partials, summed over the chunks
+// in order: W3 and b3 without the padding of each coordinate's columns, W2 and
 // b2, W1 (the sum of the products with the high and the low input parts) and
-// b1.  grad: the layer's slice of the gradient.
-__global__ void __launch_bounds__(256) k_reduce_layer(const float* __restrict__ part, int Z, int64_t zs, int dA, int dB,
-                                                      float* __restrict__ grad) {
+// b1.
+struct ReduceArgs {
+  int dA[MAXL], dB[MAXL];
+  int64_t off[MAXL], goff[MAXL];  // of the layer's partials and of its gradient
+};
+__global__ void __launch_bounds__(256) k_reduce_grad(const float* __restrict__ part_all, int Z, int64_t zs, ReduceArgs a,
+                                                     float* __restrict__ grad_all) {
+  const int dA = a.dA[blockIdx.y], dB = a.dB[blockIdx.y];
+  const float* part = part_all + a.off[blockIdx.y];
+  float* grad = grad_all + a.goff[blockIdx.y];
   const int N3 = dB * NOG, nO = dB * NO;
   const int64_t n3 = (int64_t)(H + 1) * N3, n2 = (int64_t)(H + 1) * H, n1 = (int64_t)(dA + 1) * H;
   int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -1236,6 +1270,7 @@ constexpr int RB = 1024;  // threads of the single-block batch reductions
 __global__ void __launch_bounds__(RB) k_wsum(const float* __restrict__ w, int64_t n, float* __restrict__ out) {
   __shared__ double s[RB];
   double a = 0.0;
+#pragma unroll 8
   for (int64_t i = threadIdx.x; i < n; i += RB) a += w[i];
   s[threadIdx.x] = a;
   __syncthreads();
@@ -1252,11 +1287,12 @@ __global__ void k_variance_weights(const float* __restrict__ w, const float* __r
   if (e < n) weff[e] = w[e] * w[e] * __expf(-logq[e]);
 }
 // relative variance per event of sampling q, from points uniform in y:
-// n sum w^2/q / (sum w)^2 - 1
+// n sum w^2/q / (sum w)^2 - 1; and the sum of the weights w^2/q, as k_wsum
 __global__ void __launch_bounds__(RB) k_relvar(const float* __restrict__ w, const float* __restrict__ weff, int64_t n,
-                                               float* __restrict__ out) {
+                                               float* __restrict__ out, float* __restrict__ wsum) {
   __shared__ double s1[RB], s2[RB];
   double a = 0.0, b = 0.0;
+#pragma unroll 8
   for (int64_t i = threadIdx.x; i < n; i += RB) {
     a += w[i];
     b += weff[i];
@@ -1271,12 +1307,16 @@ __global__ void __launch_bounds__(RB) k_relvar(const float* __restrict__ w, cons
     }
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[0] = (float)((double)n * s2[0] / (s1[0] * s1[0]) - 1.0);
+  if (threadIdx.x == 0) {
+    out[0] = (float)((double)n * s2[0] / (s1[0] * s1[0]) - 1.0);
+    wsum[0] = (float)s2[0];
+  }
 }
 __global__ void __launch_bounds__(RB) k_loss(const float* __restrict__ w, const float* __restrict__ logq, int64_t n,
                                              const float* __restrict__ wsum, float* __restrict__ out) {
   __shared__ double s[RB];
   double a = 0.0;
+#pragma unroll 8
   for (int64_t i = threadIdx.x; i < n; i += RB) a += (double)w[i] * logq[i];
   s[threadIdx.x] = a;
   __syncthreads();
@@ -1415,32 +1455,22 @@ struct mf_flow {
   float* d_gy = nullptr;    // [d][cap]
   float* d_lq = nullptr;    // [cap]
   float* d_weff = nullptr;  // [cap] per-point loss weights of the variance loss
-  // operands of the weight gradients, two sets: one layer's are read on the
-  // side stream while the next layer's are written
-  Operands op[2];
+  Operands op{};            // operands of the weight gradients, all layers
   bf16* d_op = nullptr;
   float* d_part = nullptr;  // partials of the weight gradients, split over events
   size_t part_cap = 0;      // floats
   float* d_scal = nullptr;  // wsum, loss
   std::vector<float*> d_losses;
-  // the backward pass runs the weight-gradient products on a second stream
-  // (default priority) beside the activation-gradient chain; events order
-  // the two
-  hipStream_t side = nullptr;
-  hipEvent_t ev[4] = {};  // operands written and read, per set
 };
 
 namespace {
 
-// Chunks of events of a layer's weight gradients: at most two workgroups per
-// compute unit over the tiles of the three products, so that all run at once
-// (43 chunks of 12 tiles, four workgroups more, took 69 us instead of 57),
-// whole slices per chunk, and at most WGRAD_MAX chunks, which the reduction
-// adds up in turn.
+// Chunks of events of the weight gradients: at most two workgroups per compute
+// unit over the tiles of all layers, so that all run at once (516 workgroups
+// for one layer took 69 us, 504 took 57), whole slices per chunk, and at most
+// WGRAD_MAX chunks, which the reduction adds up in turn.
 constexpr int64_t WGRAD_BLOCKS = 512;
 constexpr int64_t WGRAD_MAX = 64;
-// floats of one chunk's partials: (inputs + 1) x outputs of the three layers
-int64_t wgrad_outputs(int dB) { return (int64_t)(H + 1) * dB * NOG + (int64_t)(H + 1) * H + (int64_t)(KA + 1) * H; }
 
 mf_status launch_err(const char* what) {
   hipError_t e = hipGetLastError();
@@ -1449,41 +1479,52 @@ mf_status launch_err(const char* what) {
 }
 
 
-WgradArgs wgrad_args(const Operands& o, int dB, int64_t n) {
+WgradArgs wgrad_args(const mf_flow* f, int64_t n) {
   WgradArgs a{};
-  const bf16* X[3] = {o.h2, o.h1, o.xa};
-  const bf16* G[3] = {o.go, o.ga2, o.ga1};
-  const int M[3] = {H, H, KA}, N[3] = {dB * NOG, H, H};
-  for (int p = 0; p < 3; ++p) {
-    a.X[p] = X[p];
-    a.G[p] = G[p];
-    a.M[p] = M[p];
-    a.N[p] = N[p];
-    a.tiles_n[p] = (N[p] + WT - 1) / WT;
-    a.first[p] = a.tiles;
-    a.tiles += a.tiles_n[p] * ((M[p] + WT - 1) / WT);
-    a.off[p] = a.zs;
-    a.zs += (int64_t)(M[p] + 1) * N[p];
+  for (int l = 0; l < f->nl; ++l) {
+    const Operands& o = f->op;
+    const bf16* X[3] = {o.h2, o.h1, o.xa};
+    const bf16* G[3] = {o.go, o.ga2, o.ga1};
+    const int M[3] = {H, H, KA}, N[3] = {f->L.L[l].dB * NOG, H, H};
+    for (int k = 0; k < 3; ++k) {
+      Product& p = a.p[a.np++];
+      p.X = X[k] + l * o.stride;
+      p.G = G[k] + l * o.stride;
+      p.M = M[k];
+      p.N = N[k];
+      p.tiles_n = (p.N + WT - 1) / WT;
+      p.first = a.tiles;
+      a.tiles += p.tiles_n * ((p.M + WT - 1) / WT);
+      p.off = a.zs;
+      a.zs += (int64_t)(p.M + 1) * p.N;
+    }
   }
   a.n = n;
-  int64_t z = WGRAD_BLOCKS / a.tiles;
-  z = z < WGRAD_MAX ? z : WGRAD_MAX;
+  const int64_t z = std::max<int64_t>(1, std::min(WGRAD_BLOCKS / a.tiles, WGRAD_MAX));
+  a.zmax = z;
   a.chunk = ((n + z - 1) / z + WK - 1) / WK * WK;
   return a;
 }
 
-// Weight and bias gradients of layer l over n events from the operands o.
-bool weight_grads(mf_flow* f, int l, const Operands& o, int64_t n, hipStream_t s) {
-  const LayerDev& L = f->L.L[l];
-  WgradArgs a = wgrad_args(o, L.dB, n);
+// Weight and bias gradients of all layers over n events from the operands.
+bool weight_grads(mf_flow* f, int64_t n, hipStream_t s) {
+  WgradArgs a = wgrad_args(f, n);
   const int64_t Z = (n + a.chunk - 1) / a.chunk;
   // the partials of all chunks must fit the buffer sized at creation
   if ((size_t)(Z * a.zs) > f->part_cap) return false;
   a.part = f->d_part;
   hipLaunchKernelGGL(k_wgrad, dim3((unsigned)(a.tiles * Z)), dim3(256), 0, s, a);
-  const int64_t tot = a.off[2] + (int64_t)(L.dA + 1) * H;
-  hipLaunchKernelGGL(k_reduce_layer, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, f->d_part, (int)Z, a.zs,
-                     L.dA, L.dB, f->d_g + f->loff[l]);
+  ReduceArgs r{};
+  int64_t most = 0;
+  for (int l = 0; l < f->nl; ++l) {
+    r.dA[l] = f->L.L[l].dA;
+    r.dB[l] = f->L.L[l].dB;
+    r.off[l] = a.p[3 * l].off;
+    r.goff[l] = f->loff[l];
+    most = std::max(most, (int64_t)(H + 1) * (r.dB[l] * NOG + H) + (int64_t)(r.dA[l] + 1) * H);
+  }
+  hipLaunchKernelGGL(k_reduce_grad, dim3((unsigned)((most + 255) / 256), (unsigned)f->nl), dim3(256), 0, s, f->d_part,
+                     (int)Z, a.zs, r, f->d_g);
   return true;
 }
 
@@ -1526,37 +1567,14 @@ mf_status loss_grad_impl(mf_flow* f, const float* y, int64_t ldy, const float* w
     hipLaunchKernelGGL(k_variance_weights, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, w_in, f->d_lq, n,
                        f->d_weff);
     w = f->d_weff;
-    hipLaunchKernelGGL(k_relvar, dim3(1), dim3(RB), 0, s, w_in, f->d_weff, n, loss_dev);
-  }
-  hipLaunchKernelGGL(k_wsum, dim3(1), dim3(RB), 0, s, w, n, f->d_scal);
-  if (kind != MF_FLOW_LOSS_VARIANCE)
+    hipLaunchKernelGGL(k_relvar, dim3(1), dim3(RB), 0, s, w_in, f->d_weff, n, loss_dev, f->d_scal);
+  } else {
+    hipLaunchKernelGGL(k_wsum, dim3(1), dim3(RB), 0, s, w, n, f->d_scal);
     hipLaunchKernelGGL(k_loss, dim3(1), dim3(RB), 0, s, w, f->d_lq, n, f->d_scal, loss_dev);
-
-  e = hipMemsetAsync(f->d_gy, 0, sizeof(float) * d * n, s);
-  if (e != hipSuccess) return set_error(MF_EDEVICE, "gradient clear: %s", hipGetErrorString(e));
-  // Per layer the backward kernel runs on s and the weight gradients on the
-  // side stream, started once their operands exist; before a set of operands
-  // is written again, s waits for the products that read it.  All partials are
-  // on the side stream.
-  hipStream_t s2 = f->side;
-  bool ok = true;
-  auto rec = [&](int k, hipStream_t from) { ok = ok && hipEventRecord(f->ev[k], from) == hipSuccess; };
-  auto wait = [&](int k, hipStream_t on) { ok = ok && hipStreamWaitEvent(on, f->ev[k], 0) == hipSuccess; };
-  for (int l = f->nl - 1; l >= 0; --l) {
-    const int set = l & 1;
-    if (l + 2 <= f->nl - 1) wait(2 + set, s);
-    hipLaunchKernelGGL(k_layer_backward, dim3((unsigned)((n + T - 1) / T)), dim3(256), 0, s, f->L.L[l],
-                       f->d_lin + (int64_t)l * d * f->cap, n, f->d_gy, w, f->d_scal, f->op[set]);
-    rec(set, s);
-    wait(set, s2);
-    if (!weight_grads(f, l, f->op[set], n, s2))
-      return set_error(MF_EINVAL, "weight-gradient partials exceed the flow's buffer");
-    rec(2 + set, s2);
   }
-  // the gradient is complete on s once the side stream's last product is
-  // (layer 0, set 0)
-  wait(2, s);
-  if (!ok) return set_error(MF_EDEVICE, "backward stream ordering failed");
+  hipLaunchKernelGGL(k_backward, dim3((unsigned)((n + T - 1) / T)), dim3(256), 0, s, f->L, f->nl, f->d_lin,
+                     (int64_t)d * f->cap, n, f->d_gy, w, f->d_scal, f->op, d);
+  if (!weight_grads(f, n, s)) return set_error(MF_EINVAL, "weight-gradient partials exceed the flow's buffer");
   return launch_err("flow backward");
 }
 
@@ -1632,16 +1650,13 @@ mf_status mf_flow_create(const mf_flow_config* cfg, mf_flow** out) {
   const int64_t cap = cfg->max_batch;
   f->cap = cap;
 
-  // operands of the weight gradients of one layer
-  const size_t per_set = ((size_t)cap * (4 * H + KA + dBmax * NOG) + 127) / 128 * 128;
-  // the chunks depend on the tiles and so on d_B: the maximum over every one
-  int64_t pc = 0;
-  for (int dB = 1; dB <= dBmax; ++dB) {
-    const WgradArgs a = wgrad_args(Operands{}, dB, cap);
-    const int64_t z = WGRAD_BLOCKS / a.tiles;
-    pc = std::max(pc, std::min(z, (cap + WK - 1) / WK) * a.zs);
+  // operands of the weight gradients of all layers
+  const size_t per_layer = ((size_t)cap * (4 * H + KA + dBmax * NOG) + 127) / 128 * 128;
+  {
+    const WgradArgs a = wgrad_args(f, cap);
+    // fewer events may take more chunks than cap does, of whole slices
+    f->part_cap = (size_t)(std::min(a.zmax, (cap + WK - 1) / WK) * a.zs);
   }
-  f->part_cap = (size_t)pc;
   if (hipMalloc(&f->d_p, sizeof(float) * off) != hipSuccess || hipMalloc(&f->d_g, sizeof(float) * off) != hipSuccess ||
       hipMalloc(&f->d_m1, sizeof(float) * off) != hipSuccess || hipMalloc(&f->d_m2, sizeof(float) * off) != hipSuccess ||
       hipMalloc(&f->d_w16, sizeof(bf16) * w16) != hipSuccess || hipMalloc(&f->d_b3p, sizeof(float) * b3) != hipSuccess ||
@@ -1650,7 +1665,7 @@ mf_status mf_flow_create(const mf_flow_config* cfg, mf_flow** out) {
       hipMalloc(&f->d_gy, sizeof(float) * d * cap) != hipSuccess ||
       hipMalloc(&f->d_lq, sizeof(float) * cap) != hipSuccess ||
       hipMalloc(&f->d_weff, sizeof(float) * cap) != hipSuccess ||
-      hipMalloc(&f->d_op, sizeof(bf16) * 2 * per_set) != hipSuccess ||
+      hipMalloc(&f->d_op, sizeof(bf16) * f->nl * per_layer) != hipSuccess ||
       hipMalloc(&f->d_part, sizeof(float) * f->part_cap) != hipSuccess ||
       hipMalloc(&f->d_scal, sizeof(float) * 4) != hipSuccess) {
     hipGetLastError();
@@ -1662,29 +1677,15 @@ mf_status mf_flow_create(const mf_flow_config* cfg, mf_flow** out) {
       hipMemset(f->d_w16, 0, sizeof(bf16) * w16) != hipSuccess ||
       hipMemset(f->d_b3p, 0, sizeof(float) * b3) != hipSuccess)
     return cleanup(set_error(MF_EDEVICE, "flow initialisation failed"));
-  if (hipStreamCreateWithFlags(&f->side, hipStreamNonBlocking) != hipSuccess) {
-    f->side = nullptr;
-    hipGetLastError();
-    return cleanup(set_error(MF_EDEVICE, "flow stream creation failed"));
-  }
-  for (hipEvent_t& e : f->ev)
-    if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
-      e = nullptr;
-      hipGetLastError();
-      return cleanup(set_error(MF_EDEVICE, "flow event creation failed"));
-    }
   bf16* wp = f->d_w16;
   float* bp = f->d_b3p;
-  for (int k = 0; k < 2; ++k) {
-    bf16* q = f->d_op + k * per_set;
-    Operands& o = f->op[k];
-    o.h1 = q;
-    o.h2 = o.h1 + cap * H;
-    o.ga1 = o.h2 + cap * H;
-    o.ga2 = o.ga1 + cap * H;
-    o.xa = o.ga2 + cap * H;
-    o.go = o.xa + cap * KA;
-  }
+  f->op.stride = (int64_t)per_layer;
+  f->op.h1 = f->d_op;
+  f->op.h2 = f->op.h1 + cap * H;
+  f->op.ga1 = f->op.h2 + cap * H;
+  f->op.ga2 = f->op.ga1 + cap * H;
+  f->op.xa = f->op.ga2 + cap * H;
+  f->op.go = f->op.xa + cap * KA;
   for (int l = 0; l < f->nl; ++l) {
     LayerDev& L = f->L.L[l];
     L.W1t = wp;
@@ -1739,9 +1740,6 @@ void mf_flow_destroy(mf_flow* f) {
   hipFree(f->d_part);
   hipFree(f->d_scal);
   for (float* p : f->d_losses) hipFree(p);
-  for (hipEvent_t e : f->ev)
-    if (e) hipEventDestroy(e);
-  if (f->side) hipStreamDestroy(f->side);
   delete f;
 }
 

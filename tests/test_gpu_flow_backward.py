@@ -22,15 +22,16 @@ def _dev32(x):
     return torch.from_numpy(np.ascontiguousarray(np.asarray(x, dtype=np.float32).T)).to("cuda")
 
 
-@pytest.mark.parametrize("d,n", [(2, 1), (3, 63), (4, 64), (7, 65), (10, 129), (13, 1500), (16, 4000)])
-def test_gradient_is_the_mean_of_single_event_gradients(d, n):
+@pytest.mark.parametrize("d,n,batch", [(2, 1, 64), (3, 63, 4096), (4, 64, 64), (7, 65, 4096), (10, 129, 4096),
+                                       (10, 448, 500), (13, 1500, 4096), (16, 4000, 4096)])
+def test_gradient_is_the_mean_of_single_event_gradients(d, n, batch):
     """With weights 1 for a power of two of the events and 0 for the rest, an
     event's weight relative to the sum is a power of two: every rounding of its
     gradient, also to BF16, is that of the event alone, and zero weights add
     exact zeros.  What is left are the FP32 sums over events, at most k + 2
     additions in a row, a product's high and low parts, and the same for the
     single events: below 4 (k + 2) 2^-24 times the sum of the magnitudes."""
-    f = mf.Flow(d, max_batch=4096)
+    f = mf.Flow(d, max_batch=batch)
     rng = np.random.default_rng(40 + d)
     shapes = [(int((~m).sum()), 256, int(m.sum()) * (2 * K + 1)) for m in oflow.masks(d, 6)]
     f.set_params(mf.Flow.flatten(si.flow_params(shapes, seed=40 + d, scale_out=0.1)))
