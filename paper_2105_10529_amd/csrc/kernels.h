@@ -381,8 +381,11 @@ __global__ void __launch_bounds__(BLOCK) k_select(DevCfg c, const double* __rest
 // ----------------------------------------------------- fused VEGAS iteration
 // Stage 2: the weights of the events k_select kept for this block (chunks of
 // BLOCK list entries; the last chunk's idle lanes recompute the block's first
-// event with the weight masked).
-template <int NG, int CH, class RA>
+// event with the weight masked).  LISTED = false takes the block's chunks of
+// all events as they are, without stage 1: for no final-state partons, where
+// only the threshold fails events (5 x 1e5 g g -> t t~ events 299 us with the
+// selection, 260 us without); the observables need the lists.
+template <int NG, int CH, class RA, bool LISTED = true>
 __global__ void __launch_bounds__(BLOCK) k_vegas(DevCfg c, const double* __restrict__ edges_g, uint64_t iter,
                                                  int64_t N, uint64_t seed, double* __restrict__ partials,
                                                  int pstride, const int* __restrict__ list,
@@ -416,12 +419,12 @@ __global__ void __launch_bounds__(BLOCK) k_vegas(DevCfg c, const double* __restr
   // block's list), so its counter lives in scalar registers and is not
   // exposed to vector-register spills inside the divergent per-event code.
   const int* mine_list = list + (int64_t)blockIdx.x * cap;
-  const int nsel = __builtin_amdgcn_readfirstlane(cnt[blockIdx.x]);
-  const int64_t nchunk = (nsel + BLOCK - 1) / BLOCK;
+  const int nsel = LISTED ? __builtin_amdgcn_readfirstlane(cnt[blockIdx.x]) : 0;
+  const int64_t nchunk = LISTED ? (nsel + BLOCK - 1) / BLOCK : chunks_of_block(N);
   for (int64_t it = 0; it < nchunk; ++it) {
-    const int64_t j0 = it * BLOCK + tid;
-    const bool live = j0 < nsel;
-    const int64_t e = mine_list[live ? j0 : 0];
+    const int64_t j0 = (LISTED ? it * BLOCK : chunk_base(it)) + tid;
+    const bool live = j0 < (LISTED ? (int64_t)nsel : N);
+    const int64_t e = LISTED ? (int64_t)mine_list[live ? j0 : 0] : (live ? j0 : N - 1);
     {
       // map the uniforms and stage the bin indices and the Jacobian in LDS
       // before the amplitude, so no per-lane value is live across it
@@ -442,14 +445,14 @@ __global__ void __launch_bounds__(BLOCK) k_vegas(DevCfg c, const double* __restr
 #pragma unroll
     for (int j = 0; j < MAXD; ++j)
       if (j < d) x[j] = xs[j * BLOCK + tid];
-    EventOut<double> r = event_weight<NG, CH, RA, double, 1, true>(cl, x, c.mt, pdf);
+    EventOut<double> r = event_weight<NG, CH, RA, double, 1, LISTED>(cl, x, c.mt, pdf);
     asm volatile("" ::: "memory");
     double w = r.w * jac_s[tid];
     const bool finite = isfinite(w);
     nbad += __popcll(__ballot(live && !finite));
     w = (live && finite) ? w : 0.0;
     nnz += __popcll(__ballot(w != 0.0));
-    if (wk != nullptr && live) wk[(int64_t)blockIdx.x * cap + j0] = w;  // for the observable histograms
+    if (LISTED && wk != nullptr && live) wk[(int64_t)blockIdx.x * cap + j0] = w;  // for the observable histograms
     {
       double h1, l1, h2, l2;
       wave_sum_dd(w, h1, l1);
@@ -682,6 +685,13 @@ Launchers make_launchers() {
   if constexpr (FUSED != 0) {
     L.vegas = [](const DevCfg& c, const double* edges, uint64_t iter, int64_t N, uint64_t seed, double* part,
                  int pstride, int nblk, size_t lds, int* list, int* cnt, int64_t cap, double* wk, hipStream_t s) {
+      if constexpr (NG == 0) {
+        if (wk == nullptr) {
+          hipLaunchKernelGGL((k_vegas<NG, CH, RA, false>), dim3(nblk), dim3(BLOCK), lds, s, c, edges, iter, N, seed, part,
+                             pstride, list, cnt, cap, wk);
+          return;
+        }
+      }
       hipLaunchKernelGGL((k_select<NG>), dim3(nblk), dim3(BLOCK), sizeof(double) * c.ndim * (c.nb + 1), s, c, edges,
                          iter, N, seed, list, cnt, cap);
       hipLaunchKernelGGL((k_vegas<NG, CH, RA>), dim3(nblk), dim3(BLOCK), lds, s, c, edges, iter, N, seed, part, pstride,
