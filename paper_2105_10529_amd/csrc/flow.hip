@@ -648,13 +648,14 @@ __device__ __forceinline__ void pq_quad_backward(const float* o, float vlast, fl
     return t;
   });
   int b = p == 0 || start <= yv ? KP * p : -1;
-  float S = start, Sb = S;
+  float S = start, Sb = S, first2 = 0.0f;
 #pragma unroll
   for (int k = 0; k < KP; ++k) {
     const bool take = k > 0 && S <= yv;
     b = take ? KP * p + k : b;
     Sb = take ? S : Sb;
     S = __builtin_fmaf(W[k], isw, S);
+    if (k == 1) first2 = S;
   }
   b = max(b, qdpp<QX1>(b));
   b = max(b, qdpp<QX2>(b));
@@ -740,7 +741,9 @@ __device__ __forceinline__ void pq_quad_backward(const float* o, float vlast, fl
   for (int k = 0; k < KP; ++k) {
     gw[k] = W[k] * (gw[k] - SW);
     const float wl = k > 0 ? W[k - 1] : (p > 0 ? wl0 : 0.0f);
-    gv[k] = V[k] * __builtin_fmaf(-(wl + W[k]), SG * 0.5f, gv[k]);
+    // the first two widths together are the second edge
+    const float ws = k == 1 && p == 0 ? first2 : wl + W[k];
+    gv[k] = V[k] * __builtin_fmaf(-ws, SG * 0.5f, gv[k]);
   }
   glast = V[KP] * __builtin_fmaf(-W[KP - 1], SG * 0.5f, glast);
 }
