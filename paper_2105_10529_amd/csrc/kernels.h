@@ -382,9 +382,12 @@ __global__ void __launch_bounds__(BLOCK) k_select(DevCfg c, const double* __rest
 // Stage 2: the weights of the events k_select kept for this block (chunks of
 // BLOCK list entries; the last chunk's idle lanes recompute the block's first
 // event with the weight masked).  LISTED = false takes the block's chunks of
-// all events as they are, without stage 1: for no final-state partons, where
-// only the threshold fails events (5 x 1e5 g g -> t t~ events 299 us with the
-// selection, 260 us without); the observables need the lists.
+// all events as they are, without stage 1: where no final-state partons are cut
+// on, 58 to 97 % of the events are above threshold, so that up to two chunks per
+// block need as many passes with the selection as without.  5 x 1e5 g g -> t t~
+// events 297 us with the selection, 276 us without; 2 x 1e6 events on an
+// adapted grid (65 % kept) 344 us with it, 387 us without, on a uniform one 436
+// and 393 us.  The observables need the lists.
 template <int NG, int CH, class RA, bool LISTED = true>
 __global__ void __launch_bounds__(BLOCK) k_vegas(DevCfg c, const double* __restrict__ edges_g, uint64_t iter,
                                                  int64_t N, uint64_t seed, double* __restrict__ partials,
@@ -686,7 +689,7 @@ Launchers make_launchers() {
     L.vegas = [](const DevCfg& c, const double* edges, uint64_t iter, int64_t N, uint64_t seed, double* part,
                  int pstride, int nblk, size_t lds, int* list, int* cnt, int64_t cap, double* wk, hipStream_t s) {
       if constexpr (NG == 0) {
-        if (wk == nullptr) {
+        if (wk == nullptr && N <= 2 * (int64_t)nblk * BLOCK) {
           hipLaunchKernelGGL((k_vegas<NG, CH, RA, false>), dim3(nblk), dim3(BLOCK), lds, s, c, edges, iter, N, seed, part,
                              pstride, list, cnt, cap, wk);
           return;
