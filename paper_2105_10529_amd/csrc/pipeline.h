@@ -532,16 +532,17 @@ __device__ __forceinline__ EventOut<RK> event_weight(const DevCfg& c, const doub
     const V4<RA> a = to_amp<RA, double>(p1), b = to_amp<RA, double>(p2), k = to_amp<RA, double>(gl[0]);
     const V4<RA> t = to_amp<RA, RK>(top), tb = to_amp<RA, RK>(atop);
     const RA m_a = to_amp_s(mt, (RA*)nullptr);
-    // one copy of the matrix-element code for the four assignments
+    // one copy of the matrix-element code for the two beam assignments
     RK r1 = zero, r2 = zero, r3 = zero, r4 = zero;
 #pragma unroll 1
-    for (int j = 0; j < 4; ++j) {
-      const bool sw = (j & 1) != 0, cc = (j & 2) != 0;
-      const RK rj = pre * to_k(me_qg_q<RA>(sw ? b : a, sw ? a : b, cc ? tb : t, cc ? t : tb, k, m_a), (RK*)nullptr);
-      r1 = j == 0 ? rj : r1;
-      r2 = j == 1 ? rj : r2;
-      r3 = j == 2 ? rj : r3;
-      r4 = j == 3 ? rj : r4;
+    for (int j = 0; j < 2; ++j) {
+      RA conj;
+      const RK rj = pre * to_k(me_qg_q<RA>(j ? b : a, j ? a : b, t, tb, k, m_a, conj), (RK*)nullptr);
+      const RK rc = pre * to_k(conj, (RK*)nullptr);
+      r1 = j ? r1 : rj;
+      r2 = j ? rj : r2;
+      r3 = j ? r3 : rc;
+      r4 = j ? rc : r4;
     }
     const double g1 = pdf_at(c, pdf, 0, out.t1, tq), g2 = pdf_at(c, pdf, 0, out.t2, tq);
     const double qs1 = pdf_at(c, pdf, 1, out.t1, tq) + pdf_at(c, pdf, 2, out.t1, tq);

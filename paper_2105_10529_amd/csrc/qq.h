@@ -109,6 +109,11 @@ template <class R> struct SlashC {
 // light current is applied to the top spinors once.  VALU-bound, FP64:
 // q g -> t t~ q, two iterations of 1e6 events (1.7e6 kept), 6.17 -> 1.72 ms;
 // u u~ -> t t~ g at 1e5 points 248 -> 38 us, its derivatives 1497 -> 322 us.
+// The light current and the propagator next to it are applied to the top spinor
+// before the polarisation, once per helicity, so that each polarisation costs
+// a real contraction; and the two charge assignments of q g share the light
+// line: 1.46 -> 1.29 ms, derivatives at 1e5 points 360 -> 253 us (q g) and 171
+// -> 130 us (u u~ -> t t~ g).
 
 // Sum over the top and antitop helicities and the polarisations E of the
 // gluon.  X0, X1[pol]: the light current with the gluon on its incoming or
@@ -128,10 +133,12 @@ __device__ __forceinline__ R top_line_sum(const CV4<R>* X0, const CV4<R>* X1, co
   for (int h = 0; h < 4; ++h) {
     const int l3 = (h & 2) ? 1 : -1, l4 = (h & 1) ? 1 : -1;
     const Sp<R> ub3 = ubar_spinor(pt, mt, l3);
-    const Sp<R> u3 = sbar(ub3);
     const Sp<R> v4 = v_spinor(ptb, mt, l4);
     const CV4<R> J34 = vcur(ub3, v4);
-    const Sp<R> y4 = sl.col(v4), z3 = sl.row(ub3);
+    // the light current next to the antitop, then the propagator; next to the
+    // top, then the propagator: what is left is linear in the polarisation
+    const CV4<R> V2 = vcur(ub3, prop(a3, mt, f3, sl.col(v4)));
+    const CV4<R> V3 = vcur(sbar(prop(a4, mt, f4, sbar(sl.row(ub3)))), v4);
 #pragma unroll
     for (int pol = 0; pol < 2; ++pol) {
       const V4<R> e = E[pol];
@@ -140,8 +147,8 @@ __device__ __forceinline__ R top_line_sum(const CV4<R>* X0, const CV4<R>* X1, co
       K[0] = mul_mi(mdotc(X0[pol], J34));
       K[1] = mul_mi(mdotc(X1[pol], J34));
       // next to the top, next to the antitop
-      K[2] = mul_mi(cscale(ubar_dot(sbar(prop(a3, mt, f3, slash(e, u3))), y4), iL));
-      K[3] = mul_mi(cscale(ubar_dot(z3, prop(a4, mt, f4, slash(e, v4))), iL));
+      K[2] = mul_mi(cscale(mdotr(e, V2), iL));
+      K[3] = mul_mi(cscale(mdotr(e, V3), iL));
       K[4] = cscale(vertex3(e, kg, JL, qL, J34, mq34), i5);
       total = total + colour_form5(K);
     }
@@ -177,16 +184,17 @@ __device__ __forceinline__ R me_qqbar_g(const V4<R>& p1, const V4<R>& p2, const 
                       R(1.0) / (s12 * s34));
 }
 
-// q(p1) g(p2) -> t(pt) t~(ptb) q(k): colour- and helicity-summed |M|^2, g = 1.
+// q(p1) g(p2) -> t(pt) t~(ptb) q(k): colour- and helicity-summed |M|^2, g = 1;
+// and in conj the same with the top and antitop momenta exchanged, which by
+// charge conjugation is that of q~ g -> t t~ q~: the light line is the same.
 template <class R>
 __device__ __forceinline__ R me_qg_q(const V4<R>& p1, const V4<R>& p2, const V4<R>& pt, const V4<R>& ptb,
-                                     const V4<R>& k, R mt) {
+                                     const V4<R>& k, R mt, R& conj) {
   const R z = R(0.0);
   const V4<R> q12 = p1 + p2, q34 = pt + ptb, q15 = p1 - k;
   const R s12 = mdot(q12, q12), s34 = mdot(q34, q34), t15 = mdot(q15, q15);
-  const V4<R> a2 = k - p2, a3 = pt - p2, a4 = p2 - ptb;
+  const V4<R> a2 = k - p2;
   const R i0 = R(1.0) / (s12 * s34), i2 = R(1.0) / (mdot(a2, a2) * s34);
-  const R f3 = R(1.0) / (mdot(a3, a3) - mt * mt), f4 = R(1.0) / (mdot(a4, a4) - mt * mt);
   V4<R> E[2];
   lin_pols(p2, E);
   const Sp<R> u1 = sbar(ubar_spinor(p1, z, 1)), ub5 = ubar_spinor(k, z, 1), u5 = sbar(ub5);
@@ -197,9 +205,21 @@ __device__ __forceinline__ R me_qg_q(const V4<R>& p1, const V4<R>& p2, const V4<
     X0[pol] = cvscale(vcur(ub5, slash(q12, slash(E[pol], u1))), i0);
     X1[pol] = cvscale(vcur(sbar(slash(a2, slash(E[pol], u5))), u1), i2);
   }
-  // three-gluon vertex: (e, p2), (J15, p1 - k), (J34, -(pt + ptb))
-  return top_line_sum(X0, X1, vcur(ub5, u1), R(1.0) / t15, E, pt, ptb, mt, a3, f3, a4, f4, p2, q15, q34,
-                      R(1.0) / (t15 * s34));
+  const CV4<R> J15 = vcur(ub5, u1);
+  const R iL = R(1.0) / t15, i5 = R(1.0) / (t15 * s34);
+  R r = z, rc = z;
+#pragma unroll 1
+  for (int cc = 0; cc < 2; ++cc) {
+    const V4<R> a = cc ? ptb : pt, b = cc ? pt : ptb;
+    const V4<R> a3 = a - p2, a4 = p2 - b;
+    const R f3 = R(1.0) / (mdot(a3, a3) - mt * mt), f4 = R(1.0) / (mdot(a4, a4) - mt * mt);
+    // three-gluon vertex: (e, p2), (J15, p1 - k), (J34, -(pt + ptb))
+    const R t = top_line_sum(X0, X1, J15, iL, E, a, b, mt, a3, f3, a4, f4, p2, q15, q34, i5);
+    r = cc ? r : t;
+    rc = t;
+  }
+  conj = rc;
+  return r;
 }
 
 }  // namespace mf
