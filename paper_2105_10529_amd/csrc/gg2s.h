@@ -168,7 +168,7 @@ template <class R>
 __global__ void __launch_bounds__(CBLOCK) k_s2_colour(const R* __restrict__ amp, int64_t ld, int64_t nc, int nsl,
                                                       int first, int last, double* __restrict__ me,
                                                       const int* __restrict__ idx, const double* __restrict__ wpre,
-                                                      double* __restrict__ w, double inv_den) {
+                                                      double* __restrict__ w, int raw, double inv_den) {
   typedef typename Mfma<R>::v4 v4;
   __shared__ R cs[2 * 2 * 64 * 4];
   __shared__ double part[CBLOCK / 64][CT];
@@ -248,7 +248,7 @@ __global__ void __launch_bounds__(CBLOCK) k_s2_colour(const R* __restrict__ amp,
         if (last) {
           const int e = idx[col];
           const double we = wpre[e] * (v * inv_den);
-          w[e] = isfinite(we) ? we : 0.0;
+          w[e] = raw || isfinite(we) ? we : 0.0;
         }
       }
     }
@@ -278,7 +278,7 @@ inline void ws_free(void* p) {
 // states.  Synchronises the stream once (to read the number of passing
 // events).  The workspace grows on demand and belongs to the process handle.
 template <class R>
-hipError_t integrand(const DevCfg& c, const double* u, int64_t n, double* w, void** wsp, hipStream_t s) {
+hipError_t integrand(const DevCfg& c, const double* u, int64_t n, double* w, int raw, void** wsp, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   Ws* ws = static_cast<Ws*>(*wsp);
   if (!ws) {
@@ -299,7 +299,7 @@ hipError_t integrand(const DevCfg& c, const double* u, int64_t n, double* w, voi
   }
   hipLaunchKernelGGL(st::k_st_zero, dim3(1), dim3(1), 0, s, ws->d_count);
   hipLaunchKernelGGL(st::k_st_select<NG>, dim3((unsigned)((n + BLOCK - 1) / BLOCK)), dim3(BLOCK), 0, s, c, u, n, w,
-                     ws->d_wpre, ws->d_idx, ws->d_count);
+                     raw, ws->d_wpre, ws->d_idx, ws->d_count);
   S2_TRY(hipGetLastError());
   int count = 0;
   S2_TRY(hipMemcpyAsync(&count, ws->d_count, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -332,7 +332,7 @@ hipError_t integrand(const DevCfg& c, const double* u, int64_t n, double* w, voi
     for (int pass = 0; pass < NPASS; ++pass) {
       hipLaunchKernelGGL((k_s2_amp<R>), dim3(ablk), dim3(AW), 0, s, c, u, n, idx, nc, pass * HGP<R>, amp, ld);
       hipLaunchKernelGGL((k_s2_colour<R>), dim3(cblk), dim3(CBLOCK), 0, s, amp, ld, nc, SLICES<R>,
-                         pass == 0 ? 1 : 0, pass == NPASS - 1 ? 1 : 0, ws->d_me, idx, ws->d_wpre, w, inv_den);
+                         pass == 0 ? 1 : 0, pass == NPASS - 1 ? 1 : 0, ws->d_me, idx, ws->d_wpre, w, raw, inv_den);
     }
     S2_TRY(hipGetLastError());
   }

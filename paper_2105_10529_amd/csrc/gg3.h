@@ -350,12 +350,13 @@ template <class R> __device__ __forceinline__ constexpr int g3_kidx(int s, int g
 // indices 16 s .. 16 s + 15 over the four r; the result lane l holds
 // Z[g3_kidx(rb, l / 16, i)][event l % 16] in element i, whose matching
 // amplitudes are the B values the lane loaded for s = rb.
-// first: the pass overwrites me[]; last: it also writes the event weights.
+// first: the pass overwrites me[]; last: it also writes the event weights
+// (raw: also those that are not finite, else 0).
 template <class R>
 __global__ void __launch_bounds__(CBLOCK) k_g3_colour(const R* __restrict__ amp, int64_t ld, int64_t nc,
                                                       int nsl, int first, int last, double* __restrict__ me,
                                                       const int* __restrict__ idx, const double* __restrict__ wpre,
-                                                      double* __restrict__ w, double inv_den) {
+                                                      double* __restrict__ w, int raw, double inv_den) {
   typedef typename G3Mfma<R>::v4 v4;
   typedef float f4 __attribute__((ext_vector_type(4)));
   // 16-event column blocks per tile: two in FP32, one in FP64 (register budget)
@@ -434,7 +435,7 @@ __global__ void __launch_bounds__(CBLOCK) k_g3_colour(const R* __restrict__ amp,
         if (last) {
           const int e = idx[col];
           const double we = wpre[e] * (v * inv_den);
-          w[e] = isfinite(we) ? we : 0.0;
+          w[e] = raw || isfinite(we) ? we : 0.0;
         }
       }
     }
@@ -460,7 +461,7 @@ inline void ws_free(void* p) {
   } while (0)
 
 template <class R>
-hipError_t integrand(const DevCfg& c, const double* u, int64_t n, double* w, void** wsp, hipStream_t s) {
+hipError_t integrand(const DevCfg& c, const double* u, int64_t n, double* w, int raw, void** wsp, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   Ws* ws = static_cast<Ws*>(*wsp);
   if (!ws) {
@@ -481,7 +482,7 @@ hipError_t integrand(const DevCfg& c, const double* u, int64_t n, double* w, voi
   }
   hipLaunchKernelGGL(st::k_st_zero, dim3(1), dim3(1), 0, s, ws->d_count);
   hipLaunchKernelGGL(st::k_st_select<NG>, dim3((unsigned)((n + BLOCK - 1) / BLOCK)), dim3(BLOCK), 0, s, c, u, n, w,
-                     ws->d_wpre, ws->d_idx, ws->d_count);
+                     raw, ws->d_wpre, ws->d_idx, ws->d_count);
   G3_TRY(hipGetLastError());
   int count = 0;
   G3_TRY(hipMemcpyAsync(&count, ws->d_count, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -525,7 +526,7 @@ hipError_t integrand(const DevCfg& c, const double* u, int64_t n, double* w, voi
       hipLaunchKernelGGL((k_g3_amp<R>), dim3(ablk, own ? 1 : gs / gpb), dim3(AWAVE), 0, s, c, u, n, idx, nc, pass * gs,
                          gpb, amp, ld);
       hipLaunchKernelGGL((k_g3_colour<R>), dim3(cblk), dim3(CBLOCK), 0, s, amp, ld, nc, nsl, pass == 0 ? 1 : 0,
-                         pass == NPASS - 1 ? 1 : 0, ws->d_me, idx, ws->d_wpre, w, inv_den);
+                         pass == NPASS - 1 ? 1 : 0, ws->d_me, idx, ws->d_wpre, w, raw, inv_den);
     }
     G3_TRY(hipGetLastError());
   }

@@ -136,8 +136,8 @@ __device__ __forceinline__ int state_lanes(int nsel) {
 // against 120 us through the offsets).
 template <int NG, int CH, class RA, int LANES>
 __device__ __forceinline__ void integrand_loop(const DevCfg& c, const double* __restrict__ u, int64_t n,
-                                               double* __restrict__ w, const int* __restrict__ list, int64_t cap,
-                                               const int* pre, int nblk, int nsel) {
+                                               double* __restrict__ w, int raw, const int* __restrict__ list,
+                                               int64_t cap, const int* pre, int nblk, int nsel) {
   constexpr bool DEALT = NG > 0;
   constexpr int PER = BLOCK / LANES;
   const int* own = list + (int64_t)blockIdx.x * cap;
@@ -152,25 +152,27 @@ __device__ __forceinline__ void integrand_loop(const DevCfg& c, const double* __
     for (int k = 0; k < MAXD; ++k)
       if (k < c.ndim) x[k] = u[(int64_t)k * n + e];
     EventOut<double> r = event_weight<NG, CH, RA, double, LANES, true>(c, x, c.mt, c.pdfc);
-    const double v = isfinite(r.w) ? r.w : 0.0;
+    const double v = raw || isfinite(r.w) ? r.w : 0.0;
     if (live && threadIdx.x % LANES == 0) w[e] = v;
   }
 }
-// LANES = 0: state_lanes of the number of kept points.
+// LANES = 0: state_lanes of the number of kept points; raw: a weight that is
+// not finite is stored as it is instead of 0.
 template <int NG, int CH, class RA, int LANES>
 __global__ void __launch_bounds__(BLOCK) k_integrand(DevCfg c, const double* __restrict__ u, int64_t n,
-                                                     double* __restrict__ w, const int* __restrict__ list,
-                                                     const int* __restrict__ cnt, int nblk, int64_t cap) {
+                                                     double* __restrict__ w, int raw,
+                                                     const int* __restrict__ list, const int* __restrict__ cnt,
+                                                     int nblk, int64_t cap) {
   __shared__ int pre[NG > 0 ? MAX_BLOCKS + 1 : 1];
   if constexpr (NG > 0) list_offsets(cnt, nblk, pre);
   const int nsel = __builtin_amdgcn_readfirstlane(NG > 0 ? pre[nblk] : cnt[blockIdx.x]);
   if constexpr (LANES != 0) {
-    integrand_loop<NG, CH, RA, LANES>(c, u, n, w, list, cap, pre, nblk, nsel);
+    integrand_loop<NG, CH, RA, LANES>(c, u, n, w, raw, list, cap, pre, nblk, nsel);
   } else {
     const int lanes = state_lanes(nsel);
-    if (lanes == 16) integrand_loop<NG, CH, RA, 16>(c, u, n, w, list, cap, pre, nblk, nsel);
-    else if (lanes == 8) integrand_loop<NG, CH, RA, 8>(c, u, n, w, list, cap, pre, nblk, nsel);
-    else integrand_loop<NG, CH, RA, 4>(c, u, n, w, list, cap, pre, nblk, nsel);
+    if (lanes == 16) integrand_loop<NG, CH, RA, 16>(c, u, n, w, raw, list, cap, pre, nblk, nsel);
+    else if (lanes == 8) integrand_loop<NG, CH, RA, 8>(c, u, n, w, raw, list, cap, pre, nblk, nsel);
+    else integrand_loop<NG, CH, RA, 4>(c, u, n, w, raw, list, cap, pre, nblk, nsel);
   }
 }
 
@@ -674,15 +676,15 @@ Launchers make_launchers() {
   // g g -> t t~ g g, two iterations of 2000 events 1.66 -> 0.43 ms, of 1e5
   // events 3.16 -> 2.29 ms; from 1.4e5 events the fused kernel is as fast)
   L.staged_events = LANES == 0 ? 1 << 17 : 0;
-  L.integrand = [](const DevCfg& c, const double* u, int64_t n, double* w, int nblk, int* list, int* cnt,
+  L.integrand = [](const DevCfg& c, const double* u, int64_t n, double* w, int raw, int nblk, int* list, int* cnt,
                    int64_t cap, hipStream_t s) {
     hipLaunchKernelGGL((k_select_points<NG>), dim3(nblk), dim3(BLOCK), 0, s, c, u, n, w, list, cnt, cap);
     // enough blocks for every kept point, four per compute unit at most (the
     // kernels hold one to three; more would only repeat the offsets)
     const int64_t want = (n * (LANES ? LANES : 16) + BLOCK - 1) / BLOCK;
     const unsigned grid = NG == 0 ? (unsigned)nblk : (unsigned)(want < 1024 ? want : 1024);
-    hipLaunchKernelGGL((k_integrand<NG, CH, RA, LANES>), dim3(grid), dim3(BLOCK), 0, s, c, u, n, w, list, cnt, nblk,
-                       cap);
+    hipLaunchKernelGGL((k_integrand<NG, CH, RA, LANES>), dim3(grid), dim3(BLOCK), 0, s, c, u, n, w, raw, list, cnt,
+                       nblk, cap);
   };
   L.vegas = nullptr;
   if constexpr (FUSED != 0) {

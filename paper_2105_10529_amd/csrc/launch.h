@@ -112,8 +112,10 @@ struct Launchers {
   // lanes
   int64_t staged_events = 0;
   // selection (k_select_points) then the weights of the kept points
-  // (k_integrand); list/cnt/cap as for vegas
-  void (*integrand)(const DevCfg&, const double*, int64_t, double*, int, int*, int*, int64_t, hipStream_t);
+  // (k_integrand); list/cnt/cap as for vegas.  raw (an int, here and in
+  // integrand_ws): 1 stores a weight that is not finite as it is, for the
+  // accumulation that counts and drops it; 0 stores 0
+  void (*integrand)(const DevCfg&, const double*, int64_t, double*, int, int, int*, int*, int64_t, hipStream_t);
   void (*integrand_grad)(const DevCfg&, const double*, int64_t, double*, double*, int, hipStream_t);
   // selection (k_select) then the fused weight kernel (k_vegas) of one
   // iteration; list/cnt/cap: per-block event lists, [nblk][cap] and [nblk]
@@ -130,7 +132,7 @@ struct Launchers {
   // (*ws, created on first use, released with ws_free); used instead of
   // `integrand` when set.  Synchronises the stream (it reads the number of
   // events that pass the cuts).
-  hipError_t (*integrand_ws)(const DevCfg&, const double*, int64_t, double*, void**, hipStream_t);
+  hipError_t (*integrand_ws)(const DevCfg&, const double*, int64_t, double*, int, void**, hipStream_t);
   void (*ws_free)(void*);
 };
 

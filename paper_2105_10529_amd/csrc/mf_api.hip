@@ -710,9 +710,11 @@ mf_status ensure_select(mf_process* p, int64_t n, int nblk, hipStream_t s) {
 }
 
 // The integrand of the process on n mapped points (single-kernel or staged).
-mf_status run_integrand(mf_process* p, const double* x, int64_t n, double* w, hipStream_t s) {
+// raw: weights that are not finite are stored as they are, for a caller that
+// counts them; otherwise as 0.
+mf_status run_integrand(mf_process* p, const double* x, int64_t n, double* w, hipStream_t s, bool raw = false) {
   if (p->L.integrand_ws) {
-    hipError_t e = p->L.integrand_ws(p->dc, x, n, w, &p->ws, s);
+    hipError_t e = p->L.integrand_ws(p->dc, x, n, w, raw ? 1 : 0, &p->ws, s);
     if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation)
       return fail(MF_ENOMEM, "integrand workspace allocation failed");
     if (e != hipSuccess) return fail(MF_EDEVICE, "integrand: %s", hipGetErrorString(e));
@@ -720,7 +722,7 @@ mf_status run_integrand(mf_process* p, const double* x, int64_t n, double* w, hi
   }
   mf_status st = ensure_select(p, n, blocks_for(n), s);
   if (st != MF_OK) return st;
-  p->L.integrand(p->dc, x, n, w, blocks_for(n), p->d_sel, p->d_selcnt, p->sel_cap, s);
+  p->L.integrand(p->dc, x, n, w, raw ? 1 : 0, blocks_for(n), p->d_sel, p->d_selcnt, p->sel_cap, s);
   return check_stream_launch("k_integrand");
 }
 
@@ -948,7 +950,7 @@ mf_status mf_integrand_noalloc(mf_process* p, const double* u, int64_t n, double
   const int64_t cap = (n + (int64_t)nblk * BLOCK - 1) / ((int64_t)nblk * BLOCK) * BLOCK;
   int* cnt = g_noalloc_ptr[dev];
   int* list = cnt + MAX_BLOCKS;  // nblk * cap <= NOALLOC_MAX_POINTS entries (see the array's bound)
-  p->L.integrand(p->dc, u, n, w, nblk, list, cnt, cap, (hipStream_t)stream);
+  p->L.integrand(p->dc, u, n, w, 0, nblk, list, cnt, cap, (hipStream_t)stream);
   return check_stream_launch("k_integrand");
 }
 
@@ -1094,7 +1096,7 @@ mf_status mf_integrate(mf_process* p, const mf_integrate_opts* o, mf_result* r) 
       const int64_t N = o->n_events;
       hipLaunchKernelGGL(k_stage_points, dim3(nblk), dim3(256), sizeof(double) * d * (nb + 1), s, p->d_edges, d, nb,
                          iter, N, p->cfg.seed, p->d_sx, p->d_sjac, p->d_sbins);
-      mf_status sst = run_integrand(p, p->d_sx, N, p->d_sw, s);
+      mf_status sst = run_integrand(p, p->d_sx, N, p->d_sw, s, true);
       if (sst != MF_OK) return sst;
       hipLaunchKernelGGL(k_stage_accumulate, dim3(nblk), dim3(256), 0, s, p->d_sw, p->d_sjac, p->d_sbins, d, nb, N,
                          p->d_part, p->pstride);

@@ -32,10 +32,11 @@ __device__ __forceinline__ bool kinematics(const DevCfg& c, const double* x, dou
 static __global__ void k_st_zero(int* count) { *count = 0; }
 
 // Every point: w = 0, wpre = the weight without |M|^2 (0 if the point fails
-// threshold or cuts), and the passing points' indices appended to idx.
+// threshold or cuts), and the passing points' indices appended to idx.  raw: a
+// passing point whose wpre is not finite has it as its w.
 template <int NG>
 __global__ void __launch_bounds__(BLOCK) k_st_select(DevCfg c, const double* __restrict__ u, int64_t n,
-                                                     double* __restrict__ w, double* __restrict__ wpre,
+                                                     double* __restrict__ w, int raw, double* __restrict__ wpre,
                                                      int* __restrict__ idx, int* __restrict__ count) {
   const int64_t e0 = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
   const bool live = e0 < n;
@@ -50,9 +51,10 @@ __global__ void __launch_bounds__(BLOCK) k_st_select(DevCfg c, const double* __r
   const double tq = c.dyn_scale ? q_position(half_ht<NG>(c.mt, top, atop, gl)) : 0.0;
   const double pre = c.norm / (2.0 * shat_k * x[0] * x[1]) * wps *
                      (pdf_at(c, c.pdfc, 0, x_position(c, x[0]), tq) * pdf_at(c, c.pdfc, 0, x_position(c, x[1]), tq));
-  ok = ok && live && isfinite(pre) && pre != 0.0;
+  const bool bad = ok && !isfinite(pre);
+  ok = ok && live && !bad && pre != 0.0;
   if (live) {
-    w[e] = 0.0;
+    w[e] = raw && bad ? pre : 0.0;
     wpre[e] = ok ? pre : 0.0;
   }
   // compaction: one atomic per wave, ranks from the ballot
