@@ -1096,7 +1096,9 @@ mf_status mf_integrate(mf_process* p, const mf_integrate_opts* o, mf_result* r) 
       const int64_t N = o->n_events;
       hipLaunchKernelGGL(k_stage_points, dim3(nblk), dim3(256), sizeof(double) * d * (nb + 1), s, p->d_edges, d, nb,
                          iter, N, p->cfg.seed, p->d_sx, p->d_sjac, p->d_sbins);
-      mf_status sst = run_integrand(p, p->d_sx, N, p->d_sw, s, true);
+      // after a fallback from a learned proposal a count makes the call fail:
+      // kernels that never counted there stay out of it
+      mf_status sst = run_integrand(p, p->d_sx, N, p->d_sw, s, p->L.fused || !o->flow);
       if (sst != MF_OK) return sst;
       hipLaunchKernelGGL(k_stage_accumulate, dim3(nblk), dim3(256), 0, s, p->d_sw, p->d_sjac, p->d_sbins, d, nb, N,
                          p->d_part, p->pstride);

@@ -46,3 +46,12 @@ def test_all_kept_events_are_counted(process, precision, sqrt_s, kw):
     x = np.random.default_rng(3).random((500, far.ndim))
     assert torch.all(far.integrand(to_dev_soa(x)) == 0.0)
     assert torch.any(near.integrand(to_dev_soa(x)) != 0.0)
+
+
+@pytest.mark.parametrize("process,precision,sqrt_s", [("gg>ttxgg", "fp64", 1e110), ("gg>ttxggg", "fp32", 1e41)])
+def test_staged_fallback_of_a_learned_proposal_stays_accepted(process, precision, sqrt_s):
+    """A first flow iteration without a finite weight falls back to VEGAS; the
+    integrand's own non-finite values are not taken for a broken proposal."""
+    p = _p(process, precision, sqrt_s)
+    r = p.integrate(3, 1000, adapt=False, flow=mf.Flow(p.ndim, max_batch=64), fallback_rel_var=1.0)
+    assert r.fallback_iter == 1 and r.n_iter_done == 3 and r.n_nonzero == 0
