@@ -17,12 +17,12 @@
 //     (v_mfma_f32_16x16x4_f32): per slice, Z = C A for a tile of 32 events,
 //     then the dot product A . Z in the epilogue; the operand values loaded
 //     for the product are the ones the dot product needs, so each amplitude
-//     is read once.
+//     is read once.  k_g3_weight adds up the groups of states.
 //
 // This is the event weight of Sec. 2.1 (phase space -> matrix element) with
 // the colour-ordered amplitudes and colour matrix of Sec. 2.2, evaluated in
-// the three-kernel order above; the result of each event does not depend on
-// the lane or the position in the compacted list that evaluates it.
+// the order above; the result of each event does not depend on the lane or the
+// position in the compacted list that evaluates it, nor on the batch it is in.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -89,7 +89,7 @@ struct Ws {
   int* d_idx = nullptr;
   int* d_count = nullptr;
   double* d_wpre = nullptr;
-  double* d_me = nullptr;  // [ld] colour-summed |M|^2 numerators of the chunk
+  double* d_me = nullptr;  // [groups of states][ld] colour-summed |M|^2 numerators of the chunk
   void* d_amp = nullptr;   // [slices of a pass][NQ][ld][4] amplitude type
 };
 
@@ -341,8 +341,9 @@ template <class R> __device__ __forceinline__ constexpr int g3_kidx(int s, int g
   return std::is_same<R, float>::value ? 16 * s + 4 * g + r : 16 * s + g + 4 * r;
 }
 
-// Colour sum of one pass over the nsl slices (a multiple of 4) of the buffer for the nc
-// events of the chunk.  C in LDS in A-operand order (exact integer numerators,
+// Colour sums over the slices of one pass for the nc events of the chunk:
+// blockIdx.y = q takes the q-th group of nsl slices (a multiple of 4), whose sum
+// is me[q ld + event].  C in LDS in A-operand order (exact integer numerators,
 // held as FP32): entry ((rb * 8 + s) * 64 + l) * 4 + r holds
 // C[16 rb + l % 16][g3_kidx(s, l / 16, r)] (zero beyond the 120 orderings).
 // For the MFMA step (s, r) lane l supplies that entry and
@@ -350,13 +351,9 @@ template <class R> __device__ __forceinline__ constexpr int g3_kidx(int s, int g
 // indices 16 s .. 16 s + 15 over the four r; the result lane l holds
 // Z[g3_kidx(rb, l / 16, i)][event l % 16] in element i, whose matching
 // amplitudes are the B values the lane loaded for s = rb.
-// first: the pass overwrites me[]; last: it also writes the event weights
-// (raw: also those that are not finite, else 0).
 template <class R>
 __global__ void __launch_bounds__(CBLOCK) k_g3_colour(const R* __restrict__ amp, int64_t ld, int64_t nc,
-                                                      int nsl, int first, int last, double* __restrict__ me,
-                                                      const int* __restrict__ idx, const double* __restrict__ wpre,
-                                                      double* __restrict__ w, int raw, double inv_den) {
+                                                      int nsl, double* __restrict__ me) {
   typedef typename G3Mfma<R>::v4 v4;
   typedef float f4 __attribute__((ext_vector_type(4)));
   // 16-event column blocks per tile: two in FP32, one in FP64 (register budget)
@@ -372,6 +369,8 @@ __global__ void __launch_bounds__(CBLOCK) k_g3_colour(const R* __restrict__ amp,
   __syncthreads();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4, c16 = lane & 15;
   const int64_t ntile = (nc + CTR - 1) / CTR;
+  amp += (int64_t)blockIdx.y * nsl * NQ * ld * 4;
+  me += (int64_t)blockIdx.y * ld;
   for (int64_t tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
     const int64_t c0 = tile * CTR;
     double sum[2] = {0.0, 0.0};
@@ -430,17 +429,28 @@ __global__ void __launch_bounds__(CBLOCK) k_g3_colour(const R* __restrict__ amp,
         double v = part[0][threadIdx.x];
 #pragma unroll
         for (int q = 1; q < CBLOCK / 64; ++q) v += part[q][threadIdx.x];
-        if (!first) v += me[col];
         me[col] = v;
-        if (last) {
-          const int e = idx[col];
-          const double we = wpre[e] * (v * inv_den);
-          w[e] = raw || isfinite(we) ? we : 0.0;
-        }
       }
     }
     __syncthreads();
   }
+}
+
+// The event weights from the sums of all groups, added in order.  The groups
+// are those of the smallest pass whatever a pass holds, so that an event's sum
+// does not depend on its batch.  raw: a weight that is not finite is stored as
+// it is instead of 0.
+static __global__ void __launch_bounds__(256) k_g3_weight(const double* __restrict__ me, int64_t ld, int64_t nc, int ngrp,
+                                                          const int* __restrict__ idx,
+                                                          const double* __restrict__ wpre, double* __restrict__ w,
+                                                          int raw, double inv_den) {
+  const int64_t col = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (col >= nc) return;
+  double v = me[col];
+  for (int q = 1; q < ngrp; ++q) v += me[q * ld + col];
+  const int e = idx[col];
+  const double we = wpre[e] * (v * inv_den);
+  w[e] = raw || isfinite(we) ? we : 0.0;
 }
 
 inline void ws_free(void* p) {
@@ -497,6 +507,7 @@ hipError_t integrand(const DevCfg& c, const double* u, int64_t n, double* w, int
   int64_t rounds = 0;
   const int gs = own ? 1 : pass_states<R>(ld / AWAVE, rounds);
   const int NPASS = own ? 1 : GSTATES / gs, nsl = own ? 4 : 4 * NHS<R> * gs;
+  const int grp = own ? 4 : 4 * NHS<R> * GSP, ngrp = nsl / grp;  // slices of the smallest pass; groups of this one
   const int gpb = gs == GSP ? GSP : 1;  // gluon states of a block
   const size_t bytes = sizeof(R) * (size_t)nsl * NQ * (size_t)ld * 4;
   if (ws->amp_bytes < bytes) {
@@ -510,7 +521,7 @@ hipError_t integrand(const DevCfg& c, const double* u, int64_t n, double* w, int
     (void)hipFree(ws->d_me);
     ws->d_me = nullptr;
     ws->ld = 0;
-    G3_TRY(hipMalloc(&ws->d_me, sizeof(double) * ld));
+    G3_TRY(hipMalloc(&ws->d_me, sizeof(double) * (GSTATES / GSP) * ld));
     ws->ld = ld;
   }
   R* amp = static_cast<R*>(ws->d_amp);
@@ -521,13 +532,16 @@ hipError_t integrand(const DevCfg& c, const double* u, int64_t n, double* w, int
     const unsigned ablk = (unsigned)((nc + AWAVE - 1) / AWAVE);
     const int64_t ntile = (nc + (std::is_same<R, float>::value ? CT : CT / 2) - 1) /
                           (std::is_same<R, float>::value ? CT : CT / 2);
-    const unsigned cblk = (unsigned)(ntile < CMAX_BLOCKS ? ntile : CMAX_BLOCKS);
+    const int64_t cmax = CMAX_BLOCKS / ngrp;
+    const unsigned cblk = (unsigned)(ntile < cmax ? ntile : cmax);
     for (int pass = 0; pass < NPASS; ++pass) {
       hipLaunchKernelGGL((k_g3_amp<R>), dim3(ablk, own ? 1 : gs / gpb), dim3(AWAVE), 0, s, c, u, n, idx, nc, pass * gs,
                          gpb, amp, ld);
-      hipLaunchKernelGGL((k_g3_colour<R>), dim3(cblk), dim3(CBLOCK), 0, s, amp, ld, nc, nsl, pass == 0 ? 1 : 0,
-                         pass == NPASS - 1 ? 1 : 0, ws->d_me, idx, ws->d_wpre, w, raw, inv_den);
+      hipLaunchKernelGGL((k_g3_colour<R>), dim3(cblk, ngrp), dim3(CBLOCK), 0, s, amp, ld, nc, grp,
+                         ws->d_me + (int64_t)pass * ngrp * ld);
     }
+    hipLaunchKernelGGL(k_g3_weight, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, s, ws->d_me, ld, nc, NPASS * ngrp,
+                       idx, ws->d_wpre, w, raw, inv_den);
     G3_TRY(hipGetLastError());
   }
   return hipSuccess;
