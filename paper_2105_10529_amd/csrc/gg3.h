@@ -29,6 +29,7 @@
 #include <type_traits>
 
 #include "amp.h"
+#include "g3_pass.h"
 #include "gen/amp_gg_m5.h"
 #include "launch.h"
 #include "pipeline.h"
@@ -41,15 +42,13 @@ constexpr int NG = 3;
 constexpr int NF = AMP_M5_NF;          // 120 orderings
 constexpr int NQ = AMP_M5_NQ;          // 32 groups of four (padded to 128)
 constexpr int STATES = AMP_M5_STATES;  // 64 = 2 antitop helicities x 2^5 gluon polarisations
-constexpr int GSTATES = STATES / 2;    // gluon polarisation states
+static_assert(GSTATES == STATES / 2, "gluon polarisation states of either antitop helicity");
 // Antitop helicities of a summed pass: in FP64 the second repeats the first
 // (flipping both top helicities conjugates the amplitudes, whose gluon
 // polarisation vectors are real) and the sum is doubled; FP32 keeps both,
 // each with its own rounding.  g g -> t t~ g g g FP64 at 20000 points:
 // 20.7 -> 3.5 ms with the launches below.
 template <class R> constexpr int NHS = fp64_amp<R>::value ? 1 : 2;
-constexpr int GSP = 4;                 // gluon states per amplitude pass of a full chunk
-constexpr int SLICES = GSP * 2 * 4;    // (gluon state, antitop, top helicity, re/im) of it
 constexpr int AWAVE = 64;              // amplitude kernel block: one wave (LDS tables per wave)
 constexpr int CT = 32;                 // events per colour tile (two 16-column MFMA blocks)
 constexpr int CBLOCK = 256;            // colour kernel block: 4 waves x 8 slices
@@ -60,25 +59,10 @@ template <class R> constexpr int64_t NCMAX_R = std::is_same<R, float>::value ? N
 // amplitude blocks the chip holds at once (by their LDS tables: 35 or 70 KB)
 template <class R> constexpr int64_t ARES = std::is_same<R, float>::value ? 1024 : 512;
 
-// Gluon states of one amplitude pass over a chunk of ablk blocks of events
-// (one wave each).  A full chunk fills the chip by itself: GSP states per
-// pass, all in one block.  A smaller one would leave most SIMDs idle, pass
-// after pass, so it takes one block per gluon state and as many states per
-// pass as give the fewest rounds of the chip over all passes, within the same
-// buffer of 2 GiB (the smallest such pass).  FP32, 1.3e4 passing points: 196
-// blocks in each of 8 passes 13.7 ms, 6272 blocks in one pass 4.6 ms.
-template <class R> int pass_states(int64_t ablk, int64_t& rounds) {
-  int best = GSP;
-  rounds = 0;
-  for (int gs = GSP; gs <= GSTATES; gs *= 2) {
-    if (gs > GSP && (int64_t)gs * NHS<R> * ablk * AWAVE > (int64_t)GSP * 2 * NCMAX_R<R>) break;
-    const int64_t r = (GSTATES / gs) * ((ablk * gs + ARES<R> - 1) / ARES<R>);
-    if (rounds == 0 || r < rounds) {
-      rounds = r;
-      best = gs;
-    }
-  }
-  return best;
+// Gluon states of a pass over a chunk of ablk blocks of events that fit the
+// buffer of the smallest pass over a full chunk, 2 GiB.
+template <class R> constexpr int64_t buffer_states(int64_t ablk) {
+  return (int64_t)GSP * 2 * NCMAX_R<R> / (NHS<R> * ablk * AWAVE);
 }
 
 // Workspace owned by the process handle (grown on demand, freed with it).
@@ -504,11 +488,10 @@ hipError_t integrand(const DevCfg& c, const double* u, int64_t n, double* w, int
   // all states in passes of gs gluon states, or one state per point in a
   // single pass
   const bool own = c.helicity != 0;
-  int64_t rounds = 0;
-  const int gs = own ? 1 : pass_states<R>(ld / AWAVE, rounds);
+  const Pass ps = own ? Pass{1, 1} : pass_shape(ld / AWAVE, ARES<R>, buffer_states<R>(ld / AWAVE));
+  const int gs = ps.states, gpb = ps.per_block;
   const int NPASS = own ? 1 : GSTATES / gs, nsl = own ? 4 : 4 * NHS<R> * gs;
   const int grp = own ? 4 : 4 * NHS<R> * GSP, ngrp = nsl / grp;  // slices of the smallest pass; groups of this one
-  const int gpb = gs == GSP ? GSP : 1;  // gluon states of a block
   const size_t bytes = sizeof(R) * (size_t)nsl * NQ * (size_t)ld * 4;
   if (ws->amp_bytes < bytes) {
     (void)hipFree(ws->d_amp);
