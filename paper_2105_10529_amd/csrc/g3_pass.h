@@ -43,5 +43,16 @@ inline Pass pass_shape(int64_t blocks, int64_t resident, int64_t max_states) {
   return best;
 }
 
+// The pass whose buffer can be had: alloc(p) provides it or returns false, and
+// then a smaller pass is tried, down to the smallest.
+template <class Alloc> bool fitting_pass(int64_t blocks, int64_t resident, int64_t max_states, Alloc alloc, Pass& p) {
+  for (;;) {
+    p = pass_shape(blocks, resident, max_states);
+    if (alloc(p)) return true;
+    if (p.states == GSP) return false;
+    max_states = p.states / 2;
+  }
+}
+
 }  // namespace g3
 }  // namespace mf

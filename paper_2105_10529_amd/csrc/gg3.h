@@ -25,6 +25,7 @@
 // position in the compacted list that evaluates it, nor on the batch it is in.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stdint.h>
 
 #include <type_traits>
 
@@ -70,6 +71,7 @@ struct Ws {
   int64_t cap_n = 0;  // points: idx, wpre
   int64_t ld = 0;     // columns of d_me (multiple of AWAVE)
   size_t amp_bytes = 0;
+  size_t amp_max = SIZE_MAX;  // larger amplitude buffers could not be had
   int* d_idx = nullptr;
   int* d_count = nullptr;
   double* d_wpre = nullptr;
@@ -488,18 +490,36 @@ hipError_t integrand(const DevCfg& c, const double* u, int64_t n, double* w, int
   // all states in passes of gs gluon states, or one state per point in a
   // single pass
   const bool own = c.helicity != 0;
-  const Pass ps = own ? Pass{1, 1} : pass_shape(ld / AWAVE, ARES<R>, buffer_states<R>(ld / AWAVE));
-  const int gs = ps.states, gpb = ps.per_block;
-  const int NPASS = own ? 1 : GSTATES / gs, nsl = own ? 4 : 4 * NHS<R> * gs;
-  const int grp = own ? 4 : 4 * NHS<R> * GSP, ngrp = nsl / grp;  // slices of the smallest pass; groups of this one
-  const size_t bytes = sizeof(R) * (size_t)nsl * NQ * (size_t)ld * 4;
-  if (ws->amp_bytes < bytes) {
+  // the amplitude buffer of a pass; where it cannot be had a smaller pass is
+  // taken, and this handle asks for no such buffer again
+  const auto slices = [](int gs) { return 4 * NHS<R> * gs; };
+  hipError_t err = hipSuccess;
+  const auto alloc = [&](int nsl, bool smallest) {
+    const size_t bytes = sizeof(R) * (size_t)nsl * NQ * (size_t)ld * 4;
+    if (ws->amp_bytes >= bytes) return true;
+    if (bytes > ws->amp_max && !smallest) return false;
     (void)hipFree(ws->d_amp);
     ws->d_amp = nullptr;
     ws->amp_bytes = 0;
-    G3_TRY(hipMalloc(&ws->d_amp, bytes));
+    err = hipMalloc(&ws->d_amp, bytes);
+    if (err != hipSuccess) {
+      (void)hipGetLastError();
+      ws->d_amp = nullptr;
+      ws->amp_max = bytes - 1;
+      return false;
+    }
     ws->amp_bytes = bytes;
-  }
+    return true;
+  };
+  Pass ps{1, 1};
+  const int64_t eblk = ld / AWAVE;
+  const bool got = own ? alloc(4, true)
+                       : fitting_pass(eblk, ARES<R>, buffer_states<R>(eblk),
+                                      [&](Pass p) { return alloc(slices(p.states), p.states == GSP); }, ps);
+  if (!got) return err;
+  const int gs = ps.states, gpb = ps.per_block;
+  const int NPASS = own ? 1 : GSTATES / gs, nsl = own ? 4 : slices(gs);
+  const int grp = own ? 4 : slices(GSP), ngrp = nsl / grp;  // slices of the smallest pass; groups of this one
   if (ws->ld < ld) {
     (void)hipFree(ws->d_me);
     ws->d_me = nullptr;
