@@ -1,11 +1,13 @@
 """Build the HIP library libmf.so for gfx950: generate the amplitude headers,
-compile each kernel instance in parallel, link in-tree."""
+compile each kernel instance in parallel and check its assembly, link in-tree."""
 from __future__ import annotations
 
 import concurrent.futures as cf
 import os
 import subprocess
 import sys
+
+from . import check_asm
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -22,11 +24,23 @@ def sources():
 
 
 def compile_one(src: str, extra=()) -> str:
-    obj = os.path.join(OBJ, os.path.basename(src)[:-4] + ".o")
-    cmd = [HIPCC, *FLAGS, *extra, "-c", src, "-o", obj]
+    name = os.path.basename(src)[:-4]
+    obj = os.path.join(OBJ, name + ".o")
+    cmd = [HIPCC, *FLAGS, *extra, "-save-temps=obj", "-c", src, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed for {src}:\n{r.stderr[-4000:]}")
+    # of the intermediate files only the device assembly is kept
+    asm = os.path.join(OBJ, name + "-hip-amdgcn-amd-amdhsa-gfx950.s")
+    for f in os.listdir(OBJ):
+        path = os.path.join(OBJ, f)
+        if path != asm and f.startswith((name + "-hip-", name + "-host-", name + ".hip-")):
+            os.remove(path)
+    with open(asm) as f:
+        found = check_asm.join_copies(f.read())
+    if found:
+        raise RuntimeError(f"{src}: registers are copied ahead of the execution mask's restore:\n"
+                           + "\n".join(f"  {fn} {label}: {'; '.join(code[:4])}" for fn, label, code in found))
     return obj
 
 
@@ -46,6 +60,6 @@ def build(jobs: int | None = None, extra=()) -> str:
     return LIB
 
 
-if __name__ == "__main__":
+if __name__ == "__main__":  # python -m paper_2105_10529_amd.build_lib
     extra = sys.argv[1:]
     print(build(extra=extra))
