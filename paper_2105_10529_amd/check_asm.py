@@ -58,3 +58,13 @@ def join_copies(text: str):
             if not _SCALAR.match(ins):
                 ahead.append(ins)
     return found
+
+
+def divergent_loops(text: str):
+    """Functions with a loop that the lanes leave one by one, and how many."""
+    out = {}
+    for fn, _, code in _blocks(text):
+        n = sum(bool(re.match(r"s_andn2_b64\s+exec,\s*exec\b", ins)) for ins in code)
+        if n:
+            out[fn] = out.get(fn, 0) + n
+    return out

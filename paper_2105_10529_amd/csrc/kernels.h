@@ -96,12 +96,14 @@ __device__ __forceinline__ void list_offsets(const int* __restrict__ cnt, int nb
   if (tid == BLOCK - 1 && nblk == MAX_BLOCKS) pre[nblk] = base;
   __syncthreads();
 }
-// The g-th entry of the lists laid end to end (0 <= g < pre[nblk]).
+// The g-th entry of the lists laid end to end (0 <= g < pre[nblk]).  The search
+// takes the same number of steps for every lane, so that the event loops have no
+// divergent region.
 __device__ __forceinline__ int list_entry(const int* __restrict__ list, int64_t cap, const int* pre, int nblk, int g) {
-  int lo = 0, hi = nblk;  // pre[lo] <= g < pre[hi]
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (pre[mid] <= g) lo = mid; else hi = mid;
+  int lo = 0;  // the last list with pre[lo] <= g
+  for (int step = 1 << (31 - __builtin_clz(nblk)); step > 0; step >>= 1) {
+    const int t = lo + step < nblk ? lo + step : nblk;  // pre[nblk] > g
+    lo = pre[t] <= g ? t : lo;
   }
   return list[(int64_t)lo * cap + (g - pre[lo])];
 }

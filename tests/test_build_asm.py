@@ -1,4 +1,7 @@
 """The build's check of the device assembly (CPU)."""
+import glob
+import os
+
 import pytest
 
 from paper_2105_10529_amd import check_asm
@@ -61,3 +64,33 @@ kernel:
 	s_endpgm
 """
     assert check_asm.join_copies(text) == []
+
+
+def test_divergent_loops_are_counted():
+    text = """
+kernel:
+.LBB0_1:
+	s_andn2_b64 exec, exec, s[4:5]
+	s_cbranch_execnz .LBB0_1
+	s_endpgm
+other:
+	s_andn2_b64 s[0:1], exec, s[4:5]
+	s_endpgm
+"""
+    assert check_asm.divergent_loops(text) == {"kernel": 1}
+
+
+def test_the_integrand_kernels_have_no_divergent_loop():
+    """Of the kernels that evaluate the amplitudes of listed points; they fill
+    the register file, where divergent regions are where the compiler moves
+    registers."""
+    units = glob.glob(os.path.join(os.path.dirname(check_asm.__file__), "_build", "inst_*gfx950.s"))
+    if not units:
+        pytest.skip("the library was not built here")
+    seen = 0
+    for path in units:
+        with open(path) as f:
+            text = f.read()
+        seen += text.count("11k_integrandILi") > 0
+        assert [fn for fn in check_asm.divergent_loops(text) if "11k_integrandILi" in fn] == [], path
+    assert seen >= 9
