@@ -1083,7 +1083,7 @@ struct WgradArgs {
   int np, tiles;  // products and their tiles
   int64_t zs;     // floats of one chunk's partials
   int64_t n, chunk;
-  int64_t zmax;   // chunks at most, whatever n
+  int64_t zmax;   // chunks at most, of n events or fewer
   float* part;
 };
 typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -1471,9 +1471,12 @@ namespace {
 // Chunks of events of the weight gradients: at most two workgroups per compute
 // unit over the tiles of all layers, so that all run at once (516 workgroups
 // for one layer took 69 us, 504 took 57), whole slices per chunk, and at most
-// WGRAD_MAX chunks, which the reduction adds up in turn.
+// WGRAD_MAX chunks, which the reduction adds up in turn.  A chunk is one FP32
+// sum; batches whose chunks would be longer than WGRAD_CHUNK events take
+// several such rounds of workgroups instead.
 constexpr int64_t WGRAD_BLOCKS = 512;
 constexpr int64_t WGRAD_MAX = 64;
+constexpr int64_t WGRAD_CHUNK = 16384;
 
 mf_status launch_err(const char* what) {
   hipError_t e = hipGetLastError();
@@ -1503,7 +1506,9 @@ WgradArgs wgrad_args(const mf_flow* f, int64_t n) {
     }
   }
   a.n = n;
-  const int64_t z = std::max<int64_t>(1, std::min(WGRAD_BLOCKS / a.tiles, WGRAD_MAX));
+  const int64_t fit = std::max<int64_t>(1, std::min(WGRAD_BLOCKS / a.tiles, WGRAD_MAX));
+  const int64_t rounds = std::min((n + fit * WGRAD_CHUNK - 1) / (fit * WGRAD_CHUNK), WGRAD_MAX / fit);
+  const int64_t z = fit * rounds;
   a.zmax = z;
   a.chunk = ((n + z - 1) / z + WK - 1) / WK * WK;
   return a;
