@@ -516,8 +516,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
 }
 
 // -------------------------------------------------------- backward layer
-// Operands of the weight gradients, event-major; layer l's are l stride
-// elements further.
+// Operands of the weight gradients, event-major; those of the l-th layer held
+// are l stride elements further.
 struct Operands {
   bf16* xa;   // [n][KA]  inputs of the first dense layer (hi | lo)
   bf16* h1;   // [n][H]   hidden activations
@@ -748,14 +748,15 @@ __device__ __forceinline__ void pq_quad_backward(const float* o, float vlast, fl
   glast = V[KP] * __builtin_fmaf(-W[KP - 1], SG * 0.5f, glast);
 }
 
-// The backward pass through all nl layers for events [64 blockIdx.x, +64); as
-// in the forward pass a tile needs no other.  Of each layer, the last first,
+// The backward pass through layers l1 - 1 .. l0 of nl (all of them where their
+// operands fit) for events [64 blockIdx.x, +64); as in the forward pass a tile
+// needs no other.  Of each layer, the last first,
 // the hidden layers and the logits are computed again from the layer's input
 // lin + l lstride ([d][n]; the same products as in k_coupling, cheaper than
 // keeping 2.4 KB per event and layer), each coordinate's logits give the
 // gradients of its PQ transform, which are multiplied into the gradient of the
 // second hidden layer at once, and so on to the kept inputs.  g ([d][n]) holds
-// the gradient with respect to the current layer's output, zero at the start,
+// the gradient with respect to the current layer's output, zero at the last,
 // and receives the one with respect to its input; glp = dL/dlog q =
 // -w_e / sum w.  Written besides: the operands of the weight gradients, in rows
 // of 64 to 1152 bytes per event.  The products run transposed,
@@ -780,7 +781,7 @@ __device__ __forceinline__ void pq_quad_backward(const float* o, float vlast, fl
 // with BF16 epilogues 76 each, the input product 17, its addition 6, and 43 for
 // writing the caches in the forward pass.
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
-k_backward(Layers layers, int nl, const float* __restrict__ lin_all, int64_t lstride, int64_t n, float* __restrict__ g,
+k_backward(Layers layers, int nl, int l0, int l1, const float* __restrict__ lin_all, int64_t lstride, int64_t n, float* __restrict__ g,
            const float* __restrict__ w, const float* __restrict__ wsum, Operands op, int d) {
   __shared__ __attribute__((aligned(16))) bf16 h[T * H];
   __shared__ __attribute__((aligned(16))) float out[T * LDO];
@@ -789,19 +790,19 @@ k_backward(Layers layers, int nl, const float* __restrict__ lin_all, int64_t lst
   bf16* xa = reinterpret_cast<bf16*>(out);  // [T][KA]
   const int tid0 = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid0 >> 6);
   const int64_t e0 = (int64_t)blockIdx.x * T;
-  for (int idx = tid0; idx < T * d; idx += 256)
+  for (int idx = l1 == nl ? tid0 : T * d; idx < T * d; idx += 256)
     if (e0 + idx % T < n) g[(int64_t)(idx / T) * n + e0 + idx % T] = 0.0f;
 #pragma unroll 1
-  for (int l = nl - 1; l >= 0; --l) {
+  for (int l = l1 - 1; l >= l0; --l) {
     const LayerDev& L = layers.L[l];
     const float* lin = lin_all + l * lstride;
     Operands out_op = op;
-    out_op.xa += l * op.stride;
-    out_op.h1 += l * op.stride;
-    out_op.h2 += l * op.stride;
-    out_op.go += l * op.stride;
-    out_op.ga2 += l * op.stride;
-    out_op.ga1 += l * op.stride;
+    out_op.xa += (l - l0) * op.stride;
+    out_op.h1 += (l - l0) * op.stride;
+    out_op.h2 += (l - l0) * op.stride;
+    out_op.go += (l - l0) * op.stride;
+    out_op.ga2 += (l - l0) * op.stride;
+    out_op.ga1 += (l - l0) * op.stride;
     const int tid = fresh(tid0), lane = tid & 63, row = lane & 15, quad = lane >> 4;
     // inputs as in k_coupling
     {
@@ -1458,7 +1459,8 @@ struct mf_flow {
   float* d_gy = nullptr;    // [d][cap]
   float* d_lq = nullptr;    // [cap]
   float* d_weff = nullptr;  // [cap] per-point loss weights of the variance loss
-  Operands op{};            // operands of the weight gradients, all layers
+  Operands op{};            // operands of the weight gradients of `group` layers
+  int group = 0;
   bf16* d_op = nullptr;
   float* d_part = nullptr;  // partials of the weight gradients, split over events
   size_t part_cap = 0;      // floats
@@ -1485,17 +1487,18 @@ mf_status launch_err(const char* what) {
 }
 
 
-WgradArgs wgrad_args(const mf_flow* f, int64_t n) {
+// Layers l0 .. l1 - 1, whose operands are held.
+WgradArgs wgrad_args(const mf_flow* f, int l0, int l1, int64_t n) {
   WgradArgs a{};
-  for (int l = 0; l < f->nl; ++l) {
+  for (int l = l0; l < l1; ++l) {
     const Operands& o = f->op;
     const bf16* X[3] = {o.h2, o.h1, o.xa};
     const bf16* G[3] = {o.go, o.ga2, o.ga1};
     const int M[3] = {H, H, KA}, N[3] = {f->L.L[l].dB * NOG, H, H};
     for (int k = 0; k < 3; ++k) {
       Product& p = a.p[a.np++];
-      p.X = X[k] + l * o.stride;
-      p.G = G[k] + l * o.stride;
+      p.X = X[k] + (l - l0) * o.stride;
+      p.G = G[k] + (l - l0) * o.stride;
       p.M = M[k];
       p.N = N[k];
       p.tiles_n = (p.N + WT - 1) / WT;
@@ -1514,9 +1517,17 @@ WgradArgs wgrad_args(const mf_flow* f, int64_t n) {
   return a;
 }
 
-// Weight and bias gradients of all layers over n events from the operands.
-bool weight_grads(mf_flow* f, int64_t n, hipStream_t s) {
-  WgradArgs a = wgrad_args(f, n);
+// Floats of the partials of layers l0 .. l1 - 1 for up to cap events: fewer
+// events may take more chunks than cap does, of whole slices.
+size_t partials(const mf_flow* f, int l0, int l1, int64_t cap) {
+  const WgradArgs a = wgrad_args(f, l0, l1, cap);
+  return (size_t)(std::min(a.zmax, (cap + WK - 1) / WK) * a.zs);
+}
+
+// Weight and bias gradients of layers l0 .. l1 - 1 over n events from the
+// operands.
+bool weight_grads(mf_flow* f, int l0, int l1, int64_t n, hipStream_t s) {
+  WgradArgs a = wgrad_args(f, l0, l1, n);
   const int64_t Z = (n + a.chunk - 1) / a.chunk;
   // the partials of all chunks must fit the buffer sized at creation
   if ((size_t)(Z * a.zs) > f->part_cap) return false;
@@ -1524,14 +1535,14 @@ bool weight_grads(mf_flow* f, int64_t n, hipStream_t s) {
   hipLaunchKernelGGL(k_wgrad, dim3((unsigned)(a.tiles * Z)), dim3(256), 0, s, a);
   ReduceArgs r{};
   int64_t most = 0;
-  for (int l = 0; l < f->nl; ++l) {
-    r.dA[l] = f->L.L[l].dA;
-    r.dB[l] = f->L.L[l].dB;
-    r.off[l] = a.p[3 * l].off;
-    r.goff[l] = f->loff[l];
-    most = std::max(most, (int64_t)(H + 1) * (r.dB[l] * NOG + H) + (int64_t)(r.dA[l] + 1) * H);
+  for (int l = l0, k = 0; l < l1; ++l, ++k) {
+    r.dA[k] = f->L.L[l].dA;
+    r.dB[k] = f->L.L[l].dB;
+    r.off[k] = a.p[3 * k].off;
+    r.goff[k] = f->loff[l];
+    most = std::max(most, (int64_t)(H + 1) * (r.dB[k] * NOG + H) + (int64_t)(r.dA[k] + 1) * H);
   }
-  hipLaunchKernelGGL(k_reduce_grad, dim3((unsigned)((most + 255) / 256), (unsigned)f->nl), dim3(256), 0, s, f->d_part,
+  hipLaunchKernelGGL(k_reduce_grad, dim3((unsigned)((most + 255) / 256), (unsigned)(l1 - l0)), dim3(256), 0, s, f->d_part,
                      (int)Z, a.zs, r, f->d_g);
   return true;
 }
@@ -1580,9 +1591,13 @@ mf_status loss_grad_impl(mf_flow* f, const float* y, int64_t ldy, const float* w
     hipLaunchKernelGGL(k_wsum, dim3(1), dim3(RB), 0, s, w, n, f->d_scal);
     hipLaunchKernelGGL(k_loss, dim3(1), dim3(RB), 0, s, w, f->d_lq, n, f->d_scal, loss_dev);
   }
-  hipLaunchKernelGGL(k_backward, dim3((unsigned)((n + T - 1) / T)), dim3(256), 0, s, f->L, f->nl, f->d_lin,
-                     (int64_t)d * f->cap, n, f->d_gy, w, f->d_scal, f->op, d);
-  if (!weight_grads(f, n, s)) return set_error(MF_EINVAL, "weight-gradient partials exceed the flow's buffer");
+  for (int l1 = f->nl; l1 > 0; l1 -= f->group) {
+    const int l0 = std::max(0, l1 - f->group);
+    hipLaunchKernelGGL(k_backward, dim3((unsigned)((n + T - 1) / T)), dim3(256), 0, s, f->L, f->nl, l0, l1, f->d_lin,
+                       (int64_t)d * f->cap, n, f->d_gy, w, f->d_scal, f->op, d);
+    if (!weight_grads(f, l0, l1, n, s))
+      return set_error(MF_EINVAL, "weight-gradient partials exceed the flow's buffer");
+  }
   return launch_err("flow backward");
 }
 
@@ -1658,13 +1673,8 @@ mf_status mf_flow_create(const mf_flow_config* cfg, mf_flow** out) {
   const int64_t cap = cfg->max_batch;
   f->cap = cap;
 
-  // operands of the weight gradients of all layers
+  // operands of the weight gradients of one layer
   const size_t per_layer = ((size_t)cap * (4 * H + KA + dBmax * NOG) + 127) / 128 * 128;
-  {
-    const WgradArgs a = wgrad_args(f, cap);
-    // fewer events may take more chunks than cap does, of whole slices
-    f->part_cap = (size_t)(std::min(a.zmax, (cap + WK - 1) / WK) * a.zs);
-  }
   if (hipMalloc(&f->d_p, sizeof(float) * off) != hipSuccess || hipMalloc(&f->d_g, sizeof(float) * off) != hipSuccess ||
       hipMalloc(&f->d_m1, sizeof(float) * off) != hipSuccess || hipMalloc(&f->d_m2, sizeof(float) * off) != hipSuccess ||
       hipMalloc(&f->d_w16, sizeof(bf16) * w16) != hipSuccess || hipMalloc(&f->d_b3p, sizeof(float) * b3) != hipSuccess ||
@@ -1673,11 +1683,26 @@ mf_status mf_flow_create(const mf_flow_config* cfg, mf_flow** out) {
       hipMalloc(&f->d_gy, sizeof(float) * d * cap) != hipSuccess ||
       hipMalloc(&f->d_lq, sizeof(float) * cap) != hipSuccess ||
       hipMalloc(&f->d_weff, sizeof(float) * cap) != hipSuccess ||
-      hipMalloc(&f->d_op, sizeof(bf16) * f->nl * per_layer) != hipSuccess ||
-      hipMalloc(&f->d_part, sizeof(float) * f->part_cap) != hipSuccess ||
       hipMalloc(&f->d_scal, sizeof(float) * 4) != hipSuccess) {
     hipGetLastError();
     return cleanup(set_error(MF_ENOMEM, "flow allocation failed"));
+  }
+  // the operands of all layers, so that the backward pass is one launch; of a
+  // part of them, in as many launches, where the memory does not hold them
+  for (f->group = f->nl;; f->group = (f->group + 1) / 2) {
+    f->part_cap = 0;
+    for (int l1 = f->nl; l1 > 0; l1 -= f->group)
+      f->part_cap = std::max(f->part_cap, partials(f, std::max(0, l1 - f->group), l1, cap));
+    const size_t op_bytes = sizeof(bf16) * f->group * per_layer, part_bytes = sizeof(float) * f->part_cap;
+    size_t avail = 0, total = 0;
+    if (hipMemGetInfo(&avail, &total) == hipSuccess && op_bytes + part_bytes <= avail &&
+        hipMalloc(&f->d_op, op_bytes) == hipSuccess && hipMalloc(&f->d_part, part_bytes) == hipSuccess)
+      break;
+    hipGetLastError();
+    hipFree(f->d_op);
+    f->d_op = nullptr;
+    f->d_part = nullptr;
+    if (f->group == 1) return cleanup(set_error(MF_ENOMEM, "flow allocation failed"));
   }
   if (hipMemset(f->d_g, 0, sizeof(float) * off) != hipSuccess ||
       hipMemset(f->d_m1, 0, sizeof(float) * off) != hipSuccess ||
