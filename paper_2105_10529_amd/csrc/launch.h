@@ -16,15 +16,6 @@ constexpr int PART_HEAD = 8;  // S1 hi, S1 lo, S2 hi, S2 lo, nonzero, nonfinite,
 constexpr int GV = 10;        // w, dw/dm_t, dw/dtheta_0..7
 
 // ---------------------------------------------------- compensated sums
-struct KSum {
-  double s, c;  // Kahan: the exact sum is approximately s - c
-};
-__device__ __forceinline__ void kadd(KSum& k, double v) {
-  double y = v - k.c;
-  double t = k.s + y;
-  k.c = (t - k.s) - y;
-  k.s = t;
-}
 // Error-free two-sum: a + b = s + e exactly.
 __device__ __forceinline__ void two_sum(double a, double b, double& s, double& e) {
   s = a + b;

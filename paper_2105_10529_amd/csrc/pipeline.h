@@ -14,7 +14,6 @@
 #include "gen/me_gg_m2.h"
 #include "gen/me_gg_m3.h"
 #include "gen/me_gg_m3_both.h"
-#include "gen/me_gg_m4.h"
 #include "gen/me_gg_m4_grouped.h"
 #include "gen/me_gg_m4_lanes.h"
 #include "gen/me_gg_m4_quad.h"
@@ -370,8 +369,10 @@ __device__ __forceinline__ RA me_gg(double E, const V4<double>* gl, const V4<RK>
   } else if constexpr (m == 2) return me_gg_m2<RA, RK>(K, Ep, UB, VS, atop, mt);
   else if constexpr (m == 3 && fp64_amp<RA>::value) return me_gg_m3<RA, RK, RG, KG>(K, Ep, UB, VS, atop, mt);
   else if constexpr (m == 3) return me_gg_m3_both<RA, RK, RG, KG>(K, Ep, UB, VS, atop, mt);
-  else if constexpr (std::is_same<RA, float>::value) return me_gg_m4_grouped<RA, RK, RG, KG>(K, Ep, UB, VS, atop, mt);
-  else return me_gg_m4<RA, RK>(K, Ep, UB, VS, atop, mt);
+  else {
+    static_assert(std::is_same<RA, float>::value, "g g -> t t~ g g in FP64 takes four lanes per event");
+    return me_gg_m4_grouped<RA, RK, RG, KG>(K, Ep, UB, VS, atop, mt);
+  }
 }
 
 // Row spinor psibar gamma^mu chi contracted: returns the four components

@@ -446,8 +446,8 @@ def emit_me_per_ordering(m: int, share_antitop: bool = False, pair_orderings=Fal
     w = L.append
     w(f"// Generated by gen_me.py for g g -> t t~ + {m - 2} g ({m} gluons on the top line,")
     w(f"// {nf} colour orderings, {1 << (m + 2)} helicity/polarisation states),")
-    grouping = {"all": "all orderings in one block", "last": "orderings grouped by their last gluon",
-                True: "orderings in pairs"}.get(pair_orderings, "one ordering at a time")
+    grouping = {"all": "all orderings in one block", "last": "orderings grouped by their last gluon"}.get(
+        pair_orderings, "one ordering at a time")
     w(f"// per-ordering schedule, {grouping}. Do not edit.")
     w("#pragma once")
     w('#include "amp.h"')
@@ -515,8 +515,6 @@ def emit_me_per_ordering(m: int, share_antitop: bool = False, pair_orderings=Fal
         order = [[tuple(range(nf))]]
     elif pair_orderings == "last":
         order = [[pr for pr in pairs if perms[pr[0]][-1] == d] for d in range(m)]
-    elif pair_orderings:
-        order = [[pr] for pr in pairs]
     else:
         order = [[(k,)] for k in range(nf)]
     for block in order:
@@ -1084,39 +1082,34 @@ def amp_flop_count(m: int) -> dict:
             "total": states * (per_state + colour)}
 
 
+# how the gluon currents are shared (flop_count)
 SCHEDULE = {2: "memo", 3: "per_ordering_shared_antitop", 4: "per_ordering_shared_antitop", 5: "amplitudes"}
-# per-ordering schedules that handle the orderings in pairs sharing their
-# suffix currents ("all": every ordering in one block, so that besides the
-# suffix currents the reflected currents J(n..1) = (-1)^(n+1) J(1..n) are
-# shared too)
-PAIR_ORDERINGS = {2: False, 3: "all", 4: True, 5: False}
-# a second function with a wider grouping, me_gg_m4_grouped (the six orderings
-# that end with the same gluon in one block), for the FP32 amplitudes: it needs
-# more registers, which the FP32 kernel has and the FP64 one does not
 
 
-def main(outdir: str, ms=(2, 3, 4, 5)) -> None:
+def headers() -> dict:
+    """{file name: text} of every generated header."""
+    return {
+        "me_gg_m2.h": emit_me(2),
+        # g g -> t t~ g: all orderings in one block, so that besides the suffix
+        # currents the reflected currents J(n..1) = (-1)^(n+1) J(1..n) are shared;
+        # one antitop helicity for FP64, both for FP32
+        "me_gg_m3.h": emit_me_per_ordering(3, True, "all", one_antitop=True),
+        "me_gg_m3_both.h": emit_me_per_ordering(3, True, "all", "_both"),
+        # g g -> t t~ g g: the six orderings that end with the same gluon in one
+        # block for FP32, in one lane or with the states dealt out to lanes; four
+        # lanes per event for FP64; amplitudes stored for the matrix-core colour sum
+        "me_gg_m4_grouped.h": emit_me_per_ordering(4, True, "last", "_grouped"),
+        "me_gg_m4_lanes.h": emit_me_per_ordering(4, True, "last", "_lanes", lanes=True),
+        "me_gg_m4_quad.h": emit_me_quad(),
+        "amps_gg_m4.h": emit_amp_store(4),
+        "amp_gg_m5.h": emit_amp_tables(5),
+        "colour_qq.h": emit_colour_qq(),
+    }
+
+
+def main(outdir: str) -> None:
     os.makedirs(outdir, exist_ok=True)
-    for m in ms:
-        if SCHEDULE[m] == "amplitudes":
-            path = os.path.join(outdir, f"amp_gg_m{m}.h")
-            text = emit_amp_tables(m)
-        else:
-            path = os.path.join(outdir, f"me_gg_m{m}.h")
-            text = emit_me(m) if SCHEDULE[m] == "memo" else emit_me_per_ordering(
-                m, share_antitop=SCHEDULE[m] == "per_ordering_shared_antitop", pair_orderings=PAIR_ORDERINGS[m],
-                one_antitop=True)
-        old = open(path).read() if os.path.exists(path) else None
-        if old != text:
-            with open(path, "w") as f:
-                f.write(text)
-    # both antitop helicities for the FP32 amplitudes of g g -> t t~ g and, in
-    # the wider grouping, of g g -> t t~ g g; the amplitudes stored for the
-    # matrix-core colour sum; the colour matrix of the quark channels
-    for name, text in (("me_gg_m3_both.h", emit_me_per_ordering(3, True, "all", "_both")),
-                       ("me_gg_m4_grouped.h", emit_me_per_ordering(4, True, "last", "_grouped")),
-                       ("me_gg_m4_lanes.h", emit_me_per_ordering(4, True, "last", "_lanes", lanes=True)),
-                       ("me_gg_m4_quad.h", emit_me_quad()), ("amps_gg_m4.h", emit_amp_store(4)), ("colour_qq.h", emit_colour_qq())):
+    for name, text in headers().items():
         path = os.path.join(outdir, name)
         old = open(path).read() if os.path.exists(path) else None
         if old != text:
