@@ -112,8 +112,11 @@ typedef struct {
                                   precisions);
                               1 = in registers on the vector ALUs, next to
                                   the amplitudes (FP32: one fused kernel per
-                                  VEGAS iteration; FP64: points, integrand
-                                  and accumulation kernels);
+                                  VEGAS iteration of more than 131072 events,
+                                  or with observables; FP64 and smaller
+                                  iterations: points, integrand and
+                                  accumulation kernels, with staging buffers
+                                  in the handle, 202 B per event);
                               2 = on the matrix cores: the partial amplitudes
                                   are streamed to a handle-owned buffer and
                                   Z = C A is formed with FP32 (FP64)
@@ -152,7 +155,12 @@ const char* mf_last_error(void);
  *      never written (such events give 0).
  * Points that fail threshold or cuts are written as 0 without evaluating the
  * matrix element.  The call may allocate (or grow) per-block point lists
- * inside the handle (4 B per point), synchronising `stream` when it does.
+ * inside the handle (4 B per point), synchronising `stream` when it does.  For
+ * g g -> t t~ g g g it keeps in the handle 12 B per point and the partial
+ * amplitudes of some of the polarisation states of up to 131072 (FP64: 65536)
+ * points that pass the cuts, at most 2 GiB; where that much cannot be had, fewer
+ * states are taken at a time, and a point's weight is the same whatever batch it
+ * is in.
  * n = 0 is accepted and does nothing.  MF_EINVAL for n < 0, n >= 2^31 or NULL
  * pointers with n > 0. */
 mf_status mf_integrand(mf_process* p, const double* u, int64_t n, double* w, void* stream);
@@ -272,9 +280,12 @@ typedef struct mf_result_s {
   int64_t n_nonfinite;      /* events whose weight was not finite (dropped) */
   double seconds;           /* wall time of the call */
   double time_to_target;    /* seconds until error/integral <= target, -1 if never */
-  double kernel_seconds;    /* summed device time of the fused per-event kernel,
-                               from HIP events recorded around each launch on
-                               the call's stream */
+  double kernel_seconds;    /* summed device time of the iterations' per-event
+                               kernels (selection and fused kernel, with the
+                               observables' kernels if any; or points,
+                               integrand and accumulation kernels), from HIP
+                               events recorded around them on the call's
+                               stream */
   double* iter_integral;    /* host, length >= n_iter, or NULL */
   double* iter_error;       /* host, length >= n_iter, or NULL */
   int32_t fallback_iter;    /* with a flow and fallback_rel_var > 0: index of

@@ -33,11 +33,8 @@
  * mf_last_error(); "device" pointers are HIP device pointers owned by the
  * caller; points are [ndim][n] FP32 structure-of-arrays; `stream` is a
  * hipStream_t or NULL; calls are asynchronous unless stated otherwise.
- * A flow owns one more stream of its own (default priority, created with
- * the flow): mf_flow_loss_grad runs its weight-gradient products there,
- * ordered against `stream` by events, and leaves `stream` waiting for them,
- * so the gradient is complete in `stream` order when the call returns.
- * Calls on one flow must not overlap.
+ * Every kernel runs on `stream`; a flow owns no stream and no events.  Calls on
+ * one flow must not overlap.
  *
  * Parameter layout (FP32, host): layer after layer, each as
  *   W1 [d_A][256], b1 [256], W2 [256][256], b2 [256],
@@ -73,9 +70,15 @@ typedef struct {
   int32_t n_layers;   /* 1..8 */
   int32_t hidden;     /* hidden width; only 256 is built */
   int32_t bins;       /* K; only 32 is built */
-  int64_t max_batch;  /* largest n accepted by mf_flow_loss_grad (sizes the
-                         per-layer activation caches: about
-                         n_layers * max_batch * (2 KB + 0.3 KB * ndim) bytes) */
+  int64_t max_batch;  /* largest n accepted by mf_flow_loss_grad.  Sizes the
+                         training buffers, per point and layer: the layer's
+                         input, 4 ndim bytes, and the operands of its weight
+                         gradients, 2112 + 144 d_B bytes with d_B the most
+                         coordinates that a layer transforms (2.9 KB in all
+                         for 10 dimensions).  Where the operands of all
+                         layers do not fit the device's free memory, those of
+                         half of the layers (a quarter, ...) are held, and a
+                         backward pass takes as many more launches */
   uint64_t seed;      /* Philox key word 0 of the initial weights */
 } mf_flow_config;
 

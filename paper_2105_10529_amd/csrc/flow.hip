@@ -775,11 +775,13 @@ __device__ __forceinline__ void pq_quad_backward(const float* o, float vlast, fl
 // only, 1.1 GB for 65536 points of 10 dimensions, and would push the weights
 // of six layers (4.5 MB) out of the L2 (735 us, with these stores 590).
 //
-// Bound by vector instructions (51 % of the time; the matrix instructions take
-// 20 %) at two waves per SIMD.  As separate kernels over cached activations and
-// logits the same work took 285 us per layer: PQ derivatives 67, two products
-// with BF16 epilogues 76 each, the input product 17, its addition 6, and 43 for
-// writing the caches in the forward pass.
+// 65536 points of 10 dimensions, six layers: 577 us at two waves per SIMD.
+// Vector instructions other than the matrix ones are issued in 43 % of the SIMD
+// cycles, the matrix cores are busy in 19 %, and a wave waits half of its time.
+// As separate kernels over cached activations and logits the same work took 285
+// us per layer: PQ derivatives 67, two products with BF16 epilogues 76 each, the
+// input product 17, its addition 6, and 43 for writing the caches in the forward
+// pass.
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 k_backward(Layers layers, int nl, int l0, int l1, const float* __restrict__ lin_all, int64_t lstride, int64_t n, float* __restrict__ g,
            const float* __restrict__ w, const float* __restrict__ wsum, Operands op, int d) {
@@ -1065,7 +1067,7 @@ k_backward(Layers layers, int nl, int l0, int l1, const float* __restrict__ lin_
 // 16+4q..16+4q+3 for both operands; with rows of 288 bytes the 8 rows of half a
 // wave fall in different banks (no conflicts counted).  Bound by memory: six
 // layers of 65536 points of 10 dimensions have 1.1 GB of operands, read 1.5
-// times: 285 us, and 11 us for the reduction.  Launched layer by layer beside
+// times: 284 us (6.0 TB/s), and 11 us for the reduction.  Launched layer by layer beside
 // the backward pass, with six times the partials, the whole gradient took 1.42
 // ms instead of 1.11; three launches per layer of 64 x 64 tiles on
 // event-contiguous copies and three reductions took 250 us per layer.

@@ -48,7 +48,7 @@ static_assert(GSTATES == STATES / 2, "gluon polarisation states of either antito
 // (flipping both top helicities conjugates the amplitudes, whose gluon
 // polarisation vectors are real) and the sum is doubled; FP32 keeps both,
 // each with its own rounding.  g g -> t t~ g g g FP64 at 20000 points:
-// 20.7 -> 3.5 ms with the launches below.
+// 20.7 -> 3.5 ms together with the passes of g3_pass.h.
 template <class R> constexpr int NHS = fp64_amp<R>::value ? 1 : 2;
 constexpr int AWAVE = 64;              // amplitude kernel block: one wave (LDS tables per wave)
 constexpr int CT = 32;                 // events per colour tile (two 16-column MFMA blocks)

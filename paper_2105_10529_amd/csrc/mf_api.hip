@@ -631,8 +631,9 @@ int blocks_for(int64_t n) {
 }
 
 // Blocks of a VEGAS iteration: once there are more than 256 chunks of
-// events, at least 16 chunks per block, in whole rounds of 256 blocks (the
-// fused kernel runs one block per compute unit at a time), so that a
+// events, at least 16 chunks per block, in whole rounds of 256 blocks (with
+// final-state partons the fused kernel fills the register file, so that one
+// block runs per compute unit at a time; without them two fit), so that a
 // block's kept events fill several passes of its waves and no round is
 // mostly idle; one chunk per block up to 256 chunks.
 int iter_blocks(int64_t n) {

@@ -438,7 +438,8 @@ def emit_me_per_ordering(m: int, share_antitop: bool = False, pair_orderings=Fal
     lane of the group (lane broadcasts), so the result is the same bit for
     bit.  The loop over a lane's states has a bound the compiler cannot see:
     with one known to be 1 it would drop the loop and fill the registers with
-    the per-event constants (1.1 KB of scratch against 0.6).
+    the per-event constants (1.1 KB of scratch against 0.54 in a kernel of one
+    lane count; the kernel that holds the loops of all three has 1.15).
     """
     perms, Z, den = colour_matrix(m)
     nf = len(perms)
@@ -650,7 +651,7 @@ def emit_me_quad() -> str:
     One lane per event needs 48 FP64 amplitudes at once, spills 1.1 KB and
     builds most currents twice (an ordering pair at a time); four lanes need
     12 each, no scratch, and build every current once.  VALU issue bounds it
-    (94 % of the wave cycles): two iterations of 1e6 events (1.5e6 kept)
+    (88 % of the wave cycles, at about 2.0 GHz): two iterations of 1e6 events (1.5e6 kept)
     25.8 ms with one lane per event, 14.0 ms with four."""
     m = 4
     perms, Z, den = colour_matrix(m)
