@@ -1696,9 +1696,11 @@ mf_status mf_flow_create(const mf_flow_config* cfg, mf_flow** out) {
     for (int l1 = f->nl; l1 > 0; l1 -= f->group)
       f->part_cap = std::max(f->part_cap, partials(f, std::max(0, l1 - f->group), l1, cap));
     const size_t op_bytes = sizeof(bf16) * f->group * per_layer, part_bytes = sizeof(float) * f->part_cap;
-    size_t avail = 0, total = 0;
-    if (hipMemGetInfo(&avail, &total) == hipSuccess && op_bytes + part_bytes <= avail &&
-        hipMalloc(&f->d_op, op_bytes) == hipSuccess && hipMalloc(&f->d_part, part_bytes) == hipSuccess)
+    // asked for large flows only: the driver takes a millisecond to say what is free
+    size_t avail = SIZE_MAX, total = 0;
+    if ((op_bytes < ((size_t)1 << 36) || hipMemGetInfo(&avail, &total) == hipSuccess) &&
+        op_bytes + part_bytes <= avail && hipMalloc(&f->d_op, op_bytes) == hipSuccess &&
+        hipMalloc(&f->d_part, part_bytes) == hipSuccess)
       break;
     hipGetLastError();
     hipFree(f->d_op);

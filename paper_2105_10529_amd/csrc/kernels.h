@@ -63,8 +63,8 @@ __global__ void __launch_bounds__(BLOCK) k_select_points(DevCfg c, const double*
 }
 
 // Running offsets of the selection blocks' lists in LDS: pre[b] is the number
-// of entries of the blocks before b, pre[nblk] the total.  All threads of the
-// block take part.
+// of entries of the blocks before b, pre[nblk] and what follows the total.  All
+// threads of the block take part.
 __device__ __forceinline__ void list_offsets(const int* __restrict__ cnt, int nblk, int* pre) {
   constexpr int PER = MAX_BLOCKS / BLOCK;
   __shared__ int wsum[WAVES];
@@ -90,21 +90,22 @@ __device__ __forceinline__ void list_offsets(const int* __restrict__ cnt, int nb
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
     const int b = tid * PER + k;
-    if (b <= nblk) pre[b] = base;
+    pre[b] = base;
     base += v[k];
   }
-  if (tid == BLOCK - 1 && nblk == MAX_BLOCKS) pre[nblk] = base;
+  if (tid == BLOCK - 1) pre[MAX_BLOCKS] = base;
   __syncthreads();
 }
 // The g-th entry of the lists laid end to end (0 <= g < pre[nblk]).  The search
 // takes the same number of steps for every lane, so that the event loops have no
 // divergent region.
 __device__ __forceinline__ int list_entry(const int* __restrict__ list, int64_t cap, const int* pre, int nblk, int g) {
+  // steps 2^k .. 1 with 2^k < nblk: lo + step stays below MAX_BLOCKS, and below
+  // nblk where it is taken
+  static_assert((MAX_BLOCKS & (MAX_BLOCKS - 1)) == 0, "a power of two");
   int lo = 0;  // the last list with pre[lo] <= g
-  for (int step = 1 << (31 - __builtin_clz(nblk)); step > 0; step >>= 1) {
-    const int t = lo + step < nblk ? lo + step : nblk;  // pre[nblk] > g
-    lo = pre[t] <= g ? t : lo;
-  }
+  for (int step = nblk > 1 ? 1 << (31 - __builtin_clz(nblk - 1)) : 0; step > 0; step >>= 1)
+    lo = pre[lo + step] <= g ? lo + step : lo;
   return list[(int64_t)lo * cap + (g - pre[lo])];
 }
 
