@@ -202,21 +202,19 @@ __device__ __forceinline__ double solve_mass_ratio(int N, double r) {
 
 // sin and cos of the azimuth 2 pi x.  The bound on the argument tells the
 // compiler that the library's reduction of large arguments is not needed,
-// which leaves no divergent branch in an event's code.  It changes no value:
-// sincos(2 pi x) up to |x| = 128, beyond it the same azimuth with the whole
-// turns taken out of x, and NaN where x is not finite (so that the point fails
-// the cuts or its weight is dropped).  Besides the instructions this matters
-// for correctness: in kernels that fill the register file the compiler moved a
+// which leaves no divergent branch in an event's code.  In [0, 1) the values and
+// bits are those of sincos(2 pi x); whole turns are taken out of any other x;
+// and the sine is NaN where x is not finite (so that the point fails the cuts or
+// its weight is dropped).  Besides the instructions this matters for
+// correctness: in kernels that fill the register file the compiler moved a
 // live value (the thread index among them) to an accumulation register at the
 // join of that branch, under the execution mask of one of its sides, and the
 // other lanes read a stale one afterwards.
 __device__ __forceinline__ void azimuth(double x, double* sp, double* cp) {
-  const double ph = 2.0 * M_PI * (fabs(x) <= 128.0 ? x : x - floor(x));
-  double s, c;
-  sincos(fmin(fabs(ph), 1024.0), &s, &c);  // the smaller of NaN and 1024 is 1024
-  s = ph < 0.0 ? -s : s;
-  *sp = ph == ph ? s : ph;
-  *cp = ph == ph ? c : ph;
+  const double ph = 2.0 * M_PI * (x - floor(x));
+  double s;
+  sincos(fmin(fabs(ph), 1024.0), &s, cp);  // the smaller of NaN and 1024 is 1024
+  *sp = fma(0.0, ph, s);
 }
 
 // Final state from x[2..] in the partonic centre-of-mass frame: the gluons

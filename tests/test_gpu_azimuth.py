@@ -49,11 +49,10 @@ def test_an_azimuth_that_is_not_finite_gives_no_weight(process, precision, value
 @pytest.mark.parametrize("process,precision", [("gg>ttx", "fp64"), ("gg>ttxg", "fp64"), ("gg>ttxgg", "fp64")])
 @pytest.mark.parametrize("turns", [-200, -3, 3, 200, 100000])
 def test_whole_turns_do_not_change_the_weight(process, precision, turns):
-    """Azimuths are multiples of 2^-12 here, so that x + turns is exact.  Up to
-    128 turns the argument 2 pi (x + turns) is rounded to 2^-53 of at most 804,
-    9e-14 of the angle; beyond, x - floor(x) is exact.  A weight's relative
-    change is the change of the angles times the logarithmic derivative, below
-    1e3 for these points but where the cuts or a cancellation decide: 1e-9."""
+    """Azimuths are multiples of 2^-12 here, so that x + turns is exact, and
+    x - floor(x) is.  A rounding of the angle, 2^-53 of at most 2 pi, would change
+    a weight by that times its logarithmic derivative, below 1e3 for these points
+    but where the cuts or a cancellation decide: 1e-9 is wide of it."""
     p, x, phi = _case(process, precision)
     x[:, phi] = np.round(x[:, phi] * 4096) / 4096
     a = p.integrand(to_dev_soa(x)).cpu().numpy()
