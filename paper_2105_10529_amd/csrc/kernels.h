@@ -269,12 +269,15 @@ __device__ __forceinline__ void grad_point(const DevCfg& c, const double* __rest
 // and waves without events skip the evaluation: what spills goes through
 // memory, and 1000 points take 194 us on 16 waves, 354 us on 1024.  Without
 // final-state partons nearly every point passes and the points are taken as
-// they come.
+// they come; so are up to a block per compute unit of them with FP32 amplitudes,
+// which one round takes either way (g g -> t t~ g at 50000 points that all pass:
+// 220 us compacted, 207 as they come; FP64 166 and 149, but at 1000 points 111 and
+// 130, and compacted it stays).
 constexpr int GRAD_BLOCKS = 256;
-template <int NG, int CH, class RA>
+template <int NG, int CH, class RA, bool COMPACT>
 __global__ void __launch_bounds__(BLOCK) k_integrand_grad(DevCfg c, const double* __restrict__ u, int64_t n,
                                                           double* __restrict__ w, double* __restrict__ dw) {
-  if constexpr (NG == 0) {
+  if constexpr (!COMPACT) {
     const int64_t nchunk = chunks_of_block(n);
     for (int64_t it = 0; it < nchunk; ++it) {
       const int64_t e0 = chunk_base(it) + threadIdx.x;
@@ -721,8 +724,17 @@ Launchers make_launchers() {
   if constexpr (GRAD != 0) {
     L.integrand_grad = [](const DevCfg& c, const double* u, int64_t n, double* w, double* dw, int nblk,
                           hipStream_t s) {
-      const unsigned grid = NG == 0 ? (unsigned)nblk : (unsigned)((n + 63) / 64 < GRAD_BLOCKS ? (n + 63) / 64 : GRAD_BLOCKS);
-      hipLaunchKernelGGL((k_integrand_grad<NG, CH, RD>), dim3(grid), dim3(BLOCK), 0, s, c, u, n, w, dw);
+      constexpr bool PLAIN = NG == 0 || std::is_same<RD, Dual<float>>::value;
+      if constexpr (PLAIN) {
+        if (NG == 0 || n <= (int64_t)GRAD_BLOCKS * BLOCK) {
+          hipLaunchKernelGGL((k_integrand_grad<NG, CH, RD, false>), dim3(nblk), dim3(BLOCK), 0, s, c, u, n, w, dw);
+          return;
+        }
+      }
+      if constexpr (NG > 0) {
+        const unsigned grid = (unsigned)((n + 63) / 64 < GRAD_BLOCKS ? (n + 63) / 64 : GRAD_BLOCKS);
+        hipLaunchKernelGGL((k_integrand_grad<NG, CH, RD, true>), dim3(grid), dim3(BLOCK), 0, s, c, u, n, w, dw);
+      }
     };
     L.grad_vegas = [](const DevCfg& c, const double* edges, uint64_t iter, int64_t N, uint64_t seed, double* part,
                       int nblk, size_t lds, int* list, int* cnt, int64_t cap, hipStream_t s) {
